@@ -403,6 +403,155 @@ def _work_loss(c):
     return {"bytes": c["B"] * (4.0 * c["C"] + 8), "flops": 5.0 * c["B"] * c["C"]}
 
 
+# ---------------------------------------------------------------- the same results in 64 bits
+# Plain torch in FP64 from the same inputs, nothing rounded on the way.  Flags, counters and the scaler's record have no such value.
+_F64 = torch.float64
+
+
+def _d(t):
+    return t.to(_F64)
+
+
+def _f32(x):
+    return torch.tensor(x, dtype=F32).item()                                 # a parameter as the entry points take it
+
+
+def _softmax_xent(z, labels, scale):
+    p = torch.log_softmax(z, 1)
+    rows = -p.gather(1, labels.long()[:, None])[:, 0]
+    grad = p.exp_().scatter_add_(1, labels.long()[:, None], torch.full((z.shape[0], 1), -1.0, device="cuda", dtype=_F64))
+    return rows, grad.mul_(scale / z.shape[0])
+
+
+def _exact_mlp(s):
+    x, (w1, _, _, h1), (w2, _, _, h2) = _d(s["x"]), *s["weights"]
+    h1, h2 = _d(h1), _d(h2)
+    h = torch.relu(x @ h1)
+    logits = h @ h2
+    rows, dlogits = _softmax_xent(logits, s["labels"], 1024.0)
+    dw2, dw1 = h.t() @ dlogits, x.t() @ ((dlogits @ h2.t()) * (h > 0))
+    m1, m2 = dw1 / 1024.0, dw2 / 1024.0                                     # momentum starts at zero
+    w1, w2 = _d(w1) - _f32(0.01) * m1, _d(w2) - _f32(0.01) * m2
+    mom = s["momentum"] != 0.0
+    return {"loss": rows.mean().reshape(1), "logits": logits, "dw1": dw1, "dw2": dw2, "w1": w1, "w2": w2, "m1": m1 if mom else None,
+            "m2": m2 if mom else None, "w1h": w1, "w2h": w2, "flag": None}
+
+
+def _exact_layer(s):
+    x, w, g = _d(s["x"]), _d(s["w"]), _d(s["g"])
+    y, dx, dw = x @ w, g @ w.t(), x.t() @ g
+    if s["relu"]:
+        y, dx = torch.relu(y), dx * (x > 0)
+    out = {"y": y, "dx": dx, "dw": dw, "flag": None}
+    if "w32" in s:
+        m = dw / 8192.0
+        w = _d(s["w32"]) - _f32(1e-3) * m
+        out.update(w32=w, m32=m, w=w, scaler=None)
+    return out
+
+
+def _exact_recurrent(s):
+    T, (R, H4), wp = s["T"], s["wr"].shape, _d(s["wp"])
+    x, wx, wr, H = _d(s["x"]), _d(s["wx"]), _d(s["wr"]), H4 // 4
+    B = x.shape[0] // T
+    if s["direction"] == "fwd":
+        gx, c, r = x @ wx, torch.zeros(B, H, device="cuda", dtype=_F64), torch.zeros(B, R, device="cuda", dtype=_F64)
+        rs, hs, cs, acts = [r], [], [c], []
+        for t in range(T):
+            i, f, g, o = (gx[t * B:(t + 1) * B] + r @ wr).split(H, 1)
+            i, f, g, o = torch.sigmoid(i), torch.sigmoid(f), torch.tanh(g), torch.sigmoid(o)
+            c = f * c + i * g
+            h = o * torch.tanh(c)
+            r = h @ wp
+            rs.append(r), hs.append(h), cs.append(c), acts.append(torch.cat((i, f, g, o), 1))
+        return {"r": torch.cat(rs), "h": torch.cat(hs), "cell": torch.cat(cs), "act": torch.cat(acts)}
+    das, dwp, drec, dc = [None] * T, torch.zeros(H, R, device="cuda", dtype=_F64), 0.0, 0.0
+    for t in range(T - 1, -1, -1):
+        dr = _d(s["dr_t"][t]) + drec
+        dh = dr @ wp.t()
+        i, f, g, o = _d(s["act_t"][t]).split(H, 1)
+        tc = torch.tanh(_d(s["cell_t"][t + 1]))
+        d = dh * o * (1.0 - tc * tc) + dc
+        das[t] = torch.cat((d * g * i * (1.0 - i), d * _d(s["cell_t"][t]) * f * (1.0 - f), d * i * (1.0 - g * g), dh * tc * o * (1.0 - o)), 1)
+        dc = d * f
+        dwp += _d(s["h_t"][t]).t() @ dr
+        drec = das[t] @ wr.t()
+    da = torch.cat(das)
+    return {"dx": da @ wx.t(), "dwx": x.t() @ da, "dwr": _d(s["r"]).t() @ da, "dwp": dwp, "da": da, "dc": dc, "flag": None}
+
+
+def _taps(t):
+    """The nine shifted copies of an image tensor (zero outside), as matrices of its pixels."""
+    Nb, H, W, C = t.shape
+    p = torch.zeros(Nb, H + 2, W + 2, C, device="cuda", dtype=_F64)
+    p[:, 1:-1, 1:-1] = t
+    for k in range(9):
+        yield k, p[:, k // 3:k // 3 + H, k % 3:k % 3 + W].reshape(-1, C)
+
+
+def _exact_conv(s):
+    w, gamma, eps = _d(s["w"]), _d(s["gamma"]), _f32(1e-5)
+    Kf, _, _, C = w.shape
+    w = w.reshape(Kf, 9, C)
+    y = sum(x @ w[:, k].t() for k, x in _taps(s["x"]))
+    mean, var = y.mean(0), y.var(0, unbiased=False)
+    istd = 1.0 / torch.sqrt(var + eps)
+    xh = (y - mean) * istd
+    z = torch.relu(gamma * xh + _d(s["beta"]))
+    dz = _d(s["dz"]).reshape(-1, Kf) * (z > 0)
+    dgamma, dbeta = (dz * xh).sum(0), dz.sum(0)
+    dy = (gamma * istd * (dz - dbeta / len(y) - xh * (dgamma / len(y)))).reshape(s["dz"].shape)
+    dx = sum(g @ w[:, 8 - k] for k, g in _taps(dy))
+    dy = dy.reshape(-1, Kf)
+    dw = torch.stack([dy.t() @ x for _, x in _taps(s["x"])], 1)
+    return {"y": y.reshape(s["y"].shape), "z": z.reshape(s["z"].shape), "dx": dx.reshape(s["dx"].shape), "dw": dw.reshape(s["dw"].shape), "mean": mean, "var": var,
+            "dgamma": dgamma, "dbeta": dbeta, "flag": None}
+
+
+def _exact_update(s):
+    kind = s["kind"]
+    if kind == "stats" or not all(torch.isfinite(it[2]).all() for it in s["items"]):
+        return None                                                         # counts, or a step that is to be dropped
+    lr, mu, inv, out = _f32(1e-3), _f32(0.9), 2.0 ** -16, {"scaler": None}
+    if kind in ("momentum", "fused"):
+        res = []
+        for w, _, grad, _ in s["items"][-16:]:
+            m = _d(grad) * inv
+            w = _d(w) - lr * m
+            res += [w, m, w]
+        if kind == "fused":
+            out.update(flag=None, w=res[0], m=res[1], w16=res[2])
+        else:
+            out["items"] = res
+        return out
+    w, _, grad, _ = s["items"][0]
+    g = _d(grad) * inv
+    if s["clip"]:
+        norm = g.norm()
+        g *= min(1.0, 1.0 / norm.item())
+        out["norm"] = norm.reshape(1)
+    second = None
+    if kind == "nesterov":
+        m, step = g, lr * (g + mu * g)
+    elif kind == "adagrad":
+        m = g * g
+        step = lr * g / (m.sqrt() + _f32(1e-8))
+    else:
+        m, second = _f32(1.0 - 0.9) * g, _f32(1.0 - 0.999) * g * g
+        step = lr * (m / _f32(1.0 - 0.9 ** 10)) / ((second / _f32(1.0 - 0.999 ** 10)).sqrt() + _f32(1e-8))
+    w = _d(w) - step
+    out.update(w=w, m=m, second=second, w16=w)
+    return out
+
+
+def _exact_loss(s):
+    rows, grad = _softmax_xent(_d(s["logits"]), s["labels"], 128.0)
+    return {"loss": rows.mean().reshape(1), "rows": rows, "dlogits": grad}
+
+
+_EXACT = {"mlp": _exact_mlp, "layer": _exact_layer, "recurrent": _exact_recurrent, "conv": _exact_conv, "update": _exact_update, "loss": _exact_loss}
+
+
 # ---------------------------------------------------------------- what the measuring program calls
 _FAMILIES = {"mlp": (_prepare_mlp, _run_mlp, _work_mlp), "layer": (_prepare_layer, _run_layer, _work_layer),
              "recurrent": (_prepare_recurrent, _run_recurrent, _work_recurrent), "conv": (_prepare_conv, _run_conv, _work_conv),
@@ -417,6 +566,10 @@ def prepare(case, seed):
 
 def run(state):
     return _FAMILIES[state["family"]][1](state)
+
+
+def exact(case, seed):
+    return _EXACT[case["family"]](_FAMILIES[case["family"]][0](case, _gen(seed)))
 
 
 def work(case):
