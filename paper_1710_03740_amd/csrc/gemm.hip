@@ -2,40 +2,20 @@
 // (paper Sec. 3.3), for the three passes of a layer (Sec. 3.1 / Fig. 1) and for
 // the 3x3 convolution as an implicit GEMM.  gfx950 only.
 //
-// Four kernels compute C[i,j] = sum_r A(i,r) * B(r,j):
-//   k_gemm        the general one: any shape, alignment and operand view (plain matrices, gathered image windows,
-//                 filter slices), FP16 / FP32 / accumulating stores, split partials;
+// Kernels that compute C[i,j] = sum_r A(i,r) * B(r,j):
 //   k_gemm_dma64  whole 256 x 256 tiles of aligned operands - plain matrices, or the convolution's gathered image and
 //                 filter - streamed global -> LDS in stages of reduction depth 64, one wavefront per SIMD; FP16 store,
 //                 or (second instance) FP32 store / accumulate / split partials.  The square 4096^3 workload runs here;
 //   k_gemm_dma4   the same in stages of depth 32: 128 x 256 tiles (few-row outputs, split or not) and the convolution's
 //                 weight gradient with its per-tap gathered operand;
 //   k_gemm_dma    depth 32 with two wavefronts per SIMD: FP16 outputs with odd row strides, FP32 outputs over short
-//                 reductions.
+//                 reductions;
+//   k_gemm_ring, k_gemm_any (gemm_ring.hip): every other shape, alignment and convolution.
 // k_split_reduce / k_split_reduce4 add split partials in split order.
-//
-// k_gemm works on a BM x BN tile per workgroup with v_mfma_f32_32x32x16_f16.  Operands differ only in how a
-// tile is fetched:
-//   * "RC" operands are contiguous along the reduction index r: a thread fetches
-//     16-byte chunks of 8 r-values and stores them to LDS unchanged;
-//   * "OC" operands are contiguous along the outer index (i or j): a thread
-//     fetches a 4(r) x 8(outer) patch and transposes it in registers on the way
-//     to LDS.
-// Either way LDS holds [outer][64 r-values] rows of 128 bytes whose 16-byte
-// chunks are XOR-swizzled, so MFMA fragments are single ds_read_b128's.
-// LDS is double buffered: global loads for tile t+1 are issued before the MFMAs
-// of tile t and written to the other buffer after them; one barrier per tile.
-#include "mpt_internal.h"
+#include "gemm_parts.h"
 #include <algorithm>
 #include <mutex>
 #include <type_traits>
-
-typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-typedef _Float16 half4 __attribute__((ext_vector_type(4)));
-typedef float float16v __attribute__((ext_vector_type(16)));
-typedef float float4v __attribute__((ext_vector_type(4)));
-typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
-typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
 
 #ifndef MPT_GEMM_DEPTH_DEFAULT
 #define MPT_GEMM_DEPTH_DEFAULT 64  // reduction depth per stage of the streamed 256 x 256 kernel: 64 (k_gemm_dma64) or 32 (k_gemm_dma4)
@@ -43,209 +23,10 @@ typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
 
 namespace {
 
-constexpr int BK = 64;            // reduction depth of one LDS tile
-constexpr int ROWB = BK * 2;      // bytes per LDS row
+using namespace mpt_gemm;
 
-// ---------------------------------------------------------------- exact 32-bit division by an invariant
-struct FastDiv {
-  uint32_t d, m, s;               // q = (umulhi(m, n) + n') >> s  (round-up method)
-  __host__ __device__ FastDiv() : d(1), m(0), s(0) {}
-  explicit FastDiv(uint32_t div) : d(div) {
-    if (div <= 1) { m = 0; s = 0; d = 1; return; }
-    uint32_t l = 0;
-    while ((1ull << l) < div) ++l;                                 // l = ceil(log2 d), 1..32
-    m = (uint32_t)(((1ull << 32) * ((1ull << l) - div)) / div + 1);
-    s = l - 1;
-  }
-  __device__ __forceinline__ uint32_t div(uint32_t n) const {
-    if (d == 1) return n;
-    const uint32_t t = __umulhi(m, n);
-    return (t + ((n - t) >> 1)) >> s;
-  }
-  __device__ __forceinline__ void divmod(uint32_t n, uint32_t& q, uint32_t& r) const {
-    q = div(n);
-    r = n - q * d;
-  }
-};
+constexpr int BK = 64;            // reduction depth of one tile of the planner
 
-// ---------------------------------------------------------------- operand views
-// chunk(o, r, nvalid): address of the chunk that starts at outer index o and
-// reduction index r, and how many of its 8 elements exist (0 => do not touch).
-// RC views: the chunk runs along r.  OC views: the chunk runs along o.
-
-struct MatRC {                     // element (o, r) at base[o*ld + r]
-  const uint16_t* base; int64_t ld; int O, R;
-  static constexpr bool kRC = true;
-  __device__ __forceinline__ const uint16_t* chunk(int o, int r, int& nv) const {
-    nv = (o < O) ? min(max(R - r, 0), 8) : 0;
-    return base + (int64_t)o * ld + r;
-  }
-};
-
-struct MatOC {                     // element (o, r) at base[r*ld + o]
-  const uint16_t* base; int64_t ld; int O, R;
-  static constexpr bool kRC = false;
-  __device__ __forceinline__ const uint16_t* chunk(int o, int r, int& nv) const {
-    nv = (r < R) ? min(max(O - o, 0), 8) : 0;
-    return base + (int64_t)r * ld + o;
-  }
-};
-
-// Gathered image rows for the 3x3 convolution, stride 1, pad 1.
-// Outer index o = flat pixel (n, y, x); reduction index r = tap * Cc + c with
-// tap = 3*tr + ts.  Source pixel is (y + sgn*(tr-1), x + sgn*(ts-1)); sgn = +1
-// fetches the forward window, sgn = -1 the mirrored window of the input gradient.
-struct ImgRC {
-  const uint16_t* base; int H, W, Cc, O, R, sgn;
-  FastDiv dHW, dW, dC;
-  static constexpr bool kRC = true;
-  __device__ __forceinline__ const uint16_t* chunk(int o, int r, int& nv) const {
-    nv = 0;
-    if (o >= O || r >= R) return base;
-    uint32_t n, rem, y, x, tap, c;
-    dHW.divmod((uint32_t)o, n, rem);
-    dW.divmod(rem, y, x);
-    dC.divmod((uint32_t)r, tap, c);
-    const int tr = (int)tap / 3, ts = (int)tap - 3 * tr;
-    const int yy = (int)y + sgn * (tr - 1), xx = (int)x + sgn * (ts - 1);
-    if (yy < 0 || yy >= H || xx < 0 || xx >= W) return base;
-    nv = 8;
-    return base + (((int64_t)n * H + yy) * W + xx) * Cc + c;
-  }
-};
-
-// Same gather with the roles swapped: reduction index r = flat pixel (n, y, x),
-// outer index o = tap * Cc + c (weight-gradient pass reads the forward window).
-struct ImgOC {
-  const uint16_t* base; int H, W, Cc, O, R;
-  FastDiv dHW, dW, dC;
-  static constexpr bool kRC = false;
-  __device__ __forceinline__ const uint16_t* chunk(int o, int r, int& nv) const {
-    nv = 0;
-    if (o >= O || r >= R) return base;
-    uint32_t n, rem, y, x, tap, c;
-    dHW.divmod((uint32_t)r, n, rem);
-    dW.divmod(rem, y, x);
-    dC.divmod((uint32_t)o, tap, c);
-    const int tr = (int)tap / 3, ts = (int)tap - 3 * tr;
-    const int yy = (int)y + tr - 1, xx = (int)x + ts - 1;
-    if (yy < 0 || yy >= H || xx < 0 || xx >= W) return base;
-    nv = 8;
-    return base + (((int64_t)n * H + yy) * W + xx) * Cc + c;
-  }
-};
-
-// Filter w[k][tap][c] read as B(r = tap*Kf + k, o = c) for the input-gradient pass.
-struct FilterOC {
-  const uint16_t* base; int Cc, Kf, O, R;
-  FastDiv dK;
-  static constexpr bool kRC = false;
-  __device__ __forceinline__ const uint16_t* chunk(int o, int r, int& nv) const {
-    nv = 0;
-    if (o >= O || r >= R) return base;
-    uint32_t tap, k;
-    dK.divmod((uint32_t)r, tap, k);
-    nv = min(O - o, 8);
-    return base + ((int64_t)k * 9 + tap) * Cc + o;
-  }
-};
-
-// ---------------------------------------------------------------- chunk fetch
-// `safe`: an address that can always be read (the view's first element).  The element-wise form has no branch around
-// its loads: each reads an existing element (its own, the chunk's last, or `safe`) and the value is kept only if the
-// element exists.  Behind branches the loads went out one at a time, each waited for: a 256 x 1024 output over a
-// reduction of 10 took 20 us, all of it in two such chunks per operand.
-template <bool ALIGNED>
-__device__ __forceinline__ uint4v fetch(const uint16_t* p, int nv, const uint16_t* safe) {
-  uint4v v = {0u, 0u, 0u, 0u};
-  if constexpr (ALIGNED) {
-    if (nv == 8) v = *reinterpret_cast<const uint4v*>(p);
-  } else {
-    const uint16_t* q = nv > 0 ? p : safe;
-    const int last = max(nv, 1) - 1;
-    uint16_t e[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const uint16_t x = q[min(i, last)];
-      e[i] = (i < nv) ? x : (uint16_t)0;
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = (uint32_t)e[2 * i] | ((uint32_t)e[2 * i + 1] << 16);
-  }
-  return v;
-}
-
-// LDS byte offset of 16-byte chunk kc (0..7) of row `row`.
-__device__ __forceinline__ int lds_off(int row, int kc) {
-  return row * ROWB + (((kc ^ row ^ (row >> 3)) & 7) << 4);
-}
-
-// One operand tile in flight: 4 chunks per thread, whatever the flavour.
-template <class View, bool ALIGNED, int BO, int NT>
-struct TileLoader {
-  static_assert(BO * 8 == NT * 4, "4 chunks per thread");
-  uint4v reg[4];
-
-  __device__ __forceinline__ void load(const View& v, int o_base, int r_base, int t) {
-    if constexpr (View::kRC) {
-      const int kc = t & 7, row0 = t >> 3;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = row0 + i * (NT / 8);
-        int nv;
-        const uint16_t* p = v.chunk(o_base + row, r_base + kc * 8, nv);
-        reg[i] = fetch<ALIGNED>(p, nv, v.base);
-      }
-    } else {
-      const int oc = t % (BO / 8), rg = t / (BO / 8);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        int nv;
-        const uint16_t* p = v.chunk(o_base + oc * 8, r_base + rg * 4 + i, nv);
-        reg[i] = fetch<ALIGNED>(p, nv, v.base);
-      }
-    }
-  }
-
-  __device__ __forceinline__ void store(char* lds, int t) const {
-    if constexpr (View::kRC) {
-      const int kc = t & 7, row0 = t >> 3;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = row0 + i * (NT / 8);
-        *reinterpret_cast<uint4v*>(lds + lds_off(row, kc)) = reg[i];
-      }
-    } else {
-      // 4(r) x 8(o) patch -> eight rows of 4 r-values (8 bytes each)
-      const int oc = t % (BO / 8), rg = t / (BO / 8);
-      const int kc = rg >> 1, half = (rg & 1) << 3;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const uint32_t sel = (j & 1) ? 0x07060302u : 0x05040100u;
-        uint2v o2;
-        o2[0] = __builtin_amdgcn_perm(reg[1][j >> 1], reg[0][j >> 1], sel);
-        o2[1] = __builtin_amdgcn_perm(reg[3][j >> 1], reg[2][j >> 1], sel);
-        const int row = oc * 8 + j;
-        *reinterpret_cast<uint2v*>(lds + lds_off(row, kc) + half) = o2;
-      }
-    }
-  }
-};
-
-// ---------------------------------------------------------------- epilogue description
-struct Epilogue {
-  void* out;            // uint16_t* (FP16) or float* (FP32 / split partials)
-  int64_t ld;
-  int mode;             // 0: FP16 store, 1: FP32 store, 2: FP32 accumulate, 3: FP32 partial [split][I][J]
-  uint32_t* flag;       // nullable; OR 1 when an FP16/FP32 stored value is Inf/NaN (modes 0..2)
-  int act;              // FP16 store only.  0: none; 1: ReLU, store 0 unless the value is > 0;
-                        // 2: store 0 unless mask[i][j] > 0 (the ReLU of the layer below, backward)
-  const uint16_t* mask; // act == 2: FP16 matrix of the output's shape
-  int64_t ldmask;
-};
-
-// FP16 bit pattern of a value > 0 (Inf included, NaN not).
-__device__ __forceinline__ bool half_bits_positive(uint32_t b) { return (uint16_t)((b & 0xFFFFu) - 1u) < 0x7C00u; }
 // The mask values (act == 2) of 4 consecutive outputs of row i starting at column j, n of them inside the matrix
 // (n = 0: none, the mask's first element is read instead), packed like the outputs.  No branch around the loads, so a
 // caller can fetch the masks of a whole tile first and wait once: fetched one group at a time between the stores, each
@@ -260,44 +41,6 @@ __device__ __forceinline__ uint2v load_mask4(const Epilogue& ep, int64_t i, int6
   const uint32_t e0 = m[0], e1 = m[min(1, last)], e2 = m[min(2, last)], e3 = m[min(3, last)];
   return uint2v{e0 | (e1 << 16), e2 | (e3 << 16)};
 }
-// Pointwise stage of an FP16 store: 4 consecutive outputs (packed in hb); mk = their mask values when act == 2.
-__device__ __forceinline__ uint2v apply_act4(uint2v hb, const Epilogue& ep, uint2v mk) {
-  if (ep.act == 0) return hb;
-  uint32_t keep = 0;
-  const uint2v src = ep.act == 1 ? hb : mk;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) keep |= (uint32_t)half_bits_positive(src[e >> 1] >> ((e & 1) * 16)) << e;
-  hb[0] &= ((keep & 1u) ? 0x0000FFFFu : 0u) | ((keep & 2u) ? 0xFFFF0000u : 0u);
-  hb[1] &= ((keep & 4u) ? 0x0000FFFFu : 0u) | ((keep & 8u) ? 0xFFFF0000u : 0u);
-  return hb;
-}
-
-struct Problem {
-  int I, J, R;          // output rows, output cols, reduction length
-  int tiles_i, tiles_j, splits, ktiles_per_split;
-};
-
-// Workgroup id -> (tile_i, tile_j, split).  Consecutive ids land on different XCDs
-// (8 of them, round-robin), so ids are first regrouped per XCD and then walked in
-// panels of 4 tile-rows so that one XCD's L2 sees a compact block of tiles.
-__device__ __forceinline__ void tile_of(const Problem& pb, int wg, int& ti, int& tj, int& sp) {
-  const int per_split = pb.tiles_i * pb.tiles_j;
-  const int total = per_split * pb.splits;
-  const int xcd = wg & 7, local = wg >> 3;
-  const int n_per = total >> 3, rem = total & 7;
-  int id = xcd * n_per + min(xcd, rem) + local;
-  sp = id / per_split;
-  id -= sp * per_split;
-  constexpr int GM = 4;
-  const int panel = id / (GM * pb.tiles_j);
-  const int first_i = panel * GM;
-  const int rows = min(GM, pb.tiles_i - first_i);
-  const int in_panel = id - panel * GM * pb.tiles_j;
-  ti = first_i + in_panel % rows;
-  tj = in_panel / rows;
-}
-
-__device__ __forceinline__ bool half_bits_special(uint32_t b) { return (b & 0x7C00u) == 0x7C00u; }
 // Inf/NaN vote over many packed FP16 pairs at two instructions per pair: keep the running maximum of the exponent fields
 // of the low and of the high halves (v_pk_max_u16); a field of all ones anywhere shows in the maximum at the end.
 typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
@@ -335,168 +78,6 @@ __device__ __forceinline__ bool reduce_one(const float* __restrict__ part, int s
   return (__float_as_uint(s) & 0x7F800000u) == 0x7F800000u;
 }
 
-template <class AView, class BView, bool A_ALIGNED, bool B_ALIGNED, int BM, int BN, int WM, int WN>
-__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm(AView A, BView B, Problem pb, Epilogue ep) {
-  constexpr int NT = (BM / WM) * (BN / WN) * 64;
-  constexpr int FM = WM / 32, FN = WN / 32;
-  constexpr int A_BYTES = BM * ROWB, B_BYTES = BN * ROWB, STAGE = A_BYTES + B_BYTES;
-  extern __shared__ __attribute__((aligned(16))) char lds[];
-
-  const int t = threadIdx.x;
-  const int lane = t & 63, wave = t >> 6;
-  const int wm = wave / (BN / WN), wn = wave % (BN / WN);
-  int ti, tj, sp;
-  tile_of(pb, blockIdx.x, ti, tj, sp);
-  const int i0 = ti * BM, j0 = tj * BN;
-  const int kt_total = (pb.R + BK - 1) / BK;
-  const int kt_begin = sp * pb.ktiles_per_split;
-  const int kt_end = min(kt_begin + pb.ktiles_per_split, kt_total);
-
-  float16v acc[FM][FN];
-#pragma unroll
-  for (int a = 0; a < FM; ++a)
-#pragma unroll
-    for (int b = 0; b < FN; ++b)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
-
-  TileLoader<AView, A_ALIGNED, BM, NT> la;
-  TileLoader<BView, B_ALIGNED, BN, NT> lb;
-
-  // Mask values (act == 2) of the whole tile: fetched in one go - ahead of the first operand loads where the registers are there
-  // for it (the 256-thread tile), so that both round trips pass together; else before the first store.
-  constexpr bool kMasksEarly = NT == 256;
-  uint2v mk[FM][FN][4];
-#pragma unroll
-  for (int a = 0; a < FM; ++a)
-#pragma unroll
-    for (int b = 0; b < FN; ++b)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) mk[a][b][g] = uint2v{0u, 0u};
-  auto fetch_masks = [&]() {
-    if (!(ep.mode == 0 && ep.act == 2)) return;
-    const bool whole = (pb.J % 4) == 0 && (ep.ldmask % 4) == 0 && (reinterpret_cast<uintptr_t>(ep.mask) & 7) == 0;
-#pragma unroll
-    for (int a = 0; a < FM; ++a) {
-      const int i = i0 + wm * WM + a * 32 + (lane & 31);
-#pragma unroll
-      for (int b = 0; b < FN; ++b)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int j = j0 + wn * WN + b * 32 + g * 8 + ((lane >> 5) << 2);
-          mk[a][b][g] = load_mask4(ep, i, j, (i < pb.I && j < pb.J) ? min(4, pb.J - j) : 0, whole);
-        }
-    }
-  };
-  if constexpr (kMasksEarly) fetch_masks();
-  if (kt_begin < kt_end) {
-    la.load(A, i0, kt_begin * BK, t);
-    lb.load(B, j0, kt_begin * BK, t);
-    la.store(lds, t);
-    lb.store(lds + A_BYTES, t);
-  }
-  __syncthreads();
-
-  const int frag_row = lane & 31, frag_kc = lane >> 5;
-  int stage = 0;
-  for (int kt = kt_begin; kt < kt_end; ++kt) {
-    const bool more = kt + 1 < kt_end;
-    if (more) {
-      la.load(A, i0, (kt + 1) * BK, t);
-      lb.load(B, j0, (kt + 1) * BK, t);
-    }
-    const char* sa = lds + stage * STAGE;
-    const char* sb = sa + A_BYTES;
-#pragma unroll
-    for (int ks = 0; ks < BK / 16; ++ks) {
-      half8 fa[FM], fb[FN];
-#pragma unroll
-      for (int a = 0; a < FM; ++a)
-        fa[a] = *reinterpret_cast<const half8*>(sa + lds_off(wm * WM + a * 32 + frag_row, ks * 2 + frag_kc));
-#pragma unroll
-      for (int b = 0; b < FN; ++b)
-        fb[b] = *reinterpret_cast<const half8*>(sb + lds_off(wn * WN + b * 32 + frag_row, ks * 2 + frag_kc));
-      // operands swapped: the MFMA sees (B-fragment) x (A-fragment), so each lane ends
-      // up owning 4 consecutive output columns j for one output row i.
-#pragma unroll
-      for (int a = 0; a < FM; ++a)
-#pragma unroll
-        for (int b = 0; b < FN; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fb[b], fa[a], acc[a][b], 0, 0, 0);
-    }
-    if (more) {
-      char* dst = lds + (stage ^ 1) * STAGE;
-      la.store(dst, t);
-      lb.store(dst + A_BYTES, t);
-    }
-    __syncthreads();
-    stage ^= 1;
-  }
-
-  // ---- epilogue.  acc[a][b][v]: row i = lane%32, col j = 8*(v/4) + 4*(lane/32) + v%4 of the 32x32 block.
-  bool bad = false;
-  const int64_t split_off = (ep.mode == 3) ? (int64_t)sp * pb.I * pb.J : 0;
-  if constexpr (!kMasksEarly) fetch_masks();
-#pragma unroll
-  for (int a = 0; a < FM; ++a) {
-    const int i = i0 + wm * WM + a * 32 + (lane & 31);
-#pragma unroll
-    for (int b = 0; b < FN; ++b) {
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int j = j0 + wn * WN + b * 32 + g * 8 + ((lane >> 5) << 2);
-        if (i >= pb.I || j >= pb.J) continue;
-        const int nj = min(4, pb.J - j);
-        float x[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] = acc[a][b][g * 4 + e];
-        if (ep.mode == 0) {
-          uint16_t* o = reinterpret_cast<uint16_t*>(ep.out) + (int64_t)i * ep.ld + j;
-          half4 h;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) h[e] = (_Float16)x[e];
-          const uint2v hb = apply_act4(__builtin_bit_cast(uint2v, h), ep, mk[a][b][g]);
-          if (ep.flag) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) bad |= (e < nj) & half_bits_special(hb[e >> 1] >> ((e & 1) * 16));
-          }
-          if (nj == 4 && ((reinterpret_cast<uintptr_t>(o) & 7) == 0)) {
-            *reinterpret_cast<uint2v*>(o) = hb;
-          } else {
-            for (int e = 0; e < nj; ++e) o[e] = (uint16_t)(hb[e >> 1] >> ((e & 1) * 16));
-          }
-        } else {
-          float* o = reinterpret_cast<float*>(ep.out) + split_off + (int64_t)i * ep.ld + j;
-          if (nj == 4 && (reinterpret_cast<uintptr_t>(o) & 15) == 0) {     // 16 bytes per lane
-            float4v v = {x[0], x[1], x[2], x[3]};
-            if (ep.mode == 2) {
-              const float4v old = *reinterpret_cast<const float4v*>(o);
-#pragma unroll
-              for (int e = 0; e < 4; ++e) v[e] = __fadd_rn(old[e], v[e]);
-            }
-            if (ep.flag && ep.mode != 3) {
-#pragma unroll
-              for (int e = 0; e < 4; ++e) bad |= (__float_as_uint(v[e]) & 0x7F800000u) == 0x7F800000u;
-            }
-            *reinterpret_cast<float4v*>(o) = v;
-          } else {
-            for (int e = 0; e < nj; ++e) {
-              float v = x[e];
-              if (ep.mode == 2) v = __fadd_rn(o[e], v);
-              if (ep.flag && ep.mode != 3) bad |= (__float_as_uint(v) & 0x7F800000u) == 0x7F800000u;
-              o[e] = v;
-            }
-          }
-        }
-      }
-    }
-  }
-  if (ep.flag != nullptr && ep.mode != 3) {
-    const unsigned long long vote = __builtin_amdgcn_ballot_w64(bad);
-    if (vote != 0ull && lane == 0) atomicOr(ep.flag, 1u);
-  }
-}
-
 // ---------------------------------------------------------------- streamed variant for whole 256x256 tiles of plain matrices
 // Same contraction and tile on v_mfma_f32_16x16x32_f16 blocks, but operand slices go global -> LDS with the LDS-direct load
 // (global_load_lds_dwordx4: no staging registers), through a ring of four 32 KiB stages of reduction depth 32,
@@ -513,14 +94,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm(AView A, BV
 // The swizzles are applied by choosing which global chunk each lane fetches, since an LDS-direct load writes lane l
 // at base + 16*l.  Requirements (checked by the host): I, J multiples of 256, R a multiple of 64, 16-byte aligned
 // operands, FP16 store or FP32 split partials.
-typedef __attribute__((address_space(3))) void* lds_void_ptr;
-typedef const __attribute__((address_space(1))) void* global_void_ptr;
-typedef __fp16 fp16x4_t __attribute__((ext_vector_type(4)));
-
 struct DmaMat { const uint16_t* base; int64_t ld; };
-
-// XOR key of reduction row r for the 32-byte units of an OC stage row (see the layout note above).
-__device__ __forceinline__ int oc_key(int r) { return (r & 3) | ((r >> 1) & 4); }
 
 template <bool RC>
 struct DmaOperand {
@@ -551,12 +125,7 @@ struct DmaOperand {
   }
 };
 
-// LDS reads are issued through inline assembly so that their completion is tracked here, by explicit
-// s_waitcnt on the in-order LGKM counter, and not by the compiler, which would otherwise put a full vmcnt(0)
-// wait in front of every read that follows an LDS-direct load.
-__device__ __forceinline__ uint32_t lds_offset(const char* p) {
-  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
-}
+// LDS reads by inline assembly: see lds_offset in gemm_parts.h.
 __device__ __forceinline__ half8 lds_read_b128(uint32_t addr) {
   half8 v;
   asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(addr) : "memory");
@@ -605,20 +174,6 @@ struct FragAddr {
 // The same fragment addressed without arithmetic in the loop: the lane's absolute LDS address inside the first slot of
 // each pair of ring slots sits in a register, and the slot within the pair and the operand's offset inside a stage go
 // into the read's immediate offset (16 bits: a pair of slots plus an operand offset stays below 64 KiB).
-template <int IMM>
-__device__ __forceinline__ half8 lds_read_b128_imm(uint32_t addr) {
-  static_assert(IMM >= 0 && IMM < 65536, "LDS immediate offset");
-  half8 v;
-  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(IMM) : "memory");
-  return v;
-}
-template <int IMM>
-__device__ __forceinline__ uint2v lds_read_tr_b64_imm(uint32_t addr) {
-  static_assert(IMM >= 0 && IMM < 65536, "LDS immediate offset");
-  uint2v v;
-  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(IMM) : "memory");
-  return v;
-}
 template <bool RC, int BO = 256>
 struct FragAddr4 {
   uint32_t at[2][RC ? 1 : 2];
@@ -633,7 +188,7 @@ struct FragAddr4 {
   template <int PAIR, int IMM>
   __device__ __forceinline__ half8 read() const {
     if constexpr (RC) {
-      return lds_read_b128_imm<IMM>(at[PAIR][0]);
+      return __builtin_bit_cast(half8, lds_read_b128_imm<IMM>(at[PAIR][0]));
     } else {
       const uint2v lo = lds_read_tr_b64_imm<IMM>(at[PAIR][0]);
       const uint2v hi = lds_read_tr_b64_imm<IMM>(at[PAIR][1]);
@@ -642,12 +197,6 @@ struct FragAddr4 {
     }
   }
 };
-
-// The compiler takes an inline-assembly LDS read to be complete when the statement ends.  A fragment that nothing
-// consumes afterwards (the prefetch past the last stage) would leave its registers free for reuse, for instance as the
-// address of the next LDS-direct load, while the data is still on its way and lands on top of the new value.  Passing
-// such fragments through this statement after the final wait keeps their registers reserved until then.
-__device__ __forceinline__ void keep_until_here(const half8& f) { asm volatile("" ::"v"(f)); }
 
 // Wait until at most NEWER LDS reads issued after these fragments are still outstanding (the LGKM counter is
 // in order and 4 bits wide); the fragments pass through the statement so that their consumers stay below it.
@@ -1516,7 +1065,7 @@ struct FragAddr64 {
   template <int SLOT4>                                               // SLOT4 = 2 * slot + half stage
   __device__ __forceinline__ half8 read() const {
     if constexpr (RC) {
-      return lds_read_b128_imm<(SLOT4 >> 1) * 32768>(at[SLOT4 & 1]);
+      return __builtin_bit_cast(half8, lds_read_b128_imm<(SLOT4 >> 1) * 32768>(at[SLOT4 & 1]));
     } else {
       constexpr int IMM = (SLOT4 >> 1) * 32768 + (SLOT4 & 1) * 16384;
       const uint2v lo = lds_read_tr_b64_imm<IMM>(at[0]);
@@ -1859,8 +1408,6 @@ struct Plan {
   int splits, ktiles_per_split, tiles_i, tiles_j;
 };
 
-constexpr int kCUs = 256;
-
 Plan make_plan(int64_t I, int64_t J, int64_t R, bool allow_split) {
   static const int force_tile = MPT_TUNABLE("MPT_GEMM_TILE", 0);      // 128 / 256 force a tile size (tuning builds only)
   static const int force_split = MPT_TUNABLE("MPT_GEMM_SPLITS", 0);   // >0 forces a split count (tuning builds only)
@@ -1933,136 +1480,142 @@ bool plan_split128(int64_t I, int64_t J, int64_t R, Plan& p) {
   return p.splits >= 2;
 }
 
-template <class AView, class BView, bool A_ALIGNED, bool B_ALIGNED>
-int launch_tiles(hipStream_t s, const AView& A, const BView& B, const Plan& pl, int I, int J, int R, const Epilogue& ep) {
+template <bool A_RC, bool B_RC>
+bool try_launch_dma(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool aligned, const Plan& pl, int I, int J, int R, const Epilogue& ep, int& status) {
+  static const bool enabled = MPT_TUNABLE("MPT_GEMM_STREAMED", 1) != 0;
+  if (!enabled || !aligned || !pl.big || (I % 256) || (J % 256) || (R % 64)) return false;
+  if (ep.mode != 0 && ((ep.ld % 4) || !mpt_aligned(ep.out, 16))) return false;      // FP32 outputs go out 16 bytes per lane
+  // FP16 stores of unsplit problems into 16-byte aligned rows take the one-wavefront-per-SIMD kernel (same speed at one
+  // tile per CU, about 5 % faster over several); split partials and odd output strides take k_gemm_dma.
+  static const int nwaves = MPT_TUNABLE("MPT_GEMM_WAVES", 4);           // 8 forces k_gemm_dma (tuning builds only)
+  const bool four = nwaves == 4 && ep.mode == 0 && pl.splits == 1 && (ep.ld % 8) == 0 && mpt_aligned(ep.out, 16) &&
+                    (ep.act != 2 || ((ep.ldmask % 8) == 0 && mpt_aligned(ep.mask, 16)));
+  auto k4 = k_gemm_dma<A_RC, B_RC, 4>;
+  static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void*>(k4), hipFuncAttributeMaxDynamicSharedMemorySize, 4 * 32768), true);
+  (void)once;
+#ifdef MPT_TUNING
+  static const int nstage = MPT_TUNABLE("MPT_GEMM_STAGES", 4);          // 4 or 5 ring slots of 32 KiB
+  auto k5 = k_gemm_dma<A_RC, B_RC, 5>;
+  auto kw4 = k_gemm_dma4<DmaOperand4<A_RC, 256>, DmaOperand4<B_RC, 256>, 256>;
+  static bool once_t = ((void)hipFuncSetAttribute(reinterpret_cast<const void*>(k5), hipFuncAttributeMaxDynamicSharedMemorySize, 5 * 32768),
+                        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kw4), hipFuncAttributeMaxDynamicSharedMemorySize, 4 * 32768), true);
+  (void)once_t;
+#endif
   Problem pb{I, J, R, pl.tiles_i, pl.tiles_j, pl.splits, pl.ktiles_per_split};
   const unsigned grid = (unsigned)((int64_t)pl.tiles_i * pl.tiles_j * pl.splits);
-  if (pl.big) {
-    auto k = k_gemm<AView, BView, A_ALIGNED, B_ALIGNED, 256, 256, 128, 64>;
-    constexpr int lds = 2 * (256 + 256) * ROWB;
-    static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds), true);
-    (void)once;
-    hipLaunchKernelGGL(k, dim3(grid), dim3(512), lds, s, A, B, pb, ep);
-  } else {
-    auto k = k_gemm<AView, BView, A_ALIGNED, B_ALIGNED, 128, 128, 64, 64>;
-    constexpr int lds = 2 * (128 + 128) * ROWB;
-    static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds), true);
-    (void)once;
-    hipLaunchKernelGGL(k, dim3(grid), dim3(256), lds, s, A, B, pb, ep);
-  }
-  MPT_LAUNCH_CHECK();
-  return MPT_OK;
-}
-
-// Plain-matrix views can take the streamed kernel.
-template <class V> struct DmaKind { static constexpr bool ok = false; static constexpr bool rc = true; };
-template <> struct DmaKind<MatRC> { static constexpr bool ok = true; static constexpr bool rc = true; };
-template <> struct DmaKind<MatOC> { static constexpr bool ok = true; static constexpr bool rc = false; };
-
-template <class AView, class BView>
-bool try_launch_dma(hipStream_t s, const AView& A, const BView& B, bool aligned, const Plan& pl, int I, int J, int R, const Epilogue& ep, int& status) {
-  if constexpr (DmaKind<AView>::ok && DmaKind<BView>::ok) {
-    static const bool enabled = MPT_TUNABLE("MPT_GEMM_STREAMED", 1) != 0;
-    if (!enabled || !aligned || !pl.big || (I % 256) || (J % 256) || (R % 64)) return false;
-    if (ep.mode != 0 && ((ep.ld % 4) || !mpt_aligned(ep.out, 16))) return false;      // FP32 outputs go out 16 bytes per lane
-    // FP16 stores of unsplit problems into 16-byte aligned rows take the one-wavefront-per-SIMD kernel (same speed at one
-    // tile per CU, about 5 % faster over several); split partials and odd output strides take k_gemm_dma.
-    static const int nwaves = MPT_TUNABLE("MPT_GEMM_WAVES", 4);           // 8 forces k_gemm_dma (tuning builds only)
-    const bool four = nwaves == 4 && ep.mode == 0 && pl.splits == 1 && (ep.ld % 8) == 0 && mpt_aligned(ep.out, 16) &&
-                      (ep.act != 2 || ((ep.ldmask % 8) == 0 && mpt_aligned(ep.mask, 16)));
-    auto k4 = k_gemm_dma<DmaKind<AView>::rc, DmaKind<BView>::rc, 4>;
-    static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void*>(k4), hipFuncAttributeMaxDynamicSharedMemorySize, 4 * 32768), true);
-    (void)once;
+  auto k64 = k_gemm_dma64<DmaOperand64<A_RC>, DmaOperand64<B_RC>>;
+  auto k64f = k_gemm_dma64<DmaOperand64<A_RC>, DmaOperand64<B_RC>, true>;
+  static bool once64 = ((void)hipFuncSetAttribute(reinterpret_cast<const void*>(k64), hipFuncAttributeMaxDynamicSharedMemorySize, 4 * 32768),
+                        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k64f), hipFuncAttributeMaxDynamicSharedMemorySize, 4 * 32768), true);
+  (void)once64;
+  static const int depth32_f32 = MPT_TUNABLE("MPT_GEMM_F32_DEPTH32", 0);   // 1: FP32 outputs on k_gemm_dma (tuning builds only)
 #ifdef MPT_TUNING
-    static const int nstage = MPT_TUNABLE("MPT_GEMM_STAGES", 4);          // 4 or 5 ring slots of 32 KiB
-    auto k5 = k_gemm_dma<DmaKind<AView>::rc, DmaKind<BView>::rc, 5>;
-    auto kw4 = k_gemm_dma4<DmaOperand4<DmaKind<AView>::rc, 256>, DmaOperand4<DmaKind<BView>::rc, 256>, 256>;
-    static bool once_t = ((void)hipFuncSetAttribute(reinterpret_cast<const void*>(k5), hipFuncAttributeMaxDynamicSharedMemorySize, 5 * 32768),
-                          (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kw4), hipFuncAttributeMaxDynamicSharedMemorySize, 4 * 32768), true);
-    (void)once_t;
+  static const int depth = MPT_TUNABLE("MPT_GEMM_DEPTH", MPT_GEMM_DEPTH_DEFAULT);   // 32: k_gemm_dma4
+  if (four && depth != 64) {
+    hipLaunchKernelGGL(kw4, dim3(grid), dim3(256), 4 * 32768, s, DmaMat{A.base, A.ld}, DmaMat{B.base, B.ld}, pb, ep);
+  } else if (!four && nstage == 5) {
+    hipLaunchKernelGGL(k5, dim3(grid), dim3(512), 5 * 32768, s, DmaMat{A.base, A.ld}, DmaMat{B.base, B.ld}, pb, ep);
+  } else
 #endif
-    Problem pb{I, J, R, pl.tiles_i, pl.tiles_j, pl.splits, pl.ktiles_per_split};
-    const unsigned grid = (unsigned)((int64_t)pl.tiles_i * pl.tiles_j * pl.splits);
-    auto k64 = k_gemm_dma64<DmaOperand64<DmaKind<AView>::rc>, DmaOperand64<DmaKind<BView>::rc>>;
-    auto k64f = k_gemm_dma64<DmaOperand64<DmaKind<AView>::rc>, DmaOperand64<DmaKind<BView>::rc>, true>;
-    static bool once64 = ((void)hipFuncSetAttribute(reinterpret_cast<const void*>(k64), hipFuncAttributeMaxDynamicSharedMemorySize, 4 * 32768),
-                          (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k64f), hipFuncAttributeMaxDynamicSharedMemorySize, 4 * 32768), true);
-    (void)once64;
-    static const int depth32_f32 = MPT_TUNABLE("MPT_GEMM_F32_DEPTH32", 0);   // 1: FP32 outputs on k_gemm_dma (tuning builds only)
-#ifdef MPT_TUNING
-    static const int depth = MPT_TUNABLE("MPT_GEMM_DEPTH", MPT_GEMM_DEPTH_DEFAULT);   // 32: k_gemm_dma4
-    if (four && depth != 64) {
-      hipLaunchKernelGGL(kw4, dim3(grid), dim3(256), 4 * 32768, s, DmaMat{A.base, A.ld}, DmaMat{B.base, B.ld}, pb, ep);
-    } else if (!four && nstage == 5) {
-      hipLaunchKernelGGL(k5, dim3(grid), dim3(512), 5 * 32768, s, DmaMat{A.base, A.ld}, DmaMat{B.base, B.ld}, pb, ep);
-    } else
-#endif
-    if (four) {
-      hipLaunchKernelGGL(k64, dim3(grid), dim3(256), 4 * 32768, s, DmaMat{A.base, A.ld}, DmaMat{B.base, B.ld}, pb, ep);
-    } else if (ep.mode != 0 && depth32_f32 == 0 && pl.ktiles_per_split >= 8) {
-      // FP32 outputs (store, accumulate, split partials; 16 bytes per lane, checked above) on the same kernel, unless
-      // the reduction is short: over 4 stages k_gemm_dma's two wavefronts per SIMD cover the fill and the write-out of
-      // each other (projection weight gradient 8192 x 1024 x 256, accumulated: 24.5 us there, 28.4 us here)
-      hipLaunchKernelGGL(k64f, dim3(grid), dim3(256), 4 * 32768, s, DmaMat{A.base, A.ld}, DmaMat{B.base, B.ld}, pb, ep);
-    } else {
-      hipLaunchKernelGGL(k4, dim3(grid), dim3(512), 4 * 32768, s, DmaMat{A.base, A.ld}, DmaMat{B.base, B.ld}, pb, ep);
-    }
-    status = hipGetLastError() == hipSuccess ? MPT_OK : MPT_ERR_HIP;
-    return true;
+  if (four) {
+    hipLaunchKernelGGL(k64, dim3(grid), dim3(256), 4 * 32768, s, DmaMat{A.base, A.ld}, DmaMat{B.base, B.ld}, pb, ep);
+  } else if (ep.mode != 0 && depth32_f32 == 0 && pl.ktiles_per_split >= 8) {
+    // FP32 outputs (store, accumulate, split partials; 16 bytes per lane, checked above) on the same kernel, unless
+    // the reduction is short: over 4 stages k_gemm_dma's two wavefronts per SIMD cover the fill and the write-out of
+    // each other (projection weight gradient 8192 x 1024 x 256, accumulated: 24.5 us there, 28.4 us here)
+    hipLaunchKernelGGL(k64f, dim3(grid), dim3(256), 4 * 32768, s, DmaMat{A.base, A.ld}, DmaMat{B.base, B.ld}, pb, ep);
   } else {
-    return false;
+    hipLaunchKernelGGL(k4, dim3(grid), dim3(512), 4 * 32768, s, DmaMat{A.base, A.ld}, DmaMat{B.base, B.ld}, pb, ep);
   }
+  status = hipGetLastError() == hipSuccess ? MPT_OK : MPT_ERR_HIP;
+  return true;
 }
 
 // Problems with few 256-row tiles but many 128 x 256 ones (a batch-256 product against a wide weight matrix): one
 // unsplit launch of the 128-row variant of the one-wavefront-per-SIMD kernel fills the chip where 256 x 256 tiles
 // leave half of it idle; a workspace, if given, is not needed then.
-template <class AView, class BView>
-bool try_launch_dma128(hipStream_t s, const AView& A, const BView& B, bool aligned, int I, int J, int R, const Epilogue& ep, int& status) {
-  if constexpr (DmaKind<AView>::ok && DmaKind<BView>::ok) {
-    static const bool enabled = MPT_TUNABLE("MPT_GEMM_STREAMED", 1) != 0 && MPT_TUNABLE("MPT_GEMM_WAVES", 4) == 4 &&
-                                MPT_TUNABLE("MPT_GEMM_TILE128", 1) != 0;
-    if (!enabled || !aligned || (I % 128) || (J % 256) || (R % 64) || ep.mode != 0) return false;
-    if ((ep.ld % 8) || !mpt_aligned(ep.out, 16) || (ep.act == 2 && ((ep.ldmask % 8) || !mpt_aligned(ep.mask, 16)))) return false;
-    const int64_t t256 = ((int64_t)(I + 255) / 256) * (J / 256), t128 = (int64_t)(I / 128) * (J / 256);
-    if (t256 >= kCUs * 3 / 4 || t128 < kCUs * 3 / 8) return false;
-    auto k = k_gemm_dma4<DmaOperand4<DmaKind<AView>::rc, 128>, DmaOperand4<DmaKind<BView>::rc, 256>, 128>;
-    constexpr int lds = 4 * (128 + 256) * 64;
-    static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds), true);
-    (void)once;
-    Problem pb{I, J, R, I / 128, J / 256, 1, R / 64};
-    hipLaunchKernelGGL(k, dim3((unsigned)t128), dim3(256), lds, s, DmaMat{A.base, A.ld}, DmaMat{B.base, B.ld}, pb, ep);
-    status = hipGetLastError() == hipSuccess ? MPT_OK : MPT_ERR_HIP;
-    return true;
-  } else {
-    return false;
-  }
+template <bool A_RC, bool B_RC>
+bool try_launch_dma128(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool aligned, int I, int J, int R, const Epilogue& ep, int& status) {
+  static const bool enabled = MPT_TUNABLE("MPT_GEMM_STREAMED", 1) != 0 && MPT_TUNABLE("MPT_GEMM_WAVES", 4) == 4 &&
+                              MPT_TUNABLE("MPT_GEMM_TILE128", 1) != 0;
+  if (!enabled || !aligned || (I % 128) || (J % 256) || (R % 64) || ep.mode != 0) return false;
+  if ((ep.ld % 8) || !mpt_aligned(ep.out, 16) || (ep.act == 2 && ((ep.ldmask % 8) || !mpt_aligned(ep.mask, 16)))) return false;
+  const int64_t t256 = ((int64_t)(I + 255) / 256) * (J / 256), t128 = (int64_t)(I / 128) * (J / 256);
+  if (t256 >= kCUs * 3 / 4 || t128 < kCUs * 3 / 8) return false;
+  auto k = k_gemm_dma4<DmaOperand4<A_RC, 128>, DmaOperand4<B_RC, 256>, 128>;
+  constexpr int lds = 4 * (128 + 256) * 64;
+  static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds), true);
+  (void)once;
+  Problem pb{I, J, R, I / 128, J / 256, 1, R / 64};
+  hipLaunchKernelGGL(k, dim3((unsigned)t128), dim3(256), lds, s, DmaMat{A.base, A.ld}, DmaMat{B.base, B.ld}, pb, ep);
+  status = hipGetLastError() == hipSuccess ? MPT_OK : MPT_ERR_HIP;
+  return true;
 }
 
 // The split 128-row plan on the streamed kernel's FP32 epilogue: partials [split][I][J] into the workspace.
-template <class AView, class BView>
-bool try_launch_split128(hipStream_t s, const AView& A, const BView& B, bool aligned, const Plan& p, int I, int J, int R, float* ws, int& status) {
-  if constexpr (DmaKind<AView>::ok && DmaKind<BView>::ok) {
-    static const bool enabled = MPT_TUNABLE("MPT_GEMM_STREAMED", 1) != 0 && MPT_TUNABLE("MPT_GEMM_SPLIT128", 1) != 0;
-    if (!enabled || !aligned || !mpt_aligned(ws, 16)) return false;
-    auto k = k_gemm_dma4<DmaOperand4<DmaKind<AView>::rc, 128>, DmaOperand4<DmaKind<BView>::rc, 256>, 128, true>;
-    constexpr int lds = 4 * (128 + 256) * 64;
-    static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds), true);
-    (void)once;
-    Problem pb{I, J, R, p.tiles_i, p.tiles_j, p.splits, p.ktiles_per_split};
-    Epilogue part{ws, J, 3, nullptr, 0, nullptr, 0};
-    hipLaunchKernelGGL(k, dim3((unsigned)((int64_t)p.tiles_i * p.tiles_j * p.splits)), dim3(256), lds, s, DmaMat{A.base, A.ld}, DmaMat{B.base, B.ld}, pb, part);
-    status = hipGetLastError() == hipSuccess ? MPT_OK : MPT_ERR_HIP;
-    return true;
-  } else {
-    return false;
+template <bool A_RC, bool B_RC>
+bool try_launch_split128(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool aligned, const Plan& p, int I, int J, int R, float* ws, int& status) {
+  static const bool enabled = MPT_TUNABLE("MPT_GEMM_STREAMED", 1) != 0 && MPT_TUNABLE("MPT_GEMM_SPLIT128", 1) != 0;
+  if (!enabled || !aligned || !mpt_aligned(ws, 16)) return false;
+  auto k = k_gemm_dma4<DmaOperand4<A_RC, 128>, DmaOperand4<B_RC, 256>, 128, true>;
+  constexpr int lds = 4 * (128 + 256) * 64;
+  static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds), true);
+  (void)once;
+  Problem pb{I, J, R, p.tiles_i, p.tiles_j, p.splits, p.ktiles_per_split};
+  Epilogue part{ws, J, 3, nullptr, 0, nullptr, 0};
+  hipLaunchKernelGGL(k, dim3((unsigned)((int64_t)p.tiles_i * p.tiles_j * p.splits)), dim3(256), lds, s, DmaMat{A.base, A.ld}, DmaMat{B.base, B.ld}, pb, part);
+  status = hipGetLastError() == hipSuccess ? MPT_OK : MPT_ERR_HIP;
+  return true;
+}
+
+// What a launch takes, in us: a start, and a share per stage of depth 64 and workgroup on a CU - between the mean and the
+// busiest CU's count, since workgroups of one CU share it (fitted to 64 .. 4000 rows and columns over 1 .. 128 stages; mostly
+// within a fifth).  A split costs a second launch and its partials' way to memory and back.
+struct RingCost { double start, stage, alone = 1.0; };   // alone: shares of a workgroup that has its CU to itself (what its waits leave idle)
+constexpr RingCost kRing64 = {3.6, 0.25}, kRing128 = {5.6, 0.55}, kAny64 = {4.3, 0.5}, kAny128 = {8.5, 1.4}, kWhole256 = {6.0, 1.5};
+constexpr RingCost kConvWgrad64 = {4.0, 0.26, 1.6}, kConvWgrad128 = {6.0, 0.6, 1.3};
+double ring_cost(const RingCost& c, int64_t tiles, int64_t I, int64_t J, int stages, int64_t splits) {
+  const int64_t wgs = tiles * splits;
+  const double per_cu = wgs <= kCUs ? c.alone : 0.5 * ((double)wgs / kCUs + (double)((wgs + kCUs - 1) / kCUs));
+  const double partials = splits > 1 ? 2.4 + (double)splits * (double)I * (double)J * 8.0 / 5.0e6 : 0.0;
+  return c.start + c.stage * stages * per_cu + partials;
+}
+
+// The ring kernels' tile and split (gemm_ring.hip): the cheapest of the two tiles and of the splits that the workspace has
+// room for (`max_splits` partial outputs).  `cost` receives its estimate.
+struct RingPlan { RingTile tile; int splits, ktiles_per_split; double cost; };
+RingPlan ring_plan(int64_t I, int64_t J, int64_t R, int max_splits, bool whole_chunks, bool conv_wgrad = false, bool conv_rows = false) {
+  const int force_tile = MPT_TUNABLE("MPT_RING_TILE", -1), force_split = MPT_TUNABLE("MPT_RING_SPLITS", 0);   // tuning builds only
+  const int kt = (int)((R + BK - 1) / BK);
+  RingPlan best{kRing64x64, 1, kt, 1e30};
+  auto consider = [&](RingTile tile, const RingCost& c) {
+    if (force_tile >= 0 && tile != force_tile) return;
+    const int64_t tiles = ((I + ring_tile_rows(tile) - 1) / ring_tile_rows(tile)) * ((J + ring_tile_cols(tile) - 1) / ring_tile_cols(tile));
+    for (int want = 1; want <= max_splits; ++want) {
+      const int per = (kt + want - 1) / want, splits = (kt + per - 1) / per;   // no empty split
+      if (splits != want && want > 1) continue;
+      if (force_split > 0 && want != force_split && want != max_splits) continue;
+      const double cost = ring_cost(c, tiles, I, J, per, splits);
+      if (cost < best.cost) best = RingPlan{tile, splits, per, cost};
+      if (force_split > 0 && want == force_split) { best = RingPlan{tile, splits, per, 0.0}; return; }
+      if (tiles * splits >= 4 * kCUs) break;
+    }
+  };
+  if (conv_rows) {
+    // rows are pixels: many tiles, so the wide tile, or where one tile column of 64 holds the output the tall one
+    // (64 channels at 64 x 56 x 56: 32 against 48 us; 128 columns in two tall tiles were 2 us behind the square one)
+    consider(J <= 64 ? kRing256x64 : kRing128x128, kRing128);
+    if (force_tile >= 0 && best.cost == 1e30) consider((RingTile)force_tile, kRing128);
+    return best;
   }
+  consider(kRing64x64, conv_wgrad ? kConvWgrad64 : whole_chunks ? kRing64 : kAny64);
+  consider(kRing128x128, conv_wgrad ? kConvWgrad128 : whole_chunks ? kRing128 : kAny128);
+  return best;
 }
 
 // Run one contraction: single pass, or split partials + ordered reduction.
-template <class AView, class BView>
-int run(hipStream_t s, const AView& A, const BView& B, bool a_aligned, bool b_aligned, int I, int J, int R, Epilogue ep, void* ws, size_t ws_bytes) {
-  const bool aligned = a_aligned && b_aligned;
+template <bool A_RC, bool B_RC>
+int run(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool aligned, int I, int J, int R, Epilogue ep, void* ws, size_t ws_bytes) {
   const Plan pl = make_plan(I, J, R, ws != nullptr);
   if (ws != nullptr && ws_bytes < plan_ws_bytes(pl, I, J)) return MPT_ERR_WORKSPACE;
   int st = MPT_OK;
@@ -2074,10 +1627,11 @@ int run(hipStream_t s, const AView& A, const BView& B, bool a_aligned, bool b_al
   // over 8192: 88 against 70 us).
   const int64_t t128 = (int64_t)(I / 128) * (J / 256);
   const bool rather_split = ws != nullptr && pl.big && pl.splits > 1 && R >= 8192 && (int64_t)pl.tiles_i * pl.tiles_j * pl.splits * 4 >= t128 * 5;
-  if (!rather_split && try_launch_dma128(s, A, B, aligned, I, J, R, ep, st)) return st;
+  const bool ring_only = MPT_TUNABLE("MPT_RING_ONLY", 0) != 0;          // tuning builds only
+  if (!rather_split && !ring_only && try_launch_dma128<A_RC, B_RC>(s, A, B, aligned, I, J, R, ep, st)) return st;
   Plan p128;
-  if (ws != nullptr && plan_split128(I, J, R, p128) && ws_bytes >= plan_ws_bytes(p128, I, J) &&
-      try_launch_split128(s, A, B, aligned, p128, I, J, R, reinterpret_cast<float*>(ws), st)) {
+  if (!ring_only && ws != nullptr && plan_split128(I, J, R, p128) && ws_bytes >= plan_ws_bytes(p128, I, J) &&
+      try_launch_split128<A_RC, B_RC>(s, A, B, aligned, p128, I, J, R, reinterpret_cast<float*>(ws), st)) {
     if (st != MPT_OK) return st;
     launch_split_reduce(s, ws, p128.splits, I, J, ep);
     MPT_LAUNCH_CHECK();
@@ -2087,17 +1641,27 @@ int run(hipStream_t s, const AView& A, const BView& B, bool a_aligned, bool b_al
   if (pl.splits > 1) {
     first.out = ws; first.ld = J; first.mode = 3; first.flag = nullptr;
   }
-  if (!try_launch_dma(s, A, B, aligned, pl, I, J, R, first, st))
-    st = a_aligned ? (b_aligned ? launch_tiles<AView, BView, true, true>(s, A, B, pl, I, J, R, first)
-                                : launch_tiles<AView, BView, true, false>(s, A, B, pl, I, J, R, first))
-                   : (b_aligned ? launch_tiles<AView, BView, false, true>(s, A, B, pl, I, J, R, first)
-                                : launch_tiles<AView, BView, false, false>(s, A, B, pl, I, J, R, first));
-  if (st != MPT_OK) return st;
-  if (pl.splits > 1) {
-    launch_split_reduce(s, ws, pl.splits, I, J, ep);
+  const RingPlan rp = ring_plan(I, J, R, ws != nullptr ? pl.splits : 1, aligned);
+  // Whole tiles whose reduction is short for its splits: the partials cost more than the smaller tiles' extra reads (the
+  // projection's weight gradient, 8192 x 1024 over 256 accumulated in FP32: 39.6 us in two splits, 18.7 us unsplit)
+  const bool rather_ring = pl.splits > 1 && rp.cost < 0.8 * ring_cost(kWhole256, (int64_t)pl.tiles_i * pl.tiles_j, I, J, pl.ktiles_per_split, pl.splits);
+  if (!ring_only && !rather_ring && try_launch_dma<A_RC, B_RC>(s, A, B, aligned, pl, I, J, R, first, st)) {
+    if (st == MPT_OK && pl.splits > 1) {
+      launch_split_reduce(s, ws, pl.splits, I, J, ep);
+      MPT_LAUNCH_CHECK();
+    }
+    return st;
+  }
+  first = ep;
+  if (rp.splits > 1) {
+    first.out = ws; first.ld = J; first.mode = 3; first.flag = nullptr;
+  }
+  st = launch_ring_plain(s, A_RC, B_RC, A, B, aligned, rp.tile, rp.ktiles_per_split, I, J, R, first);
+  if (st == MPT_OK && rp.splits > 1) {
+    launch_split_reduce(s, ws, rp.splits, I, J, ep);
     MPT_LAUNCH_CHECK();
   }
-  return MPT_OK;
+  return st;
 }
 
 bool dims_ok(int64_t a, int64_t b, int64_t c) {
@@ -2135,10 +1699,9 @@ int gemm_fwd_impl(void* stream, int64_t M, int64_t N, int64_t K, const uint16_t*
   if (X == nullptr || W == nullptr || Y == nullptr) return MPT_ERR_NULL;
   if (!dims_ok(M, N, K) || ldx < K || ldw < N || ldy < N) return MPT_ERR_SHAPE;
   if (!mpt_aligned(X, 2) || !mpt_aligned(W, 2) || !mpt_aligned(Y, 2) || (ws && !mpt_aligned(ws, 16))) return MPT_ERR_ALIGN;
-  MatRC A{X, ldx, (int)M, (int)K};
-  MatOC B{W, ldw, (int)N, (int)K};
+  const RingMatSrc A{X, ldx, (int)M, (int)K}, B{W, ldw, (int)N, (int)K};
   Epilogue ep{Y, ldy, 0, nullptr, act, nullptr, 0};
-  return run(static_cast<hipStream_t>(stream), A, B, mat_fast(X, ldx, K), mat_fast(W, ldw, N), (int)M, (int)N, (int)K, ep, ws, ws_bytes);
+  return run<true, false>(static_cast<hipStream_t>(stream), A, B, mat_fast(X, ldx, K) && mat_fast(W, ldw, N), (int)M, (int)N, (int)K, ep, ws, ws_bytes);
 }
 
 int gemm_dgrad_impl(void* stream, int64_t M, int64_t N, int64_t K, const uint16_t* dY, int64_t ldy, const uint16_t* W, int64_t ldw,
@@ -2147,10 +1710,9 @@ int gemm_dgrad_impl(void* stream, int64_t M, int64_t N, int64_t K, const uint16_
   if (!dims_ok(M, N, K) || ldy < N || ldw < N || ldx < K || (masked && ldh < K)) return MPT_ERR_SHAPE;
   if (!mpt_aligned(dY, 2) || !mpt_aligned(W, 2) || !mpt_aligned(dX, 2) || (masked && !mpt_aligned(H, 2)) || (ws && !mpt_aligned(ws, 16)))
     return MPT_ERR_ALIGN;
-  MatRC A{dY, ldy, (int)M, (int)N};
-  MatRC B{W, ldw, (int)K, (int)N};
+  const RingMatSrc A{dY, ldy, (int)M, (int)N}, B{W, ldw, (int)K, (int)N};
   Epilogue ep{dX, ldx, 0, nullptr, masked ? 2 : 0, masked ? H : nullptr, masked ? ldh : 0};
-  return run(static_cast<hipStream_t>(stream), A, B, mat_fast(dY, ldy, N), mat_fast(W, ldw, N), (int)M, (int)K, (int)N, ep, ws, ws_bytes);
+  return run<true, true>(static_cast<hipStream_t>(stream), A, B, mat_fast(dY, ldy, N) && mat_fast(W, ldw, N), (int)M, (int)K, (int)N, ep, ws, ws_bytes);
 }
 }  // namespace
 
@@ -2184,10 +1746,9 @@ extern "C" int mpt_gemm_wgrad(void* stream, int64_t M, int64_t N, int64_t K, con
   if (!mpt_aligned(X, 2) || !mpt_aligned(dY, 2) || !mpt_aligned(dW, out_fp32 ? 4 : 2) || (flag && !mpt_aligned(flag, 4)) ||
       (ws && !mpt_aligned(ws, 16)))
     return MPT_ERR_ALIGN;
-  MatOC A{X, ldx, (int)K, (int)M};
-  MatOC B{dY, ldy, (int)N, (int)M};
+  const RingMatSrc A{X, ldx, (int)K, (int)M}, B{dY, ldy, (int)N, (int)M};
   Epilogue ep{dW, lddw, out_fp32 ? (accumulate ? 2 : 1) : 0, flag, 0, nullptr, 0};
-  return run(static_cast<hipStream_t>(stream), A, B, mat_fast(X, ldx, K), mat_fast(dY, ldy, N), (int)K, (int)N, (int)M, ep, ws, ws_bytes);
+  return run<false, false>(static_cast<hipStream_t>(stream), A, B, mat_fast(X, ldx, K) && mat_fast(dY, ldy, N), (int)K, (int)N, (int)M, ep, ws, ws_bytes);
 }
 
 // ---------------------------------------------------------------- weight gradient for callers that cannot allocate
@@ -2302,6 +1863,28 @@ bool try_launch_conv_dma(hipStream_t s, const uint16_t* img, int64_t H, int64_t 
 }
 }  // namespace
 
+namespace {
+// Every other convolution: the ring kernels with gathered operands, split through the workspace where that fills the chip.
+int run_conv_ring(hipStream_t s, int op, int64_t Nb, int64_t H, int64_t W, int64_t C, int64_t Kf, const uint16_t* img, const uint16_t* other,
+                  const Epilogue& ep, void* ws, size_t ws_bytes) {
+  const int64_t P = Nb * H * W, I = op == MPT_OP_WGRAD ? Kf : P, J = op == MPT_OP_FWD ? Kf : op == MPT_OP_DGRAD ? C : 9 * C,
+                R = op == MPT_OP_FWD ? 9 * C : op == MPT_OP_DGRAD ? 9 * Kf : P;
+  const Plan pl = make_plan(I, J, R, ws != nullptr);
+  if (ws != nullptr && ws_bytes < plan_ws_bytes(pl, I, J)) return MPT_ERR_WORKSPACE;
+  const RingPlan rp = ring_plan(I, J, R, ws != nullptr ? pl.splits : 1, true, op == MPT_OP_WGRAD, op != MPT_OP_WGRAD);
+  Epilogue first = ep;
+  if (rp.splits > 1) {
+    first.out = ws; first.ld = J; first.mode = 3; first.flag = nullptr;
+  }
+  const int st = launch_ring_conv(s, op, Nb, H, W, C, Kf, img, other, rp.tile, rp.ktiles_per_split, first);
+  if (st == MPT_OK && rp.splits > 1) {
+    launch_split_reduce(s, ws, rp.splits, (int)I, (int)J, ep);
+    MPT_LAUNCH_CHECK();
+  }
+  return st;
+}
+}  // namespace
+
 extern "C" int mpt_conv3x3_fwd(void* stream, int64_t Nb, int64_t H, int64_t W, int64_t C, int64_t Kf, const uint16_t* x,
                                const uint16_t* w, uint16_t* y, void* ws, size_t ws_bytes) {
   if (x == nullptr || w == nullptr || y == nullptr) return MPT_ERR_NULL;
@@ -2313,11 +1896,7 @@ extern "C" int mpt_conv3x3_fwd(void* stream, int64_t Nb, int64_t H, int64_t W, i
       if (try_launch_conv_dma<DmaOperand4<true, 256>, DmaOperand64<true>>(static_cast<hipStream_t>(stream), x, H, W, C, +1, DmaMat{w, 9 * C}, DmaMat{w, 9 * C},
                                                                           Nb * H * W, Kf, y, st)) return st;
   }
-  const int P = (int)(Nb * H * W), R = (int)(9 * C);
-  ImgRC A{x, (int)H, (int)W, (int)C, P, R, +1, FastDiv((uint32_t)(H * W)), FastDiv((uint32_t)W), FastDiv((uint32_t)C)};
-  MatRC B{w, 9 * C, (int)Kf, R};
-  Epilogue ep{y, Kf, 0, nullptr, 0, nullptr, 0};
-  return run(static_cast<hipStream_t>(stream), A, B, true, true, P, (int)Kf, R, ep, ws, ws_bytes);
+  return run_conv_ring(static_cast<hipStream_t>(stream), MPT_OP_FWD, Nb, H, W, C, Kf, x, w, Epilogue{y, Kf, 0, nullptr, 0, nullptr, 0}, ws, ws_bytes);
 }
 
 extern "C" int mpt_conv3x3_dgrad(void* stream, int64_t Nb, int64_t H, int64_t W, int64_t C, int64_t Kf, const uint16_t* dy,
@@ -2332,11 +1911,7 @@ extern "C" int mpt_conv3x3_dgrad(void* stream, int64_t Nb, int64_t H, int64_t W,
                                                           DmaFilterSrc{w, (int)C, (int)Kf, FastDiv((uint32_t)(Kf / 32))},
                                                           DmaFilterSrc{w, (int)C, (int)Kf, FastDiv((uint32_t)(Kf / 64))}, Nb * H * W, C, dx, st)) return st;
   }
-  const int P = (int)(Nb * H * W), R = (int)(9 * Kf);
-  ImgRC A{dy, (int)H, (int)W, (int)Kf, P, R, -1, FastDiv((uint32_t)(H * W)), FastDiv((uint32_t)W), FastDiv((uint32_t)Kf)};
-  FilterOC B{w, (int)C, (int)Kf, (int)C, R, FastDiv((uint32_t)Kf)};
-  Epilogue ep{dx, C, 0, nullptr, 0, nullptr, 0};
-  return run(static_cast<hipStream_t>(stream), A, B, true, true, P, (int)C, R, ep, ws, ws_bytes);
+  return run_conv_ring(static_cast<hipStream_t>(stream), MPT_OP_DGRAD, Nb, H, W, C, Kf, dy, w, Epilogue{dx, C, 0, nullptr, 0, nullptr, 0}, ws, ws_bytes);
 }
 
 namespace {
@@ -2386,9 +1961,5 @@ extern "C" int mpt_conv3x3_wgrad(void* stream, int64_t Nb, int64_t H, int64_t W,
     const Epilogue epw{dw, 9 * C, 0, flag, 0, nullptr, 0};
     if (try_launch_conv_wgrad_dma(static_cast<hipStream_t>(stream), x, dy, H, W, C, Kf, Nb * H * W, epw, ws, ws_bytes, st)) return st;
   }
-  const int P = (int)(Nb * H * W), J = (int)(9 * C);
-  MatOC A{dy, Kf, (int)Kf, P};
-  ImgOC B{x, (int)H, (int)W, (int)C, J, P, FastDiv((uint32_t)(H * W)), FastDiv((uint32_t)W), FastDiv((uint32_t)C)};
-  Epilogue ep{dw, J, 0, flag, 0, nullptr, 0};
-  return run(static_cast<hipStream_t>(stream), A, B, true, true, (int)Kf, J, P, ep, ws, ws_bytes);
+  return run_conv_ring(static_cast<hipStream_t>(stream), MPT_OP_WGRAD, Nb, H, W, C, Kf, x, dy, Epilogue{dw, 9 * C, 0, flag, 0, nullptr, 0}, ws, ws_bytes);
 }

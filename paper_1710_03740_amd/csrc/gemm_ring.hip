@@ -1,0 +1,777 @@
+// FP16 contractions with FP32 accumulation for the shapes that are no whole number of 256 x 256 tiles: ragged and odd
+// sizes, narrow outputs, small matrices, and 3x3 convolutions with any channel count (paper Sec. 3.1, 3.3).  gfx950 only.
+//
+//   k_gemm_ring  operands in 16-byte aligned pieces: global -> LDS directly, through a ring of stages of reduction depth 64;
+//   k_gemm_any   any alignment and stride: the same pieces through registers with 2-byte aligned 16-byte loads.
+//
+// Both hold the operands in LDS as gemm.hip's streamed kernels do (reduction-contiguous rows of 128 bytes, or
+// outer-contiguous rows read with the transposing LDS read), so no operand is transposed in registers, and both work on
+// four wavefronts per workgroup with two workgroups on a CU, which cover each other's barriers, fills and stores.
+//
+// Ragged edges cost no branch: rows beyond the output read the last row again, pieces beyond the reduction read a line
+// of zeros, and the store leaves out what does not exist.
+#include "gemm_parts.h"
+#include <type_traits>
+#include <utility>
+
+namespace mpt_gemm {
+namespace {
+
+// Source of zeros for pieces that do not exist (an LDS-direct load needs an address to read).
+__device__ __attribute__((aligned(64))) const uint32_t k_ring_zeros[16] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
+
+// A select on the address, not a branch around the load.
+__device__ __forceinline__ const uint16_t* there_or_zeros(bool there, const uint16_t* p) {
+  const uintptr_t mask = there ? ~(uintptr_t)0 : (uintptr_t)0;
+  return reinterpret_cast<const uint16_t*>((reinterpret_cast<uintptr_t>(p) & mask) | (reinterpret_cast<uintptr_t>(k_ring_zeros) & ~mask));
+}
+
+template <class F, int... K>
+__device__ __forceinline__ void static_for_each(F&& f, std::integer_sequence<int, K...>) { (f(std::integral_constant<int, K>{}), ...); }
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) { static_for_each(f, std::make_integer_sequence<int, N>{}); }
+
+// Key of the 32-byte units of an outer-contiguous stage row.  A transposing read serves 32 lanes at a time: 4 rows at r
+// and 4 at r + 8; with 128-byte rows (64 outer indices) two rows share the 64 banks, so rows 0, 2, 8, 10 need the four
+// unit positions and rows 1, 3, 9, 11 again.
+template <int BO>
+__device__ __forceinline__ int ring_key(int r) {
+  if constexpr (BO == 64) return ((r >> 1) & 1) | ((r >> 2) & 2);
+  else return oc_key(r);
+}
+
+// ---------------------------------------------------------------- operands
+// A stage of an operand is BO outer x 64 reduction indices = BO * 128 bytes = BO / 8 blocks of 1 KiB; a wavefront moves
+// NB of them, lane l the 16 bytes at block + 16 l.  Which piece that is makes the LDS layout:
+//   RC: 8 rows of 128 bytes per block, one cache line each; 16-byte piece c of row o sits at piece c ^ ((o >> 1) & 7);
+//   OC: 512 / BO reduction rows per block; 32-byte unit u of row r sits at unit u ^ ring_key(r).
+template <bool RC, int BO>
+struct Piece {
+  static constexpr int NB = BO / 32;
+  static constexpr int RPB = RC ? 8 : 512 / BO, LPR = 64 / RPB;
+  // row inside the stage (RC: outer, OC: reduction) and first element of the piece along the row, of block k
+  __device__ static __forceinline__ int row(int wave, int lane, int k) { return (wave * NB + k) * RPB + lane / LPR; }
+  __device__ static __forceinline__ int col(int wave, int lane, int k) {
+    const int r = row(wave, lane, k), pc = lane % LPR;
+    if constexpr (RC) return (pc ^ ((r >> 1) & 7)) * 8;              // NB is even: the same for all even k, and for all odd k
+    else return (2 * ((pc >> 1) ^ ring_key<BO>(r)) + (pc & 1)) * 8;
+  }
+};
+
+__device__ __forceinline__ void to_lds(const uint16_t* p, char* lds_block) {
+  __builtin_amdgcn_global_load_lds((global_void_ptr)p, (lds_void_ptr)lds_block, 16, 0, 0);
+}
+
+// A scalar address that stays one: folded into the lane offsets it would be a 64-bit addition per load.
+__device__ __forceinline__ const char* scalar_base(const char* p) {
+  asm("" : "+s"(p));
+  return p;
+}
+
+// A value whose uses are worked out where they stand, not ahead of the loop: for code that seldom runs.
+__device__ __forceinline__ int here_only(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
+// Plain matrix, 16-byte aligned pieces.  A stage that lies inside the reduction needs no arithmetic per lane: a scalar base that
+// moves with the stage and a 32-bit lane offset.  (With a 64-bit address and a select per load the vector units had as much
+// to do as the matrix cores: 2000 x 3000 over 1000 took 24 us.)  The last, ragged stage and row strides too long for 32-bit offsets
+// form the whole address.
+template <bool RC, int BO>
+struct RingMat {
+  typedef RingMatSrc Src;
+  typedef Piece<RC, BO> P;
+  static constexpr bool kRC = RC;
+  static constexpr int NB = P::NB;
+  const char* base;                // of the tile, stage 0 (wavefront-uniform)
+  int64_t ld, step;                // step: bytes per stage
+  uint32_t off[NB];
+  int left, outer_left, inside, wave, lane;
+  bool wide;
+  // element offset of the lane's piece of block k from the tile's corner; rows and columns beyond the matrix are its last ones again
+  __device__ __forceinline__ int64_t place(int lane, int k) const {
+    const int row = P::row(wave, lane, k), col = P::col(wave, lane, k);
+    return RC ? (int64_t)min(row, outer_left - 1) * ld + col : (int64_t)row * ld + min(col, outer_left - 8);
+  }
+  __device__ __forceinline__ void init(const Src& m, int o0, int r0, int wave_, int lane_) {
+    ld = m.ld; wave = wave_; lane = lane_;
+    base = reinterpret_cast<const char*>(m.base + (RC ? (int64_t)o0 * ld + r0 : (int64_t)r0 * ld + o0));
+    step = RC ? 128 : 128 * ld;
+    left = m.R - r0;
+    outer_left = m.O - o0;
+    wide = ld >= (1 << 21);
+    inside = wide ? 0 : left >> 6;                                   // stages that need no select
+#pragma unroll
+    for (int k = 0; k < NB; ++k) off[k] = (uint32_t)(place(lane, k) * 2);
+  }
+  __device__ __forceinline__ void issue(int s, char* blocks) {
+    const char* at = scalar_base(base + s * step);
+    if (s < inside) {
+#pragma unroll
+      for (int k = 0; k < NB; ++k) to_lds(reinterpret_cast<const uint16_t*>(at + off[k]), blocks + k * 1024);
+      return;
+    }
+    const int l = here_only(lane), end = left - s * 64;
+    if (!wide) {
+#pragma unroll
+      for (int k = 0; k < NB; ++k)
+        to_lds(there_or_zeros((RC ? P::col(wave, l, k) : P::row(wave, l, k)) < end, reinterpret_cast<const uint16_t*>(at + off[k])), blocks + k * 1024);
+    } else {
+#pragma unroll
+      for (int k = 0; k < NB; ++k)
+        to_lds(there_or_zeros((RC ? P::col(wave, l, k) : P::row(wave, l, k)) < end, reinterpret_cast<const uint16_t*>(at) + place(l, k)), blocks + k * 1024);
+    }
+  }
+};
+
+// 3x3 convolution, stride 1, pad 1: outer index = pixel (n, y, x), reduction index r = tap * Cc + c with tap = 3*tr + ts;
+// the source pixel is (y + sgn*(tr-1), x + sgn*(ts-1)): sgn = +1 the forward window, -1 the mirrored one of the input
+// gradient.  Cc is a multiple of 8, so a piece lies inside one tap.
+// A lane keeps, per pixel, its offset and one bit per tap (is the shifted pixel inside the image), and steps (tap, c) of its
+// two piece columns along, stage by stage: issue is called once per stage, in order.
+struct ImgSrc { const uint16_t* base; int H, W, Cc, sgn, O, R; FastDiv dHW, dW, dC; };
+template <int BO>
+struct RingImg {
+  typedef ImgSrc Src;
+  typedef Piece<true, BO> P;
+  static constexpr bool kRC = true;
+  static constexpr int NB = P::NB;
+  const uint16_t* p[NB];           // the lane's pixel, centre tap
+  uint32_t taps[NB];
+  int W, Cc, sgn, wraps;
+  int tap[2], c[2];                // of the even and the odd blocks' pieces in the stage to come
+  __device__ __forceinline__ void init(const Src& m, int o0, int r0, int wave, int lane) {
+    W = m.W; Cc = m.Cc; sgn = m.sgn;
+    wraps = (63 + Cc) / Cc;                                          // a stage crosses at most so many taps
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      uint32_t t, cc;
+      m.dC.divmod((uint32_t)(r0 + P::col(wave, lane, q)), t, cc);
+      tap[q] = (int)t; c[q] = (int)cc;
+    }
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      const int o = min(o0 + P::row(wave, lane, k), m.O - 1);
+      uint32_t n, rem, y, x;
+      m.dHW.divmod((uint32_t)o, n, rem);
+      m.dW.divmod(rem, y, x);
+      p[k] = m.base + (int64_t)o * m.Cc;
+      const bool up = sgn > 0 ? y > 0 : y + 1 < (uint32_t)m.H, down = sgn > 0 ? y + 1 < (uint32_t)m.H : y > 0;      // rows of taps 0-2 and 6-8
+      const bool left = sgn > 0 ? x > 0 : x + 1 < (uint32_t)m.W, right = sgn > 0 ? x + 1 < (uint32_t)m.W : x > 0;
+      const uint32_t cols = (left ? 1u : 0u) | 2u | (right ? 4u : 0u);
+      taps[k] = (up ? cols : 0u) | cols << 3 | (down ? cols << 6 : 0u);   // taps from 9 on, behind the reduction's end: none
+    }
+  }
+  __device__ __forceinline__ void issue(int, char* blocks) {
+    int64_t off[2];
+    uint32_t bit[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int tr = (tap[q] * 11) >> 5, ts = tap[q] - 3 * tr;       // tap / 3 for the taps 0 .. 8
+      off[q] = (int64_t)(sgn * ((tr - 1) * W + ts - 1)) * Cc + c[q];
+      bit[q] = 1u << tap[q];
+      c[q] += 64;
+      for (int w = 0; w < wraps; ++w) {
+        const bool over = c[q] >= Cc;
+        c[q] -= over ? Cc : 0;
+        tap[q] += over ? 1 : 0;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < NB; ++k) to_lds(there_or_zeros((taps[k] & bit[k & 1]) != 0, p[k] + off[k & 1]), blocks + k * 1024);
+  }
+};
+
+// Filter w[k][tap][c] read as B(r = tap * Kf + k, o = c) for the input gradient.
+struct FilterSrc { const uint16_t* base; int Cc, Kf, O, R; FastDiv dK; };
+template <int BO>
+struct RingFilter {
+  typedef FilterSrc Src;
+  typedef Piece<false, BO> P;
+  static constexpr bool kRC = false;
+  static constexpr int NB = P::NB;
+  const uint16_t* p[NB];           // the lane's channels of its (k, tap) in the stage to come
+  int k[NB], Kf, wraps, left;
+  int64_t step, wrap;
+  __device__ __forceinline__ void init(const Src& m, int o0, int r0, int wave, int lane) {
+    Kf = m.Kf;
+    wraps = (63 + Kf) / Kf;
+    step = (int64_t)64 * 9 * m.Cc;
+    wrap = (int64_t)(1 - 9 * (int64_t)Kf) * m.Cc;                    // Kf rows of k back, one tap on
+    left = m.R - r0 - P::row(wave, lane, 0);
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      uint32_t tap, kk;
+      m.dK.divmod((uint32_t)(r0 + P::row(wave, lane, q)), tap, kk);
+      k[q] = (int)kk;
+      p[q] = m.base + ((int64_t)kk * 9 + tap) * m.Cc + min(o0 + P::col(wave, lane, q), m.O - 8);
+    }
+  }
+  __device__ __forceinline__ void issue(int s, char* blocks) {
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      to_lds(there_or_zeros(s * 64 + q * P::RPB < left, p[q]), blocks + q * 1024);
+      k[q] += 64;
+      p[q] += step;
+      for (int w = 0; w < wraps; ++w) {
+        const bool over = k[q] >= Kf;
+        k[q] -= over ? Kf : 0;
+        p[q] += over ? wrap : 0;
+      }
+    }
+  }
+};
+
+// The image read as B(r = pixel, o = tap * Cc + c) for the weight gradient.  A lane's outer indices, so its tap and
+// channels, are fixed; the pixel's (y, x), which only the bounds test needs, is stepped along stage by stage: issue is
+// called once per stage, in order.
+struct ImgOCSrc { const uint16_t* base; int H, W, Cc, O, R; FastDiv dH, dW, dC; };
+template <int BO>
+struct RingImgOC {
+  typedef ImgOCSrc Src;
+  typedef Piece<false, BO> P;
+  static constexpr bool kRC = false;
+  static constexpr int NB = P::NB;
+  const uint16_t* p[NB];           // the lane's channels of its shifted pixel in the stage to come
+  int y[NB], x[NB];                // the shifted pixel's coordinates, before any carry: y in -1 .. H, x in -1 .. W
+  int H, W, step_y, step_x, left;
+  int x_end[NB], y_end[NB];        // where the unshifted coordinate wraps, shifted
+  int64_t step;
+  __device__ __forceinline__ void init(const Src& m, int o0, int r0, int wave, int lane) {
+    H = m.H; W = m.W;
+    step_x = 64 % m.W; step_y = (64 / m.W) % m.H;
+    step = (int64_t)64 * m.Cc;
+    left = m.R - r0 - P::row(wave, lane, 0);
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      const int o = min(o0 + P::col(wave, lane, k), m.O - 8), r = r0 + P::row(wave, lane, k);
+      uint32_t tap, c, q, xx, n, yy;
+      m.dC.divmod((uint32_t)o, tap, c);
+      const int dy = (((int)tap * 11) >> 5) - 1, dx = (int)tap - 3 * (dy + 1) - 1;
+      m.dW.divmod((uint32_t)r, q, xx);
+      m.dH.divmod(q, n, yy);
+      y[k] = (int)yy + dy; x[k] = (int)xx + dx;
+      y_end[k] = m.H + dy; x_end[k] = m.W + dx;
+      p[k] = m.base + ((int64_t)r + dy * m.W + dx) * m.Cc + (int)c;
+    }
+  }
+  __device__ __forceinline__ void issue(int s, char* blocks) {
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      const bool in = s * 64 + k * P::RPB < left && (unsigned)y[k] < (unsigned)H && (unsigned)x[k] < (unsigned)W;
+      to_lds(there_or_zeros(in, p[k]), blocks + k * 1024);
+      p[k] += step;
+      x[k] += step_x;
+      const bool carry = x[k] >= x_end[k];
+      x[k] -= carry ? W : 0;
+      y[k] += step_y + (carry ? 1 : 0);
+      y[k] -= y[k] >= y_end[k] ? H : 0;
+    }
+  }
+};
+
+// Any alignment: the pieces of RingMat through registers.  A 16-byte load needs no alignment beyond its elements' here
+// (global memory, unaligned access mode); a piece that runs over its row's end is read as the last 8 elements of the row and
+// shifted down.  Rows of fewer than 8 elements are gathered element by element.
+typedef uint32_t uint4u __attribute__((ext_vector_type(4), aligned(2)));
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// Drops the first `n` (0 .. 7) of 8 elements; zeros follow the others.
+__device__ __forceinline__ uint4v drop_front(uint4v v, int n) {
+  uint64_t lo = (uint64_t)v[0] | (uint64_t)v[1] << 32, hi = (uint64_t)v[2] | (uint64_t)v[3] << 32;
+  if (n >= 4) { lo = hi; hi = 0; }
+  const int sh = (n & 3) * 16;
+  lo = (lo >> sh) | (sh ? hi << (64 - sh) : 0ull);
+  hi >>= sh;
+  return uint4v{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+}
+
+template <bool RC, int BO>
+struct RegMat {
+  typedef RingMatSrc Src;
+  typedef Piece<RC, BO> P;
+  static constexpr bool kRC = RC;
+  static constexpr int NB = P::NB;
+  const char* base;                // of the tile, stage 0 (wavefront-uniform); OC: 8 elements in front, so that a piece moved back over the tile's edge has an offset >= 0
+  int64_t ld, step;                // step: bytes per stage
+  uint32_t off[NB];                // OC: of the row's last 8 elements where the piece runs over its end
+  int left, outer_left, inside, wave, lane;   // inside: stages that end before the reduction does
+  bool narrow, wide, ragged;       // ragged: the tile's last columns are no whole piece
+  uint4v reg[NB];
+  // elements of the piece of block k along the row that exist (8 or more: all)
+  __device__ __forceinline__ int along(int s, int lane, int k) const { return (RC ? left - s * 64 : outer_left) - P::col(wave, lane, k); }
+  __device__ __forceinline__ void init(const Src& m, int o0, int r0, int r_end, int wave_, int lane_) {
+    ld = m.ld; wave = wave_; lane = lane_;
+    base = reinterpret_cast<const char*>(m.base + (RC ? (int64_t)o0 * ld + r0 : (int64_t)r0 * ld + o0 - 8));
+    step = RC ? 128 : 128 * ld;
+    left = r_end - r0;
+    outer_left = m.O - o0;
+    narrow = (RC ? m.R : m.O) < 8;
+    wide = ld >= (1 << 21);
+    ragged = !RC && outer_left < BO && (outer_left & 7) != 0;
+    inside = narrow || wide ? 0 : left >> 6;
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      const int row = P::row(wave, lane, k), col = P::col(wave, lane, k);
+      const int c = RC ? col : 8 + min(col, outer_left - 8);         // (outer_left - 8 >= -7 unless narrow)
+      off[k] = (uint32_t)(((RC ? (int64_t)min(row, outer_left - 1) : (int64_t)row) * ld + c) * 2);
+    }
+  }
+  __device__ __forceinline__ void load(int s) {
+    const char* at = scalar_base(base + s * step);
+    if (s < inside) {
+#pragma unroll
+      for (int k = 0; k < NB; ++k) reg[k] = *reinterpret_cast<const uint4u*>(at + off[k]);
+      return;
+    }
+    const int l = here_only(lane);
+    if (!narrow && !wide) {
+      // the last stage: RC pieces that run over the row's end are read as its last 8 elements (256 bytes taken off the base
+      // keep the lane offsets positive: a piece starts at most 55 elements behind the end); OC rows beyond the end as the last
+#pragma unroll
+      for (int k = 0; k < NB; ++k) {
+        if constexpr (RC) {
+          reg[k] = *reinterpret_cast<const uint4u*>(scalar_base(at - 256) + (uint32_t)(off[k] + 256u - 2u * (uint32_t)max(8 - along(s, l, k), 0)));
+        } else {
+          const int over = max(P::row(wave, l, k) - (left - s * 64 - 1), 0);
+          reg[k] = *reinterpret_cast<const uint4u*>(at + (off[k] - (uint32_t)over * (uint32_t)(ld * 2)));
+        }
+      }
+      return;
+    }
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      const int row = P::row(wave, l, k), col = P::col(wave, l, k);
+      const int n = RC || row < left - s * 64 ? min(max(along(s, l, k), 0), 8) : 0;
+      const int64_t place = (RC ? (int64_t)min(row, outer_left - 1) : (int64_t)row) * ld + col + (RC ? 0 : 8);
+      const uint16_t* q = there_or_zeros(n > 0, reinterpret_cast<const uint16_t*>(at) + place);
+      if (!narrow) {
+        reg[k] = *reinterpret_cast<const uint4u*>(q - (n > 0 ? 8 - n : 0));
+      } else {
+        const int last = max(n, 1) - 1;
+        uint32_t e[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) e[i] = q[min(i, last)];
+        reg[k] = uint4v{e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16};
+      }
+    }
+  }
+  __device__ __forceinline__ void store(int s, char* lds_lane) const {
+    if (s < inside && !ragged) {
+#pragma unroll
+      for (int k = 0; k < NB; ++k) *reinterpret_cast<uint4v*>(lds_lane + k * 1024) = reg[k];
+      return;
+    }
+    const int l = here_only(lane);
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      const int n = RC || P::row(wave, l, k) < left - s * 64 ? along(s, l, k) : 0;
+      uint4v v = reg[k];
+      if (narrow) {                                                  // keep the first n
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] &= (2 * i < n ? 0x0000FFFFu : 0u) | (2 * i + 1 < n ? 0xFFFF0000u : 0u);
+      } else {
+        v = drop_front(v, min(max(8 - n, 0), 7));                    // n <= 0: one element of the eight is left, and goes too
+        const uint32_t any = n > 0 ? ~0u : 0u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] &= any;
+      }
+      *reinterpret_cast<uint4v*>(lds_lane + k * 1024) = v;
+    }
+  }
+};
+
+// ---------------------------------------------------------------- fragments
+// 16 outer x 32 reduction indices (half a stage) for v_mfma_f32_16x16x32_f16.  The fragments of one wavefront are 16 outer
+// indices apart: RC fragments differ by a constant (the key repeats), the halves of the stage by an XOR; OC fragments by an
+// XOR with the lane's key, the halves by a constant, and the second part of a fragment lies 4 rows below the first whatever
+// the key.
+template <bool RC, int BO, int NF>
+struct RingFrag {
+  uint32_t at[RC ? 2 : NF];
+  __device__ __forceinline__ void init(int outer0, int lane, uint32_t operand0) {
+    if constexpr (RC) {
+      const int r = outer0 + (lane & 15), c = lane >> 4;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) at[h] = operand0 + r * 128 + ((((h << 2) | c) ^ ((r >> 1) & 7)) << 4);
+    } else {
+      const int r = ((lane >> 4) << 3) + ((lane & 15) >> 2);
+#pragma unroll
+      for (int f = 0; f < NF; ++f) at[f] = operand0 + r * (BO * 2) + ((((outer0 >> 4) + f) ^ ring_key<BO>(r)) << 5) + ((lane & 3) << 3);
+    }
+  }
+  template <int HALF>
+  __device__ __forceinline__ void read(uint32_t slot, uint4v (&frag)[NF]) const {
+    static_for<NF>([&](auto fc) {
+      constexpr int f = decltype(fc)::value;
+      if constexpr (RC) {
+        frag[f] = lds_read_b128_imm<f * 2048>(at[HALF] + slot);
+      } else {
+        const uint2v lo = lds_read_tr_b64_imm<HALF * BO * 64>(at[f] + slot);
+        const uint2v hi = lds_read_tr_b64_imm<HALF * BO * 64 + 4 * BO * 2>(at[f] + slot);
+        frag[f] = uint4v{lo[0], lo[1], hi[0], hi[1]};
+      }
+    });
+  }
+};
+// The waited-for fragments pass through here, so that what uses them stays below the wait (and, behind the last wait, so
+// that the registers of a read that nothing uses stay reserved until it has returned).
+template <int N>
+__device__ __forceinline__ void arrived(uint4v (&f)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) asm volatile("" : "+v"(f[i]));
+}
+
+template <int A0, int A1, int FM, int FN>
+__device__ __forceinline__ void multiply(float4v (&acc)[FM][FN], const uint4v (&fa)[FM], const uint4v (&fb)[FN]) {
+#pragma unroll
+  for (int a = A0; a < A1; ++a)
+#pragma unroll
+    for (int b = 0; b < FN; ++b)      // operands swapped: each lane ends up with 4 consecutive output columns of one row
+      acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, fb[b]), __builtin_bit_cast(half8, fa[a]), acc[a][b], 0, 0, 0);
+}
+
+// ---------------------------------------------------------------- store
+// acc[a][b][e]: row i0 + 16a + lane%16, column j0 + 16b + 4*(lane/16) + e.  The wavefront's block goes through its own part
+// of the (now idle) LDS and out in 16-byte pieces of whole row segments, in a loop: unrolled over the accumulators, the
+// guards and the three kinds of store were 10 KiB of code that a short launch fetched once and ran once (a 128 x 128 tile
+// over one stage: 7.1 us against 4.0 us for 64 x 64).  Pieces and mask reads need only the elements' alignment; the last
+// columns of a row that is no whole number of pieces go out one by one.
+template <int FM, int FN>
+__device__ __forceinline__ void store_tile(const Problem& pb, const Epilogue& ep, int sp, int i0, int j0, int lane, const float4v (&acc)[FM][FN], char* mine) {
+  constexpr int WM = FM * 16, WN = FN * 16;
+  const int li = lane & 15, lg = lane >> 4;
+  bool bad = false;
+  if (ep.mode == 0) {
+    constexpr int U = WN / 8, RPI = 64 / U, IT = WM / RPI;             // 16-byte units per row, rows per trip, trips
+    const int unit = lane % U, r0 = lane / U, j = j0 + unit * 8, n = pb.J - j;
+    if (ep.act == 2) {                                                 // the masks, all in flight at once, beside the block's FP16 values
+      uint4v mk[IT];
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        const uint16_t* row = ep.mask + (int64_t)min(i0 + it * RPI + r0, pb.I - 1) * ep.ldmask;
+        if (pb.J >= 8) {                                               // the last piece is read as the row's last 8 values
+          mk[it] = *reinterpret_cast<const uint4u*>(row + min(j, pb.J - 8));
+        } else {
+          uint32_t e[8];
+#pragma unroll
+          for (int k = 0; k < 8; ++k) e[k] = row[min(k, pb.J - 1)];
+          mk[it] = uint4v{e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16};
+        }
+      }
+#pragma unroll
+      for (int it = 0; it < IT; ++it) *reinterpret_cast<uint4v*>(mine + WM * WN * 2 + it * 1024 + lane * 16) = mk[it];
+    }
+#pragma unroll
+    for (int a = 0; a < FM; ++a)
+#pragma unroll
+      for (int b = 0; b < FN; ++b) {
+        half4 h;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) h[e] = (_Float16)acc[a][b][e];
+        *reinterpret_cast<half4*>(mine + (a * 16 + li) * (WN * 2) + (((2 * b + (lg >> 1)) ^ (li & (U - 1))) << 4) + (lg & 1) * 8) = h;
+      }
+#pragma unroll 1
+    for (int it = 0; it < IT; ++it) {
+      const int r = it * RPI + r0, i = i0 + r;
+      uint4v q = *reinterpret_cast<const uint4v*>(mine + r * (WN * 2) + ((unit ^ (r & (U - 1))) << 4));
+      if (ep.act != 0) {
+        uint4v m = q;
+        if (ep.act == 2) {
+          m = *reinterpret_cast<const uint4v*>(mine + WM * WN * 2 + it * 1024 + lane * 16);
+          if (pb.J >= 8 && n < 8 && n > 0) m = drop_front(m, 8 - n);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          q[e] &= (half_bits_positive(m[e]) ? 0x0000FFFFu : 0u) | (half_bits_positive(m[e] >> 16) ? 0xFFFF0000u : 0u);
+      }
+      if (i >= pb.I) continue;
+      uint16_t* o = reinterpret_cast<uint16_t*>(ep.out) + (int64_t)i * ep.ld + j;
+      if (n >= 8) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bad |= half_bits_special(q[e]) | half_bits_special(q[e] >> 16);
+        *reinterpret_cast<uint4u*>(o) = q;
+      } else {
+        for (int e = 0; e < n; ++e) {
+          const uint16_t b = (uint16_t)q[0];
+          bad |= half_bits_special(b);
+          o[e] = b;
+          q = drop_front(q, 1);
+        }
+      }
+    }
+  } else {
+    constexpr int U = WN / 4, RPI = 64 / U, IT = WM / RPI;
+    const int unit = lane % U, r0 = lane / U, j = j0 + unit * 4, n = pb.J - j;
+    float* out = reinterpret_cast<float*>(ep.out) + (ep.mode == 3 ? (int64_t)sp * pb.I * pb.J : 0) + j;
+#pragma unroll
+    for (int a = 0; a < FM; ++a)
+#pragma unroll
+      for (int b = 0; b < FN; ++b)
+        *reinterpret_cast<float4v*>(mine + (a * 16 + li) * (WN * 4) + (((4 * b + lg) ^ (li & (U - 1))) << 4)) = acc[a][b];
+#pragma unroll 2
+    for (int it = 0; it < IT; ++it) {
+      const int r = it * RPI + r0, i = i0 + r;
+      float4v v = *reinterpret_cast<const float4v*>(mine + r * (WN * 4) + ((unit ^ (r & (U - 1))) << 4));
+      if (i >= pb.I) continue;
+      float* o = out + (int64_t)i * ep.ld;
+      if (n >= 4) {
+        if (ep.mode == 2) {
+          const float4v old = *reinterpret_cast<const float4u*>(o);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = __fadd_rn(old[e], v[e]);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bad |= (__float_as_uint(v[e]) & 0x7F800000u) == 0x7F800000u;
+        *reinterpret_cast<float4u*>(o) = v;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+          if (e < n) {
+            const float t = ep.mode == 2 ? __fadd_rn(o[e], v[e]) : v[e];
+            bad |= (__float_as_uint(t) & 0x7F800000u) == 0x7F800000u;
+            o[e] = t;
+          }
+      }
+    }
+  }
+  if (ep.flag != nullptr && ep.mode != 3) {
+    const unsigned long long vote = __builtin_amdgcn_ballot_w64(bad);
+    if (vote != 0ull && lane == 0) atomicOr(ep.flag, 1u);
+  }
+}
+
+// ---------------------------------------------------------------- the ring
+// A stage is multiplied in two halves; while the fragments of one half are multiplied those of the next come out of LDS.
+// One barrier per stage, between its halves: every wavefront then holds its fragments of the second half in registers, so
+// the slot can be refilled (stage s + NS), and stage s + 1, which the reads behind the barrier belong to, has landed
+// everywhere.
+template <class AOp, class BOp, int BM, int BN, int WM, int WN, int NS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_ring(typename AOp::Src A, typename BOp::Src B, Problem pb, Epilogue ep) {
+  static_assert((BM / WM) * (BN / WN) == 4, "four wavefronts");
+  constexpr int FM = WM / 16, FN = WN / 16, A_BYTES = BM * 128, STAGE = (BM + BN) * 128, LA = AOp::NB, LB = BOp::NB, L = LA + LB;
+  static_assert((NS & (NS - 1)) == 0 && (NS - 1) * L < 64, "slots; loads in flight fit the counter");
+  static_assert(NS * STAGE >= 4 * WM * WN * 4, "the store's buffers fit the ring");
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wm = wave / (BN / WN), wn = wave % (BN / WN);
+  int ti, tj, sp;
+  tile_of(pb, blockIdx.x, ti, tj, sp);
+  const int i0 = ti * BM, j0 = tj * BN;
+  const int st_begin = sp * pb.ktiles_per_split;
+  const int nst = min(pb.ktiles_per_split, (pb.R + 63) / 64 - st_begin);           // stages of this workgroup (>= 1: no split is empty)
+
+  AOp da;
+  BOp db;
+  da.init(A, i0, st_begin * 64, wave, lane);
+  db.init(B, j0, st_begin * 64, wave, lane);
+  auto issue = [&](int s) {
+    char* st = lds + (s & (NS - 1)) * STAGE;
+    da.issue(s, st + wave * (LA * 1024));
+    db.issue(s, st + A_BYTES + wave * (LB * 1024));
+  };
+  // wait until at most `newer` stages' loads of this wavefront are in flight
+  auto wait_stages = [&](int newer) {
+    static_for<NS>([&](auto k) {
+      constexpr int n = NS - 1 - decltype(k)::value;
+      if (newer == n || (n == 0 && newer < 0)) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(n * L) : "memory");
+    });
+  };
+
+  for (int q = 0; q < min(NS, nst); ++q) issue(q);
+  float4v acc[FM][FN];
+#pragma unroll
+  for (int a = 0; a < FM; ++a)
+#pragma unroll
+    for (int b = 0; b < FN; ++b)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[a][b][v] = 0.f;
+  RingFrag<AOp::kRC, BM, FM> ra;
+  RingFrag<BOp::kRC, BN, FN> rb;
+  const uint32_t lds0 = lds_offset(lds);
+  ra.init(wm * WM, lane, lds0);
+  rb.init(wn * WN, lane, lds0 + A_BYTES);
+  uint4v fa[2][FM], fb[2][FN];
+  wait_stages(min(NS, nst) - 1);
+  asm volatile("s_barrier" ::: "memory");
+  ra.template read<0>(0, fa[0]);
+  rb.template read<0>(0, fb[0]);
+  for (int s = 0; s < nst; ++s) {
+    const uint32_t slot = (s & (NS - 1)) * STAGE, next = ((s + 1) & (NS - 1)) * STAGE;   // next, past the end: old data that nobody uses
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    arrived(fa[0]);
+    arrived(fb[0]);
+    ra.template read<1>(slot, fa[1]);
+    rb.template read<1>(slot, fb[1]);
+    multiply<0, FM>(acc, fa[0], fb[0]);
+    __builtin_amdgcn_sched_barrier(0);
+    wait_stages(min(NS - 2, nst - 2 - s));
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    arrived(fa[1]);
+    arrived(fb[1]);
+    ra.template read<0>(next, fa[0]);
+    rb.template read<0>(next, fb[0]);
+    multiply<0, FM / 2>(acc, fa[1], fb[1]);
+    __builtin_amdgcn_sched_barrier(0);
+    if (s + NS < nst) issue(s + NS);                                 // under the multiplications already issued
+    multiply<FM / 2, FM>(acc, fa[1], fb[1]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  arrived(fa[0]);
+  arrived(fb[0]);
+  store_tile<FM, FN>(pb, ep, sp, i0 + wm * WM, j0 + wn * WN, lane, acc, lds + wave * (WM * WN * 4));
+}
+
+// The same with the pieces of one stage in registers on their way to one of two LDS slots: behind the barrier of stage s the
+// pieces of stage s + 2 are written into the slot that stage s has left, and those of stage s + 3 are loaded.
+template <class AOp, class BOp, int BM, int BN, int WM, int WN>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_any(RingMatSrc A, RingMatSrc B, Problem pb, Epilogue ep) {
+  static_assert((BM / WM) * (BN / WN) == 4, "four wavefronts");
+  constexpr int FM = WM / 16, FN = WN / 16, A_BYTES = BM * 128, STAGE = (BM + BN) * 128, LA = AOp::NB, LB = BOp::NB;
+  static_assert(2 * STAGE >= 4 * WM * WN * 4, "the store's buffers fit the slots");
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wm = wave / (BN / WN), wn = wave % (BN / WN);
+  int ti, tj, sp;
+  tile_of(pb, blockIdx.x, ti, tj, sp);
+  const int i0 = ti * BM, j0 = tj * BN;
+  const int st_begin = sp * pb.ktiles_per_split;
+  const int nst = min(pb.ktiles_per_split, (pb.R + 63) / 64 - st_begin);
+  const int r_end = (int)min((int64_t)pb.R, (int64_t)(st_begin + nst) * 64);
+
+  AOp da;
+  BOp db;
+  da.init(A, i0, st_begin * 64, r_end, wave, lane);
+  db.init(B, j0, st_begin * 64, r_end, wave, lane);
+  auto load = [&](int s) {
+    if (s >= nst) return;
+    da.load(s);
+    db.load(s);
+  };
+  auto store = [&](int s) {
+    if (s >= nst) return;
+    char* st = lds + (s & 1) * STAGE + lane * 16;
+    da.store(s, st + wave * (LA * 1024));
+    db.store(s, st + A_BYTES + wave * (LB * 1024));
+  };
+  load(0);
+  float4v acc[FM][FN];
+#pragma unroll
+  for (int a = 0; a < FM; ++a)
+#pragma unroll
+    for (int b = 0; b < FN; ++b)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[a][b][v] = 0.f;
+  RingFrag<AOp::kRC, BM, FM> ra;
+  RingFrag<BOp::kRC, BN, FN> rb;
+  const uint32_t lds0 = lds_offset(lds);
+  ra.init(wm * WM, lane, lds0);
+  rb.init(wn * WN, lane, lds0 + A_BYTES);
+  uint4v fa[2][FM], fb[2][FN];
+#pragma unroll 1
+  for (int q = 0; q < 2; ++q) {
+    store(q);
+    load(q + 1);
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  ra.template read<0>(0, fa[0]);
+  rb.template read<0>(0, fb[0]);
+  for (int s = 0; s < nst; ++s) {
+    const uint32_t slot = (s & 1) * STAGE, next = STAGE - slot;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    arrived(fa[0]);
+    arrived(fb[0]);
+    ra.template read<1>(slot, fa[1]);
+    rb.template read<1>(slot, fb[1]);
+    multiply<0, FM>(acc, fa[0], fb[0]);
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    arrived(fa[1]);
+    arrived(fb[1]);
+    ra.template read<0>(next, fa[0]);
+    rb.template read<0>(next, fb[0]);
+    multiply<0, FM / 2>(acc, fa[1], fb[1]);
+    __builtin_amdgcn_sched_barrier(0);
+    store(s + 2);
+    load(s + 3);
+    multiply<FM / 2, FM>(acc, fa[1], fb[1]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  arrived(fa[0]);
+  arrived(fb[0]);
+  store_tile<FM, FN>(pb, ep, sp, i0 + wm * WM, j0 + wn * WN, lane, acc, lds + wave * (WM * WN * 4));
+}
+
+// ---------------------------------------------------------------- launches
+Problem ring_problem(RingTile tile, int ktiles_per_split, int I, int J, int R) {
+  const int bm = ring_tile_rows(tile), bn = ring_tile_cols(tile), kt = (R + 63) / 64;
+  return Problem{I, J, R, (I + bm - 1) / bm, (J + bn - 1) / bn, (kt + ktiles_per_split - 1) / ktiles_per_split, ktiles_per_split};
+}
+
+template <class AOp, class BOp, int BM, int BN, int WM, int WN, int NS>
+int launch_ring(hipStream_t s, const typename AOp::Src& A, const typename BOp::Src& B, const Problem& pb, const Epilogue& ep) {
+#ifdef MPT_TUNING
+  if constexpr (NS == 2 && 4 * (BM + BN) * 128 <= 163840) { if (MPT_TUNABLE("MPT_RING_DEEP", 0)) return launch_ring<AOp, BOp, BM, BN, WM, WN, 4>(s, A, B, pb, ep); }
+  if constexpr (NS == 4) { if (MPT_TUNABLE("MPT_RING_SHALLOW", 0)) return launch_ring<AOp, BOp, BM, BN, WM, WN, 2>(s, A, B, pb, ep); }
+#endif
+  auto k = k_gemm_ring<AOp, BOp, BM, BN, WM, WN, NS>;
+  constexpr int lds = NS * (BM + BN) * 128;
+  static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds), true);
+  (void)once;
+  hipLaunchKernelGGL(k, dim3((unsigned)((int64_t)pb.tiles_i * pb.tiles_j * pb.splits)), dim3(256), lds, s, A, B, pb, ep);
+  MPT_LAUNCH_CHECK();
+  return MPT_OK;
+}
+
+template <bool A_RC, bool B_RC>
+int launch_plain(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool whole_chunks, RingTile tile, const Problem& pb, const Epilogue& ep) {
+  if (whole_chunks) {
+    if (tile == kRing64x64) return launch_ring<RingMat<A_RC, 64>, RingMat<B_RC, 64>, 64, 64, 32, 32, 4>(s, A, B, pb, ep);
+    return launch_ring<RingMat<A_RC, 128>, RingMat<B_RC, 128>, 128, 128, 64, 64, 2>(s, A, B, pb, ep);
+  }
+  const dim3 grid((unsigned)((int64_t)pb.tiles_i * pb.tiles_j * pb.splits));
+  if (tile == kRing64x64) hipLaunchKernelGGL((k_gemm_any<RegMat<A_RC, 64>, RegMat<B_RC, 64>, 64, 64, 32, 32>), grid, dim3(256), 2 * 128 * 128, s, A, B, pb, ep);
+  else hipLaunchKernelGGL((k_gemm_any<RegMat<A_RC, 128>, RegMat<B_RC, 128>, 128, 128, 64, 64>), grid, dim3(256), 2 * 256 * 128, s, A, B, pb, ep);
+  MPT_LAUNCH_CHECK();
+  return MPT_OK;
+}
+
+}  // namespace
+
+int launch_ring_plain(hipStream_t s, bool a_rc, bool b_rc, const RingMatSrc& A, const RingMatSrc& B, bool whole_chunks, RingTile tile,
+                      int ktiles_per_split, int I, int J, int R, const Epilogue& ep) {
+  if (tile != kRing64x64) tile = kRing128x128;
+  const Problem pb = ring_problem(tile, ktiles_per_split, I, J, R);
+  if (a_rc) return b_rc ? launch_plain<true, true>(s, A, B, whole_chunks, tile, pb, ep) : launch_plain<true, false>(s, A, B, whole_chunks, tile, pb, ep);
+  return launch_plain<false, false>(s, A, B, whole_chunks, tile, pb, ep);       // both along the output: no product here has only A so
+}
+
+int launch_ring_conv(hipStream_t s, int op, int64_t Nb, int64_t H, int64_t W, int64_t C, int64_t Kf, const uint16_t* img, const uint16_t* other,
+                     RingTile tile, int ktiles_per_split, const Epilogue& ep) {
+  const int P = (int)(Nb * H * W);
+  const FastDiv dHW((uint32_t)(H * W)), dW((uint32_t)W), dH((uint32_t)H), dC((uint32_t)C), dK((uint32_t)Kf);
+  if (op == MPT_OP_WGRAD) {
+    const RingMatSrc A{other, Kf, (int)Kf, P};
+    const ImgOCSrc B{img, (int)H, (int)W, (int)C, (int)(9 * C), P, dH, dW, dC};
+    const Problem pb = ring_problem(tile, ktiles_per_split, (int)Kf, (int)(9 * C), P);
+    if (tile == kRing64x64) return launch_ring<RingMat<false, 64>, RingImgOC<64>, 64, 64, 32, 32, 4>(s, A, B, pb, ep);
+    return launch_ring<RingMat<false, 128>, RingImgOC<128>, 128, 128, 64, 64, 2>(s, A, B, pb, ep);
+  }
+  if (op == MPT_OP_FWD) {
+    const ImgSrc A{img, (int)H, (int)W, (int)C, +1, P, (int)(9 * C), dHW, dW, dC};
+    const RingMatSrc B{other, 9 * C, (int)Kf, (int)(9 * C)};
+    const Problem pb = ring_problem(tile, ktiles_per_split, P, (int)Kf, (int)(9 * C));
+    if (tile == kRing256x64) return launch_ring<RingImg<256>, RingMat<true, 64>, 256, 64, 64, 64, 2>(s, A, B, pb, ep);
+    return launch_ring<RingImg<128>, RingMat<true, 128>, 128, 128, 64, 64, 2>(s, A, B, pb, ep);
+  }
+  const ImgSrc A{img, (int)H, (int)W, (int)Kf, -1, P, (int)(9 * Kf), dHW, dW, dK};
+  const FilterSrc B{other, (int)C, (int)Kf, (int)C, (int)(9 * Kf), dK};
+  const Problem pb = ring_problem(tile, ktiles_per_split, P, (int)C, (int)(9 * Kf));
+  if (tile == kRing256x64) return launch_ring<RingImg<256>, RingFilter<64>, 256, 64, 64, 64, 2>(s, A, B, pb, ep);
+  return launch_ring<RingImg<128>, RingFilter<128>, 128, 128, 64, 64, 2>(s, A, B, pb, ep);
+}
+
+}  // namespace mpt_gemm

@@ -1,0 +1,31 @@
+"""The ring and any-alignment GEMM kernels, compiled for gfx950, never touch a register that an LDS read in flight will
+still write (see asm_check.py).  Compiles csrc/gemm_ring.hip to device assembly and walks every instantiation."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+import asm_check
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def test_ring_kernels_keep_in_flight_read_registers_untouched(tmp_path):
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if not (os.path.exists(hipcc) or shutil.which(hipcc)):
+        pytest.skip("no hipcc")
+    from paper_1710_03740_amd import build as mpt_build
+    out = tmp_path / "gemm_ring.s"
+    csrc = os.path.join(ROOT, "paper_1710_03740_amd", "csrc")
+    flags = [f for f in mpt_build.HIP_FLAGS if f != "-fPIC"]
+    cmd = [hipcc] + flags + ["-I", os.path.join(ROOT, "include"), "-I", csrc, "-x", "hip", "-S", "--cuda-device-only", "-o", str(out), os.path.join(csrc, "gemm_ring.hip")]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout[-2000:]
+    n = 0
+    for name, lines in asm_check.kernels(out.read_text(), r"k_gemm_(ring|any)"):
+        found = asm_check.check_kernel(lines)
+        assert not found, "%s: %s" % (name, found[:5])
+        assert sum("v_mfma" in l for l in lines) >= 8
+        n += 1
+    assert n >= 15

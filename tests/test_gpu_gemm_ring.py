@@ -1,0 +1,111 @@
+"""The ring and any-alignment GEMM kernels at the sizes where a tile, a stage or a 16-byte piece ends.
+
+Operands are -1, 0 or 1, so every partial sum is a whole number below 2^11 and exact in FP32 and FP16: the results must equal
+the matrix product exactly, whatever the order of the sums.  Operands are windows of buffers filled with NaN (a read outside a window that reaches
+a result shows), outputs windows of buffers whose surroundings must stay as they were."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import conv, fp16
+from paper_1710_03740_amd import binding as mpt
+from gpu_util import dev16, host, host16
+
+pytestmark = pytest.mark.gpu
+
+# (M, N, K): below, at and above tiles of 64 and 128, stages of 64 and pieces of 8; the last two take the 128 x 128 tiles
+SIZES = [(1, 8, 8), (7, 3, 5), (63, 72, 200), (64, 64, 64), (65, 136, 72), (127, 129, 191), (128, 192, 256), (200, 56, 1000),
+         (65, 63, 509), (2056, 1544, 520), (3001, 3003, 517)]
+# row padding in elements and offset of the window's first element: whole 16-byte pieces; odd strides; odd bases
+LAYOUTS = [(0, 0), (8, 0), (8, 16), (1, 0), (3, 5)]
+
+
+def window(rows, cols, pad, offset, values=None, dtype=torch.float16):
+    ld = cols + pad
+    buf = torch.full((rows * ld + offset + 64,), float("nan"), dtype=dtype, device="cuda")
+    view = buf[offset:offset + rows * ld].view(rows, ld)[:, :cols]
+    if values is not None:
+        view.copy_(dev16(values) if values.dtype == np.float16 else torch.from_numpy(values).cuda())
+    return buf, view
+
+
+def outside_untouched(buf, view):
+    inside = torch.zeros_like(buf, dtype=torch.bool)
+    inside.as_strided(view.shape, view.stride(), view.storage_offset()).fill_(True)
+    return bool(torch.isnan(buf[~inside]).all())
+
+
+def ws_for(op, M, N, K):
+    need = mpt.mpt_gemm_workspace_bytes(op, M, N, K)
+    return torch.empty(need // 4, dtype=torch.float32, device="cuda") if need else None
+
+
+@pytest.mark.parametrize("pad,offset", LAYOUTS)
+@pytest.mark.parametrize("M,N,K", SIZES)
+def test_edges_of_tiles_stages_and_pieces(M, N, K, pad, offset):
+    if M > 1000 and (pad, offset) not in ((0, 0), (3, 5)):
+        pytest.skip("the large sizes are there for their tiles: two layouts do")
+    rng = np.random.default_rng(M + 3 * N + 7 * K + pad)
+    X, W, G, H = (rng.integers(-1, 2, s).astype(np.float16) for s in ((M, K), (K, N), (M, N), (M, K)))
+    x, w, g, h = (window(*a.shape, pad, offset, a)[1] for a in (X, W, G, H))
+    X, W, G = (a.astype(np.float64) for a in (X, W, G))
+    want = {"fwd": X @ W, "dgrad": G @ W.T, "wgrad": X.T @ G}
+    for split in (False, True):
+        def run(name, op, shape, call, expect):
+            print(name, (M, N, K), (pad, offset), split, flush=True)
+            buf, out = window(*shape, pad, offset)
+            call(out, ws_for(op, M, N, K) if split else None)
+            assert np.array_equal(host16(out.contiguous()).astype(np.float64), expect), name
+            assert outside_untouched(buf, out), name
+        run("fwd", 0, (M, N), lambda o, ws: mpt.mpt_gemm_fwd(x, w, o, ws), want["fwd"])
+        run("fwd relu", 0, (M, N), lambda o, ws: mpt.mpt_gemm_fwd_relu(x, w, o, ws), np.maximum(want["fwd"], 0))
+        run("dgrad", 1, (M, K), lambda o, ws: mpt.mpt_gemm_dgrad(g, w, o, ws), want["dgrad"])
+        run("dgrad relu", 1, (M, K), lambda o, ws: mpt.mpt_gemm_dgrad_relu(g, w, h, o, ws), np.where(H > 0, want["dgrad"], 0))
+        flag = torch.zeros(1, dtype=torch.int32, device="cuda")
+        run("wgrad", 2, (K, N), lambda o, ws: mpt.mpt_gemm_wgrad(x, g, o, flag=flag, ws=ws), want["wgrad"])
+        assert int(flag.item()) == 0
+        buf, out = window(K, N, pad, offset, dtype=torch.float32)
+        mpt.mpt_gemm_wgrad(x, g, out, flag=flag, ws=ws_for(2, M, N, K) if split else None)
+        mpt.mpt_gemm_wgrad(x, g, out, accumulate=True, flag=flag, ws=ws_for(2, M, N, K) if split else None)
+        assert np.array_equal(host(out.contiguous()).astype(np.float64), 2 * want["wgrad"]) and outside_untouched(buf, out)
+        assert int(flag.item()) == 0
+
+
+@pytest.mark.parametrize("pad", [0, 1])
+def test_special_values_stay_in_their_rows_and_columns(pad):
+    """Pieces read past a ragged edge must not carry an Inf or NaN of one row or column into others."""
+    M, N, K = 130, 72 + pad, 136 + pad
+    X, W = np.ones((M, K), np.float16), np.ones((K, N), np.float16)
+    X[M - 1, K - 1] = np.inf
+    W[K - 1, N - 1] = np.nan
+    y = torch.empty((M, N), dtype=torch.float16, device="cuda")
+    mpt.mpt_gemm_fwd(dev16(X), dev16(W), y)
+    got = host16(y)
+    assert np.isnan(got[:, N - 1]).all()
+    assert np.isinf(got[M - 1, :N - 1]).all()
+    assert (got[:M - 1, :N - 1] == K).all()
+    flag = torch.zeros(1, dtype=torch.int32, device="cuda")
+    dw = torch.empty((K, N), dtype=torch.float16, device="cuda")
+    G = np.ones((M, N), np.float16)
+    mpt.mpt_gemm_wgrad(dev16(X), dev16(G), dw, flag=flag)
+    got = host16(dw)
+    assert np.isinf(got[K - 1]).all() and (got[:K - 1] == M).all() and int(flag.item()) == 1
+
+
+# channel counts below, at and between the stages of 64; output columns around the tiles; images smaller than a stage and wider
+@pytest.mark.parametrize("Nb,H,W,C,Kf", [(1, 3, 3, 8, 64), (2, 5, 70, 8, 72), (1, 1, 65, 16, 24), (3, 9, 1, 40, 136), (2, 7, 7, 64, 64), (2, 8, 6, 72, 200),
+                                         (1, 13, 13, 192, 56), (4, 14, 14, 128, 64)])
+def test_convolution_edges(Nb, H, W, C, Kf):
+    rng = np.random.default_rng(Nb + H + W + C + Kf)
+    x, w, dy = (rng.integers(-1, 2, s).astype(np.float16) for s in ((Nb, H, W, C), (Kf, 3, 3, C), (Nb, H, W, Kf)))
+    d_x, d_w, d_dy = dev16(x), dev16(w), dev16(dy)
+    want = (conv.conv3x3_fwd(x, w)[0], conv.conv3x3_dgrad(dy, w)[0], conv.conv3x3_wgrad(x, dy)[0])
+    for split in (False, True):
+        for op, shape, call in ((0, (Nb, H, W, Kf), lambda o, ws: mpt.mpt_conv3x3_fwd(d_x, d_w, o, ws)), (1, (Nb, H, W, C), lambda o, ws: mpt.mpt_conv3x3_dgrad(d_dy, d_w, o, ws)),
+                                (2, (Kf, 3, 3, C), lambda o, ws: mpt.mpt_conv3x3_wgrad(d_x, d_dy, o, ws=ws))):
+            need = mpt.mpt_conv3x3_workspace_bytes(op, Nb, H, W, C, Kf) if split else 0
+            out = torch.full(shape, float("nan"), dtype=torch.float16, device="cuda")
+            print("conv", op, (Nb, H, W, C, Kf), split, flush=True)
+            call(out, torch.empty(need // 4, dtype=torch.float32, device="cuda") if need else None)
+            got = host16(out)
+            assert np.array_equal(got.astype(np.float64), want[op].astype(np.float64)), (op, split)      # (a zero may carry either sign)
