@@ -212,20 +212,34 @@ __global__ __launch_bounds__(kThreads) void k_master_update_scalar(
 // kernel's arguments; a workgroup finds its tensor by walking the table of first workgroups (wavefront-uniform) and
 // then does what k_master_update / k_master_update_scalar do for that tensor: pairs where the tensor's buffers are
 // aligned for them, single elements else, one trip per thread.  Same operations, same results.
+//
+// The table comes in sizes of 4, 16 and 48 tensors: with room for 48 (2.2 KB of arguments) the launch kept the host busy for
+// 26 us, a smaller kernel's arguments for 3.5 us, and a step has often two or three tensors to update.
 constexpr int kMultiMax = 48;
+template <int MAX>
 struct MultiItems {
-  float* w32[kMultiMax];
-  float* m32[kMultiMax];
-  const void* grad[kMultiMax];
-  uint16_t* w16[kMultiMax];
-  unsigned long long n[kMultiMax];
-  unsigned first_block[kMultiMax + 1];     // workgroups [first_block[k], first_block[k + 1]) belong to tensor k
+  float* w32[MAX];
+  float* m32[MAX];
+  const void* grad[MAX];
+  uint16_t* w16[MAX];
+  unsigned long long n[MAX];
+  unsigned first_block[MAX + 1];           // workgroups [first_block[k], first_block[k + 1]) belong to tensor k
   unsigned pairs_mask_lo, pairs_mask_hi;   // bit k: tensor k moves in pairs
   int count;
 };
+template <int MAX>
+MultiItems<MAX> smaller_table(const MultiItems<kMultiMax>& all) {
+  MultiItems<MAX> it{};
+  for (int k = 0; k < all.count; ++k) {
+    it.w32[k] = all.w32[k]; it.m32[k] = all.m32[k]; it.grad[k] = all.grad[k]; it.w16[k] = all.w16[k]; it.n[k] = all.n[k];
+    it.first_block[k + 1] = all.first_block[k + 1];
+  }
+  it.pairs_mask_lo = all.pairs_mask_lo; it.pairs_mask_hi = all.pairs_mask_hi; it.count = all.count;
+  return it;
+}
 
-template <bool MOM, bool G32>
-__global__ __launch_bounds__(kThreads) void k_master_update_multi(MultiItems it, float inv_scale, const mpt_scaler* __restrict__ scaler,
+template <bool MOM, bool G32, int MAX>
+__global__ __launch_bounds__(kThreads) void k_master_update_multi(MultiItems<MAX> it, float inv_scale, const mpt_scaler* __restrict__ scaler,
                                                                  float lr, float mu, const uint32_t* __restrict__ flag) {
   int k = 0;
   while (k + 1 < it.count && blockIdx.x >= it.first_block[k + 1]) ++k;
@@ -793,12 +807,17 @@ extern "C" int mpt_master_update_multi(void* stream, int count, const mpt_update
   if (with_mom != 0 && with_mom != live) return MPT_ERR_ARG;      // momentum buffers for all tensors or for none
   const bool mom = with_mom != 0, g32 = grad_is_fp32 != 0;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  MultiItems it;
+  MultiItems<kMultiMax> it;
   auto flush = [&](int filled) -> int {
     if (filled == 0) return MPT_OK;
     it.count = filled;
     const unsigned grid = it.first_block[filled];
-#define MPT_MM(M, G) hipLaunchKernelGGL((k_master_update_multi<M, G>), dim3(grid), dim3(kThreads), 0, s, it, inv_scale, scaler, lr, momentum, flag)
+#define MPT_MM(M, G)                                                                                                                                     \
+  do {                                                                                                                                                   \
+    if (filled <= 4) hipLaunchKernelGGL((k_master_update_multi<M, G, 4>), dim3(grid), dim3(kThreads), 0, s, smaller_table<4>(it), inv_scale, scaler, lr, momentum, flag);          \
+    else if (filled <= 16) hipLaunchKernelGGL((k_master_update_multi<M, G, 16>), dim3(grid), dim3(kThreads), 0, s, smaller_table<16>(it), inv_scale, scaler, lr, momentum, flag);   \
+    else hipLaunchKernelGGL((k_master_update_multi<M, G, kMultiMax>), dim3(grid), dim3(kThreads), 0, s, it, inv_scale, scaler, lr, momentum, flag);                                \
+  } while (0)
     if (mom) { if (g32) MPT_MM(true, true); else MPT_MM(true, false); }
     else     { if (g32) MPT_MM(false, true); else MPT_MM(false, false); }
 #undef MPT_MM
