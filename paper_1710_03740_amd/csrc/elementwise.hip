@@ -669,7 +669,23 @@ __global__ __launch_bounds__(1024) void k_softmax_xent_long(
 __global__ __launch_bounds__(kThreads) void k_loss_mean(int64_t B, const float* __restrict__ row_loss, float* __restrict__ loss) {
   __shared__ float part[kThreads];
   float acc = 0.f;
-  for (int64_t r = threadIdx.x; r < B; r += kThreads) acc = __fadd_rn(acc, row_loss[r]);
+  int64_t r = threadIdx.x;
+  constexpr int kInFlight = 16;                    // added in row order all the same; one load at a time, 5120 rows took 7.5 us
+  for (; r + (kInFlight - 1) * kThreads < B; r += kInFlight * kThreads) {
+    float v[kInFlight];
+#pragma unroll
+    for (int u = 0; u < kInFlight; ++u) v[u] = row_loss[r + u * kThreads];
+#pragma unroll
+    for (int u = 0; u < kInFlight; ++u) acc = __fadd_rn(acc, v[u]);
+  }
+  {                                                // the rest likewise; a row beyond the last is read as the last and left out
+    float v[kInFlight];
+#pragma unroll
+    for (int u = 0; u < kInFlight; ++u) v[u] = row_loss[min(r + u * kThreads, B - 1)];
+#pragma unroll
+    for (int u = 0; u < kInFlight; ++u)
+      if (r + u * kThreads < B) acc = __fadd_rn(acc, v[u]);
+  }
   part[threadIdx.x] = acc;
   __syncthreads();
   for (int w = kThreads / 2; w > 0; w >>= 1) {
