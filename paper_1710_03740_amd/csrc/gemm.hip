@@ -1350,19 +1350,25 @@ __global__ __launch_bounds__(256) void k_split_reduce4(const float* __restrict__
     const float4v* p4 = reinterpret_cast<const float4v*>(part);
     float4v s = p4[q];
     int k = 1;
-    for (; k + 8 <= splits; k += 8) {
-      float4v v[8];
+    for (; k + 16 <= splits; k += 16) {                                // a small output has one wavefront per SIMD: what it has in flight is all there is
+      float4v v[16];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = p4[(int64_t)(k + u) * total4 + q];
+      for (int u = 0; u < 16; ++u) v[u] = p4[(int64_t)(k + u) * total4 + q];
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
+      for (int u = 0; u < 16; ++u)
 #pragma unroll
         for (int e = 0; e < 4; ++e) s[e] = __fadd_rn(s[e], v[u][e]);
     }
-    for (; k < splits; ++k) {
-      const float4v v = p4[(int64_t)k * total4 + q];
+    for (; k < splits; k += 8) {                                       // up to 8 at a time, those beyond the last left out
+      float4v v[8];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) s[e] = __fadd_rn(s[e], v[e]);
+      for (int u = 0; u < 8; ++u) v[u] = p4[(int64_t)min(k + u, splits - 1) * total4 + q];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (k + u < splits) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) s[e] = __fadd_rn(s[e], v[u][e]);
+        }
     }
     const int64_t idx = q << 2, i = idx / J, j = idx - i * J;
     if (ep.mode == 0) {
@@ -1568,15 +1574,17 @@ bool try_launch_split128(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B
   return true;
 }
 
-// What a launch takes, in us: a start, and a share per stage of depth 64 and workgroup on a CU - between the mean and the
-// busiest CU's count, since workgroups of one CU share it (fitted to 64 .. 4000 rows and columns over 1 .. 128 stages; mostly
-// within a fifth).  A split costs a second launch and its partials' way to memory and back.
+// What a launch takes, in us: a start, and a share per stage of depth 64 and workgroup on the busiest CUs, which workgroups of one
+// CU share (fitted to 64 .. 4000 rows and columns over 1 .. 128 stages; mostly within a fifth).  Rows that do not start on
+// cache lines (`lines` false) need two lines for one line's data.  A split costs a second launch and its partials' way to
+// memory and back.
 struct RingCost { double start, stage, alone = 1.0; };   // alone: shares of a workgroup that has its CU to itself (what its waits leave idle)
-constexpr RingCost kRing64 = {3.6, 0.25}, kRing128 = {5.6, 0.55}, kAny64 = {4.3, 0.5}, kAny128 = {8.5, 1.4}, kWhole256 = {6.0, 1.5};
+constexpr RingCost kRing64[2] = {{3.6, 0.26, 1.05}, {3.6, 0.22, 1.1}}, kRing128x64Cost[2] = {{4.6, 0.42}, {4.6, 0.36}}, kRing128[2] = {{5.6, 0.58, 1.05}, {5.6, 0.5}};
+constexpr RingCost kAny64 = {4.3, 0.5}, kAny128 = {8.5, 1.4}, kWhole256 = {6.0, 1.5};
 constexpr RingCost kConvWgrad64 = {4.0, 0.26, 1.6}, kConvWgrad128 = {6.0, 0.6, 1.3};
 double ring_cost(const RingCost& c, int64_t tiles, int64_t I, int64_t J, int stages, int64_t splits) {
   const int64_t wgs = tiles * splits;
-  const double per_cu = wgs <= kCUs ? c.alone : 0.5 * ((double)wgs / kCUs + (double)((wgs + kCUs - 1) / kCUs));
+  const double per_cu = wgs <= kCUs ? c.alone : 0.2 * ((double)wgs / kCUs) + 0.8 * (double)((wgs + kCUs - 1) / kCUs);
   const double partials = splits > 1 ? 2.4 + (double)splits * (double)I * (double)J * 8.0 / 5.0e6 : 0.0;
   return c.start + c.stage * stages * per_cu + partials;
 }
@@ -1584,7 +1592,7 @@ double ring_cost(const RingCost& c, int64_t tiles, int64_t I, int64_t J, int sta
 // The ring kernels' tile and split (gemm_ring.hip): the cheapest of the two tiles and of the splits that the workspace has
 // room for (`max_splits` partial outputs).  `cost` receives its estimate.
 struct RingPlan { RingTile tile; int splits, ktiles_per_split; double cost; };
-RingPlan ring_plan(int64_t I, int64_t J, int64_t R, int max_splits, bool whole_chunks, bool conv_wgrad = false, bool conv_rows = false) {
+RingPlan ring_plan(int64_t I, int64_t J, int64_t R, int max_splits, bool whole_chunks, bool lines, bool conv_wgrad = false, bool conv_rows = false) {
   const int force_tile = MPT_TUNABLE("MPT_RING_TILE", -1), force_split = MPT_TUNABLE("MPT_RING_SPLITS", 0);   // tuning builds only
   const int kt = (int)((R + BK - 1) / BK);
   RingPlan best{kRing64x64, 1, kt, 1e30};
@@ -1604,14 +1612,17 @@ RingPlan ring_plan(int64_t I, int64_t J, int64_t R, int max_splits, bool whole_c
   if (conv_rows) {
     // rows are pixels: many tiles, so the wide tile, or where one tile column of 64 holds the output the tall one
     // (64 channels at 64 x 56 x 56: 32 against 48 us; 128 columns in two tall tiles were 2 us behind the square one)
-    consider(J <= 64 ? kRing256x64 : kRing128x128, kRing128);
-    if (force_tile >= 0 && best.cost == 1e30) consider((RingTile)force_tile, kRing128);
+    consider(J <= 64 ? kRing256x64 : kRing128x128, kRing128[1]);
+    if (force_tile >= 0 && best.cost == 1e30) consider((RingTile)force_tile, kRing128[1]);
     return best;
   }
-  consider(kRing64x64, conv_wgrad ? kConvWgrad64 : whole_chunks ? kRing64 : kAny64);
-  consider(kRing128x128, conv_wgrad ? kConvWgrad128 : whole_chunks ? kRing128 : kAny128);
+  consider(kRing64x64, conv_wgrad ? kConvWgrad64 : whole_chunks ? kRing64[lines] : kAny64);
+  if (whole_chunks && !conv_wgrad) consider(kRing128x64, kRing128x64Cost[lines]);
+  consider(kRing128x128, conv_wgrad ? kConvWgrad128 : whole_chunks ? kRing128[lines] : kAny128);
   return best;
 }
+
+bool on_lines(const RingMatSrc& m) { return (m.ld % 64) == 0 && mpt_aligned(m.base, 128); }
 
 // Run one contraction: single pass, or split partials + ordered reduction.
 template <bool A_RC, bool B_RC>
@@ -1641,7 +1652,7 @@ int run(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool aligned, i
   if (pl.splits > 1) {
     first.out = ws; first.ld = J; first.mode = 3; first.flag = nullptr;
   }
-  const RingPlan rp = ring_plan(I, J, R, ws != nullptr ? pl.splits : 1, aligned);
+  const RingPlan rp = ring_plan(I, J, R, ws != nullptr ? pl.splits : 1, aligned, on_lines(A) && on_lines(B));
   // Whole tiles whose reduction is short for its splits: the partials cost more than the smaller tiles' extra reads (the
   // projection's weight gradient, 8192 x 1024 over 256 accumulated in FP32: 39.6 us in two splits, 18.7 us unsplit)
   const bool rather_ring = pl.splits > 1 && rp.cost < 0.8 * ring_cost(kWhole256, (int64_t)pl.tiles_i * pl.tiles_j, I, J, pl.ktiles_per_split, pl.splits);
@@ -1871,7 +1882,7 @@ int run_conv_ring(hipStream_t s, int op, int64_t Nb, int64_t H, int64_t W, int64
                 R = op == MPT_OP_FWD ? 9 * C : op == MPT_OP_DGRAD ? 9 * Kf : P;
   const Plan pl = make_plan(I, J, R, ws != nullptr);
   if (ws != nullptr && ws_bytes < plan_ws_bytes(pl, I, J)) return MPT_ERR_WORKSPACE;
-  const RingPlan rp = ring_plan(I, J, R, ws != nullptr ? pl.splits : 1, true, op == MPT_OP_WGRAD, op != MPT_OP_WGRAD);
+  const RingPlan rp = ring_plan(I, J, R, ws != nullptr ? pl.splits : 1, true, true, op == MPT_OP_WGRAD, op != MPT_OP_WGRAD);
   Epilogue first = ep;
   if (rp.splits > 1) {
     first.out = ws; first.ld = J; first.mode = 3; first.flag = nullptr;

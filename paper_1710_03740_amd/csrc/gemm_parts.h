@@ -127,8 +127,8 @@ __device__ __forceinline__ void keep_until_here(const half8& f) { asm volatile("
 // One matrix operand: element (o, r) at base[o*ld + r] (reduction-contiguous) or base[r*ld + o] (outer-contiguous).
 struct RingMatSrc { const uint16_t* base; int64_t ld; int O, R; };
 // Tiles of the ring kernels (output rows x columns per workgroup).
-enum RingTile { kRing128x128 = 0, kRing64x64 = 1, kRing256x64 = 2 };
-constexpr int ring_tile_rows(RingTile t) { return t == kRing128x128 ? 128 : t == kRing256x64 ? 256 : 64; }
+enum RingTile { kRing128x128 = 0, kRing64x64 = 1, kRing256x64 = 2, kRing128x64 = 3 };
+constexpr int ring_tile_rows(RingTile t) { return t == kRing64x64 ? 64 : t == kRing256x64 ? 256 : 128; }
 constexpr int ring_tile_cols(RingTile t) { return t == kRing128x128 ? 128 : 64; }
 
 // C[i,j] = sum_r A(i,r) * B(r,j) over plain matrices; `whole_chunks`: both operands can be fetched in 16-byte aligned

@@ -713,10 +713,12 @@ Problem ring_problem(RingTile tile, int ktiles_per_split, int I, int J, int R) {
 
 template <class AOp, class BOp, int BM, int BN, int WM, int WN, int NS>
 int launch_ring(hipStream_t s, const typename AOp::Src& A, const typename BOp::Src& B, const Problem& pb, const Epilogue& ep) {
-#ifdef MPT_TUNING
-  if constexpr (NS == 2 && 4 * (BM + BN) * 128 <= 163840) { if (MPT_TUNABLE("MPT_RING_DEEP", 0)) return launch_ring<AOp, BOp, BM, BN, WM, WN, 4>(s, A, B, pb, ep); }
-  if constexpr (NS == 4) { if (MPT_TUNABLE("MPT_RING_SHALLOW", 0)) return launch_ring<AOp, BOp, BM, BN, WM, WN, 2>(s, A, B, pb, ep); }
-#endif
+  // Two slots let two workgroups share a CU, which cover each other's waits.  A workgroup that has its CU to itself has only
+  // its own loads in flight: four slots (2000 x 1000 over 3000 in 256 tiles of 128 x 64: 39 -> 25 us; with 752 workgroups four
+  // slots would cost a quarter).  Not for the convolutions: their small ones lose a microsecond.
+  if constexpr (NS == 2 && 4 * (BM + BN) * 128 <= 163840 && std::is_same<typename AOp::Src, RingMatSrc>::value && std::is_same<typename BOp::Src, RingMatSrc>::value) {
+    if ((int64_t)pb.tiles_i * pb.tiles_j * pb.splits <= kCUs) return launch_ring<AOp, BOp, BM, BN, WM, WN, 4>(s, A, B, pb, ep);
+  }
   auto k = k_gemm_ring<AOp, BOp, BM, BN, WM, WN, NS>;
   constexpr int lds = NS * (BM + BN) * 128;
   static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds), true);
@@ -730,6 +732,7 @@ template <bool A_RC, bool B_RC>
 int launch_plain(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool whole_chunks, RingTile tile, const Problem& pb, const Epilogue& ep) {
   if (whole_chunks) {
     if (tile == kRing64x64) return launch_ring<RingMat<A_RC, 64>, RingMat<B_RC, 64>, 64, 64, 32, 32, 4>(s, A, B, pb, ep);
+    if (tile == kRing128x64) return launch_ring<RingMat<A_RC, 128>, RingMat<B_RC, 64>, 128, 64, 64, 32, 2>(s, A, B, pb, ep);
     return launch_ring<RingMat<A_RC, 128>, RingMat<B_RC, 128>, 128, 128, 64, 64, 2>(s, A, B, pb, ep);
   }
   const dim3 grid((unsigned)((int64_t)pb.tiles_i * pb.tiles_j * pb.splits));
@@ -743,7 +746,7 @@ int launch_plain(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool w
 
 int launch_ring_plain(hipStream_t s, bool a_rc, bool b_rc, const RingMatSrc& A, const RingMatSrc& B, bool whole_chunks, RingTile tile,
                       int ktiles_per_split, int I, int J, int R, const Epilogue& ep) {
-  if (tile != kRing64x64) tile = kRing128x128;
+  if (tile == kRing256x64 || (tile == kRing128x64 && !whole_chunks)) tile = kRing128x128;
   const Problem pb = ring_problem(tile, ktiles_per_split, I, J, R);
   if (a_rc) return b_rc ? launch_plain<true, true>(s, A, B, whole_chunks, tile, pb, ep) : launch_plain<true, false>(s, A, B, whole_chunks, tile, pb, ep);
   return launch_plain<false, false>(s, A, B, whole_chunks, tile, pb, ep);       // both along the output: no product here has only A so

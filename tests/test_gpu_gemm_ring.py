@@ -13,9 +13,9 @@ from gpu_util import dev16, host, host16
 
 pytestmark = pytest.mark.gpu
 
-# (M, N, K): below, at and above tiles of 64 and 128, stages of 64 and pieces of 8; the last two take the 128 x 128 tiles
+# (M, N, K): below, at and above tiles of 64 and 128, stages of 64 and pieces of 8; the last three take the 128 x 64 and 128 x 128 tiles
 SIZES = [(1, 8, 8), (7, 3, 5), (63, 72, 200), (64, 64, 64), (65, 136, 72), (127, 129, 191), (128, 192, 256), (200, 56, 1000),
-         (65, 63, 509), (2056, 1544, 520), (3001, 3003, 517)]
+         (65, 63, 509), (520, 2000, 1992), (2056, 1544, 520), (3001, 3003, 517)]
 # row padding in elements and offset of the window's first element: whole 16-byte pieces; odd strides; odd bases
 LAYOUTS = [(0, 0), (8, 0), (8, 16), (1, 0), (3, 5)]
 
