@@ -678,12 +678,12 @@ __global__ __launch_bounds__(kThreads) void k_loss_mean(int64_t B, const float* 
 #pragma unroll
     for (int u = 0; u < kInFlight; ++u) acc = __fadd_rn(acc, v[u]);
   }
-  {                                                // the rest likewise; a row beyond the last is read as the last and left out
-    float v[kInFlight];
+  for (; r < B; r += 4 * kThreads) {               // the rest likewise; a row beyond the last is read as the last and left out
+    float v[4];
 #pragma unroll
-    for (int u = 0; u < kInFlight; ++u) v[u] = row_loss[min(r + u * kThreads, B - 1)];
+    for (int u = 0; u < 4; ++u) v[u] = row_loss[min(r + u * kThreads, B - 1)];
 #pragma unroll
-    for (int u = 0; u < kInFlight; ++u)
+    for (int u = 0; u < 4; ++u)
       if (r + u * kThreads < B) acc = __fadd_rn(acc, v[u]);
   }
   part[threadIdx.x] = acc;

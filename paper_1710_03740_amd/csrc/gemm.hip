@@ -1667,7 +1667,9 @@ int run(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool aligned, i
   if (rp.splits > 1) {
     first.out = ws; first.ld = J; first.mode = 3; first.flag = nullptr;
   }
-  st = launch_ring_plain(s, A_RC, B_RC, A, B, aligned, rp.tile, rp.ktiles_per_split, I, J, R, first);
+  // an FP32 result keeps the pieces that the planner's split would have summed it in
+  const int cut = !A_RC && ep.mode != 0 && ws != nullptr && pl.ktiles_per_split < rp.ktiles_per_split ? pl.ktiles_per_split : 0;
+  st = launch_ring_plain(s, A_RC, B_RC, A, B, aligned, rp.tile, rp.ktiles_per_split, cut, I, J, R, first);
   if (st == MPT_OK && rp.splits > 1) {
     launch_split_reduce(s, ws, rp.splits, I, J, ep);
     MPT_LAUNCH_CHECK();

@@ -547,8 +547,24 @@ __device__ __forceinline__ void store_tile(const Problem& pb, const Epilogue& ep
 // One barrier per stage, between its halves: every wavefront then holds its fragments of the second half in registers, so
 // the slot can be refilled (stage s + NS), and stage s + 1, which the reads behind the barrier belong to, has landed
 // everywhere.
-template <class AOp, class BOp, int BM, int BN, int WM, int WN, int NS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_ring(typename AOp::Src A, typename BOp::Src B, Problem pb, Epilogue ep) {
+//
+// CUT: the sums are cut every `cut` stages, the pieces added up in order by FP32 additions of their own, as split partials are.
+// An FP32 result shows the length of its accumulation chain (512 terms in one chain 1.45e-7 off, in four 0.87e-7), so an
+// unsplit launch that takes the place of a split one keeps the split's pieces.
+template <int FM, int FN>
+__device__ __forceinline__ void add_piece(float4v (&total)[FM][FN], float4v (&acc)[FM][FN]) {
+#pragma unroll
+  for (int a = 0; a < FM; ++a)
+#pragma unroll
+    for (int b = 0; b < FN; ++b)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        total[a][b][v] = __fadd_rn(total[a][b][v], acc[a][b][v]);
+        acc[a][b][v] = 0.f;
+      }
+}
+template <class AOp, class BOp, int BM, int BN, int WM, int WN, int NS, bool CUT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_ring(typename AOp::Src A, typename BOp::Src B, Problem pb, Epilogue ep, int cut) {
   static_assert((BM / WM) * (BN / WN) == 4, "four wavefronts");
   constexpr int FM = WM / 16, FN = WN / 16, A_BYTES = BM * 128, STAGE = (BM + BN) * 128, LA = AOp::NB, LB = BOp::NB, L = LA + LB;
   static_assert((NS & (NS - 1)) == 0 && (NS - 1) * L < 64, "slots; loads in flight fit the counter");
@@ -580,13 +596,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   };
 
   for (int q = 0; q < min(NS, nst); ++q) issue(q);
-  float4v acc[FM][FN];
+  float4v acc[FM][FN], total[CUT ? FM : 1][CUT ? FN : 1];
+  int to_cut = cut;
 #pragma unroll
   for (int a = 0; a < FM; ++a)
 #pragma unroll
     for (int b = 0; b < FN; ++b)
 #pragma unroll
       for (int v = 0; v < 4; ++v) acc[a][b][v] = 0.f;
+  if constexpr (CUT) {
+#pragma unroll
+    for (int a = 0; a < FM; ++a)
+#pragma unroll
+      for (int b = 0; b < FN; ++b) total[a][b] = acc[a][b];
+  }
   RingFrag<AOp::kRC, BM, FM> ra;
   RingFrag<BOp::kRC, BN, FN> rb;
   const uint32_t lds0 = lds_offset(lds);
@@ -616,18 +639,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     __builtin_amdgcn_sched_barrier(0);
     if (s + NS < nst) issue(s + NS);                                 // under the multiplications already issued
     multiply<FM / 2, FM>(acc, fa[1], fb[1]);
+    if constexpr (CUT) {
+      if (--to_cut == 0) {
+        to_cut = cut;
+        add_piece<FM, FN>(total, acc);
+      }
+    }
     __builtin_amdgcn_sched_barrier(0);
   }
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
   arrived(fa[0]);
   arrived(fb[0]);
+  if constexpr (CUT) {
+    if (to_cut != cut) add_piece<FM, FN>(total, acc);
+    store_tile<FM, FN>(pb, ep, sp, i0 + wm * WM, j0 + wn * WN, lane, total, lds + wave * (WM * WN * 4));
+    return;
+  }
   store_tile<FM, FN>(pb, ep, sp, i0 + wm * WM, j0 + wn * WN, lane, acc, lds + wave * (WM * WN * 4));
 }
 
 // The same with the pieces of one stage in registers on their way to one of two LDS slots: behind the barrier of stage s the
 // pieces of stage s + 2 are written into the slot that stage s has left, and those of stage s + 3 are loaded.
-template <class AOp, class BOp, int BM, int BN, int WM, int WN>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_any(RingMatSrc A, RingMatSrc B, Problem pb, Epilogue ep) {
+template <class AOp, class BOp, int BM, int BN, int WM, int WN, bool CUT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_any(RingMatSrc A, RingMatSrc B, Problem pb, Epilogue ep, int cut) {
   static_assert((BM / WM) * (BN / WN) == 4, "four wavefronts");
   constexpr int FM = WM / 16, FN = WN / 16, A_BYTES = BM * 128, STAGE = (BM + BN) * 128, LA = AOp::NB, LB = BOp::NB;
   static_assert(2 * STAGE >= 4 * WM * WN * 4, "the store's buffers fit the slots");
@@ -657,13 +691,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     db.store(s, st + A_BYTES + wave * (LB * 1024));
   };
   load(0);
-  float4v acc[FM][FN];
+  float4v acc[FM][FN], total[CUT ? FM : 1][CUT ? FN : 1];
+  int to_cut = cut;
 #pragma unroll
   for (int a = 0; a < FM; ++a)
 #pragma unroll
     for (int b = 0; b < FN; ++b)
 #pragma unroll
       for (int v = 0; v < 4; ++v) acc[a][b][v] = 0.f;
+  if constexpr (CUT) {
+#pragma unroll
+    for (int a = 0; a < FM; ++a)
+#pragma unroll
+      for (int b = 0; b < FN; ++b) total[a][b] = acc[a][b];
+  }
   RingFrag<AOp::kRC, BM, FM> ra;
   RingFrag<BOp::kRC, BN, FN> rb;
   const uint32_t lds0 = lds_offset(lds);
@@ -697,11 +738,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     store(s + 2);
     load(s + 3);
     multiply<FM / 2, FM>(acc, fa[1], fb[1]);
+    if constexpr (CUT) {
+      if (--to_cut == 0) {
+        to_cut = cut;
+        add_piece<FM, FN>(total, acc);
+      }
+    }
     __builtin_amdgcn_sched_barrier(0);
   }
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
   arrived(fa[0]);
   arrived(fb[0]);
+  if constexpr (CUT) {
+    if (to_cut != cut) add_piece<FM, FN>(total, acc);
+    store_tile<FM, FN>(pb, ep, sp, i0 + wm * WM, j0 + wn * WN, lane, total, lds + wave * (WM * WN * 4));
+    return;
+  }
   store_tile<FM, FN>(pb, ep, sp, i0 + wm * WM, j0 + wn * WN, lane, acc, lds + wave * (WM * WN * 4));
 }
 
@@ -711,33 +763,39 @@ Problem ring_problem(RingTile tile, int ktiles_per_split, int I, int J, int R) {
   return Problem{I, J, R, (I + bm - 1) / bm, (J + bn - 1) / bn, (kt + ktiles_per_split - 1) / ktiles_per_split, ktiles_per_split};
 }
 
-template <class AOp, class BOp, int BM, int BN, int WM, int WN, int NS>
-int launch_ring(hipStream_t s, const typename AOp::Src& A, const typename BOp::Src& B, const Problem& pb, const Epilogue& ep) {
+template <class AOp, class BOp, int BM, int BN, int WM, int WN, int NS, bool CUT = false>
+int launch_ring(hipStream_t s, const typename AOp::Src& A, const typename BOp::Src& B, const Problem& pb, const Epilogue& ep, int cut = 0) {
   // Two slots let two workgroups share a CU, which cover each other's waits.  A workgroup that has its CU to itself has only
   // its own loads in flight: four slots (2000 x 1000 over 3000 in 256 tiles of 128 x 64: 39 -> 25 us; with 752 workgroups four
   // slots would cost a quarter).  Not for the convolutions: their small ones lose a microsecond.
   if constexpr (NS == 2 && 4 * (BM + BN) * 128 <= 163840 && std::is_same<typename AOp::Src, RingMatSrc>::value && std::is_same<typename BOp::Src, RingMatSrc>::value) {
-    if ((int64_t)pb.tiles_i * pb.tiles_j * pb.splits <= kCUs) return launch_ring<AOp, BOp, BM, BN, WM, WN, 4>(s, A, B, pb, ep);
+    if ((int64_t)pb.tiles_i * pb.tiles_j * pb.splits <= kCUs) return launch_ring<AOp, BOp, BM, BN, WM, WN, 4, CUT>(s, A, B, pb, ep, cut);
   }
-  auto k = k_gemm_ring<AOp, BOp, BM, BN, WM, WN, NS>;
+  auto k = k_gemm_ring<AOp, BOp, BM, BN, WM, WN, NS, CUT>;
   constexpr int lds = NS * (BM + BN) * 128;
   static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds), true);
   (void)once;
-  hipLaunchKernelGGL(k, dim3((unsigned)((int64_t)pb.tiles_i * pb.tiles_j * pb.splits)), dim3(256), lds, s, A, B, pb, ep);
+  hipLaunchKernelGGL(k, dim3((unsigned)((int64_t)pb.tiles_i * pb.tiles_j * pb.splits)), dim3(256), lds, s, A, B, pb, ep, cut);
   MPT_LAUNCH_CHECK();
   return MPT_OK;
 }
 
-template <bool A_RC, bool B_RC>
-int launch_plain(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool whole_chunks, RingTile tile, const Problem& pb, const Epilogue& ep) {
+template <bool A_RC, bool B_RC, bool CUT>
+int launch_plain(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool whole_chunks, RingTile tile, const Problem& pb, const Epilogue& ep, int cut) {
   if (whole_chunks) {
-    if (tile == kRing64x64) return launch_ring<RingMat<A_RC, 64>, RingMat<B_RC, 64>, 64, 64, 32, 32, 4>(s, A, B, pb, ep);
-    if (tile == kRing128x64) return launch_ring<RingMat<A_RC, 128>, RingMat<B_RC, 64>, 128, 64, 64, 32, 2>(s, A, B, pb, ep);
-    return launch_ring<RingMat<A_RC, 128>, RingMat<B_RC, 128>, 128, 128, 64, 64, 2>(s, A, B, pb, ep);
+    if (tile == kRing64x64) return launch_ring<RingMat<A_RC, 64>, RingMat<B_RC, 64>, 64, 64, 32, 32, 4, CUT>(s, A, B, pb, ep, cut);
+    if (tile == kRing128x64) return launch_ring<RingMat<A_RC, 128>, RingMat<B_RC, 64>, 128, 64, 64, 32, 2, CUT>(s, A, B, pb, ep, cut);
+    return launch_ring<RingMat<A_RC, 128>, RingMat<B_RC, 128>, 128, 128, 64, 64, 2, CUT>(s, A, B, pb, ep, cut);
   }
   const dim3 grid((unsigned)((int64_t)pb.tiles_i * pb.tiles_j * pb.splits));
-  if (tile == kRing64x64) hipLaunchKernelGGL((k_gemm_any<RegMat<A_RC, 64>, RegMat<B_RC, 64>, 64, 64, 32, 32>), grid, dim3(256), 2 * 128 * 128, s, A, B, pb, ep);
-  else hipLaunchKernelGGL((k_gemm_any<RegMat<A_RC, 128>, RegMat<B_RC, 128>, 128, 128, 64, 64>), grid, dim3(256), 2 * 256 * 128, s, A, B, pb, ep);
+  if constexpr (!CUT) {
+    if (tile != kRing64x64) {
+      hipLaunchKernelGGL((k_gemm_any<RegMat<A_RC, 128>, RegMat<B_RC, 128>, 128, 128, 64, 64, false>), grid, dim3(256), 2 * 256 * 128, s, A, B, pb, ep, 0);
+      MPT_LAUNCH_CHECK();
+      return MPT_OK;
+    }
+  }
+  hipLaunchKernelGGL((k_gemm_any<RegMat<A_RC, 64>, RegMat<B_RC, 64>, 64, 64, 32, 32, CUT>), grid, dim3(256), 2 * 128 * 128, s, A, B, pb, ep, cut);
   MPT_LAUNCH_CHECK();
   return MPT_OK;
 }
@@ -745,11 +803,14 @@ int launch_plain(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool w
 }  // namespace
 
 int launch_ring_plain(hipStream_t s, bool a_rc, bool b_rc, const RingMatSrc& A, const RingMatSrc& B, bool whole_chunks, RingTile tile,
-                      int ktiles_per_split, int I, int J, int R, const Epilogue& ep) {
+                      int ktiles_per_split, int cut, int I, int J, int R, const Epilogue& ep) {
+  // the cut sums of 128 x 128 tiles through registers would not fit the register file
+  if (!whole_chunks && cut > 0) tile = kRing64x64;
   if (tile == kRing256x64 || (tile == kRing128x64 && !whole_chunks)) tile = kRing128x128;
   const Problem pb = ring_problem(tile, ktiles_per_split, I, J, R);
-  if (a_rc) return b_rc ? launch_plain<true, true>(s, A, B, whole_chunks, tile, pb, ep) : launch_plain<true, false>(s, A, B, whole_chunks, tile, pb, ep);
-  return launch_plain<false, false>(s, A, B, whole_chunks, tile, pb, ep);       // both along the output: no product here has only A so
+  if (a_rc) return b_rc ? launch_plain<true, true, false>(s, A, B, whole_chunks, tile, pb, ep, 0) : launch_plain<true, false, false>(s, A, B, whole_chunks, tile, pb, ep, 0);
+  // both along the output (no product here has only A so): the weight gradient, the one with FP32 results
+  return cut > 0 ? launch_plain<false, false, true>(s, A, B, whole_chunks, tile, pb, ep, cut) : launch_plain<false, false, false>(s, A, B, whole_chunks, tile, pb, ep, 0);
 }
 
 int launch_ring_conv(hipStream_t s, int op, int64_t Nb, int64_t H, int64_t W, int64_t C, int64_t Kf, const uint16_t* img, const uint16_t* other,
