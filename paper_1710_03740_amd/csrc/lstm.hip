@@ -1,12 +1,12 @@
 // Pointwise part of an LSTM cell with FP16 tensors and FP32 math (paper Sec. 3.3, "point-wise operations"; the
 // recurrent layers of Sec. 4), forward and backward, for gfx950.  The matrix products around it are the GEMM entry
-// points.  Gate order (i, f, g, o) along the 4H axis.  A thread owns 8 consecutive hidden units of one batch row:
-// every tensor is touched with 16-byte accesses, once.  HBM-bound at large B*H: 30 bytes per hidden unit forward
+// points.  Gate order (i, f, g, o) along the 4H axis.  A thread owns 4 consecutive hidden units of one batch row
+// (or one of the up to 3 that are left at its end), wherever the rows start (250 x 8001 forward: 19.5 us element by element, 15.9 so):
+// every tensor is touched once, 8 bytes per lane.  HBM-bound at large B*H: 30 bytes per hidden unit forward
 // (two pre-activation tensors of 4 gates, previous state in; activations, state, output out), 22 bytes backward.
 #include "mpt_internal.h"
 
-typedef _Float16 lh8 __attribute__((ext_vector_type(8)));
-typedef _Float16 lh4 __attribute__((ext_vector_type(4)));
+typedef _Float16 lh4 __attribute__((ext_vector_type(4), aligned(2)));    // at any address: 8-byte accesses need no more alignment than their elements
 
 namespace {
 
@@ -29,11 +29,7 @@ __device__ __forceinline__ float tanhf_(float x) {
 // slower for small tensors that the next kernel reads again).
 template <int V, bool NT = false>
 __device__ __forceinline__ void ld16(const uint16_t* p, float (&v)[V]) {
-  if constexpr (V == 8) {
-    const lh8 q = NT ? __builtin_nontemporal_load(reinterpret_cast<const lh8*>(p)) : *reinterpret_cast<const lh8*>(p);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = (float)q[e];
-  } else if constexpr (V == 4) {
+  if constexpr (V == 4) {
     const lh4 q = NT ? __builtin_nontemporal_load(reinterpret_cast<const lh4*>(p)) : *reinterpret_cast<const lh4*>(p);
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] = (float)q[e];
@@ -43,13 +39,7 @@ __device__ __forceinline__ void ld16(const uint16_t* p, float (&v)[V]) {
 }
 template <int V, bool NT = false>
 __device__ __forceinline__ void st16(uint16_t* p, const float (&v)[V]) {
-  if constexpr (V == 8) {
-    lh8 q;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) q[e] = (_Float16)mpt_rounded_f32(v[e]);
-    if constexpr (NT) __builtin_nontemporal_store(q, reinterpret_cast<lh8*>(p));
-    else *reinterpret_cast<lh8*>(p) = q;
-  } else if constexpr (V == 4) {
+  if constexpr (V == 4) {
     lh4 q;
 #pragma unroll
     for (int e = 0; e < 4; ++e) q[e] = (_Float16)mpt_rounded_f32(v[e]);
@@ -60,15 +50,12 @@ __device__ __forceinline__ void st16(uint16_t* p, const float (&v)[V]) {
   }
 }
 
+// V cells of row b from unit j on
 template <int V, bool NT>
-__global__ __launch_bounds__(kT) void k_lstm_cell_fwd(int64_t B, int64_t H, const uint16_t* __restrict__ gx, int64_t ldgx,
-                                                      const uint16_t* __restrict__ gr, int64_t ldgr, const float* __restrict__ bias,
-                                                      const uint16_t* cprev, int64_t ldcp, uint16_t* __restrict__ act, int64_t ldact,
-                                                      uint16_t* c, int64_t ldc, uint16_t* __restrict__ h, int64_t ldh) {
-  const int64_t per_row = H / V;
-  const int64_t u = (int64_t)blockIdx.x * kT + threadIdx.x;
-  if (u >= B * per_row) return;
-  const int64_t b = u / per_row, j = (u - b * per_row) * V;
+__device__ __forceinline__ void cell_fwd(int64_t b, int64_t j, int64_t H, const uint16_t* __restrict__ gx, int64_t ldgx,
+                                         const uint16_t* __restrict__ gr, int64_t ldgr, const float* __restrict__ bias,
+                                         const uint16_t* cprev, int64_t ldcp, uint16_t* __restrict__ act, int64_t ldact,
+                                         uint16_t* c, int64_t ldc, uint16_t* __restrict__ h, int64_t ldh) {
   float a[4][V], cp[V];
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
@@ -99,15 +86,24 @@ __global__ __launch_bounds__(kT) void k_lstm_cell_fwd(int64_t B, int64_t H, cons
   st16<V, NT>(h + b * ldh + j, hn);
 }
 
-template <int V, bool NT>
-__global__ __launch_bounds__(kT) void k_lstm_cell_bwd(int64_t B, int64_t H, const uint16_t* __restrict__ dh, int64_t lddh,
-                                                      const uint16_t* dcn, int64_t lddcn, const uint16_t* __restrict__ act, int64_t ldact,
-                                                      const uint16_t* __restrict__ c, int64_t ldc, const uint16_t* __restrict__ cprev, int64_t ldcp,
-                                                      uint16_t* __restrict__ da, int64_t ldda, uint16_t* dcp, int64_t lddcp) {
-  const int64_t per_row = H / V;
+template <bool NT>
+__global__ __launch_bounds__(kT) void k_lstm_cell_fwd(int64_t B, int64_t H, const uint16_t* __restrict__ gx, int64_t ldgx,
+                                                      const uint16_t* __restrict__ gr, int64_t ldgr, const float* __restrict__ bias,
+                                                      const uint16_t* cprev, int64_t ldcp, uint16_t* __restrict__ act, int64_t ldact,
+                                                      uint16_t* c, int64_t ldc, uint16_t* __restrict__ h, int64_t ldh) {
+  const int64_t quads = H / 4, per_row = quads + (H & 3);
   const int64_t u = (int64_t)blockIdx.x * kT + threadIdx.x;
   if (u >= B * per_row) return;
-  const int64_t b = u / per_row, j = (u - b * per_row) * V;
+  const int64_t b = u / per_row, k = u - b * per_row;
+  if (k < quads) cell_fwd<4, NT>(b, k * 4, H, gx, ldgx, gr, ldgr, bias, cprev, ldcp, act, ldact, c, ldc, h, ldh);
+  else cell_fwd<1, false>(b, quads * 3 + k, H, gx, ldgx, gr, ldgr, bias, cprev, ldcp, act, ldact, c, ldc, h, ldh);
+}
+
+template <int V, bool NT>
+__device__ __forceinline__ void cell_bwd(int64_t b, int64_t j, int64_t H, const uint16_t* __restrict__ dh, int64_t lddh,
+                                         const uint16_t* dcn, int64_t lddcn, const uint16_t* __restrict__ act, int64_t ldact,
+                                         const uint16_t* __restrict__ c, int64_t ldc, const uint16_t* __restrict__ cprev, int64_t ldcp,
+                                         uint16_t* __restrict__ da, int64_t ldda, uint16_t* dcp, int64_t lddcp) {
   float a[4][V], dhv[V], dc[V], cv[V], cp[V];
 #pragma unroll
   for (int g = 0; g < 4; ++g) ld16<V, NT>(act + b * ldact + g * H + j, a[g]);
@@ -137,7 +133,19 @@ __global__ __launch_bounds__(kT) void k_lstm_cell_bwd(int64_t B, int64_t H, cons
   st16<V, NT>(dcp + b * lddcp + j, dprev);
 }
 
-bool vec_ok(const void* p, int64_t ld) { return p == nullptr || (mpt_aligned(p, 16) && (ld % 8) == 0); }
+template <bool NT>
+__global__ __launch_bounds__(kT) void k_lstm_cell_bwd(int64_t B, int64_t H, const uint16_t* __restrict__ dh, int64_t lddh,
+                                                      const uint16_t* dcn, int64_t lddcn, const uint16_t* __restrict__ act, int64_t ldact,
+                                                      const uint16_t* __restrict__ c, int64_t ldc, const uint16_t* __restrict__ cprev, int64_t ldcp,
+                                                      uint16_t* __restrict__ da, int64_t ldda, uint16_t* dcp, int64_t lddcp) {
+  const int64_t quads = H / 4, per_row = quads + (H & 3);
+  const int64_t u = (int64_t)blockIdx.x * kT + threadIdx.x;
+  if (u >= B * per_row) return;
+  const int64_t b = u / per_row, k = u - b * per_row;
+  if (k < quads) cell_bwd<4, NT>(b, k * 4, H, dh, lddh, dcn, lddcn, act, ldact, c, ldc, cprev, ldcp, da, ldda, dcp, lddcp);
+  else cell_bwd<1, false>(b, quads * 3 + k, H, dh, lddh, dcn, lddcn, act, ldact, c, ldc, cprev, ldcp, da, ldda, dcp, lddcp);
+}
+
 bool dims_ok(int64_t B, int64_t H) { return B >= 1 && H >= 1 && B <= (1LL << 31) && H <= (1LL << 24); }
 
 }  // namespace
@@ -151,13 +159,11 @@ extern "C" int mpt_lstm_cell_fwd(void* stream, int64_t B, int64_t H, const uint1
       !mpt_aligned(bias, 4))
     return MPT_ERR_ALIGN;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const bool vec = (H % 8) == 0 && vec_ok(gx, ldgx) && vec_ok(gr, ldgr) && vec_ok(c_prev, ldcp) && vec_ok(act, ldact) && vec_ok(c, ldc) && vec_ok(h, ldh);
-  const int64_t units = vec ? B * (H / 4) : B * H;          // 4 cells (8 bytes) per lane: measured 5.5 vs 5.3 TB/s against 8 cells
+  const int64_t units = B * (H / 4 + (H & 3));                   // 4 cells (8 bytes) per lane: measured 5.5 vs 5.3 TB/s against 8 cells
   const unsigned grid = (unsigned)((units + kT - 1) / kT);
-  const bool stream_it = vec && B * H * 30 > (192LL << 20);   // bytes moved beyond the memory-side cache
-  if (stream_it) hipLaunchKernelGGL((k_lstm_cell_fwd<4, true>), dim3(grid), dim3(kT), 0, st, B, H, gx, ldgx, gr, ldgr, bias, c_prev, ldcp, act, ldact, c, ldc, h, ldh);
-  else if (vec) hipLaunchKernelGGL((k_lstm_cell_fwd<4, false>), dim3(grid), dim3(kT), 0, st, B, H, gx, ldgx, gr, ldgr, bias, c_prev, ldcp, act, ldact, c, ldc, h, ldh);
-  else hipLaunchKernelGGL((k_lstm_cell_fwd<1, false>), dim3(grid), dim3(kT), 0, st, B, H, gx, ldgx, gr, ldgr, bias, c_prev, ldcp, act, ldact, c, ldc, h, ldh);
+  const bool stream_it = B * H * 30 > (192LL << 20);         // bytes moved beyond the memory-side cache
+  if (stream_it) hipLaunchKernelGGL(k_lstm_cell_fwd<true>, dim3(grid), dim3(kT), 0, st, B, H, gx, ldgx, gr, ldgr, bias, c_prev, ldcp, act, ldact, c, ldc, h, ldh);
+  else hipLaunchKernelGGL(k_lstm_cell_fwd<false>, dim3(grid), dim3(kT), 0, st, B, H, gx, ldgx, gr, ldgr, bias, c_prev, ldcp, act, ldact, c, ldc, h, ldh);
   MPT_LAUNCH_CHECK();
   return MPT_OK;
 }
@@ -171,14 +177,11 @@ extern "C" int mpt_lstm_cell_bwd(void* stream, int64_t B, int64_t H, const uint1
       !mpt_aligned(dc_prev, 2))
     return MPT_ERR_ALIGN;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const bool vec = (H % 8) == 0 && vec_ok(dh, lddh) && vec_ok(dc_next, lddcn) && vec_ok(act, ldact) && vec_ok(c, ldc) && vec_ok(c_prev, ldcp) &&
-                   vec_ok(da, ldda) && vec_ok(dc_prev, lddcp);
-  const int64_t units = vec ? B * (H / 4) : B * H;          // 4 cells (8 bytes) per lane: measured 5.5 vs 5.3 TB/s against 8 cells
+  const int64_t units = B * (H / 4 + (H & 3));
   const unsigned grid = (unsigned)((units + kT - 1) / kT);
-  const bool stream_it = vec && B * H * 22 > (192LL << 20);
-  if (stream_it) hipLaunchKernelGGL((k_lstm_cell_bwd<4, true>), dim3(grid), dim3(kT), 0, st, B, H, dh, lddh, dc_next, lddcn, act, ldact, c, ldc, c_prev, ldcp, da, ldda, dc_prev, lddcp);
-  else if (vec) hipLaunchKernelGGL((k_lstm_cell_bwd<4, false>), dim3(grid), dim3(kT), 0, st, B, H, dh, lddh, dc_next, lddcn, act, ldact, c, ldc, c_prev, ldcp, da, ldda, dc_prev, lddcp);
-  else hipLaunchKernelGGL((k_lstm_cell_bwd<1, false>), dim3(grid), dim3(kT), 0, st, B, H, dh, lddh, dc_next, lddcn, act, ldact, c, ldc, c_prev, ldcp, da, ldda, dc_prev, lddcp);
+  const bool stream_it = B * H * 22 > (192LL << 20);
+  if (stream_it) hipLaunchKernelGGL(k_lstm_cell_bwd<true>, dim3(grid), dim3(kT), 0, st, B, H, dh, lddh, dc_next, lddcn, act, ldact, c, ldc, c_prev, ldcp, da, ldda, dc_prev, lddcp);
+  else hipLaunchKernelGGL(k_lstm_cell_bwd<false>, dim3(grid), dim3(kT), 0, st, B, H, dh, lddh, dc_next, lddcn, act, ldact, c, ldc, c_prev, ldcp, da, ldda, dc_prev, lddcp);
   MPT_LAUNCH_CHECK();
   return MPT_OK;
 }
