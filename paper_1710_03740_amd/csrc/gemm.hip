@@ -27,18 +27,10 @@ using namespace mpt_gemm;
 
 constexpr int BK = 64;            // reduction depth of one tile of the planner
 
-// The mask values (act == 2) of 4 consecutive outputs of row i starting at column j, n of them inside the matrix
-// (n = 0: none, the mask's first element is read instead), packed like the outputs.  No branch around the loads, so a
-// caller can fetch the masks of a whole tile first and wait once: fetched one group at a time between the stores, each
-// group cost a memory round trip (16 of them made a 256 x 1024 masked store take 17 us).
-// `whole`: the caller has checked (uniformly) that every group is 4 wide or absent and 8-byte aligned, so one load
-// fetches it; element by element each wavefront instruction touches 32 rows for 2 bytes apiece, and the 64 of them that
-// a 128 x 128 tile needs took 8 us.
-__device__ __forceinline__ uint2v load_mask4(const Epilogue& ep, int64_t i, int64_t j, int n, bool whole) {
-  const uint16_t* m = n > 0 ? ep.mask + i * ep.ldmask + j : ep.mask;
-  if (whole) return *reinterpret_cast<const uint2v*>(m);
-  const int last = max(n, 1) - 1;
-  const uint32_t e0 = m[0], e1 = m[min(1, last)], e2 = m[min(2, last)], e3 = m[min(3, last)];
+// The mask values (act == 2) of 4 consecutive outputs of row i starting at column j, packed like the outputs.
+__device__ __forceinline__ uint2v load_mask4(const Epilogue& ep, int64_t i, int64_t j) {
+  const uint16_t* m = ep.mask + i * ep.ldmask + j;
+  const uint32_t e0 = m[0], e1 = m[1], e2 = m[2], e3 = m[3];
   return uint2v{e0 | (e1 << 16), e2 | (e3 << 16)};
 }
 // Inf/NaN vote over many packed FP16 pairs at two instructions per pair: keep the running maximum of the exponent fields
@@ -342,7 +334,7 @@ __global__ __launch_bounds__(512) void k_gemm_dma(DmaMat A, DmaMat B, Problem pb
         half4 h;
 #pragma unroll
         for (int e = 0; e < 4; ++e) h[e] = (_Float16)acc[a][b][e];
-        const uint2v hb = apply_act4(__builtin_bit_cast(uint2v, h), ep, ep.act == 2 ? load_mask4(ep, i, j, 4, false) : uint2v{0u, 0u});
+        const uint2v hb = apply_act4(__builtin_bit_cast(uint2v, h), ep, ep.act == 2 ? load_mask4(ep, i, j) : uint2v{0u, 0u});
         if (ep.flag) bad |= half_bits_special(hb[0]) | half_bits_special(hb[0] >> 16) | half_bits_special(hb[1]) | half_bits_special(hb[1] >> 16);
         uint16_t* o = reinterpret_cast<uint16_t*>(ep.out) + (int64_t)i * ep.ld + j;
         if ((reinterpret_cast<uintptr_t>(o) & 7) == 0) {
@@ -1667,8 +1659,8 @@ int run(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool aligned, i
   if (rp.splits > 1) {
     first.out = ws; first.ld = J; first.mode = 3; first.flag = nullptr;
   }
-  // an FP32 result keeps the pieces that the planner's split would have summed it in
-  const int cut = !A_RC && ep.mode != 0 && ws != nullptr && pl.ktiles_per_split < rp.ktiles_per_split ? pl.ktiles_per_split : 0;
+  // the result keeps the pieces that the split of its workspace sums it in
+  const int cut = ws != nullptr && pl.ktiles_per_split < rp.ktiles_per_split ? pl.ktiles_per_split : 0;
   st = launch_ring_plain(s, A_RC, B_RC, A, B, aligned, rp.tile, rp.ktiles_per_split, cut, I, J, R, first);
   if (st == MPT_OK && rp.splits > 1) {
     launch_split_reduce(s, ws, rp.splits, I, J, ep);

@@ -5,7 +5,6 @@
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half4 __attribute__((ext_vector_type(4)));
-typedef float float16v __attribute__((ext_vector_type(16)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
@@ -133,8 +132,8 @@ constexpr int ring_tile_cols(RingTile t) { return t == kRing128x128 ? 128 : 64; 
 
 // C[i,j] = sum_r A(i,r) * B(r,j) over plain matrices; `whole_chunks`: both operands can be fetched in 16-byte aligned
 // pieces (base and row stride 16-byte aligned, contiguous extent a multiple of 8).  ktiles_per_split > 0 and
-// splits = ceil(ceil(R / 64) / ktiles_per_split); the caller reduces the partials of more than one split.  cut > 0 (weight
-// gradient only): sums in pieces of so many tiles of 64, added in order.
+// splits = ceil(ceil(R / 64) / ktiles_per_split); the caller reduces the partials of more than one split.  cut > 0:
+// sums in pieces of so many tiles of 64, added in order.
 int launch_ring_plain(hipStream_t s, bool a_rc, bool b_rc, const RingMatSrc& A, const RingMatSrc& B, bool whole_chunks, RingTile tile,
                       int ktiles_per_split, int cut, int I, int J, int R, const Epilogue& ep);
 // The three passes of the 3x3 convolution (op: MPT_OP_*): x[Nb,H,W,C], w[Kf,3,3,C], y / dy[Nb,H,W,Kf].

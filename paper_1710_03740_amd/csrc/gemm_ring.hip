@@ -549,8 +549,8 @@ __device__ __forceinline__ void store_tile(const Problem& pb, const Epilogue& ep
 // everywhere.
 //
 // CUT: the sums are cut every `cut` stages, the pieces added up in order by FP32 additions of their own, as split partials are.
-// An FP32 result shows the length of its accumulation chain (512 terms in one chain 1.45e-7 off, in four 0.87e-7), so an
-// unsplit launch that takes the place of a split one keeps the split's pieces.
+// An FP32 result shows the length of its accumulation chain (512 terms in one chain 1.45e-7 off, in four 0.87e-7), so a
+// launch with fewer splits than the workspace has room for keeps the pieces of that many.
 template <int FM, int FN>
 __device__ __forceinline__ void add_piece(float4v (&total)[FM][FN], float4v (&acc)[FM][FN]) {
 #pragma unroll
@@ -808,9 +808,12 @@ int launch_ring_plain(hipStream_t s, bool a_rc, bool b_rc, const RingMatSrc& A, 
   if (!whole_chunks && cut > 0) tile = kRing64x64;
   if (tile == kRing256x64 || (tile == kRing128x64 && !whole_chunks)) tile = kRing128x128;
   const Problem pb = ring_problem(tile, ktiles_per_split, I, J, R);
+  if (cut > 0) {
+    if (a_rc) return b_rc ? launch_plain<true, true, true>(s, A, B, whole_chunks, tile, pb, ep, cut) : launch_plain<true, false, true>(s, A, B, whole_chunks, tile, pb, ep, cut);
+    return launch_plain<false, false, true>(s, A, B, whole_chunks, tile, pb, ep, cut);
+  }
   if (a_rc) return b_rc ? launch_plain<true, true, false>(s, A, B, whole_chunks, tile, pb, ep, 0) : launch_plain<true, false, false>(s, A, B, whole_chunks, tile, pb, ep, 0);
-  // both along the output (no product here has only A so): the weight gradient, the one with FP32 results
-  return cut > 0 ? launch_plain<false, false, true>(s, A, B, whole_chunks, tile, pb, ep, cut) : launch_plain<false, false, false>(s, A, B, whole_chunks, tile, pb, ep, 0);
+  return launch_plain<false, false, false>(s, A, B, whole_chunks, tile, pb, ep, 0);      // (no product here has only A along the output)
 }
 
 int launch_ring_conv(hipStream_t s, int op, int64_t Nb, int64_t H, int64_t W, int64_t C, int64_t Kf, const uint16_t* img, const uint16_t* other,
