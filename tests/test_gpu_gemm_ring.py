@@ -109,3 +109,19 @@ def test_convolution_edges(Nb, H, W, C, Kf):
             call(out, torch.empty(need // 4, dtype=torch.float32, device="cuda") if need else None)
             got = host16(out)
             assert np.array_equal(got.astype(np.float64), want[op].astype(np.float64)), (op, split)      # (a zero may carry either sign)
+
+
+@pytest.mark.parametrize("ld", [1 << 21, (1 << 21) + 1])
+def test_rows_too_far_apart_for_32_bit_offsets(ld):
+    """Row strides from which the kernels form whole 64-bit addresses, aligned and odd, with ragged last stages and tiles."""
+    rng = np.random.default_rng(ld)
+    M, N, K = 70, 72, 136
+    X, W, G = (rng.integers(-1, 2, s).astype(np.float16) for s in ((M, K), (K, N), (M, N)))
+    x, w, g = (window(*a.shape, ld - a.shape[1], 0, a)[1] for a in (X, W, G))
+    X, W, G = (a.astype(np.float64) for a in (X, W, G))
+    for shape, call, want in (((M, N), lambda o: mpt.mpt_gemm_fwd(x, w, o), X @ W), ((M, K), lambda o: mpt.mpt_gemm_dgrad(g, w, o), G @ W.T),
+                              ((K, N), lambda o: mpt.mpt_gemm_wgrad(x, g, o), X.T @ G)):
+        print("far apart", ld, shape, flush=True)
+        _, out = window(*shape, ld - shape[1], 0)
+        call(out)
+        assert np.array_equal(host16(out.contiguous()).astype(np.float64), want)
