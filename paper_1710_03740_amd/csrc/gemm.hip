@@ -25,8 +25,6 @@ namespace {
 
 using namespace mpt_gemm;
 
-constexpr int BK = 64;            // reduction depth of one tile of the planner
-
 // The mask values (act == 2) of 4 consecutive outputs of row i starting at column j, packed like the outputs.
 __device__ __forceinline__ uint2v load_mask4(const Epilogue& ep, int64_t i, int64_t j) {
   const uint16_t* m = ep.mask + i * ep.ldmask + j;
@@ -1400,84 +1398,7 @@ void launch_split_reduce(hipStream_t s, const void* ws, int splits, int I, int J
     hipLaunchKernelGGL(k_split_reduce, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, reinterpret_cast<const float*>(ws), splits, I, J, ep);
 }
 
-// ---------------------------------------------------------------- host-side planning
-struct Plan {
-  bool big;             // 256x256 tiles (8 wavefronts) or 128x128 (4 wavefronts)
-  int splits, ktiles_per_split, tiles_i, tiles_j;
-};
-
-Plan make_plan(int64_t I, int64_t J, int64_t R, bool allow_split) {
-  static const int force_tile = MPT_TUNABLE("MPT_GEMM_TILE", 0);      // 128 / 256 force a tile size (tuning builds only)
-  static const int force_split = MPT_TUNABLE("MPT_GEMM_SPLITS", 0);   // >0 forces a split count (tuning builds only)
-  Plan p;
-  const int64_t t256 = ((I + 255) / 256) * ((J + 255) / 256);
-  p.big = t256 >= kCUs / 2;
-  if (allow_split && !p.big) {
-    // with a workspace, splitting the reduction can fill the chip with 256 x 256 tiles too (measured: the batch-256
-    // gate product's activation gradient 83 -> 58 us, the convolution's weight gradient 195 -> 140 us)
-    const int64_t kt64 = (R + BK - 1) / BK;
-    int64_t sp = kCUs / t256;
-    if (sp > kt64 / 8) sp = kt64 / 8;
-    if (sp > 64) sp = 64;
-    if (sp >= 1 && t256 * sp >= kCUs / 2) p.big = true;
-  }
-  if (force_tile == 128) p.big = false;
-  if (force_tile == 256) p.big = true;
-  const int tile = p.big ? 256 : 128;
-  p.tiles_i = (int)((I + tile - 1) / tile);
-  p.tiles_j = (int)((J + tile - 1) / tile);
-  const int64_t tiles = (int64_t)p.tiles_i * p.tiles_j;
-  const int kt = (int)((R + BK - 1) / BK);
-  int splits = 1;
-  if (allow_split && tiles < kCUs) {
-    splits = (int)(kCUs / tiles);
-    // keep >= 8 k-tiles per split; a short reduction (the latency-bound layers of a small network, one memory round
-    // trip per k-tile) may go down to 2 per split, up to 8 splits
-    int max_by_depth = kt / 8;
-    const int short_r = kt / 2 < 8 ? kt / 2 : 8;
-    if (max_by_depth < short_r) max_by_depth = short_r;
-    if (max_by_depth < 1) max_by_depth = 1;
-    if (splits > max_by_depth) splits = max_by_depth;
-    if (splits > 64) splits = 64;
-  }
-  if (allow_split && force_split > 0) splits = force_split < kt ? force_split : kt;
-  if (splits < 1) splits = 1;
-  p.ktiles_per_split = (kt + splits - 1) / splits;
-  p.splits = (kt + p.ktiles_per_split - 1) / p.ktiles_per_split;   // no empty split
-  return p;
-}
-
-size_t plan_ws_bytes(const Plan& p, int64_t I, int64_t J) {
-  return p.splits > 1 ? (size_t)p.splits * (size_t)I * (size_t)J * sizeof(float) : 0;
-}
-
-// A second way to split: 128 x 256 tiles of the streamed kernel, for outputs whose row count is an odd multiple of 128
-// (256-row tiles would compute a padded half tile: 128 x 4096 x 4096 forward 27.5 -> 18.8 us) and whose time the memory
-// traffic decides: few tiles and an arithmetic intensity (every operand and the result once) below the ridge of
-// 2.5 PFLOP/s / 8 TB/s.  (For row counts that are multiples of 256 it measured within 2 % of the 256-row plans either
-// way - gate input gradient 55.8 against 55.5 us, projection 22.7 against 23.2 - and is used only as noted below.)
-// Depends on the shape only, so that the workspace size can be asked for beforehand.
-bool plan_split128(int64_t I, int64_t J, int64_t R, Plan& p) {
-  if ((I % 128) || (J % 256) || (R % 64)) return false;
-  const int64_t t128 = (I / 128) * (J / 256), kt = R / 64;
-  // rows a multiple of 256: only the smallest outputs over the longest reductions, where 256-row tiles would need 64
-  // splits (256 x 1024 over 32768: 40.5 -> 34.1 us; 256 x 2048 over 32768 is 3 us slower this way, over 8192 the same)
-  if ((I % 256) == 0 && !(t128 <= 8 && kt / 8 >= kCUs / t128)) return false;
-  if (t128 >= kCUs * 3 / 4) return false;
-  int64_t splits = kCUs / t128;
-  if (splits > kt / 8) splits = kt / 8;                               // at least 8 stages of 64 per workgroup
-  if (splits > 64) splits = 64;
-  if (splits < 2 || t128 * splits < kCUs * 3 / 8) return false;
-  const double flops = 2.0 * (double)I * (double)J * (double)R, bytes = 2.0 * ((double)I * R + (double)R * J + (double)I * J);
-  if (flops >= 312.5 * bytes) return false;
-  p.big = false;
-  p.tiles_i = (int)(I / 128);
-  p.tiles_j = (int)(J / 256);
-  p.ktiles_per_split = (int)((kt + splits - 1) / splits);
-  p.splits = (int)((kt + p.ktiles_per_split - 1) / p.ktiles_per_split);   // no empty split
-  return p.splits >= 2;
-}
-
+// ---------------------------------------------------------------- launches of the streamed kernels (planned in gemm_plan.h)
 template <bool A_RC, bool B_RC>
 bool try_launch_dma(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool aligned, const Plan& pl, int I, int J, int R, const Epilogue& ep, int& status) {
   static const bool enabled = MPT_TUNABLE("MPT_GEMM_STREAMED", 1) != 0;
@@ -1564,54 +1485,6 @@ bool try_launch_split128(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B
   hipLaunchKernelGGL(k, dim3((unsigned)((int64_t)p.tiles_i * p.tiles_j * p.splits)), dim3(256), lds, s, DmaMat{A.base, A.ld}, DmaMat{B.base, B.ld}, pb, part);
   status = hipGetLastError() == hipSuccess ? MPT_OK : MPT_ERR_HIP;
   return true;
-}
-
-// What a launch takes, in us: a start, and a share per stage of depth 64 and workgroup on the busiest CUs, which workgroups of one
-// CU share (fitted to 64 .. 4000 rows and columns over 1 .. 128 stages; mostly within a fifth).  Rows that do not start on
-// cache lines (`lines` false) need two lines for one line's data.  A split costs a second launch and its partials' way to
-// memory and back.
-struct RingCost { double start, stage, alone = 1.0; };   // alone: shares of a workgroup that has its CU to itself (what its waits leave idle)
-constexpr RingCost kRing64[2] = {{3.6, 0.26, 1.05}, {3.6, 0.22, 1.1}}, kRing128x64Cost[2] = {{4.6, 0.42}, {4.6, 0.36}}, kRing128[2] = {{5.6, 0.58, 1.05}, {5.6, 0.5}};
-constexpr RingCost kAny64 = {4.3, 0.5}, kAny128 = {8.5, 1.4}, kWhole256 = {6.0, 1.5};
-constexpr RingCost kConvWgrad64 = {4.0, 0.26, 1.6}, kConvWgrad128 = {6.0, 0.6, 1.3};
-double ring_cost(const RingCost& c, int64_t tiles, int64_t I, int64_t J, int stages, int64_t splits) {
-  const int64_t wgs = tiles * splits;
-  const double per_cu = wgs <= kCUs ? c.alone : 0.2 * ((double)wgs / kCUs) + 0.8 * (double)((wgs + kCUs - 1) / kCUs);
-  const double partials = splits > 1 ? 2.4 + (double)splits * (double)I * (double)J * 8.0 / 5.0e6 : 0.0;
-  return c.start + c.stage * stages * per_cu + partials;
-}
-
-// The ring kernels' tile and split (gemm_ring.hip): the cheapest of the two tiles and of the splits that the workspace has
-// room for (`max_splits` partial outputs).  `cost` receives its estimate.
-struct RingPlan { RingTile tile; int splits, ktiles_per_split; double cost; };
-RingPlan ring_plan(int64_t I, int64_t J, int64_t R, int max_splits, bool whole_chunks, bool lines, bool conv_wgrad = false, bool conv_rows = false) {
-  const int force_tile = MPT_TUNABLE("MPT_RING_TILE", -1), force_split = MPT_TUNABLE("MPT_RING_SPLITS", 0);   // tuning builds only
-  const int kt = (int)((R + BK - 1) / BK);
-  RingPlan best{kRing64x64, 1, kt, 1e30};
-  auto consider = [&](RingTile tile, const RingCost& c) {
-    if (force_tile >= 0 && tile != force_tile) return;
-    const int64_t tiles = ((I + ring_tile_rows(tile) - 1) / ring_tile_rows(tile)) * ((J + ring_tile_cols(tile) - 1) / ring_tile_cols(tile));
-    for (int want = 1; want <= max_splits; ++want) {
-      const int per = (kt + want - 1) / want, splits = (kt + per - 1) / per;   // no empty split
-      if (splits != want && want > 1) continue;
-      if (force_split > 0 && want != force_split && want != max_splits) continue;
-      const double cost = ring_cost(c, tiles, I, J, per, splits);
-      if (cost < best.cost) best = RingPlan{tile, splits, per, cost};
-      if (force_split > 0 && want == force_split) { best = RingPlan{tile, splits, per, 0.0}; return; }
-      if (tiles * splits >= 4 * kCUs) break;
-    }
-  };
-  if (conv_rows) {
-    // rows are pixels: many tiles, so the wide tile, or where one tile column of 64 holds the output the tall one
-    // (64 channels at 64 x 56 x 56: 32 against 48 us; 128 columns in two tall tiles were 2 us behind the square one)
-    consider(J <= 64 ? kRing256x64 : kRing128x128, kRing128[1]);
-    if (force_tile >= 0 && best.cost == 1e30) consider((RingTile)force_tile, kRing128[1]);
-    return best;
-  }
-  consider(kRing64x64, conv_wgrad ? kConvWgrad64 : whole_chunks ? kRing64[lines] : kAny64);
-  if (whole_chunks && !conv_wgrad) consider(kRing128x64, kRing128x64Cost[lines]);
-  consider(kRing128x128, conv_wgrad ? kConvWgrad128 : whole_chunks ? kRing128[lines] : kAny128);
-  return best;
 }
 
 bool on_lines(const RingMatSrc& m) { return (m.ld % 64) == 0 && mpt_aligned(m.base, 128); }

@@ -2,6 +2,7 @@
 // walk over output tiles, the LDS reads that are waited for by hand, and the launchers of gemm_ring.hip.
 #pragma once
 #include "mpt_internal.h"
+#include "gemm_plan.h"
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half4 __attribute__((ext_vector_type(4)));
@@ -10,8 +11,6 @@ typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
 
 namespace mpt_gemm {
-
-constexpr int kCUs = 256;
 
 // ---------------------------------------------------------------- exact 32-bit division by an invariant
 struct FastDiv {
@@ -125,11 +124,6 @@ __device__ __forceinline__ void keep_until_here(const half8& f) { asm volatile("
 // ---------------------------------------------------------------- launchers of gemm_ring.hip
 // One matrix operand: element (o, r) at base[o*ld + r] (reduction-contiguous) or base[r*ld + o] (outer-contiguous).
 struct RingMatSrc { const uint16_t* base; int64_t ld; int O, R; };
-// Tiles of the ring kernels (output rows x columns per workgroup).
-enum RingTile { kRing128x128 = 0, kRing64x64 = 1, kRing256x64 = 2, kRing128x64 = 3 };
-constexpr int ring_tile_rows(RingTile t) { return t == kRing64x64 ? 64 : t == kRing256x64 ? 256 : 128; }
-constexpr int ring_tile_cols(RingTile t) { return t == kRing128x128 ? 128 : 64; }
-
 // C[i,j] = sum_r A(i,r) * B(r,j) over plain matrices; `whole_chunks`: both operands can be fetched in 16-byte aligned
 // pieces (base and row stride 16-byte aligned, contiguous extent a multiple of 8).  ktiles_per_split > 0 and
 // splits = ceil(ceil(R / 64) / ktiles_per_split); the caller reduces the partials of more than one split.  cut > 0:

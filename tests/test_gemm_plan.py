@@ -1,0 +1,63 @@
+"""The planner of the matrix products (csrc/gemm_plan.h), compiled by itself for the host: which tile a product is launched with
+and which pieces its reduction is summed in."""
+import ctypes
+import os
+import random
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SOURCE = r"""
+#include "gemm_plan.h"
+using namespace mpt_gemm;
+extern "C" void planned(long I, long J, long R, int ws, int* out) {
+  const Plan p = make_plan(I, J, R, ws != 0);
+  out[0] = p.splits; out[1] = p.ktiles_per_split;
+}
+extern "C" void ring(long I, long J, long R, int ws, int whole_chunks, int lines, int conv, int* out) {
+  const Plan p = make_plan(I, J, R, ws != 0);
+  const RingPlan r = ring_plan(I, J, R, p.splits, whole_chunks != 0, lines != 0, conv == 2, conv == 1);
+  out[0] = r.tile; out[1] = r.splits; out[2] = r.ktiles_per_split;
+}
+"""
+PLAIN, CONV_ROWS, CONV_WGRAD = 0, 1, 2
+
+
+@pytest.fixture(scope="module")
+def planner(tmp_path_factory):
+    cxx = shutil.which("g++")
+    if cxx is None:
+        pytest.skip("no g++")
+    d = tmp_path_factory.mktemp("plan")
+    (d / "plan.cpp").write_text(SOURCE)
+    subprocess.run([cxx, "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_1710_03740_amd", "csrc"),
+                    "-o", str(d / "plan.so"), str(d / "plan.cpp")], check=True)
+    L = ctypes.CDLL(str(d / "plan.so"))
+    L.planned.argtypes = [ctypes.c_long] * 3 + [ctypes.c_int, ctypes.c_void_p]
+    L.ring.argtypes = [ctypes.c_long] * 3 + [ctypes.c_int] * 4 + [ctypes.c_void_p]
+
+    def call(f, *args):
+        out = (ctypes.c_int * 4)()
+        f(*args, ctypes.addressof(out))
+        return tuple(out)
+    return lambda *a: call(L.planned, *a)[:2], lambda *a: call(L.ring, *a)
+
+
+def shapes(n):
+    """Output rows, columns and reduction of products up to 4096, spread over the logarithm."""
+    rng = random.Random(n)
+    return [tuple(int(2 ** rng.uniform(0, 12)) for _ in range(3)) for _ in range(n)]
+
+
+def test_no_split_is_empty_and_the_partials_fit_the_workspace(planner):
+    planned, ring = planner
+    for I, J, R in shapes(2000):
+        kt = -(-R // 64)
+        splits, per = planned(I, J, R, 1)
+        assert (splits - 1) * per < kt <= splits * per
+        for args in ((1, 1, PLAIN), (1, 0, PLAIN), (0, 0, PLAIN), (1, 1, CONV_ROWS), (1, 1, CONV_WGRAD)):
+            s, p = ring(I, J, R, 1, *args)[1:3]
+            assert 1 <= s <= splits and (s - 1) * p < kt <= s * p
+            assert ring(I, J, R, 0, *args)[1:3] == (1, kt)
