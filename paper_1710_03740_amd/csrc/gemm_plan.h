@@ -112,24 +112,29 @@ inline double ring_cost(const RingCost& c, int64_t tiles, int64_t I, int64_t J, 
   return c.start + c.stage * stages * per_cu + partials;
 }
 
-// The ring kernels' tile and split (gemm_ring.hip): the cheapest of the two tiles and of the splits that the workspace has
-// room for (`max_splits` partial outputs).  `cost` receives its estimate.
-struct RingPlan { RingTile tile; int splits, ktiles_per_split; double cost; };
-inline RingPlan ring_plan(int64_t I, int64_t J, int64_t R, int max_splits, bool whole_chunks, bool lines, bool conv_wgrad = false, bool conv_rows = false) {
+// The ring kernels' tile and split (gemm_ring.hip): the cheapest.  A result does not depend on it: with a workspace the sums are
+// the pieces of the planned split added in order, from partials if the launch is split so and by `cut` in a launch that
+// is not.  A plain product has therefore no split in between (the projection of a recurrent layer, 256 x 1024 over 8192, summed
+// its 16 pieces in 4 groups of 4, and the same product at another alignment in other groups).
+struct RingPlan { RingTile tile; int splits, ktiles_per_split, cut; double cost; };
+inline RingPlan ring_plan(const Plan& pl, int64_t I, int64_t J, int64_t R, bool whole_chunks, bool lines, bool conv_wgrad = false, bool conv_rows = false) {
   const int force_tile = MPT_TUNABLE("MPT_RING_TILE", -1), force_split = MPT_TUNABLE("MPT_RING_SPLITS", 0);   // tuning builds only
   const int kt = (int)((R + BK - 1) / BK);
-  RingPlan best{kRing64x64, 1, kt, 1e30};
+  const bool conv = conv_wgrad || conv_rows;
+  RingPlan best{kRing64x64, 1, kt, 0, 1e30};
   auto consider = [&](RingTile tile, const RingCost& c) {
     if (force_tile >= 0 && tile != force_tile) return;
     const int64_t tiles = ((I + ring_tile_rows(tile) - 1) / ring_tile_rows(tile)) * ((J + ring_tile_cols(tile) - 1) / ring_tile_cols(tile));
-    for (int want = 1; want <= max_splits; ++want) {
+    for (int want = 1; want <= pl.splits; ++want) {
+      if (!conv && want != 1 && want != pl.splits) continue;
       const int per = (kt + want - 1) / want, splits = (kt + per - 1) / per;   // no empty split
       if (splits != want && want > 1) continue;
-      if (force_split > 0 && want != force_split && want != max_splits) continue;
+      if (force_split > 0 && want != force_split && want != pl.splits) continue;
+      const int cut = !conv && pl.ktiles_per_split < per ? pl.ktiles_per_split : 0;
       const double cost = ring_cost(c, tiles, I, J, per, splits);
-      if (cost < best.cost) best = RingPlan{tile, splits, per, cost};
-      if (force_split > 0 && want == force_split) { best = RingPlan{tile, splits, per, 0.0}; return; }
-      if (tiles * splits >= 4 * kCUs) break;
+      if (cost < best.cost) best = RingPlan{tile, splits, per, cut, cost};
+      if (force_split > 0 && want == force_split) { best = RingPlan{tile, splits, per, cut, 0.0}; return; }
+      if (conv && tiles * splits >= 4 * kCUs) break;
     }
   };
   if (conv_rows) {

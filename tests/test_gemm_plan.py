@@ -18,8 +18,8 @@ extern "C" void planned(long I, long J, long R, int ws, int* out) {
 }
 extern "C" void ring(long I, long J, long R, int ws, int whole_chunks, int lines, int conv, int* out) {
   const Plan p = make_plan(I, J, R, ws != 0);
-  const RingPlan r = ring_plan(I, J, R, p.splits, whole_chunks != 0, lines != 0, conv == 2, conv == 1);
-  out[0] = r.tile; out[1] = r.splits; out[2] = r.ktiles_per_split;
+  const RingPlan r = ring_plan(p, I, J, R, whole_chunks != 0, lines != 0, conv == 2, conv == 1);
+  out[0] = r.tile; out[1] = r.splits; out[2] = r.ktiles_per_split; out[3] = r.cut;
 }
 """
 PLAIN, CONV_ROWS, CONV_WGRAD = 0, 1, 2
@@ -61,3 +61,15 @@ def test_no_split_is_empty_and_the_partials_fit_the_workspace(planner):
             s, p = ring(I, J, R, 1, *args)[1:3]
             assert 1 <= s <= splits and (s - 1) * p < kt <= s * p
             assert ring(I, J, R, 0, *args)[1:3] == (1, kt)
+
+
+def test_a_plain_product_is_summed_in_the_planned_pieces(planner):
+    """Split as planned, or in one launch that cuts its sums there: the result is the same at every alignment.  Among them: the
+    projection of a recurrent layer, and two whose 6 and 8 pieces were summed in groups."""
+    planned, ring = planner
+    for I, J, R in shapes(4000) + [(256, 1024, 8192), (172, 1157, 714), (608, 2392, 3528)]:
+        splits, per = planned(I, J, R, 1)
+        for whole, lines in ((1, 1), (1, 0), (0, 0)):
+            _, s, p, cut = ring(I, J, R, 1, whole, lines, PLAIN)
+            assert (s, p, cut) in ((splits, per, 0), (1, -(-R // 64), per if splits > 1 else 0)), (I, J, R)
+            assert ring(I, J, R, 0, whole, lines, PLAIN)[3] == 0
