@@ -121,7 +121,7 @@ inline RingPlan ring_plan(const Plan& pl, int64_t I, int64_t J, int64_t R, bool 
   const int force_tile = MPT_TUNABLE("MPT_RING_TILE", -1), force_split = MPT_TUNABLE("MPT_RING_SPLITS", 0);   // tuning builds only
   const int kt = (int)((R + BK - 1) / BK);
   const bool conv = conv_wgrad || conv_rows;
-  RingPlan best{kRing64x64, 1, kt, 0, 1e30};
+  RingPlan best{kRing64x64, 1, kt, conv || pl.splits == 1 ? 0 : pl.ktiles_per_split, 1e30};
   auto consider = [&](RingTile tile, const RingCost& c) {
     if (force_tile >= 0 && tile != force_tile) return;
     const int64_t tiles = ((I + ring_tile_rows(tile) - 1) / ring_tile_rows(tile)) * ((J + ring_tile_cols(tile) - 1) / ring_tile_cols(tile));
@@ -131,6 +131,7 @@ inline RingPlan ring_plan(const Plan& pl, int64_t I, int64_t J, int64_t R, bool 
       if (splits != want && want > 1) continue;
       if (force_split > 0 && want != force_split && want != pl.splits) continue;
       const int cut = !conv && pl.ktiles_per_split < per ? pl.ktiles_per_split : 0;
+      if (!whole_chunks && cut > 0 && tile != kRing64x64) continue;          // k_gemm_any cuts the sums of 64 x 64 tiles only: see launch_plain
       const double cost = ring_cost(c, tiles, I, J, per, splits);
       if (cost < best.cost) best = RingPlan{tile, splits, per, cut, cost};
       if (force_split > 0 && want == force_split) { best = RingPlan{tile, splits, per, cut, 0.0}; return; }

@@ -788,7 +788,7 @@ int launch_plain(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool w
     return launch_ring<RingMat<A_RC, 128>, RingMat<B_RC, 128>, 128, 128, 64, 64, 2, CUT>(s, A, B, pb, ep, cut);
   }
   const dim3 grid((unsigned)((int64_t)pb.tiles_i * pb.tiles_j * pb.splits));
-  if constexpr (!CUT) {
+  if constexpr (!CUT) {                                              // the cut sums of 128 x 128 tiles through registers would not fit the register file
     if (tile != kRing64x64) {
       hipLaunchKernelGGL((k_gemm_any<RegMat<A_RC, 128>, RegMat<B_RC, 128>, 128, 128, 64, 64, false>), grid, dim3(256), 2 * 256 * 128, s, A, B, pb, ep, 0);
       MPT_LAUNCH_CHECK();
@@ -804,9 +804,8 @@ int launch_plain(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool w
 
 int launch_ring_plain(hipStream_t s, bool a_rc, bool b_rc, const RingMatSrc& A, const RingMatSrc& B, bool whole_chunks, RingTile tile,
                       int ktiles_per_split, int cut, int I, int J, int R, const Epilogue& ep) {
-  // the cut sums of 128 x 128 tiles through registers would not fit the register file
-  if (!whole_chunks && cut > 0) tile = kRing64x64;
-  if (tile == kRing256x64 || (tile == kRing128x64 && !whole_chunks)) tile = kRing128x128;
+  // the forms that there are kernels for, and ring_plan asks for no others
+  if (tile != kRing64x64 && (whole_chunks ? tile == kRing256x64 : tile != kRing128x128 || cut > 0)) return MPT_ERR_ARG;
   const Problem pb = ring_problem(tile, ktiles_per_split, I, J, R);
   if (cut > 0) {
     if (a_rc) return b_rc ? launch_plain<true, true, true>(s, A, B, whole_chunks, tile, pb, ep, cut) : launch_plain<true, false, true>(s, A, B, whole_chunks, tile, pb, ep, cut);

@@ -73,3 +73,13 @@ def test_a_plain_product_is_summed_in_the_planned_pieces(planner):
             _, s, p, cut = ring(I, J, R, 1, whole, lines, PLAIN)
             assert (s, p, cut) in ((splits, per, 0), (1, -(-R // 64), per if splits > 1 else 0)), (I, J, R)
             assert ring(I, J, R, 0, whole, lines, PLAIN)[3] == 0
+
+
+def test_the_tile_priced_is_the_tile_launched(planner):
+    """Operands through registers have kernels for 64 x 64 tiles and, where the sums are not cut, for 128 x 128 ones."""
+    planned, ring = planner
+    tile128, tile64 = 0, 1
+    for I, J, R in shapes(4000) + [(3139, 991, 2269), (2518, 3052, 3968)]:
+        for ws in (0, 1):
+            tile, _, _, cut = ring(I, J, R, ws, 0, 0, PLAIN)
+            assert tile == tile64 or (tile == tile128 and cut == 0), (I, J, R)

@@ -9,10 +9,11 @@ from paper_1710_03740_amd import binding as mpt
 pytestmark = pytest.mark.gpu
 
 
-# reductions of one to many pieces, with and without a ragged last stage; aligned, odd; a whole-tile output and ragged ones; the last
-# two are those for which a split into fewer partials than pieces looks the cheapest (16 pieces; 6 pieces of 2 stages)
+# reductions of one to many pieces, with and without a ragged last stage; aligned, odd; a whole-tile output and ragged ones; then
+# two for which a split into fewer partials than pieces looks the cheapest (16 pieces; 6 pieces of 2 stages) and one for which tiles
+# that the kernel does not cut do
 @pytest.mark.parametrize("M,N,K", [(512, 264, 136), (256, 1024, 8192), (1000, 264, 136), (513, 263, 135), (130, 136, 264), (2048, 1024, 2048),
-                                   (8192, 1024, 256), (714, 1157, 172)])
+                                   (8192, 1024, 256), (714, 1157, 172), (2269, 991, 3139)])
 @pytest.mark.parametrize("accumulate", [False, True])
 def test_fp32_sums_are_those_of_the_pieces(M, N, K, accumulate):
     need = mpt.mpt_gemm_workspace_bytes(mpt.OP_WGRAD, M, N, K)
