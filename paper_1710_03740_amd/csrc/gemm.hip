@@ -1752,7 +1752,7 @@ int run_conv_ring(hipStream_t s, int op, int64_t Nb, int64_t H, int64_t W, int64
   if (rp.splits > 1) {
     first.out = ws; first.ld = J; first.mode = 3; first.flag = nullptr;
   }
-  const int st = launch_ring_conv(s, op, Nb, H, W, C, Kf, img, other, rp.tile, rp.ktiles_per_split, first);
+  const int st = launch_ring_conv(s, op, Nb, H, W, C, Kf, img, other, rp.tile, rp.ktiles_per_split, rp.cut, first);
   if (st == MPT_OK && rp.splits > 1) {
     launch_split_reduce(s, ws, rp.splits, (int)I, (int)J, ep);
     MPT_LAUNCH_CHECK();

@@ -114,29 +114,23 @@ inline double ring_cost(const RingCost& c, int64_t tiles, int64_t I, int64_t J, 
 
 // The ring kernels' tile and split (gemm_ring.hip): the cheapest.  A result does not depend on it: with a workspace the sums are
 // the pieces of the planned split added in order, from partials if the launch is split so and by `cut` in a launch that
-// is not.  A plain product has therefore no split in between (the projection of a recurrent layer, 256 x 1024 over 8192, summed
-// its 16 pieces in 4 groups of 4, and the same product at another alignment in other groups).
+// is not.  So there is no split in between (the projection of a recurrent layer, 256 x 1024 over 8192, summed its 16 pieces in
+// 4 groups of 4, and the same product at another alignment in other groups).
 struct RingPlan { RingTile tile; int splits, ktiles_per_split, cut; double cost; };
 inline RingPlan ring_plan(const Plan& pl, int64_t I, int64_t J, int64_t R, bool whole_chunks, bool lines, bool conv_wgrad = false, bool conv_rows = false) {
   const int force_tile = MPT_TUNABLE("MPT_RING_TILE", -1), force_split = MPT_TUNABLE("MPT_RING_SPLITS", 0);   // tuning builds only
-  const int kt = (int)((R + BK - 1) / BK);
-  const bool conv = conv_wgrad || conv_rows;
-  RingPlan best{kRing64x64, 1, kt, conv || pl.splits == 1 ? 0 : pl.ktiles_per_split, 1e30};
+  const int kt = (int)((R + BK - 1) / BK), pieces = pl.splits > 1 ? pl.ktiles_per_split : 0;
+  RingPlan best{kRing64x64, 1, kt, pieces, 1e30};
   auto consider = [&](RingTile tile, const RingCost& c) {
     if (force_tile >= 0 && tile != force_tile) return;
     const int64_t tiles = ((I + ring_tile_rows(tile) - 1) / ring_tile_rows(tile)) * ((J + ring_tile_cols(tile) - 1) / ring_tile_cols(tile));
-    for (int want = 1; want <= pl.splits; ++want) {
-      if (!conv && want != 1 && want != pl.splits) continue;
-      const int per = (kt + want - 1) / want, splits = (kt + per - 1) / per;   // no empty split
-      if (splits != want && want > 1) continue;
-      if (force_split > 0 && want != force_split && want != pl.splits) continue;
-      const int cut = !conv && pl.ktiles_per_split < per ? pl.ktiles_per_split : 0;
-      if (!whole_chunks && cut > 0 && tile != kRing64x64) continue;          // k_gemm_any cuts the sums of 64 x 64 tiles only: see launch_plain
+    auto form = [&](int splits, int per, int cut) {
       const double cost = ring_cost(c, tiles, I, J, per, splits);
       if (cost < best.cost) best = RingPlan{tile, splits, per, cut, cost};
-      if (force_split > 0 && want == force_split) { best = RingPlan{tile, splits, per, cut, 0.0}; return; }
-      if (conv && tiles * splits >= 4 * kCUs) break;
-    }
+    };
+    // (k_gemm_any cuts the sums of 64 x 64 tiles only: see launch_plain)
+    if ((pl.splits == 1 || force_split <= 1) && (whole_chunks || pieces == 0 || tile == kRing64x64)) form(1, kt, pieces);
+    if (pl.splits > 1 && force_split != 1) form(pl.splits, pl.ktiles_per_split, 0);
   };
   if (conv_rows) {
     // rows are pixels: many tiles, so the wide tile, or where one tile column of 64 holds the output the tall one

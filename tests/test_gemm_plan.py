@@ -63,16 +63,17 @@ def test_no_split_is_empty_and_the_partials_fit_the_workspace(planner):
             assert ring(I, J, R, 0, *args)[1:3] == (1, kt)
 
 
-def test_a_plain_product_is_summed_in_the_planned_pieces(planner):
+def test_a_product_is_summed_in_the_planned_pieces(planner):
     """Split as planned, or in one launch that cuts its sums there: the result is the same at every alignment.  Among them: the
-    projection of a recurrent layer, and two whose 6 and 8 pieces were summed in groups."""
+    projection of a recurrent layer, two whose 6 and 8 pieces were summed in groups, and weight gradients of convolutions (32 x 28 x
+    28, 128 channels; 64 x 56 x 56, 64 channels) that took longer ones."""
     planned, ring = planner
-    for I, J, R in shapes(4000) + [(256, 1024, 8192), (172, 1157, 714), (608, 2392, 3528)]:
+    for I, J, R in shapes(4000) + [(256, 1024, 8192), (172, 1157, 714), (608, 2392, 3528), (128, 1152, 25088), (64, 576, 200704)]:
         splits, per = planned(I, J, R, 1)
-        for whole, lines in ((1, 1), (1, 0), (0, 0)):
-            _, s, p, cut = ring(I, J, R, 1, whole, lines, PLAIN)
+        for args in ((1, 1, PLAIN), (1, 0, PLAIN), (0, 0, PLAIN), (1, 1, CONV_ROWS), (1, 1, CONV_WGRAD)):
+            _, s, p, cut = ring(I, J, R, 1, *args)
             assert (s, p, cut) in ((splits, per, 0), (1, -(-R // 64), per if splits > 1 else 0)), (I, J, R)
-            assert ring(I, J, R, 0, whole, lines, PLAIN)[3] == 0
+            assert ring(I, J, R, 0, *args)[3] == 0
 
 
 def test_the_tile_priced_is_the_tile_launched(planner):

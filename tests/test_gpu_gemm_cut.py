@@ -60,3 +60,37 @@ def test_results_do_not_depend_on_the_alignment(M, N, K):
             out = torch.empty(shape, device="cuda", dtype=torch.float16)
             call(out, torch.empty(need // 4, device="cuda") if need else None)
             assert torch.equal(out, want.setdefault(name, out)), (name, pad, offset)
+
+
+def gathered(x, sgn):
+    """[pixels][tap][channel]: what tap 3 * tr + ts of the window multiplies, (y + sgn * (tr - 1), x + sgn * (ts - 1)) or zeros."""
+    Nb, H, W, C = x.shape
+    z = torch.zeros(Nb, H + 2, W + 2, C, device="cuda", dtype=x.dtype)
+    z[:, 1:-1, 1:-1] = x
+    at = [(1 + sgn * (t // 3 - 1), 1 + sgn * (t % 3 - 1)) for t in range(9)]
+    return torch.stack([z[:, a:a + H, b:b + W] for a, b in at], 3).reshape(Nb * H * W, 9 * C)
+
+
+# Tiles of 128 x 128 and 256 x 64 (64 x 64 for the weight gradient) with the sums cut, split and whole; the last three take 128 x 128 for
+# the weight gradient: split, cut and whole
+@pytest.mark.parametrize("Nb,H,W,C,Kf", [(1, 7, 7, 24, 72), (1, 7, 7, 64, 72), (1, 7, 7, 24, 8), (1, 7, 7, 64, 8), (1, 14, 14, 8, 8), (16, 7, 7, 384, 512), (32, 28, 28, 128, 128),
+                                         (32, 28, 28, 192, 64), (32, 28, 28, 64, 192), (4, 56, 56, 136, 72), (16, 9, 9, 1000, 384), (1, 14, 14, 768, 1000)])
+@pytest.mark.parametrize("split", [False, True])
+def test_convolutions_are_the_products_of_the_gathered_window(Nb, H, W, C, Kf, split):
+    """The same sums in the same pieces, so the same bits."""
+    g = torch.Generator(device="cuda").manual_seed(Nb + H + C + Kf)
+    x, w, dy = (torch.empty(*s, device="cuda").normal_(generator=g).half() for s in ((Nb, H, W, C), (Kf, 3, 3, C), (Nb, H, W, Kf)))
+    P = Nb * H * W
+
+    def ws(need):
+        return torch.empty(need // 4, device="cuda") if split and need else None
+    for op, out, conv, plain, A, B, MNK in (
+            (mpt.OP_FWD, torch.empty_like(dy), lambda o, s: mpt.mpt_conv3x3_fwd(x, w, o, s), mpt.mpt_gemm_fwd, gathered(x, 1), w.view(Kf, 9 * C).t().contiguous(), (P, Kf, 9 * C)),
+            (mpt.OP_DGRAD, torch.empty_like(x), lambda o, s: mpt.mpt_conv3x3_dgrad(dy, w, o, s), mpt.mpt_gemm_fwd, gathered(dy, -1),
+             w.view(Kf, 9, C).transpose(0, 1).reshape(9 * Kf, C), (P, C, 9 * Kf)),
+            (mpt.OP_WGRAD, torch.empty_like(w), lambda o, s: mpt.mpt_conv3x3_wgrad(x, dy, o, ws=s), mpt.mpt_gemm_wgrad, dy.view(P, Kf), gathered(x, 1), (P, 9 * C, Kf))):
+        print(op, (Nb, H, W, C, Kf), split, flush=True)
+        conv(out, ws(mpt.mpt_conv3x3_workspace_bytes(op, Nb, H, W, C, Kf)))
+        want = torch.empty(out.numel(), device="cuda", dtype=torch.float16).view(*((Kf, 9 * C) if op == mpt.OP_WGRAD else MNK[:2]))
+        plain(A, B, want, ws=ws(mpt.mpt_gemm_workspace_bytes(mpt.OP_WGRAD if op == mpt.OP_WGRAD else mpt.OP_FWD, *MNK)))
+        assert torch.equal(out.view_as(want), want), op
