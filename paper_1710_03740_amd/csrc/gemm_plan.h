@@ -97,19 +97,22 @@ constexpr int ring_tile_rows(RingTile t) { return t == kRing64x64 ? 64 : t == kR
 constexpr int ring_tile_cols(RingTile t) { return t == kRing128x128 ? 128 : 64; }
 
 
-// What a launch takes, in us: a start, and a share per stage of depth 64 and workgroup on the busiest CUs, which workgroups of one
-// CU share (fitted to 64 .. 4000 rows and columns over 1 .. 128 stages; mostly within a fifth).  Rows that do not start on
-// cache lines (`lines` false) need two lines for one line's data.  A split costs a second launch and its partials' way to
-// memory and back.
-struct RingCost { double start, stage, alone = 1.0; };   // alone: shares of a workgroup that has its CU to itself (what its waits leave idle)
-inline constexpr RingCost kRing64[2] = {{3.6, 0.26, 1.05}, {3.6, 0.22, 1.1}}, kRing128x64Cost[2] = {{4.6, 0.42}, {4.6, 0.36}}, kRing128[2] = {{5.6, 0.58, 1.05}, {5.6, 0.5}};
-constexpr RingCost kAny64 = {4.3, 0.5}, kAny128 = {8.5, 1.4}, kWhole256 = {6.0, 1.5};
-constexpr RingCost kConvWgrad64 = {4.0, 0.26, 1.6}, kConvWgrad128 = {6.0, 0.6, 1.3};
+// What a launch takes, in us: a start; and on the busiest CUs, for each workgroup, its fill and its store (`each`) and a share per
+// stage of depth 64, which workgroups of one CU share.  Rows that do not start on cache lines (`lines` false) need two lines for
+// one line's data.  A split costs a second launch and its partials' way to memory and back.  Fitted to 648 products of 64 .. 16000
+// rows, columns and reductions at each tile and split: 96 % of the launches are within a fifth; the form chosen takes 0.5 to
+// 1.1 % more than the fastest on average and at worst a fifth.  (Without `each`, outputs of many tiles over one or two stages took
+// 64 x 64 tiles: 12816 x 984 over 72 22 us, in 128 x 128 tiles 14.5.)
+struct RingCost { double start, each, stage, alone = 1.0; };   // alone: shares of a workgroup that has its CU to itself (what its waits leave idle)
+inline constexpr RingCost kRing64[2] = {{2.3, 0.98, 0.24, 1.23}, {2.0, 1.1, 0.2, 1.44}}, kRing128x64Cost[2] = {{3.2, 0.89, 0.36, 1.12}, {2.95, 1.04, 0.29, 1.32}},
+                          kRing128[2] = {{3.3, 2.16, 0.51, 1.16}, {2.6, 2.46, 0.45, 1.31}};
+inline constexpr RingCost kAny64 = {2.7, 0.55, 0.37, 1.68}, kAny128 = {1.7, 3.03, 0.83, 1.39}, kWhole256 = {6.0, 0.0, 1.5};
+inline constexpr RingCost kConvRows = {5.6, 0.0, 0.5}, kConvWgrad64 = {4.0, 0.0, 0.26, 1.6}, kConvWgrad128 = {6.0, 0.0, 0.6, 1.3};
 inline double ring_cost(const RingCost& c, int64_t tiles, int64_t I, int64_t J, int stages, int64_t splits) {
   const int64_t wgs = tiles * splits;
   const double per_cu = wgs <= kCUs ? c.alone : 0.2 * ((double)wgs / kCUs) + 0.8 * (double)((wgs + kCUs - 1) / kCUs);
   const double partials = splits > 1 ? 2.4 + (double)splits * (double)I * (double)J * 8.0 / 5.0e6 : 0.0;
-  return c.start + c.stage * stages * per_cu + partials;
+  return c.start + (c.each + c.stage * stages) * per_cu + partials;
 }
 
 // The ring kernels' tile and split (gemm_ring.hip): the cheapest.  A result does not depend on it: with a workspace the sums are
@@ -135,8 +138,8 @@ inline RingPlan ring_plan(const Plan& pl, int64_t I, int64_t J, int64_t R, bool 
   if (conv_rows) {
     // rows are pixels: many tiles, so the wide tile, or where one tile column of 64 holds the output the tall one
     // (64 channels at 64 x 56 x 56: 32 against 48 us; 128 columns in two tall tiles were 2 us behind the square one)
-    consider(J <= 64 ? kRing256x64 : kRing128x128, kRing128[1]);
-    if (force_tile >= 0 && best.cost == 1e30) consider((RingTile)force_tile, kRing128[1]);
+    consider(J <= 64 ? kRing256x64 : kRing128x128, kConvRows);
+    if (force_tile >= 0 && best.cost == 1e30) consider((RingTile)force_tile, kConvRows);
     return best;
   }
   consider(kRing64x64, conv_wgrad ? kConvWgrad64 : whole_chunks ? kRing64[lines] : kAny64);

@@ -84,3 +84,16 @@ def test_the_tile_priced_is_the_tile_launched(planner):
         for ws in (0, 1):
             tile, _, _, cut = ring(I, J, R, ws, 0, 0, PLAIN)
             assert tile == tile64 or (tile == tile128 and cut == 0), (I, J, R)
+
+
+@pytest.mark.parametrize("I,J,R", [(12816, 984, 72), (584, 14920, 112), (3080, 1840, 112), (6288, 1840, 64)])
+def test_outputs_of_many_tiles_over_a_stage_or_two_take_large_tiles(planner, I, J, R):
+    """What counts there is each workgroup's fill and store: in tiles of 64 x 64 these took up to half as long again."""
+    for lines in (0, 1):
+        assert planner[1](I, J, R, 1, 1, lines, PLAIN)[0] != 1
+
+
+def test_a_long_reduction_of_few_tiles_through_registers_is_split(planner):
+    """One workgroup per CU takes 0.8 us a stage there: 388 x 1488 over 2840 39 us in one launch, 24 in the planned pieces."""
+    for I, J, R in ((388, 1488, 2840), (172, 1157, 714), (1000, 520, 2000)):
+        assert planner[1](I, J, R, 1, 0, 0, PLAIN)[1] > 1
