@@ -10,10 +10,11 @@ pytestmark = pytest.mark.gpu
 
 
 # reductions of one to many pieces, with and without a ragged last stage; aligned, odd; a whole-tile output and ragged ones; then
-# two for which a split into fewer partials than pieces looks the cheapest (16 pieces; 6 pieces of 2 stages) and one for which tiles
-# that the kernel does not cut do
+# two for which a split into fewer partials than pieces looks the cheapest (16 pieces; 6 pieces of 2 stages) one for which tiles
+# that the kernel does not cut do, and two whose partials are added up by more than 512 workgroups
 @pytest.mark.parametrize("M,N,K", [(512, 264, 136), (256, 1024, 8192), (1000, 264, 136), (513, 263, 135), (130, 136, 264), (2048, 1024, 2048),
-                                   (8192, 1024, 256), (714, 1157, 172), (2269, 991, 3139)])
+                                   (8192, 1024, 256), (714, 1157, 172), (2269, 991, 3139),
+                                   (8192, 4096, 256), (8192, 1032, 1000)])
 @pytest.mark.parametrize("accumulate", [False, True])
 def test_fp32_sums_are_those_of_the_pieces(M, N, K, accumulate):
     need = mpt.mpt_gemm_workspace_bytes(mpt.OP_WGRAD, M, N, K)
