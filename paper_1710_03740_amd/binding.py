@@ -109,10 +109,16 @@ def _check(fn, st):
 
 
 # A small launch takes 3.5 us in the library; what stands around it here is written to cost no more than that (a GEMM call
-# took 11.3 us with torch's stream object, a ctypes object per argument and the checks in their reporting form; 6 us now).
+# took 11.3 us with torch's stream object, a ctypes object per argument and the checks in their reporting form; 7.0 us now).
+# The raw stream comes from two calls that torch keeps for itself; a torch without them gives the stream object.
+_raw_stream, _device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream():
     """The current device's current stream, as torch.cuda.current_stream() gives it, without the Python object."""
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _raw_stream is None or _device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device())
 
 
 def _p(t):

@@ -2,6 +2,9 @@
 pointers and sizes): wrong dtype, transposed or strided views, element counts that differ between the buffers of one
 update, inconsistent GEMM / convolution / batch-norm / LSTM shapes.  All on CPU tensors: the checks run before the
 device check and before the library is loaded, so a well-formed CPU call ends in the "device tensors only" error."""
+import importlib.util
+import types
+
 import pytest
 import torch
 
@@ -137,3 +140,13 @@ def test_many_tensor_update_entries_are_checked_one_by_one():
     rejected("momentum buffers", mpt.mpt_master_update_multi, [good, (f(5), None, h(5), h(5))], 1.0, 0.1, 0.9)
     with pytest.raises(TypeError, match="gradient dtype"):
         mpt.mpt_master_update_multi([good, (f(5), f(5), f(5), h(5))], 1.0, 0.1, 0.9)
+
+
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_a_torch_without_the_raw_stream_call_gives_the_stream_object(monkeypatch, missing):
+    monkeypatch.delattr(torch._C, missing)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=4711))
+    spec = importlib.util.spec_from_file_location("binding_without_raw_stream", mpt.__file__)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    assert module._stream() == 4711
