@@ -97,3 +97,9 @@ def test_a_long_reduction_of_few_tiles_through_registers_is_split(planner):
     """One workgroup per CU takes 0.8 us a stage there: 388 x 1488 over 2840 39 us in one launch, 24 in the planned pieces."""
     for I, J, R in ((388, 1488, 2840), (172, 1157, 714), (1000, 520, 2000)):
         assert planner[1](I, J, R, 1, 0, 0, PLAIN)[1] > 1
+
+
+@pytest.mark.parametrize("Nb,H,W,C,Kf,splits,cut", [(4, 56, 56, 136, 72, 22, 0), (16, 9, 9, 1000, 384, 1, 7), (1, 14, 14, 768, 1000, 1, 0)])
+def test_weight_gradients_of_the_wide_tile_tests_take_it(planner, Nb, H, W, C, Kf, splits, cut):
+    tile, s, _, c = planner[1](Kf, 9 * C, Nb * H * W, 1, 1, 1, CONV_WGRAD)
+    assert (tile, s, c) == (0, splits, cut)

@@ -111,6 +111,23 @@ def test_convolution_edges(Nb, H, W, C, Kf):
             assert np.array_equal(got.astype(np.float64), want[op].astype(np.float64)), (op, split)      # (a zero may carry either sign)
 
 
+# The weight gradient's 128 x 128 tile (test_gemm_plan.py holds the planner to it): split with the workspace, cut, and whole; a ragged last tile
+# of output channels, of window columns and of pixels, and images whose rows a stage crosses once or many times
+@pytest.mark.parametrize("Nb,H,W,C,Kf", [(4, 56, 56, 136, 72), (16, 9, 9, 1000, 384), (1, 14, 14, 768, 1000)])
+def test_convolution_weight_gradient_in_wide_tiles(Nb, H, W, C, Kf):
+    rng = np.random.default_rng(Nb + H + W + C + Kf)
+    x, dy = (rng.integers(-1, 2, s).astype(np.float16) for s in ((Nb, H, W, C), (Nb, H, W, Kf)))
+    want = conv.conv3x3_wgrad(x, dy)[0].astype(np.float64)
+    d_x, d_dy = dev16(x), dev16(dy)
+    need = mpt.mpt_conv3x3_workspace_bytes(2, Nb, H, W, C, Kf)
+    flag = torch.zeros(1, dtype=torch.int32, device="cuda")
+    for ws in (None, torch.empty(need // 4, dtype=torch.float32, device="cuda") if need else None):
+        out = torch.full((Kf, 3, 3, C), float("nan"), dtype=torch.float16, device="cuda")
+        print("conv weight gradient", (Nb, H, W, C, Kf), ws is not None, flush=True)
+        mpt.mpt_conv3x3_wgrad(d_x, d_dy, out, flag=flag, ws=ws)
+        assert np.array_equal(host16(out).astype(np.float64), want) and int(flag.item()) == 0
+
+
 @pytest.mark.parametrize("ld", [1 << 21, (1 << 21) + 1])
 def test_rows_too_far_apart_for_32_bit_offsets(ld):
     """Row strides from which the kernels form whole 64-bit addresses, aligned and odd, with ragged last stages and tiles."""
