@@ -809,9 +809,13 @@ int launch_conv(hipStream_t s, int op, int64_t Nb, int64_t H, int64_t W, int64_t
     const RingMatSrc A{other, Kf, (int)Kf, P};
     const ImgOCSrc B{img, (int)H, (int)W, (int)C, (int)(9 * C), P, dH, dW, dC};
     const Problem pb = ring_problem(tile, ktiles_per_split, (int)Kf, (int)(9 * C), P);
-    // two slots: with four, two workgroups fill a CU's LDS and a third waits (64 x 56 x 56 with 64 channels, 576 workgroups: 54 against 41 us;
-    // 198 workgroups 11.5 against 11.0)
-    if (tile == kRing64x64) return launch_ring<RingMat<false, 64>, RingImgOC<64>, 64, 64, 32, 32, 2, CUT>(s, A, B, pb, ep, cut);
+    if (tile == kRing64x64) {
+      // Four slots fill a CU's LDS with two workgroups; where there are more, two slots, or the third would wait (576 workgroups, 64 x 56 x 56
+      // with 64 channels: 54 against 41 us).  Not for fewer, whose few loads in flight are all there is when the images come from
+      // memory (252 workgroups, 32 x 56 x 56 with 24 and 40 channels: 20 against 26 us).
+      if ((int64_t)pb.tiles_i * pb.tiles_j * pb.splits <= 2 * kCUs) return launch_ring<RingMat<false, 64>, RingImgOC<64>, 64, 64, 32, 32, 4, CUT>(s, A, B, pb, ep, cut);
+      return launch_ring<RingMat<false, 64>, RingImgOC<64>, 64, 64, 32, 32, 2, CUT>(s, A, B, pb, ep, cut);
+    }
     return launch_ring<RingMat<false, 128>, RingImgOC<128>, 128, 128, 64, 64, 2, CUT>(s, A, B, pb, ep, cut);
   }
   if (op == MPT_OP_FWD) {
