@@ -107,7 +107,7 @@ struct RingCost { double start, each, stage, alone = 1.0; };   // alone: shares 
 inline constexpr RingCost kRing64[2] = {{2.3, 0.98, 0.24, 1.23}, {2.0, 1.1, 0.2, 1.44}}, kRing128x64Cost[2] = {{3.2, 0.89, 0.36, 1.12}, {2.95, 1.04, 0.29, 1.32}},
                           kRing128[2] = {{3.3, 2.16, 0.51, 1.16}, {2.6, 2.46, 0.45, 1.31}};
 inline constexpr RingCost kAny64 = {2.7, 0.55, 0.37, 1.68}, kAny128 = {1.7, 3.03, 0.83, 1.39}, kWhole256 = {6.0, 0.0, 1.5};
-inline constexpr RingCost kConvRows = {5.6, 0.0, 0.5}, kConvWgrad64 = {4.0, 0.0, 0.26, 1.6}, kConvWgrad128 = {6.0, 0.0, 0.6, 1.3};
+inline constexpr RingCost kConvRows = {2.5, 3.2, 0.52, 1.25}, kConvRows64 = {2.2, 1.0, 0.25, 1.65}, kConvWgrad64 = {4.0, 0.0, 0.26, 1.6}, kConvWgrad128 = {6.0, 0.0, 0.6, 1.3};
 inline double ring_cost(const RingCost& c, int64_t tiles, int64_t I, int64_t J, int stages, int64_t splits) {
   const int64_t wgs = tiles * splits;
   const double per_cu = wgs <= kCUs ? c.alone : 0.2 * ((double)wgs / kCUs) + 0.8 * (double)((wgs + kCUs - 1) / kCUs);
@@ -131,14 +131,18 @@ inline RingPlan ring_plan(const Plan& pl, int64_t I, int64_t J, int64_t R, bool 
       const double cost = ring_cost(c, tiles, I, J, per, splits);
       if (cost < best.cost) best = RingPlan{tile, splits, per, cut, cost};
     };
-    // (k_gemm_any cuts the sums of 64 x 64 tiles only: see launch_plain)
-    if ((pl.splits == 1 || force_split <= 1) && (whole_chunks || pieces == 0 || tile == kRing64x64)) form(1, kt, pieces);
+    // (k_gemm_any cuts the sums of 64 x 64 tiles only, see launch_plain; outputs of few enough 256 x 64 tiles to be split take 64 x 64 ones)
+    const bool cuts = tile != kRing256x64 && (whole_chunks || tile == kRing64x64);
+    if ((pl.splits == 1 || force_split <= 1) && (cuts || pieces == 0)) form(1, kt, pieces);
     if (pl.splits > 1 && force_split != 1) form(pl.splits, pl.ktiles_per_split, 0);
   };
   if (conv_rows) {
-    // rows are pixels: many tiles, so the wide tile, or where one tile column of 64 holds the output the tall one
-    // (64 channels at 64 x 56 x 56: 32 against 48 us; 128 columns in two tall tiles were 2 us behind the square one)
+    // rows are pixels: mostly many tiles, so the wide tile, or where one tile column of 64 holds the output the tall one
+    // (64 channels at 64 x 56 x 56: 32 against 48 us; 128 columns in two tall tiles were 2 us behind the square one), and
+    // 64 x 64 where that still is a workgroup or two per CU (4 x 8 x 8 with 8 channels 4.6 against 7.7 us, 64 x 14 x 14 with 64
+    // 7.1 against 11.5, 256 x 14 x 14 15.4 against 12.2)
     consider(J <= 64 ? kRing256x64 : kRing128x128, kConvRows);
+    consider(kRing64x64, kConvRows64);
     if (force_tile >= 0 && best.cost == 1e30) consider((RingTile)force_tile, kConvRows);
     return best;
   }

@@ -803,6 +803,7 @@ int launch_plain(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool w
 template <bool CUT>
 int launch_conv(hipStream_t s, int op, int64_t Nb, int64_t H, int64_t W, int64_t C, int64_t Kf, const uint16_t* img, const uint16_t* other,
                 RingTile tile, int ktiles_per_split, int cut, const Epilogue& ep) {
+  if (CUT && tile == kRing256x64) return MPT_ERR_ARG;               // ring_plan does not ask for it
   const int P = (int)(Nb * H * W);
   const FastDiv dHW((uint32_t)(H * W)), dW((uint32_t)W), dH((uint32_t)H), dC((uint32_t)C), dK((uint32_t)Kf);
   if (op == MPT_OP_WGRAD) {
@@ -822,13 +823,15 @@ int launch_conv(hipStream_t s, int op, int64_t Nb, int64_t H, int64_t W, int64_t
     const ImgSrc A{img, (int)H, (int)W, (int)C, +1, P, (int)(9 * C), dHW, dW, dC};
     const RingMatSrc B{other, 9 * C, (int)Kf, (int)(9 * C)};
     const Problem pb = ring_problem(tile, ktiles_per_split, P, (int)Kf, (int)(9 * C));
-    if (tile == kRing256x64) return launch_ring<RingImg<256>, RingMat<true, 64>, 256, 64, 64, 64, 2, CUT>(s, A, B, pb, ep, cut);
+    if (tile == kRing64x64) return launch_ring<RingImg<64>, RingMat<true, 64>, 64, 64, 32, 32, 4, CUT>(s, A, B, pb, ep, cut);
+    if constexpr (!CUT) if (tile == kRing256x64) return launch_ring<RingImg<256>, RingMat<true, 64>, 256, 64, 64, 64, 2>(s, A, B, pb, ep);
     return launch_ring<RingImg<128>, RingMat<true, 128>, 128, 128, 64, 64, 2, CUT>(s, A, B, pb, ep, cut);
   }
   const ImgSrc A{img, (int)H, (int)W, (int)Kf, -1, P, (int)(9 * Kf), dHW, dW, dK};
   const FilterSrc B{other, (int)C, (int)Kf, (int)C, (int)(9 * Kf), dK};
   const Problem pb = ring_problem(tile, ktiles_per_split, P, (int)C, (int)(9 * Kf));
-  if (tile == kRing256x64) return launch_ring<RingImg<256>, RingFilter<64>, 256, 64, 64, 64, 2, CUT>(s, A, B, pb, ep, cut);
+  if (tile == kRing64x64) return launch_ring<RingImg<64>, RingFilter<64>, 64, 64, 32, 32, 4, CUT>(s, A, B, pb, ep, cut);
+  if constexpr (!CUT) if (tile == kRing256x64) return launch_ring<RingImg<256>, RingFilter<64>, 256, 64, 64, 64, 2>(s, A, B, pb, ep);
   return launch_ring<RingImg<128>, RingFilter<128>, 128, 128, 64, 64, 2, CUT>(s, A, B, pb, ep, cut);
 }
 

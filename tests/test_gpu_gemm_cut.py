@@ -72,11 +72,15 @@ def gathered(x, sgn):
     return torch.stack([z[:, a:a + H, b:b + W] for a, b in at], 3).reshape(Nb * H * W, 9 * C)
 
 
-# Tiles of 128 x 128 and 256 x 64 (64 x 64 for the weight gradient) with the sums cut, split and whole; the last six take for the
-# weight gradient 128 x 128 split, cut and whole and more than 512 workgroups of 64 x 64 split, cut and whole
-@pytest.mark.parametrize("Nb,H,W,C,Kf", [(1, 7, 7, 24, 72), (1, 7, 7, 64, 72), (1, 7, 7, 24, 8), (1, 7, 7, 64, 8), (1, 14, 14, 8, 8), (18, 5, 5, 8, 8), (16, 7, 7, 384, 512), (32, 28, 28, 128, 128),
-                                         (32, 28, 28, 192, 64), (32, 28, 28, 64, 192), (4, 56, 56, 136, 72), (16, 9, 9, 1000, 384), (1, 14, 14, 768, 1000),
-                                         (51, 7, 7, 712, 8), (12, 9, 9, 888, 264), (1, 3, 3, 912, 200)])
+# Every form of launch: forward and input gradient in tiles of 64 x 64 and 128 x 128, cut, split and whole, and of 256 x 64, split and whole; the
+# weight gradient in 64 x 64, at most and more than 512 workgroups, and 128 x 128, each cut, split and whole (test_gemm_plan.py counts them)
+CONVOLUTIONS = [(1, 3, 3, 8, 8), (1, 3, 3, 24, 8), (1, 3, 3, 64, 8), (1, 3, 3, 8, 24), (1, 3, 3, 8, 64), (1, 14, 14, 8, 8), (18, 5, 5, 8, 8), (16, 7, 7, 384, 512),
+                (32, 28, 28, 128, 128), (128, 13, 13, 128, 72), (128, 13, 13, 72, 128), (1, 56, 56, 200, 72), (1, 56, 56, 72, 200), (8, 56, 56, 8, 72), (8, 56, 56, 72, 8),
+                (64, 13, 13, 192, 8), (64, 13, 13, 8, 192), (16, 56, 56, 8, 8), (4, 56, 56, 136, 72), (16, 9, 9, 1000, 384), (1, 14, 14, 768, 1000),
+                (51, 7, 7, 712, 8), (12, 9, 9, 888, 264), (1, 3, 3, 912, 200)]
+
+
+@pytest.mark.parametrize("Nb,H,W,C,Kf", CONVOLUTIONS)
 @pytest.mark.parametrize("split", [False, True])
 def test_convolutions_are_the_products_of_the_gathered_window(Nb, H, W, C, Kf, split):
     """The same sums in the same pieces, so the same bits."""
