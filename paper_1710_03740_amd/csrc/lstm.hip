@@ -86,17 +86,17 @@ __device__ __forceinline__ void cell_fwd(int64_t b, int64_t j, int64_t H, const 
   st16<V, NT>(h + b * ldh + j, hn);
 }
 
-template <bool NT>
+template <int V, bool NT>
 __global__ __launch_bounds__(kT) void k_lstm_cell_fwd(int64_t B, int64_t H, const uint16_t* __restrict__ gx, int64_t ldgx,
                                                       const uint16_t* __restrict__ gr, int64_t ldgr, const float* __restrict__ bias,
                                                       const uint16_t* cprev, int64_t ldcp, uint16_t* __restrict__ act, int64_t ldact,
                                                       uint16_t* c, int64_t ldc, uint16_t* __restrict__ h, int64_t ldh) {
-  const int64_t quads = H / 4, per_row = quads + (H & 3);
+  const int64_t groups = H / V, per_row = groups + H % V;
   const int64_t u = (int64_t)blockIdx.x * kT + threadIdx.x;
   if (u >= B * per_row) return;
   const int64_t b = u / per_row, k = u - b * per_row;
-  if (k < quads) cell_fwd<4, NT>(b, k * 4, H, gx, ldgx, gr, ldgr, bias, cprev, ldcp, act, ldact, c, ldc, h, ldh);
-  else cell_fwd<1, false>(b, quads * 3 + k, H, gx, ldgx, gr, ldgr, bias, cprev, ldcp, act, ldact, c, ldc, h, ldh);
+  if (V == 1 || k < groups) cell_fwd<V, NT>(b, k * V, H, gx, ldgx, gr, ldgr, bias, cprev, ldcp, act, ldact, c, ldc, h, ldh);
+  else cell_fwd<1, false>(b, groups * (V - 1) + k, H, gx, ldgx, gr, ldgr, bias, cprev, ldcp, act, ldact, c, ldc, h, ldh);
 }
 
 template <int V, bool NT>
@@ -133,18 +133,23 @@ __device__ __forceinline__ void cell_bwd(int64_t b, int64_t j, int64_t H, const 
   st16<V, NT>(dcp + b * lddcp + j, dprev);
 }
 
-template <bool NT>
+template <int V, bool NT>
 __global__ __launch_bounds__(kT) void k_lstm_cell_bwd(int64_t B, int64_t H, const uint16_t* __restrict__ dh, int64_t lddh,
                                                       const uint16_t* dcn, int64_t lddcn, const uint16_t* __restrict__ act, int64_t ldact,
                                                       const uint16_t* __restrict__ c, int64_t ldc, const uint16_t* __restrict__ cprev, int64_t ldcp,
                                                       uint16_t* __restrict__ da, int64_t ldda, uint16_t* dcp, int64_t lddcp) {
-  const int64_t quads = H / 4, per_row = quads + (H & 3);
+  const int64_t groups = H / V, per_row = groups + H % V;
   const int64_t u = (int64_t)blockIdx.x * kT + threadIdx.x;
   if (u >= B * per_row) return;
   const int64_t b = u / per_row, k = u - b * per_row;
-  if (k < quads) cell_bwd<4, NT>(b, k * 4, H, dh, lddh, dcn, lddcn, act, ldact, c, ldc, cprev, ldcp, da, ldda, dcp, lddcp);
-  else cell_bwd<1, false>(b, quads * 3 + k, H, dh, lddh, dcn, lddcn, act, ldact, c, ldc, cprev, ldcp, da, ldda, dcp, lddcp);
+  if (V == 1 || k < groups) cell_bwd<V, NT>(b, k * V, H, dh, lddh, dcn, lddcn, act, ldact, c, ldc, cprev, ldcp, da, ldda, dcp, lddcp);
+  else cell_bwd<1, false>(b, groups * (V - 1) + k, H, dh, lddh, dcn, lddcn, act, ldact, c, ldc, cprev, ldcp, da, ldda, dcp, lddcp);
 }
+
+// Few cells: one per thread.  A launch that does not fill the chip takes as long as one thread does, and that is the longer the
+// more cells the thread has, longer still where a wavefront holds a row's left-over cells as well (64 x 1023 forward
+// 5.1 us in fours, 3.2 singly, backward 2.9 and 2.2; 512 x 1023 6.8 and 5.4, 4.5 and 4.1; 768 x 1023 8.6 and 10.7, 5.5 and 5.0).
+bool one_per_thread(int64_t B, int64_t H) { return B * H <= 512 * 1024; }
 
 bool dims_ok(int64_t B, int64_t H) { return B >= 1 && H >= 1 && B <= (1LL << 31) && H <= (1LL << 24); }
 
@@ -159,11 +164,13 @@ extern "C" int mpt_lstm_cell_fwd(void* stream, int64_t B, int64_t H, const uint1
       !mpt_aligned(bias, 4))
     return MPT_ERR_ALIGN;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const int64_t units = B * (H / 4 + (H & 3));                   // 4 cells (8 bytes) per lane: measured 5.5 vs 5.3 TB/s against 8 cells
+  const bool singly = one_per_thread(B, H);
+  const int64_t units = singly ? B * H : B * (H / 4 + (H & 3));  // 4 cells (8 bytes) per lane: measured 5.5 vs 5.3 TB/s against 8 cells
   const unsigned grid = (unsigned)((units + kT - 1) / kT);
   const bool stream_it = B * H * 30 > (192LL << 20);         // bytes moved beyond the memory-side cache
-  if (stream_it) hipLaunchKernelGGL(k_lstm_cell_fwd<true>, dim3(grid), dim3(kT), 0, st, B, H, gx, ldgx, gr, ldgr, bias, c_prev, ldcp, act, ldact, c, ldc, h, ldh);
-  else hipLaunchKernelGGL(k_lstm_cell_fwd<false>, dim3(grid), dim3(kT), 0, st, B, H, gx, ldgx, gr, ldgr, bias, c_prev, ldcp, act, ldact, c, ldc, h, ldh);
+  if (singly) hipLaunchKernelGGL((k_lstm_cell_fwd<1, false>), dim3(grid), dim3(kT), 0, st, B, H, gx, ldgx, gr, ldgr, bias, c_prev, ldcp, act, ldact, c, ldc, h, ldh);
+  else if (stream_it) hipLaunchKernelGGL((k_lstm_cell_fwd<4, true>), dim3(grid), dim3(kT), 0, st, B, H, gx, ldgx, gr, ldgr, bias, c_prev, ldcp, act, ldact, c, ldc, h, ldh);
+  else hipLaunchKernelGGL((k_lstm_cell_fwd<4, false>), dim3(grid), dim3(kT), 0, st, B, H, gx, ldgx, gr, ldgr, bias, c_prev, ldcp, act, ldact, c, ldc, h, ldh);
   MPT_LAUNCH_CHECK();
   return MPT_OK;
 }
@@ -177,11 +184,13 @@ extern "C" int mpt_lstm_cell_bwd(void* stream, int64_t B, int64_t H, const uint1
       !mpt_aligned(dc_prev, 2))
     return MPT_ERR_ALIGN;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const int64_t units = B * (H / 4 + (H & 3));
+  const bool singly = one_per_thread(B, H);
+  const int64_t units = singly ? B * H : B * (H / 4 + (H & 3));
   const unsigned grid = (unsigned)((units + kT - 1) / kT);
   const bool stream_it = B * H * 22 > (192LL << 20);
-  if (stream_it) hipLaunchKernelGGL(k_lstm_cell_bwd<true>, dim3(grid), dim3(kT), 0, st, B, H, dh, lddh, dc_next, lddcn, act, ldact, c, ldc, c_prev, ldcp, da, ldda, dc_prev, lddcp);
-  else hipLaunchKernelGGL(k_lstm_cell_bwd<false>, dim3(grid), dim3(kT), 0, st, B, H, dh, lddh, dc_next, lddcn, act, ldact, c, ldc, c_prev, ldcp, da, ldda, dc_prev, lddcp);
+  if (singly) hipLaunchKernelGGL((k_lstm_cell_bwd<1, false>), dim3(grid), dim3(kT), 0, st, B, H, dh, lddh, dc_next, lddcn, act, ldact, c, ldc, c_prev, ldcp, da, ldda, dc_prev, lddcp);
+  else if (stream_it) hipLaunchKernelGGL((k_lstm_cell_bwd<4, true>), dim3(grid), dim3(kT), 0, st, B, H, dh, lddh, dc_next, lddcn, act, ldact, c, ldc, c_prev, ldcp, da, ldda, dc_prev, lddcp);
+  else hipLaunchKernelGGL((k_lstm_cell_bwd<4, false>), dim3(grid), dim3(kT), 0, st, B, H, dh, lddh, dc_next, lddcn, act, ldact, c, ldc, c_prev, ldcp, da, ldda, dc_prev, lddcp);
   MPT_LAUNCH_CHECK();
   return MPT_OK;
 }
