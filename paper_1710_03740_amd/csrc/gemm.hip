@@ -1525,7 +1525,7 @@ int run(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool aligned, i
   if (pl.splits > 1) {
     first.out = ws; first.ld = J; first.mode = 3; first.flag = nullptr;
   }
-  const RingPlan rp = ring_plan(pl, I, J, R, aligned, on_lines(A) && on_lines(B));
+  const RingPlan rp = ring_plan(pl, I, J, R, aligned, on_lines(A) && on_lines(B), ep.mode == 2);
   // Whole tiles whose reduction is short for its splits: the partials cost more than the smaller tiles' extra reads (the
   // projection's weight gradient, 8192 x 1024 over 256 accumulated in FP32: 39.6 us in two splits, 18.7 us unsplit)
   const bool rather_ring = pl.splits > 1 && rp.cost < 0.8 * ring_cost(kWhole256, (int64_t)pl.tiles_i * pl.tiles_j, I, J, pl.ktiles_per_split, pl.splits);
@@ -1755,7 +1755,7 @@ int run_conv_ring(hipStream_t s, int op, int64_t Nb, int64_t H, int64_t W, int64
                 R = op == MPT_OP_FWD ? 9 * C : op == MPT_OP_DGRAD ? 9 * Kf : P;
   const Plan pl = make_plan(I, J, R, ws != nullptr);
   if (ws != nullptr && ws_bytes < plan_ws_bytes(pl, I, J)) return MPT_ERR_WORKSPACE;
-  const RingPlan rp = ring_plan(pl, I, J, R, true, true, op == MPT_OP_WGRAD, op != MPT_OP_WGRAD);
+  const RingPlan rp = ring_plan(pl, I, J, R, true, true, false, op == MPT_OP_WGRAD, op != MPT_OP_WGRAD);
   Epilogue first = ep;
   if (rp.splits > 1) {
     first.out = ws; first.ld = J; first.mode = 3; first.flag = nullptr;

@@ -102,17 +102,19 @@ constexpr int ring_tile_cols(RingTile t) { return t == kRing128x128 ? 128 : 64; 
 // one line's data.  A split costs a second launch and its partials' way to memory and back.  Fitted to 648 products of 64 .. 16000
 // rows, columns and reductions at each tile and split: 96 % of the launches are within a fifth; the form chosen takes 0.5 to
 // 1.1 % more than the fastest on average and at worst a fifth.  (Without `each`, outputs of many tiles over one or two stages took
-// 64 x 64 tiles: 12816 x 984 over 72 22 us, in 128 x 128 tiles 14.5.)
-struct RingCost { double start, each, stage, alone = 1.0; };   // alone: shares of a workgroup that has its CU to itself (what its waits leave idle)
-inline constexpr RingCost kRing64[2] = {{2.3, 0.98, 0.24, 1.23}, {2.0, 1.1, 0.2, 1.44}}, kRing128x64Cost[2] = {{3.2, 0.89, 0.36, 1.12}, {2.95, 1.04, 0.29, 1.32}},
-                          kRing128[2] = {{3.3, 2.16, 0.51, 1.16}, {2.6, 2.46, 0.45, 1.31}};
-inline constexpr RingCost kAny64 = {2.7, 0.55, 0.37, 1.68}, kAny128 = {1.7, 3.03, 0.83, 1.39}, kWhole256 = {6.0, 0.0, 1.5};
+// 64 x 64 tiles: 12816 x 984 over 72 22 us, in 128 x 128 tiles 14.5.)  Accumulating stores read 64 KiB per 128 x 128 tile first: 4000 x 3000
+// over 64 through registers 26.5 us so, in 64 x 64 tiles 21.4.
+struct RingCost { double start, each, stage, alone = 1.0, old = 0.0; };   // alone: shares of a workgroup that has its CU to itself (what its waits
+                                                                           // leave idle); old: more for `each` where the store adds to FP32 values
+inline constexpr RingCost kRing64[2] = {{2.3, 0.98, 0.24, 1.23, 0.8}, {2.0, 1.1, 0.2, 1.44, 0.8}}, kRing128x64Cost[2] = {{3.2, 0.89, 0.36, 1.12, 2.5}, {2.95, 1.04, 0.29, 1.32, 2.5}},
+                          kRing128[2] = {{3.3, 2.16, 0.51, 1.16, 4.2}, {2.6, 2.46, 0.45, 1.31, 4.2}};
+inline constexpr RingCost kAny64 = {2.7, 0.55, 0.37, 1.68, 0.7}, kAny128 = {1.7, 3.03, 0.83, 1.39, 4.5}, kWhole256 = {6.0, 0.0, 1.5};
 inline constexpr RingCost kConvRows = {2.5, 3.2, 0.52, 1.25}, kConvRows64 = {2.2, 1.0, 0.25, 1.65}, kConvWgrad64 = {4.0, 0.0, 0.26, 1.6}, kConvWgrad128 = {6.0, 0.0, 0.6, 1.3};
-inline double ring_cost(const RingCost& c, int64_t tiles, int64_t I, int64_t J, int stages, int64_t splits) {
+inline double ring_cost(const RingCost& c, int64_t tiles, int64_t I, int64_t J, int stages, int64_t splits, bool accumulate = false) {
   const int64_t wgs = tiles * splits;
   const double per_cu = wgs <= kCUs ? c.alone : 0.2 * ((double)wgs / kCUs) + 0.8 * (double)((wgs + kCUs - 1) / kCUs);
   const double partials = splits > 1 ? 2.4 + (double)splits * (double)I * (double)J * 8.0 / 5.0e6 : 0.0;
-  return c.start + (c.each + c.stage * stages) * per_cu + partials;
+  return c.start + (c.each + (accumulate && splits == 1 ? c.old : 0.0) + c.stage * stages) * per_cu + partials;
 }
 
 // The ring kernels' tile and split (gemm_ring.hip): the cheapest.  A result does not depend on it: with a workspace the sums are
@@ -120,7 +122,7 @@ inline double ring_cost(const RingCost& c, int64_t tiles, int64_t I, int64_t J, 
 // is not.  So there is no split in between (the projection of a recurrent layer, 256 x 1024 over 8192, summed its 16 pieces in
 // 4 groups of 4, and the same product at another alignment in other groups).
 struct RingPlan { RingTile tile; int splits, ktiles_per_split, cut; double cost; };
-inline RingPlan ring_plan(const Plan& pl, int64_t I, int64_t J, int64_t R, bool whole_chunks, bool lines, bool conv_wgrad = false, bool conv_rows = false) {
+inline RingPlan ring_plan(const Plan& pl, int64_t I, int64_t J, int64_t R, bool whole_chunks, bool lines, bool accumulate, bool conv_wgrad = false, bool conv_rows = false) {
   const int force_tile = MPT_TUNABLE("MPT_RING_TILE", -1), force_split = MPT_TUNABLE("MPT_RING_SPLITS", 0);   // tuning builds only
   const int kt = (int)((R + BK - 1) / BK), pieces = pl.splits > 1 ? pl.ktiles_per_split : 0;
   RingPlan best{kRing64x64, 1, kt, pieces, 1e30};
@@ -128,7 +130,7 @@ inline RingPlan ring_plan(const Plan& pl, int64_t I, int64_t J, int64_t R, bool 
     if (force_tile >= 0 && tile != force_tile) return;
     const int64_t tiles = ((I + ring_tile_rows(tile) - 1) / ring_tile_rows(tile)) * ((J + ring_tile_cols(tile) - 1) / ring_tile_cols(tile));
     auto form = [&](int splits, int per, int cut) {
-      const double cost = ring_cost(c, tiles, I, J, per, splits);
+      const double cost = ring_cost(c, tiles, I, J, per, splits, accumulate);
       if (cost < best.cost) best = RingPlan{tile, splits, per, cut, cost};
     };
     // (k_gemm_any cuts the sums of 64 x 64 tiles only, see launch_plain; outputs of few enough 256 x 64 tiles to be split take 64 x 64 ones)
