@@ -105,6 +105,22 @@ def test_a_long_reduction_of_few_tiles_through_registers_is_split(planner):
         assert planner[1](I, J, R, 1, 0, 0, PLAIN)[1] > 1
 
 
+def test_every_form_of_a_product_launch_is_run_on_the_gpu(planner):
+    from test_gpu_gemm_ring import FORMS
+    rows_cols, seen = {0: (128, 128), 1: (64, 64), 3: (128, 64)}, set()
+    for op, M, N, K, ws in FORMS:
+        I, J, R = {"f": (M, N, K), "d": (M, K, N), "w": (K, N, M)}[op]
+        strides = {"f": (K, N), "d": (N, N), "w": (K, N)}[op]
+        whole = all(s % 8 == 0 for s in strides)
+        assert not (whole and I % 128 == J % 256 == R % 64 == 0)             # (the streamed kernels may have those)
+        tile, splits, _, cut = planner[1](I, J, R, ws, int(whole), int(all(s % 64 == 0 for s in strides)), PLAIN)
+        workgroups = -(-I // rows_cols[tile][0]) * -(-J // rows_cols[tile][1]) * splits
+        slots = (4 if tile == 1 or workgroups <= 256 else 2) if whole else 0     # launch_ring
+        seen.add((op, tile, slots, "split" if splits > 1 else "cut" if cut else "whole"))
+    forms = {(tile, slots, form) for tile, slots in ((1, 4), (3, 4), (3, 2), (0, 4), (0, 2), (1, 0), (0, 0)) for form in ("split", "cut", "whole")} - {(0, 0, "cut")}
+    assert seen == {(op,) + form for op in "fdw" for form in forms}
+
+
 def test_every_form_of_a_convolution_launch_is_run_on_the_gpu(planner):
     """The shapes of the bitwise comparison with plain products reach all forms that the planner chooses."""
     from test_gpu_gemm_cut import CONVOLUTIONS

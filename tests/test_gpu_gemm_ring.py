@@ -13,7 +13,7 @@ from gpu_util import dev16, host, host16
 
 pytestmark = pytest.mark.gpu
 
-# (M, N, K): below, at and above tiles of 64 and 128, stages of 64 and pieces of 8; the last three take the 128 x 64 and 128 x 128 tiles
+# (M, N, K): below, at and above tiles of 64 and 128, stages of 64 and pieces of 8
 SIZES = [(1, 8, 8), (7, 3, 5), (63, 72, 200), (64, 64, 64), (65, 136, 72), (127, 129, 191), (128, 192, 256), (200, 56, 1000),
          (65, 63, 509), (520, 2000, 1992), (2056, 1544, 520), (3001, 3003, 517)]
 # row padding in elements and offset of the window's first element: whole 16-byte pieces; odd strides; odd bases
@@ -69,6 +69,36 @@ def test_edges_of_tiles_stages_and_pieces(M, N, K, pad, offset):
         mpt.mpt_gemm_wgrad(x, g, out, accumulate=True, flag=flag, ws=ws_for(2, M, N, K) if split else None)
         assert np.array_equal(host(out.contiguous()).astype(np.float64), 2 * want["wgrad"]) and outside_untouched(buf, out)
         assert int(flag.item()) == 0
+
+
+# One product (pass, M, N, K, with workspace) for each form of launch that the planner chooses: operands in whole pieces (sizes are multiples of 8)
+# and through registers, tiles, two or four slots, split, cut and whole (test_gemm_plan.py counts them)
+FORMS = [("d", 577, 1549, 839, 1), ("d", 1415, 265, 2123, 0), ("d", 9, 211, 9, 1), ("d", 9, 329, 9, 1), ("d", 9, 9, 9, 0), ("d", 8048, 200, 800, 1),
+         ("d", 672, 5904, 784, 1), ("d", 2888, 136, 2120, 0), ("d", 2336, 1488, 1040, 1), ("d", 776, 3104, 592, 1), ("d", 1168, 720, 2232, 0),
+         ("d", 2888, 976, 1520, 1), ("d", 368, 2048, 648, 1), ("d", 136, 8, 11040, 0), ("d", 776, 216, 1328, 1), ("d", 344, 1320, 392, 1),
+         ("d", 136, 8, 7768, 0), ("d", 8, 200, 8, 1), ("d", 8, 720, 8, 1), ("d", 8, 8, 8, 0), ("f", 691, 647, 1563, 1), ("f", 2151, 1477, 261, 0),
+         ("f", 9, 9, 193, 1), ("f", 9, 11, 323, 1), ("f", 9, 9, 9, 0), ("f", 1824, 4040, 272, 1), ("f", 1040, 552, 5344, 1), ("f", 664, 8200, 144, 0),
+         ("f", 2160, 1168, 1504, 1), ("f", 400, 968, 3144, 1), ("f", 1168, 2336, 656, 0), ("f", 2024, 2088, 1032, 1), ("f", 680, 392, 2120, 1),
+         ("f", 11072, 144, 8, 0), ("f", 928, 1120, 208, 1), ("f", 368, 440, 1288, 1), ("f", 136, 7800, 8, 0), ("f", 8, 8, 200, 1), ("f", 8, 8, 712, 1),
+         ("f", 8, 8, 8, 0), ("w", 1549, 647, 655, 1), ("w", 199, 1749, 1891, 0), ("w", 193, 9, 9, 1), ("w", 351, 9, 9, 1), ("w", 9, 9, 9, 0),
+         ("w", 224, 1888, 3920, 1), ("w", 5832, 592, 840, 1), ("w", 144, 5568, 1048, 0), ("w", 1520, 1088, 2096, 1), ("w", 3304, 680, 704, 1),
+         ("w", 712, 1688, 1552, 0), ("w", 1032, 3264, 1184, 1), ("w", 2024, 736, 328, 1), ("w", 8, 11056, 136, 0), ("w", 208, 984, 1088, 1),
+         ("w", 1304, 328, 424, 1), ("w", 8, 136, 7992, 0), ("w", 200, 8, 8, 1), ("w", 720, 8, 8, 1), ("w", 8, 8, 8, 0)]
+
+
+@pytest.mark.parametrize("op,M,N,K,split", FORMS)
+def test_every_form_of_launch(op, M, N, K, split):
+    g = torch.Generator(device="cuda").manual_seed(M + 3 * N + 7 * K)
+    shapes = {"f": ((M, K), (K, N)), "d": ((M, N), (K, N)), "w": ((M, K), (M, N))}[op]
+    a, b = (torch.randint(-1, 2, s, device="cuda", generator=g).half() for s in shapes)
+    x, y = a.double(), b.double()
+    want = {"f": lambda: x @ y, "d": lambda: x @ y.t(), "w": lambda: x.t() @ y}[op]()
+    run = {"f": mpt.mpt_gemm_fwd, "d": mpt.mpt_gemm_dgrad, "w": mpt.mpt_gemm_wgrad}[op]
+    for dtype in (torch.float16, torch.float32) if op == "w" else (torch.float16,):
+        buf, out = window(*want.shape, 8, 16, dtype=dtype)
+        print("form", op, (M, N, K), split, dtype, flush=True)
+        run(a, b, out, ws=ws_for("fdw".index(op), M, N, K) if split else None)
+        assert torch.equal(out.double(), want) and outside_untouched(buf, out)
 
 
 @pytest.mark.parametrize("pad", [0, 1])

@@ -71,6 +71,34 @@ def test_lstm_cell(H, pad, offset):
         assert torch.equal(a, b)
 
 
+# more than 512 Ki cells take four per thread, with 0 to 3 left over in each row; the last moves more than the memory-side cache holds
+@pytest.mark.parametrize("B,H", [(520, 1022), (520, 1023), (520, 1024), (520, 1025), (2300, 4099)])
+@pytest.mark.parametrize("pad,offset", [(0, 0), (5, 2)])
+def test_lstm_cell_has_the_same_bits_singly_and_in_fours(B, H, pad, offset):
+    g = torch.Generator(device="cuda").manual_seed(H)
+
+    def rows(n):
+        w = window(B, n, pad, offset, 7.0)
+        w[1].copy_(torch.empty(B, n, device="cuda").normal_(generator=g))
+        return w[1]
+    gx, gr, cp, dh, dc, bias = rows(4 * H), rows(4 * H), rows(H), rows(H), rows(H), torch.empty(4 * H, device="cuda").normal_(generator=g)
+    out = [window(B, n, pad, offset, 7.0) for n in (4 * H, H, H, 4 * H, H)]
+    act, c, h, da, dcp = (o[1] for o in out)
+    mpt.mpt_lstm_cell_fwd(gx, gr, bias, cp, act, c, h)
+    mpt.mpt_lstm_cell_bwd(dh, dc, act, c, cp, da, dcp)
+    step = 64                                                               # (rows of at most 512 Ki cells: one per thread)
+    for r in range(0, B, step):
+        s = slice(r, min(r + step, B))
+        want = [torch.empty(o[1][s].shape, device="cuda", dtype=F16) for o in out]
+        mpt.mpt_lstm_cell_fwd(gx[s], gr[s], bias, cp[s], *want[:3])
+        mpt.mpt_lstm_cell_bwd(dh[s], dc[s], want[0], want[1], cp[s], *want[3:])
+        for o, w in zip(out, want):
+            assert torch.equal(o[1][s], w), r
+    for buf, view in out:                                                   # nothing beside the rows was written
+        view.fill_(7.0)
+        assert bool((buf == 7.0).all())
+
+
 @pytest.mark.parametrize("n", [1, 7, 8, 9, 2047, 4099])
 @pytest.mark.parametrize("offset", [0, 1, 3])
 def test_pointwise_glue(n, offset):
