@@ -55,8 +55,11 @@ int mpt_version(void);
  * and backward-weight of a layer).  X[M,K] activations, W[K,N] weights,
  * Y[M,N] outputs, dY[M,N] upstream gradient, all row-major with a leading
  * dimension in elements.  Any M,N,K from 1 to 2^31 - 513 (else MPT_ERR_SHAPE).
- * Fast path: base pointers 16-byte aligned and leading dimensions multiples of 8; anything else (2-byte alignment is the
- * minimum) takes a slower element-wise loader with identical results.
+ * Fast path: base pointers 16-byte aligned, leading dimensions and contiguous extents multiples of 8; anything else (2-byte
+ * alignment is the minimum) takes a slower loader.  Results are the same from run to run.  The sums of a product are cut
+ * into the same pieces, added in the same order, whatever the alignment, except for outputs that are whole tiles (rows a
+ * multiple of 128, columns of 256): at aligned addresses those have launches with pieces of their own.  Without a workspace
+ * a product is summed in one piece.
  *
  * Workspace: split-reduction needs FP32 partials in caller memory.  Pass
  * ws_dev = NULL, ws_bytes = 0 to forbid splitting (always legal), or a device
@@ -281,7 +284,7 @@ int mpt_master_update_fused(void* stream, size_t n, const float* w32_in_dev, con
  *       dlogits[b,c] = rne16( scale * (p[b,c] - [c==label_b]) / B )
  *     which applies Sec. 3.2's loss scale at the head of back-propagation.
  *     labels_dev: int32, each in [0, C) (a value outside is clamped into the range).  C <= 2^24.  Each row is read once and written once when C <= 65536
- *     (16-byte accesses when both tensors are 16-byte aligned with C and the row strides multiples of 8).
+ *     (16 bytes per lane wherever the rows start, from 8 classes on).
  * ------------------------------------------------------------------------- */
 int mpt_add_fp16(void* stream, size_t n, const uint16_t* a_dev, const uint16_t* b_dev, uint16_t* out_dev);
 int mpt_relu_fwd(void* stream, size_t n, const uint16_t* y_dev, uint16_t* h_dev);
@@ -435,8 +438,8 @@ int mpt_bn_bwd_apply(void* stream, int64_t P, int64_t C, const uint16_t* x_dev, 
  * gr and bias (FP32[4H]) may be NULL.  c may alias c_prev and dc_prev may
  * alias dc_next (each element is read and written by the same thread);
  * otherwise outputs must not overlap inputs.  Row strides are in elements.
- * 16-byte accesses when H % 8 == 0 and every tensor is 16-byte aligned with
- * a stride that is a multiple of 8; else element-wise, same results.
+ * Any alignment and stride: a thread has one cell, or four in 8-byte accesses
+ * where there are more than 512 Ki; same results.
  * Results agree with an FP64 evaluation to within one FP16 step (hardware
  * exponential and reciprocal, library tanh); they are not specified bit for bit.
  * Errors: NULL, SHAPE (B, H < 1, stride too small), ALIGN.

@@ -15,7 +15,7 @@ constexpr int kCUs = 256;
 constexpr int BK = 64;            // reduction depth of one tile of the planner
 
 struct Plan {
-  bool big;             // 256x256 tiles (8 wavefronts) or 128x128 (4 wavefronts)
+  bool big;             // planned over tiles of 256 x 256 (else 128 x 128): what the streamed kernels need to take the product
   int splits, ktiles_per_split, tiles_i, tiles_j;
 };
 
@@ -100,8 +100,8 @@ constexpr int ring_tile_cols(RingTile t) { return t == kRing128x128 ? 128 : 64; 
 // What a launch takes, in us: a start; and on the busiest CUs, for each workgroup, its fill and its store (`each`) and a share per
 // stage of depth 64, which workgroups of one CU share.  Rows that do not start on cache lines (`lines` false) need two lines for
 // one line's data.  A split costs a second launch and its partials' way to memory and back.  Fitted to 648 products of 64 .. 16000
-// rows, columns and reductions at each tile and split: 96 % of the launches are within a fifth; the form chosen takes 0.5 to
-// 1.1 % more than the fastest on average and at worst a fifth.  (Without `each`, outputs of many tiles over one or two stages took
+// rows, columns and reductions at each tile and split: 97 % of the launches are within a fifth; the form chosen takes 0.5 to
+// 1.3 % more than the fastest on average and at worst a fifth.  (Without `each`, outputs of many tiles over one or two stages took
 // 64 x 64 tiles: 12816 x 984 over 72 22 us, in 128 x 128 tiles 14.5.)  Accumulating stores read 64 KiB per 128 x 128 tile first: 4000 x 3000
 // over 64 through registers 26.5 us so, in 64 x 64 tiles 21.4.
 struct RingCost { double start, each, stage, alone = 1.0, old = 0.0; };   // alone: shares of a workgroup that has its CU to itself (what its waits

@@ -146,8 +146,8 @@ __global__ __launch_bounds__(kT) void k_lstm_cell_bwd(int64_t B, int64_t H, cons
   else cell_bwd<1, false>(b, groups * (V - 1) + k, H, dh, lddh, dcn, lddcn, act, ldact, c, ldc, cprev, ldcp, da, ldda, dcp, lddcp);
 }
 
-// Few cells: one per thread.  A launch that does not fill the chip takes as long as one thread does, and that is the longer the
-// more cells the thread has, longer still where a wavefront holds a row's left-over cells as well (64 x 1023 forward
+// Few cells: one per thread.  A launch whose threads are all on the chip at once takes as long as one of them does, and that is the
+// longer the more cells it has, longer still where a wavefront holds a row's left-over cells as well (64 x 1023 forward
 // 5.1 us in fours, 3.2 singly, backward 2.9 and 2.2; 512 x 1023 6.8 and 5.4, 4.5 and 4.1; 768 x 1023 8.6 and 10.7, 5.5 and 5.0).
 bool one_per_thread(int64_t B, int64_t H) { return B * H <= 512 * 1024; }
 
