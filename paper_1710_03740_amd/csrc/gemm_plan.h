@@ -145,7 +145,7 @@ inline RingPlan ring_plan(const Plan& pl, int64_t I, int64_t J, int64_t R, bool 
     // 7.1 against 11.5, 256 x 14 x 14 15.4 against 12.2)
     consider(J <= 64 ? kRing256x64 : kRing128x128, kConvRows);
     consider(kRing64x64, kConvRows64);
-    if (force_tile >= 0 && best.cost == 1e30) consider((RingTile)force_tile, kConvRows);
+    if ((force_tile == kRing128x128 || force_tile == kRing256x64) && best.cost == 1e30) consider((RingTile)force_tile, kConvRows);
     return best;
   }
   consider(kRing64x64, conv_wgrad ? kConvWgrad64 : whole_chunks ? kRing64[lines] : kAny64);

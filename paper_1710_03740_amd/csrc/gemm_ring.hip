@@ -803,7 +803,8 @@ int launch_plain(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool w
 template <bool CUT>
 int launch_conv(hipStream_t s, int op, int64_t Nb, int64_t H, int64_t W, int64_t C, int64_t Kf, const uint16_t* img, const uint16_t* other,
                 RingTile tile, int ktiles_per_split, int cut, const Epilogue& ep) {
-  if (CUT && tile == kRing256x64) return MPT_ERR_ARG;               // ring_plan does not ask for it
+  // the forms that there are kernels for, and ring_plan asks for no others
+  if (tile == kRing128x64 || (tile == kRing256x64 && (CUT || op == MPT_OP_WGRAD))) return MPT_ERR_ARG;
   const int P = (int)(Nb * H * W);
   const FastDiv dHW((uint32_t)(H * W)), dW((uint32_t)W), dH((uint32_t)H), dC((uint32_t)C), dK((uint32_t)Kf);
   if (op == MPT_OP_WGRAD) {
