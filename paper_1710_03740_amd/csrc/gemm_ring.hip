@@ -287,73 +287,83 @@ __device__ __forceinline__ uint4v drop_front(uint4v v, int n) {
   return uint4v{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
 }
 
-template <bool RC, int BO>
+// A load of device memory through a pointer that the compiler cannot trace to it.  As a flat load it would be counted with the LDS
+// reads too, and the next wait for those would wait for the stage that is fetched meanwhile (1001 x 1999 over 1503 28.9 us so, 22.1 now).
+template <class T>
+__device__ __forceinline__ T from_global(const void* p) { return *(const __attribute__((address_space(1))) T*)p; }
+
+// ANY: also rows of fewer than 8 elements, gathered element by element, and row strides too long for 32-bit offsets; kept apart, since
+// their branches around the loads cost the others a tenth (3999 x 1777 over 999 51 against 47 us).
+template <bool RC, int BO, bool ANY>
 struct RegMat {
   typedef RingMatSrc Src;
   typedef Piece<RC, BO> P;
   static constexpr bool kRC = RC;
   static constexpr int NB = P::NB;
-  const char* base;                // of the tile, stage 0 (wavefront-uniform); OC: 8 elements in front, so that a piece moved back over the tile's edge has an offset >= 0
+  static constexpr int kFront = RC ? 128 : 8;
+  uint4v reg[NB];                  // the pieces of a stage on their way
+  const char* base;                // of the tile's corner, stage 0 (wavefront-uniform), kFront elements in front: a piece moved back over an edge has an offset >= 0
   int64_t ld, step;                // step: bytes per stage
   uint32_t off[NB];                // OC: of the row's last 8 elements where the piece runs over its end
   int left, outer_left, inside, wave, lane;   // inside: stages that end before the reduction does
   bool narrow, wide, ragged;       // ragged: the tile's last columns are no whole piece
-  uint4v reg[NB];
   // elements of the piece of block k along the row that exist (8 or more: all)
   __device__ __forceinline__ int along(int s, int lane, int k) const { return (RC ? left - s * 64 : outer_left) - P::col(wave, lane, k); }
   __device__ __forceinline__ void init(const Src& m, int o0, int r0, int r_end, int wave_, int lane_) {
     ld = m.ld; wave = wave_; lane = lane_;
-    base = reinterpret_cast<const char*>(m.base + (RC ? (int64_t)o0 * ld + r0 : (int64_t)r0 * ld + o0 - 8));
+    base = reinterpret_cast<const char*>(m.base + (RC ? (int64_t)o0 * ld + r0 : (int64_t)r0 * ld + o0) - kFront);
     step = RC ? 128 : 128 * ld;
     left = r_end - r0;
     outer_left = m.O - o0;
-    narrow = (RC ? m.R : m.O) < 8;
-    wide = ld >= (1 << 21);
+    narrow = ANY && (RC ? m.R : m.O) < 8;
+    wide = ANY && ld >= (1 << 21);
     ragged = !RC && outer_left < BO && (outer_left & 7) != 0;
     inside = narrow || wide ? 0 : left >> 6;
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
       const int row = P::row(wave, lane, k), col = P::col(wave, lane, k);
-      const int c = RC ? col : 8 + min(col, outer_left - 8);         // (outer_left - 8 >= -7 unless narrow)
+      const int c = kFront + (RC ? col : min(col, outer_left - 8));  // (outer_left - 8 >= -7 unless narrow)
       off[k] = (uint32_t)(((RC ? (int64_t)min(row, outer_left - 1) : (int64_t)row) * ld + c) * 2);
     }
   }
+  // How far in front of its place the piece of block k is read in the last, ragged stage: RC pieces that run over the row's end as
+  // its last 8 elements (a piece starts at most 55 elements behind the end, less than the base lies in front), OC rows beyond the end as the last.
+  __device__ __forceinline__ uint32_t back(int s, int l, int k) const {
+    return RC ? 2u * (uint32_t)max(8 - along(s, l, k), 0) : (uint32_t)max(P::row(wave, l, k) - (left - s * 64 - 1), 0) * (uint32_t)(ld * 2);
+  }
+  // The pieces of stage s.
   __device__ __forceinline__ void load(int s) {
     const char* at = scalar_base(base + s * step);
-    if (s < inside) {
+    if (!narrow && !wide) {
+      uint32_t o[NB];
 #pragma unroll
-      for (int k = 0; k < NB; ++k) reg[k] = *reinterpret_cast<const uint4u*>(at + off[k]);
+      for (int k = 0; k < NB; ++k) o[k] = off[k];
+      if (s >= inside) {
+        const int l = here_only(lane);
+#pragma unroll
+        for (int k = 0; k < NB; ++k) o[k] -= back(s, l, k);
+      }
+#pragma unroll
+      for (int k = 0; k < NB; ++k) reg[k] = from_global<uint4u>(at + o[k]);
       return;
     }
-    const int l = here_only(lane);
-    if (!narrow && !wide) {
-      // the last stage: RC pieces that run over the row's end are read as its last 8 elements (256 bytes taken off the base
-      // keep the lane offsets positive: a piece starts at most 55 elements behind the end); OC rows beyond the end as the last
+    if constexpr (ANY) {
+      const int l = here_only(lane);
 #pragma unroll
       for (int k = 0; k < NB; ++k) {
-        if constexpr (RC) {
-          reg[k] = *reinterpret_cast<const uint4u*>(scalar_base(at - 256) + (uint32_t)(off[k] + 256u - 2u * (uint32_t)max(8 - along(s, l, k), 0)));
+        const int row = P::row(wave, l, k), col = P::col(wave, l, k);
+        const int n = RC || row < left - s * 64 ? min(max(along(s, l, k), 0), 8) : 0;
+        const int64_t place = (RC ? (int64_t)min(row, outer_left - 1) : (int64_t)row) * ld + col + kFront;
+        const uint16_t* q = there_or_zeros(n > 0, reinterpret_cast<const uint16_t*>(at) + place);
+        if (!narrow) {
+          reg[k] = from_global<uint4u>(q - (n > 0 ? 8 - n : 0));
         } else {
-          const int over = max(P::row(wave, l, k) - (left - s * 64 - 1), 0);
-          reg[k] = *reinterpret_cast<const uint4u*>(at + (off[k] - (uint32_t)over * (uint32_t)(ld * 2)));
+          const int end = max(n, 1) - 1;
+          uint32_t e[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) e[i] = from_global<uint16_t>(q + min(i, end));
+          reg[k] = uint4v{e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16};
         }
-      }
-      return;
-    }
-#pragma unroll
-    for (int k = 0; k < NB; ++k) {
-      const int row = P::row(wave, l, k), col = P::col(wave, l, k);
-      const int n = RC || row < left - s * 64 ? min(max(along(s, l, k), 0), 8) : 0;
-      const int64_t place = (RC ? (int64_t)min(row, outer_left - 1) : (int64_t)row) * ld + col + (RC ? 0 : 8);
-      const uint16_t* q = there_or_zeros(n > 0, reinterpret_cast<const uint16_t*>(at) + place);
-      if (!narrow) {
-        reg[k] = *reinterpret_cast<const uint4u*>(q - (n > 0 ? 8 - n : 0));
-      } else {
-        const int last = max(n, 1) - 1;
-        uint32_t e[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) e[i] = q[min(i, last)];
-        reg[k] = uint4v{e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16};
       }
     }
   }
@@ -368,7 +378,7 @@ struct RegMat {
     for (int k = 0; k < NB; ++k) {
       const int n = RC || P::row(wave, l, k) < left - s * 64 ? along(s, l, k) : 0;
       uint4v v = reg[k];
-      if (narrow) {                                                  // keep the first n
+      if (ANY && narrow) {                                           // keep the first n
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[i] &= (2 * i < n ? 0x0000FFFFu : 0u) | (2 * i + 1 < n ? 0xFFFF0000u : 0u);
       } else {
@@ -659,7 +669,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 }
 
 // The same with the pieces of one stage in registers on their way to one of two LDS slots: behind the barrier of stage s the
-// pieces of stage s + 2 are written into the slot that stage s has left, and those of stage s + 3 are loaded.
+// pieces of stage s + 2 are written into the slot that stage s has left, and those of stage s + 3 are loaded.  What bounds it is the
+// rate of the loads: a row's 128 bytes lie in two cache lines (1001 x 1999 over 1503: 16 of its 22 us for them alone, 7.5 if rows started
+// on lines), so further stages in flight give nothing (two sets of registers: 24.4 us).
 template <class AOp, class BOp, int BM, int BN, int WM, int WN, bool CUT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_any(RingMatSrc A, RingMatSrc B, Problem pb, Epilogue ep, int cut) {
   static_assert((BM / WM) * (BN / WN) == 4, "four wavefronts");
@@ -733,11 +745,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     arrived(fb[1]);
     ra.template read<0>(next, fa[0]);
     rb.template read<0>(next, fb[0]);
-    multiply<0, FM / 2>(acc, fa[1], fb[1]);
-    __builtin_amdgcn_sched_barrier(0);
     store(s + 2);
     load(s + 3);
-    multiply<FM / 2, FM>(acc, fa[1], fb[1]);
+    multiply<0, FM>(acc, fa[1], fb[1]);
     if constexpr (CUT) {
       if (--to_cut == 0) {
         to_cut = cut;
@@ -780,24 +790,30 @@ int launch_ring(hipStream_t s, const typename AOp::Src& A, const typename BOp::S
   return MPT_OK;
 }
 
-template <bool A_RC, bool B_RC, bool CUT>
-int launch_plain(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool whole_chunks, RingTile tile, const Problem& pb, const Epilogue& ep, int cut) {
-  if (whole_chunks) {
-    if (tile == kRing64x64) return launch_ring<RingMat<A_RC, 64>, RingMat<B_RC, 64>, 64, 64, 32, 32, 4, CUT>(s, A, B, pb, ep, cut);
-    if (tile == kRing128x64) return launch_ring<RingMat<A_RC, 128>, RingMat<B_RC, 64>, 128, 64, 64, 32, 2, CUT>(s, A, B, pb, ep, cut);
-    return launch_ring<RingMat<A_RC, 128>, RingMat<B_RC, 128>, 128, 128, 64, 64, 2, CUT>(s, A, B, pb, ep, cut);
-  }
+template <bool A_RC, bool B_RC, bool ANY, bool CUT>
+int launch_any(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, RingTile tile, const Problem& pb, const Epilogue& ep, int cut) {
   const dim3 grid((unsigned)((int64_t)pb.tiles_i * pb.tiles_j * pb.splits));
   if constexpr (!CUT) {                                              // the cut sums of 128 x 128 tiles through registers would not fit the register file
     if (tile != kRing64x64) {
-      hipLaunchKernelGGL((k_gemm_any<RegMat<A_RC, 128>, RegMat<B_RC, 128>, 128, 128, 64, 64, false>), grid, dim3(256), 2 * 256 * 128, s, A, B, pb, ep, 0);
+      hipLaunchKernelGGL((k_gemm_any<RegMat<A_RC, 128, ANY>, RegMat<B_RC, 128, ANY>, 128, 128, 64, 64, false>), grid, dim3(256), 2 * 256 * 128, s, A, B, pb, ep, 0);
       MPT_LAUNCH_CHECK();
       return MPT_OK;
     }
   }
-  hipLaunchKernelGGL((k_gemm_any<RegMat<A_RC, 64>, RegMat<B_RC, 64>, 64, 64, 32, 32, CUT>), grid, dim3(256), 2 * 128 * 128, s, A, B, pb, ep, cut);
+  hipLaunchKernelGGL((k_gemm_any<RegMat<A_RC, 64, ANY>, RegMat<B_RC, 64, ANY>, 64, 64, 32, 32, CUT>), grid, dim3(256), 2 * 128 * 128, s, A, B, pb, ep, cut);
   MPT_LAUNCH_CHECK();
   return MPT_OK;
+}
+
+template <bool A_RC, bool B_RC, bool CUT>
+int launch_plain(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool whole_chunks, RingTile tile, const Problem& pb, const Epilogue& ep, int cut) {
+  if (!whole_chunks) {
+    const bool ordinary = (A_RC ? A.R : A.O) >= 8 && (B_RC ? B.R : B.O) >= 8 && A.ld < (1 << 21) && B.ld < (1 << 21);
+    return ordinary ? launch_any<A_RC, B_RC, false, CUT>(s, A, B, tile, pb, ep, cut) : launch_any<A_RC, B_RC, true, CUT>(s, A, B, tile, pb, ep, cut);
+  }
+  if (tile == kRing64x64) return launch_ring<RingMat<A_RC, 64>, RingMat<B_RC, 64>, 64, 64, 32, 32, 4, CUT>(s, A, B, pb, ep, cut);
+  if (tile == kRing128x64) return launch_ring<RingMat<A_RC, 128>, RingMat<B_RC, 64>, 128, 64, 64, 32, 2, CUT>(s, A, B, pb, ep, cut);
+  return launch_ring<RingMat<A_RC, 128>, RingMat<B_RC, 128>, 128, 128, 64, 64, 2, CUT>(s, A, B, pb, ep, cut);
 }
 
 template <bool CUT>
