@@ -1512,7 +1512,9 @@ int run(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool aligned, i
   const int64_t t128 = (int64_t)(I / 128) * (J / 256);
   const bool rather_split = ws != nullptr && pl.big && pl.splits > 1 && R >= 8192 && (int64_t)pl.tiles_i * pl.tiles_j * pl.splits * 4 >= t128 * 5;
   const bool ring_only = MPT_TUNABLE("MPT_RING_ONLY", 0) != 0;          // tuning builds only
-  if (!rather_split && !ring_only && try_launch_dma128<A_RC, B_RC>(s, A, B, aligned, I, J, R, ep, st)) return st;
+  const int64_t kt = (R + BK - 1) / BK;
+  const bool fp16_ring = pl.splits == 1 && ring_for_fp16(t128, kt);
+  if (!rather_split && !fp16_ring && !ring_only && try_launch_dma128<A_RC, B_RC>(s, A, B, aligned, I, J, R, ep, st)) return st;
   Plan p128;
   if (!ring_only && ws != nullptr && plan_split128(I, J, R, p128) && ws_bytes >= plan_ws_bytes(p128, I, J) &&
       try_launch_split128<A_RC, B_RC>(s, A, B, aligned, p128, I, J, R, reinterpret_cast<float*>(ws), st)) {
@@ -1527,8 +1529,10 @@ int run(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool aligned, i
   }
   const RingPlan rp = ring_plan(pl, I, J, R, aligned, on_lines(A) && on_lines(B), ep.mode == 2);
   // Whole tiles whose reduction is short for its splits: the partials cost more than the smaller tiles' extra reads (the
-  // projection's weight gradient, 8192 x 1024 over 256 accumulated in FP32: 39.6 us in two splits, 18.7 us unsplit)
-  const bool rather_ring = pl.splits > 1 && rp.cost < 0.8 * ring_cost(kWhole256, (int64_t)pl.tiles_i * pl.tiles_j, I, J, pl.ktiles_per_split, pl.splits);
+  // projection's weight gradient, 8192 x 1024 over 256 accumulated in FP32: 39.6 us in two splits, 17.2 us unsplit)
+  const int64_t tiles = (int64_t)pl.tiles_i * pl.tiles_j;
+  const bool rather_ring = pl.splits > 1 ? rp.cost < 0.8 * ring_cost(kWhole256, tiles, I, J, pl.ktiles_per_split, pl.splits)
+                                         : ep.mode != 0 && ring_for_fp32(tiles, kt, ep.mode == 2);
   if (!ring_only && !rather_ring && try_launch_dma<A_RC, B_RC>(s, A, B, aligned, pl, I, J, R, first, st)) {
     if (st == MPT_OK && pl.splits > 1) {
       launch_split_reduce(s, ws, pl.splits, I, J, ep);

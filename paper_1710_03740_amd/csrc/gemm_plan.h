@@ -154,4 +154,17 @@ inline RingPlan ring_plan(const Plan& pl, int64_t I, int64_t J, int64_t R, bool 
   return best;
 }
 
+// Whole-tile products that one launch of the streamed kernels could take, but that the ring kernels' smaller tiles take in less time
+// (both sides measured over reductions of 64 .. 4096; the sums are the same).
+// FP32 outputs in tiles of 256 x 256: where these occupy half the chip (8192 x 1024 over 64 accumulated 20.4 -> 11.8 us, over 256
+// stored 18.5 -> 12.6, over 4096 79.6 -> 69.4; at 192 tiles over 256 18.6 against 19.0, over 1024 32.1 against 37.9), and adding to FP32
+// values over two rounds of tiles or more, whose reads wait in the smaller tiles' shadow (16384 x 4096 over 64 124 -> 102 us,
+// over 1024 231 -> 210, over 2048 322 against 339).
+inline bool ring_for_fp32(int64_t tiles256, int64_t ktiles, bool accumulate) {
+  return (tiles256 <= kCUs / 2 && ktiles <= 64) || (accumulate && tiles256 >= 2 * kCUs && ktiles <= 16);
+}
+// FP16 outputs in tiles of 128 x 256, unsplit by plan: 2048 x 2048 (128 tiles) over 256 8.8 -> 7.4 us, over 512 11.4 -> 9.5; 1536 x 2048 (96)
+// over 1024 15.9 -> 13.4; 3072 x 2048 (192) over 256 9.5 -> 9.1, over 512 12.2 against 12.4.
+inline bool ring_for_fp16(int64_t tiles128, int64_t ktiles) { return tiles128 <= kCUs / 2 ? tiles128 * ktiles <= 6 * kCUs : ktiles <= 4 && tiles128 < kCUs; }
+
 }  // namespace mpt_gemm
