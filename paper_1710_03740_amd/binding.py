@@ -1,17 +1,22 @@
-"""ctypes binding for libmpt.so: argument marshalling only.
+"""Binding for libmpt.so: argument marshalling only.
 
 Each function has the name of the C entry point it calls (include/mpt.h) and
 takes torch CUDA tensors purely as carriers of device pointers; torch's current
 stream is passed as the hipStream_t.  Every step of the method runs in the
 library's kernels.  A missing library is an error, never a fallback.
+
+Two ways lead to an entry point.  Calls whose arguments are plainly as they should be go through csrc/calls.cpp; whatever
+that leaves, all other accepted forms and every error, goes through the checks here and ctypes.
 """
 import ctypes
+import importlib.util
 import os
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libmpt.so")
+CALLS_PATH = os.path.join(_HERE, "_calls.so")
 
 OP_FWD, OP_DGRAD, OP_WGRAD = 0, 1, 2
 
@@ -85,21 +90,33 @@ SIGNATURES = {
     "mpt_bn_bwd_apply": (c_i, [c_vp, c_i64, c_i64, c_vp, c_i64, c_vp, c_i64, c_vp, c_vp, c_vp, c_f, c_vp, c_vp, c_vp, c_i64]),
 }
 
+class _NotLoaded:
+    """Stands for the native calls until the library is loaded: each says that it has not made the call."""
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
 _lib = None
+_native = _NotLoaded()
 
 
 def lib():
-    """Load libmpt.so (once).  Raises if it has not been built."""
-    global _lib
+    """Load libmpt.so and the native calls into it (once).  Raises if they have not been built."""
+    global _lib, _native
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
-            raise RuntimeError("libmpt.so is not built (%s); run `python -m paper_1710_03740_amd.build`. "
-                               "There is no fallback path." % LIB_PATH)
+        for path in (LIB_PATH, CALLS_PATH):
+            if not os.path.exists(path):
+                raise RuntimeError("%s is not built (%s); run `python -m paper_1710_03740_amd.build`. "
+                                   "There is no fallback path." % (os.path.basename(path), path))
         L = ctypes.CDLL(LIB_PATH)
         for name, (res, args) in SIGNATURES.items():
             f = getattr(L, name)
             f.restype, f.argtypes = res, args
-        _lib = L
+        spec = importlib.util.spec_from_file_location("_calls", CALLS_PATH)
+        calls = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(calls)
+        calls.bind({name: ctypes.cast(getattr(L, name), c_vp).value for name in SIGNATURES})
+        _lib, _native = L, calls
     return _lib
 
 
@@ -108,9 +125,8 @@ def _check(fn, st):
         raise MptError(fn, st, lib().mpt_status_string(st).decode())
 
 
-# A small launch takes 3.5 us in the library; what stands around it here is written to cost no more than that (a GEMM call
-# took 11.3 us with torch's stream object, a ctypes object per argument and the checks in their reporting form; 7.0 us now).
-# The raw stream comes from two calls that torch keeps for itself; a torch without them gives the stream object.
+# What stands around a call that comes this way costs about as much as its launch, 3.5 us each.  The raw stream comes from two
+# calls that torch keeps for itself; a torch without them gives the stream object.
 _raw_stream, _device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
 
 
@@ -230,6 +246,9 @@ def _dgrad_shapes(dY, W, dX):
 
 
 def mpt_gemm_fwd(X, W, Y, ws=None):
+    st = _native.gemm_fwd(X, W, Y, ws)
+    if st is not None:
+        return _check("mpt_gemm_fwd", st)
     M, N, K = _fwd_shapes(X, W, Y, "Y")
     _ws_ok(ws)
     _dev(X, W, Y, ws)
@@ -238,6 +257,9 @@ def mpt_gemm_fwd(X, W, Y, ws=None):
 
 
 def mpt_gemm_dgrad(dY, W, dX, ws=None):
+    st = _native.gemm_dgrad(dY, W, dX, ws)
+    if st is not None:
+        return _check("mpt_gemm_dgrad", st)
     M, N, K = _dgrad_shapes(dY, W, dX)
     _ws_ok(ws)
     _dev(dY, W, dX, ws)
@@ -246,6 +268,9 @@ def mpt_gemm_dgrad(dY, W, dX, ws=None):
 
 
 def mpt_gemm_fwd_relu(X, W, H, ws=None):
+    st = _native.gemm_fwd_relu(X, W, H, ws)
+    if st is not None:
+        return _check("mpt_gemm_fwd_relu", st)
     M, N, K = _fwd_shapes(X, W, H, "H")
     _ws_ok(ws)
     _dev(X, W, H, ws)
@@ -254,6 +279,9 @@ def mpt_gemm_fwd_relu(X, W, H, ws=None):
 
 
 def mpt_gemm_dgrad_relu(dY, W, H, dX, ws=None):
+    st = _native.gemm_dgrad_relu(dY, W, H, dX, ws)
+    if st is not None:
+        return _check("mpt_gemm_dgrad_relu", st)
     M, N, K = _dgrad_shapes(dY, W, dX)
     _mat("H", H, _F16, (M, K))
     _ws_ok(ws)
@@ -264,6 +292,9 @@ def mpt_gemm_dgrad_relu(dY, W, H, dX, ws=None):
 
 
 def mpt_gemm_wgrad(X, dY, dW, accumulate=False, flag=None, ws=None):
+    st = _native.gemm_wgrad(X, dY, dW, accumulate, flag, ws)
+    if st is not None:
+        return _check("mpt_gemm_wgrad", st)
     M, K = _dim2("X", X)
     N = _dim2("dY", dY)[1]
     _mat("X", X, _F16, (M, K)); _mat("dY", dY, _F16, (M, N)); _mat("dW", dW, (_F16, _F32), (K, N))
@@ -312,6 +343,9 @@ def _conv_shapes(x, xname, w, y, yname):
 
 
 def mpt_conv3x3_fwd(x, w, y, ws=None):
+    st = _native.conv3x3_fwd(x, w, y, ws)
+    if st is not None:
+        return _check("mpt_conv3x3_fwd", st)
     Nb, H, W, C, Kf = _conv_shapes(x, "x", w, y, "y")
     _ws_ok(ws)
     _dev(x, w, y, ws)
@@ -320,6 +354,9 @@ def mpt_conv3x3_fwd(x, w, y, ws=None):
 
 
 def mpt_conv3x3_dgrad(dy, w, dx, ws=None):
+    st = _native.conv3x3_dgrad(dy, w, dx, ws)
+    if st is not None:
+        return _check("mpt_conv3x3_dgrad", st)
     Nb, H, W, C, Kf = _conv_shapes(dx, "dx", w, dy, "dy")
     _ws_ok(ws)
     _dev(dy, w, dx, ws)
@@ -328,6 +365,9 @@ def mpt_conv3x3_dgrad(dy, w, dx, ws=None):
 
 
 def mpt_conv3x3_wgrad(x, dy, dw, flag=None, ws=None):
+    st = _native.conv3x3_wgrad(x, dy, dw, flag, ws)
+    if st is not None:
+        return _check("mpt_conv3x3_wgrad", st)
     Nb, H, W, C, Kf = _conv_shapes(x, "x", dw, dy, "dy")
     _want("flag", flag, _I32, numel=1, optional=True)
     _ws_ok(ws)
@@ -338,6 +378,9 @@ def mpt_conv3x3_wgrad(x, dy, dw, flag=None, ws=None):
 
 # ---------------------------------------------------------------- loss-scaled update path
 def mpt_unscale_check(grad, inv_scale, flag, g32_out=None):
+    st = _native.unscale_check(grad, inv_scale, flag, g32_out)
+    if st is not None:
+        return _check("mpt_unscale_check", st)
     _want("grad", grad, (_F16, _F32)); _flat("grad", grad)
     _want("flag", flag, _I32, numel=1)
     _want("g32_out", g32_out, _F32, numel=grad.numel(), optional=True); _flat("g32_out", g32_out, optional=True)
@@ -360,6 +403,9 @@ def _update_buffers(w32, states, grad, w16, flag, scaler_dev):
 
 
 def mpt_master_update(w32, m32, grad, w16, inv_scale, lr, momentum, flag=None, scaler_dev=None):
+    st = _native.master_update(w32, m32, grad, w16, inv_scale, lr, momentum, flag, scaler_dev)
+    if st is not None:
+        return _check("mpt_master_update", st)
     _update_buffers(w32, [("m32", m32)], grad, w16, flag, scaler_dev)
     _dev(w32, m32, grad, w16, flag, scaler_dev)
     _check("mpt_master_update", lib().mpt_master_update(_stream(), w32.numel(), _p(w32), _p(m32), _p(grad),
@@ -370,6 +416,9 @@ def mpt_master_update(w32, m32, grad, w16, inv_scale, lr, momentum, flag=None, s
 def mpt_master_update_multi(tensors, inv_scale, lr, momentum, flag=None, scaler_dev=None):
     """tensors: a sequence of (w32, m32 or None, grad, w16) device tensors, one entry per parameter tensor; the gradients
     share one dtype and the momentum buffers are given for all entries or for none."""
+    st = _native.master_update_multi(tensors, inv_scale, lr, momentum, flag, scaler_dev)
+    if st is not None:
+        return _check("mpt_master_update_multi", st)
     tensors = list(tensors)
     if not tensors:
         return
@@ -465,6 +514,9 @@ def mpt_loss_scale_update(s, overflow):
 
 
 def mpt_loss_scale_update_dev(scaler_dev, flag):
+    st = _native.loss_scale_update_dev(scaler_dev, flag)
+    if st is not None:
+        return _check("mpt_loss_scale_update_dev", st)
     _want("scaler_dev", scaler_dev, _U8, numel=ctypes.sizeof(mpt_scaler)); _want("flag", flag, _I32, numel=1)
     _dev(scaler_dev, flag)
     _check("mpt_loss_scale_update_dev", lib().mpt_loss_scale_update_dev(_stream(), _p(scaler_dev), _p(flag)))
@@ -488,6 +540,9 @@ def mpt_probe_mfma(iters, random_operands, sink):
 
 # ---------------------------------------------------------------- glue
 def mpt_add_fp16(a, b, out):
+    st = _native.add_fp16(a, b, out)
+    if st is not None:
+        return _check("mpt_add_fp16", st)
     _want("a", a, _F16); _flat("a", a)
     _want("b", b, _F16, numel=a.numel()); _flat("b", b); _want("out", out, _F16, numel=a.numel()); _flat("out", out)
     _dev(a, b, out)
@@ -501,6 +556,9 @@ def mpt_relu_fwd(y, h):
 
 
 def mpt_relu_bwd(dh, y, dy):
+    st = _native.relu_bwd(dh, y, dy)
+    if st is not None:
+        return _check("mpt_relu_bwd", st)
     _want("y", y, _F16); _flat("y", y)
     _want("dh", dh, _F16, numel=y.numel()); _flat("dh", dh); _want("dy", dy, _F16, numel=y.numel()); _flat("dy", dy)
     _dev(dh, y, dy)
@@ -508,6 +566,9 @@ def mpt_relu_bwd(dh, y, dy):
 
 
 def mpt_softmax_xent_scaled(logits, labels, scale, dlogits, loss=None, row_loss=None):
+    st = _native.softmax_xent_scaled(logits, labels, scale, dlogits, loss, row_loss)
+    if st is not None:
+        return _check("mpt_softmax_xent_scaled", st)
     B, C = _dim2("logits", logits)
     _mat("logits", logits, _F16, (B, C)); _mat("dlogits", dlogits, _F16, (B, C))
     _want("labels", labels, _I32, numel=B); _flat("labels", labels)
@@ -537,6 +598,9 @@ def _bn_shapes(x, vectors, tensors):
 
 
 def mpt_bn_stats(x, mean, var, ws):
+    st = _native.bn_stats(x, mean, var, ws)
+    if st is not None:
+        return _check("mpt_bn_stats", st)
     P, C = _bn_shapes(x, [("mean", mean), ("var", var)], [])
     _ws_ok(ws)
     _dev(x, mean, var, ws)
@@ -545,6 +609,9 @@ def mpt_bn_stats(x, mean, var, ws):
 
 
 def mpt_bn_apply(x, mean, var, gamma, beta, eps, y, relu=False):
+    st = _native.bn_apply(x, mean, var, gamma, beta, eps, y, relu)
+    if st is not None:
+        return _check("mpt_bn_apply", st)
     P, C = _bn_shapes(x, [("mean", mean), ("var", var), ("gamma", gamma), ("beta", beta)], [("y", y)])
     _dev(x, mean, var, gamma, beta, y)
     _check("mpt_bn_apply", lib().mpt_bn_apply(_stream(), P, C, _p(x), x.stride(0), _p(mean), _p(var), _p(gamma), _p(beta),
@@ -552,6 +619,9 @@ def mpt_bn_apply(x, mean, var, gamma, beta, eps, y, relu=False):
 
 
 def mpt_bn_bwd_reduce(x, dy, mean, var, eps, dgamma, dbeta, ws):
+    st = _native.bn_bwd_reduce(x, dy, mean, var, eps, dgamma, dbeta, ws)
+    if st is not None:
+        return _check("mpt_bn_bwd_reduce", st)
     P, C = _bn_shapes(x, [("mean", mean), ("var", var), ("dgamma", dgamma), ("dbeta", dbeta)], [("dy", dy)])
     _ws_ok(ws)
     _dev(x, dy, mean, var, dgamma, dbeta, ws)
@@ -561,6 +631,9 @@ def mpt_bn_bwd_reduce(x, dy, mean, var, eps, dgamma, dbeta, ws):
 
 
 def mpt_bn_bwd_apply(x, dy, mean, var, gamma, eps, dgamma, dbeta, dx):
+    st = _native.bn_bwd_apply(x, dy, mean, var, gamma, eps, dgamma, dbeta, dx)
+    if st is not None:
+        return _check("mpt_bn_bwd_apply", st)
     P, C = _bn_shapes(x, [("mean", mean), ("var", var), ("gamma", gamma), ("dgamma", dgamma), ("dbeta", dbeta)], [("dy", dy), ("dx", dx)])
     _dev(x, dy, mean, var, gamma, dgamma, dbeta, dx)
     _check("mpt_bn_bwd_apply", lib().mpt_bn_bwd_apply(_stream(), P, C, _p(x), x.stride(0), _p(dy), dy.stride(0), _p(mean), _p(var),
@@ -573,6 +646,9 @@ def _ld(t):
 
 
 def mpt_lstm_cell_fwd(gx, gr, bias, c_prev, act, c, h):
+    st = _native.lstm_cell_fwd(gx, gr, bias, c_prev, act, c, h)
+    if st is not None:
+        return _check("mpt_lstm_cell_fwd", st)
     B, H = _dim2("c_prev", c_prev)
     _mat("c_prev", c_prev, _F16, (B, H)); _mat("c", c, _F16, (B, H)); _mat("h", h, _F16, (B, H))
     _mat("gx", gx, _F16, (B, 4 * H)); _mat("gr", gr, _F16, (B, 4 * H), optional=True); _mat("act", act, _F16, (B, 4 * H))
@@ -583,6 +659,9 @@ def mpt_lstm_cell_fwd(gx, gr, bias, c_prev, act, c, h):
 
 
 def mpt_lstm_cell_bwd(dh, dc_next, act, c, c_prev, da, dc_prev):
+    st = _native.lstm_cell_bwd(dh, dc_next, act, c, c_prev, da, dc_prev)
+    if st is not None:
+        return _check("mpt_lstm_cell_bwd", st)
     B, H = _dim2("c", c)
     for name, t in (("dh", dh), ("c", c), ("c_prev", c_prev), ("dc_prev", dc_prev)):
         _mat(name, t, _F16, (B, H))

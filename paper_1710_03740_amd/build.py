@@ -1,16 +1,18 @@
-"""Compile the HIP sources into paper_1710_03740_amd/libmpt.so for gfx950.
+"""Compile the HIP sources into paper_1710_03740_amd/libmpt.so for gfx950, and the binding's native calls into _calls.so.
 
 Run as `python -m paper_1710_03740_amd.build`.  hipcc cross-compiles without a
-GPU.  The library is built in-tree so that it travels with the source tree.
+GPU.  Both are built in-tree so that they travel with the source tree.
 """
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libmpt.so")
+CALLS = os.path.join(HERE, "_calls.so")
 OBJDIR = os.path.join(HERE, "_build")
 
 HIP_SOURCES = ["elementwise.hip", "gemm.hip", "gemm_ring.hip", "norm.hip", "optim.hip", "lstm.hip", "probe.hip"]
@@ -21,6 +23,18 @@ CXX_SOURCES = ["host.cpp"]
 HIP_FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-ffp-contract=off",
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
              "-Wno-unused-command-line-argument", "-I", INCLUDE, "-I", CSRC]
+
+
+def _calls_command():
+    """The extension module that unpacks torch's tensors: host code against the installed torch's headers."""
+    import torch
+    from torch.utils import cpp_extension
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    inc = [INCLUDE, *cpp_extension.include_paths(), os.path.join(rocm, "include"), sysconfig.get_path("include")]
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    return (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+             "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI]
+            + ["-I" + d for d in inc] + [os.path.join(CSRC, "calls.cpp"), "-o", CALLS, "-L" + lib, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"])
 
 
 def _run(cmd):
@@ -48,6 +62,10 @@ def build(verbose=True):
         if verbose:
             print("[mpt build]", src, flush=True)
         procs.append((cmd, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    cmd = _calls_command()
+    if verbose:
+        print("[mpt build] calls.cpp", flush=True)
+    procs.append((cmd, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     for cmd, p in procs:
         out, _ = p.communicate()
         out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l)
@@ -57,7 +75,7 @@ def build(verbose=True):
             print(out)
     _run([hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB] + objs)
     if verbose:
-        print("[mpt build] wrote", LIB, flush=True)
+        print("[mpt build] wrote", LIB, CALLS, flush=True)
     return LIB
 
 
