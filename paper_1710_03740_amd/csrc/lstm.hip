@@ -4,7 +4,7 @@
 // (or one of the up to 3 that are left at its end), wherever the rows start (250 x 8001 forward: 19.5 us element by element, 15.9 so):
 // every tensor is touched once, 8 bytes per lane.  HBM-bound at large B*H: 30 bytes per hidden unit forward
 // (two pre-activation tensors of 4 gates, previous state in; activations, state, output out), 22 bytes backward.
-#include "mpt_internal.h"
+#include "gemm_parts.h"
 
 typedef _Float16 lh4 __attribute__((ext_vector_type(4), aligned(2)));    // at any address: 8-byte accesses need no more alignment than their elements
 
@@ -27,16 +27,26 @@ __device__ __forceinline__ float tanhf_(float x) {
 
 // NT: nontemporal accesses, for tensors that outgrow the 256 MB memory-side cache (streaming them is faster there,
 // slower for small tensors that the next kernel reads again).
-template <int V, bool NT = false>
-__device__ __forceinline__ void ld16(const uint16_t* p, float (&v)[V]) {
-  if constexpr (V == 4) {
-    const lh4 q = NT ? __builtin_nontemporal_load(reinterpret_cast<const lh4*>(p)) : *reinterpret_cast<const lh4*>(p);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = (float)q[e];
+template <int V> struct RawOf { typedef lh4 type; };
+template <> struct RawOf<1> { typedef _Float16 type; };
+template <int V> using Raw = typename RawOf<V>::type;
+template <int V, bool NT>
+__device__ __forceinline__ Raw<V> raw(const uint16_t* p) {
+  const Raw<V>* q = reinterpret_cast<const Raw<V>*>(p);
+  if constexpr (NT) return __builtin_nontemporal_load(q);
+  else return *q;
+}
+template <int V>
+__device__ __forceinline__ void widen(const Raw<V>& q, float (&v)[V]) {
+  if constexpr (V == 1) {
+    v[0] = (float)q;
   } else {
-    v[0] = (float)*reinterpret_cast<const _Float16*>(p);
+#pragma unroll
+    for (int e = 0; e < V; ++e) v[e] = (float)q[e];
   }
 }
+template <int V, bool NT = false>
+__device__ __forceinline__ void ld16(const uint16_t* p, float (&v)[V]) { widen<V>(raw<V, NT>(p), v); }
 template <int V, bool NT = false>
 __device__ __forceinline__ void st16(uint16_t* p, const float (&v)[V]) {
   if constexpr (V == 4) {
@@ -50,28 +60,77 @@ __device__ __forceinline__ void st16(uint16_t* p, const float (&v)[V]) {
   }
 }
 
+using mpt_gemm::FastDiv;
+
+// Which V cells a thread has.  ROWS: a workgroup lies in one row, whose addresses are then formed once per wavefront, a lane adding 32
+// bits; else threads are dealt over the rows one after the other.  The division of a 64-bit index per thread that stood here
+// was, with the 64-bit addresses, a third of the kernel's instructions.
+struct Share {
+  int64_t B;
+  uint32_t H, groups, per_row;     // groups of V cells; and the cells left over, one per thread
+  FastDiv blocks;                  // ROWS: workgroups per row; else: threads per row
+};
+template <bool ROWS>
+__device__ __forceinline__ bool my_cells(const Share& s, int64_t& b, uint32_t& k) {
+  uint32_t q, r;
+  if constexpr (ROWS) {
+    s.blocks.divmod(blockIdx.x, q, r);
+    k = r * kT + threadIdx.x;
+    b = q;
+    return k < s.per_row;
+  } else {
+    s.blocks.divmod(blockIdx.x * kT + threadIdx.x, q, k);
+    b = q;
+    return b < s.B;
+  }
+}
+
 // V cells of row b from unit j on
 template <int V, bool NT>
-__device__ __forceinline__ void cell_fwd(int64_t b, int64_t j, int64_t H, const uint16_t* __restrict__ gx, int64_t ldgx,
+__device__ __forceinline__ void cell_fwd(int64_t b, uint32_t j, uint32_t H, const uint16_t* __restrict__ gx, int64_t ldgx,
                                          const uint16_t* __restrict__ gr, int64_t ldgr, const float* __restrict__ bias,
                                          const uint16_t* cprev, int64_t ldcp, uint16_t* __restrict__ act, int64_t ldact,
                                          uint16_t* c, int64_t ldc, uint16_t* __restrict__ h, int64_t ldh) {
-  float a[4][V], cp[V];
+  // All loads first, those of optional tensors behind one branch each: with a branch behind every load the nine of a thread went out
+  // one after the other, each waited for (both changes: 250 x 8001 14.1 -> 11.6 us, 1000 x 8192 44.6 -> 39.4, 256 x 8192 12.5 -> 11.7, 64 x 1023 3.1 -> 2.6).
+  float a[4][V], r[4][V], bi[4][V], cp[V];
+  Raw<V> qa[4], qr[4], qc;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) qa[g] = raw<V, NT>(gx + b * ldgx + (int64_t)g * H + j);
+  qc = raw<V, NT>(cprev + b * ldcp + j);
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
-    ld16<V, NT>(gx + b * ldgx + g * H + j, a[g]);
-    if (gr != nullptr) {
-      float r[V];
-      ld16<V, NT>(gr + b * ldgr + g * H + j, r);
+    qr[g] = Raw<V>{};
 #pragma unroll
-      for (int e = 0; e < V; ++e) a[g][e] = __fadd_rn(a[g][e], r[e]);
-    }
-    if (bias != nullptr) {
+    for (int e = 0; e < V; ++e) bi[g][e] = 0.f;
+  }
+  if (gr != nullptr) {
 #pragma unroll
-      for (int e = 0; e < V; ++e) a[g][e] = __fadd_rn(a[g][e], bias[g * H + j + e]);
+    for (int g = 0; g < 4; ++g) qr[g] = raw<V, NT>(gr + b * ldgr + (int64_t)g * H + j);
+  }
+  if (bias != nullptr) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int e = 0; e < V; ++e) bi[g][e] = bias[(int64_t)g * H + j + e];
+  }
+#pragma unroll
+  for (int g = 0; g < 4; ++g) widen<V>(qa[g], a[g]);
+  if (gr != nullptr) {                            // (adding nothing would turn -0 into +0)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      widen<V>(qr[g], r[g]);
+#pragma unroll
+      for (int e = 0; e < V; ++e) a[g][e] = __fadd_rn(a[g][e], r[g][e]);
     }
   }
-  ld16<V, NT>(cprev + b * ldcp + j, cp);
+  if (bias != nullptr) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int e = 0; e < V; ++e) a[g][e] = __fadd_rn(a[g][e], bi[g][e]);
+  }
+  widen<V>(qc, cp);
   float cn[V], hn[V];
 #pragma unroll
   for (int e = 0; e < V; ++e) {
@@ -81,41 +140,41 @@ __device__ __forceinline__ void cell_fwd(int64_t b, int64_t j, int64_t H, const 
     hn[e] = __fmul_rn(o, tanhf_(cn[e]));
   }
 #pragma unroll
-  for (int g = 0; g < 4; ++g) st16<V, NT>(act + b * ldact + g * H + j, a[g]);
+  for (int g = 0; g < 4; ++g) st16<V, NT>(act + b * ldact + (int64_t)g * H + j, a[g]);
   st16<V, NT>(c + b * ldc + j, cn);
   st16<V, NT>(h + b * ldh + j, hn);
 }
 
-template <int V, bool NT>
-__global__ __launch_bounds__(kT) void k_lstm_cell_fwd(int64_t B, int64_t H, const uint16_t* __restrict__ gx, int64_t ldgx,
+template <int V, bool NT, bool ROWS>
+__global__ __launch_bounds__(kT) void k_lstm_cell_fwd(Share s, const uint16_t* __restrict__ gx, int64_t ldgx,
                                                       const uint16_t* __restrict__ gr, int64_t ldgr, const float* __restrict__ bias,
                                                       const uint16_t* cprev, int64_t ldcp, uint16_t* __restrict__ act, int64_t ldact,
                                                       uint16_t* c, int64_t ldc, uint16_t* __restrict__ h, int64_t ldh) {
-  const int64_t groups = H / V, per_row = groups + H % V;
-  const int64_t u = (int64_t)blockIdx.x * kT + threadIdx.x;
-  if (u >= B * per_row) return;
-  const int64_t b = u / per_row, k = u - b * per_row;
-  if (V == 1 || k < groups) cell_fwd<V, NT>(b, k * V, H, gx, ldgx, gr, ldgr, bias, cprev, ldcp, act, ldact, c, ldc, h, ldh);
-  else cell_fwd<1, false>(b, groups * (V - 1) + k, H, gx, ldgx, gr, ldgr, bias, cprev, ldcp, act, ldact, c, ldc, h, ldh);
+  int64_t b;
+  uint32_t k;
+  if (!my_cells<ROWS>(s, b, k)) return;
+  if (V == 1 || k < s.groups) cell_fwd<V, NT>(b, k * V, s.H, gx, ldgx, gr, ldgr, bias, cprev, ldcp, act, ldact, c, ldc, h, ldh);
+  else cell_fwd<1, false>(b, s.groups * (V - 1) + k, s.H, gx, ldgx, gr, ldgr, bias, cprev, ldcp, act, ldact, c, ldc, h, ldh);
 }
 
 template <int V, bool NT>
-__device__ __forceinline__ void cell_bwd(int64_t b, int64_t j, int64_t H, const uint16_t* __restrict__ dh, int64_t lddh,
+__device__ __forceinline__ void cell_bwd(int64_t b, uint32_t j, uint32_t H, const uint16_t* __restrict__ dh, int64_t lddh,
                                          const uint16_t* dcn, int64_t lddcn, const uint16_t* __restrict__ act, int64_t ldact,
                                          const uint16_t* __restrict__ c, int64_t ldc, const uint16_t* __restrict__ cprev, int64_t ldcp,
                                          uint16_t* __restrict__ da, int64_t ldda, uint16_t* dcp, int64_t lddcp) {
   float a[4][V], dhv[V], dc[V], cv[V], cp[V];
+  Raw<V> qa[4];
 #pragma unroll
-  for (int g = 0; g < 4; ++g) ld16<V, NT>(act + b * ldact + g * H + j, a[g]);
-  ld16<V, NT>(dh + b * lddh + j, dhv);
-  ld16<V, NT>(c + b * ldc + j, cv);
-  ld16<V, NT>(cprev + b * ldcp + j, cp);
-  if (dcn != nullptr) {
-    ld16<V, NT>(dcn + b * lddcn + j, dc);
-  } else {
+  for (int g = 0; g < 4; ++g) qa[g] = raw<V, NT>(act + b * ldact + (int64_t)g * H + j);
+  const Raw<V> qh = raw<V, NT>(dh + b * lddh + j), qc = raw<V, NT>(c + b * ldc + j), qp = raw<V, NT>(cprev + b * ldcp + j);
+  Raw<V> qd = Raw<V>{};
+  if (dcn != nullptr) qd = raw<V, NT>(dcn + b * lddcn + j);
 #pragma unroll
-    for (int e = 0; e < V; ++e) dc[e] = 0.f;
-  }
+  for (int g = 0; g < 4; ++g) widen<V>(qa[g], a[g]);
+  widen<V>(qh, dhv);
+  widen<V>(qc, cv);
+  widen<V>(qp, cp);
+  widen<V>(qd, dc);
   float out[4][V], dprev[V];
 #pragma unroll
   for (int e = 0; e < V; ++e) {
@@ -129,27 +188,34 @@ __device__ __forceinline__ void cell_bwd(int64_t b, int64_t j, int64_t H, const 
     dprev[e] = __fmul_rn(d, f);
   }
 #pragma unroll
-  for (int g = 0; g < 4; ++g) st16<V, NT>(da + b * ldda + g * H + j, out[g]);
+  for (int g = 0; g < 4; ++g) st16<V, NT>(da + b * ldda + (int64_t)g * H + j, out[g]);
   st16<V, NT>(dcp + b * lddcp + j, dprev);
 }
 
-template <int V, bool NT>
-__global__ __launch_bounds__(kT) void k_lstm_cell_bwd(int64_t B, int64_t H, const uint16_t* __restrict__ dh, int64_t lddh,
+template <int V, bool NT, bool ROWS>
+__global__ __launch_bounds__(kT) void k_lstm_cell_bwd(Share s, const uint16_t* __restrict__ dh, int64_t lddh,
                                                       const uint16_t* dcn, int64_t lddcn, const uint16_t* __restrict__ act, int64_t ldact,
                                                       const uint16_t* __restrict__ c, int64_t ldc, const uint16_t* __restrict__ cprev, int64_t ldcp,
                                                       uint16_t* __restrict__ da, int64_t ldda, uint16_t* dcp, int64_t lddcp) {
-  const int64_t groups = H / V, per_row = groups + H % V;
-  const int64_t u = (int64_t)blockIdx.x * kT + threadIdx.x;
-  if (u >= B * per_row) return;
-  const int64_t b = u / per_row, k = u - b * per_row;
-  if (V == 1 || k < groups) cell_bwd<V, NT>(b, k * V, H, dh, lddh, dcn, lddcn, act, ldact, c, ldc, cprev, ldcp, da, ldda, dcp, lddcp);
-  else cell_bwd<1, false>(b, groups * (V - 1) + k, H, dh, lddh, dcn, lddcn, act, ldact, c, ldc, cprev, ldcp, da, ldda, dcp, lddcp);
+  int64_t b;
+  uint32_t k;
+  if (!my_cells<ROWS>(s, b, k)) return;
+  if (V == 1 || k < s.groups) cell_bwd<V, NT>(b, k * V, s.H, dh, lddh, dcn, lddcn, act, ldact, c, ldc, cprev, ldcp, da, ldda, dcp, lddcp);
+  else cell_bwd<1, false>(b, s.groups * (V - 1) + k, s.H, dh, lddh, dcn, lddcn, act, ldact, c, ldc, cprev, ldcp, da, ldda, dcp, lddcp);
 }
 
 // Few cells: one per thread.  A launch whose threads are all on the chip at once takes as long as one of them does, and that is the
 // longer the more cells it has, longer still where a wavefront holds a row's left-over cells as well (64 x 1023 forward
 // 5.1 us in fours, 3.2 singly, backward 2.9 and 2.2; 512 x 1023 6.8 and 5.4, 4.5 and 4.1; 768 x 1023 8.6 and 10.7, 5.5 and 5.0).
 bool one_per_thread(int64_t B, int64_t H) { return B * H <= 512 * 1024; }
+
+// The launch over cells of V: by rows where at most a fifth of the workgroups' threads stay idle so, and where the flat index is too long for 32 bits.
+struct Launch { Share s; int64_t grid; bool rows; };
+Launch plan(int64_t B, int64_t H, int V) {
+  const int64_t groups = H / V, per_row = groups + H % V, blocks = (per_row + kT - 1) / kT, flat = (B * per_row + kT - 1) / kT;
+  const bool rows = per_row * 5 >= blocks * kT * 4 || flat * kT > 0xFFFFFFFFLL;
+  return {{B, (uint32_t)H, (uint32_t)groups, (uint32_t)per_row, FastDiv((uint32_t)(rows ? blocks : per_row))}, rows ? B * blocks : flat, rows};
+}
 
 bool dims_ok(int64_t B, int64_t H) { return B >= 1 && H >= 1 && B <= (1LL << 31) && H <= (1LL << 24); }
 
@@ -165,12 +231,12 @@ extern "C" int mpt_lstm_cell_fwd(void* stream, int64_t B, int64_t H, const uint1
     return MPT_ERR_ALIGN;
   hipStream_t st = static_cast<hipStream_t>(stream);
   const bool singly = one_per_thread(B, H);
-  const int64_t units = singly ? B * H : B * (H / 4 + (H & 3));  // 4 cells (8 bytes) per lane: measured 5.5 vs 5.3 TB/s against 8 cells
-  const unsigned grid = (unsigned)((units + kT - 1) / kT);
+  const Launch l = plan(B, H, singly ? 1 : 4);               // 4 cells (8 bytes) per lane: measured 5.5 vs 5.3 TB/s against 8 cells
   const bool stream_it = B * H * 30 > (192LL << 20);         // bytes moved beyond the memory-side cache
-  if (singly) hipLaunchKernelGGL((k_lstm_cell_fwd<1, false>), dim3(grid), dim3(kT), 0, st, B, H, gx, ldgx, gr, ldgr, bias, c_prev, ldcp, act, ldact, c, ldc, h, ldh);
-  else if (stream_it) hipLaunchKernelGGL((k_lstm_cell_fwd<4, true>), dim3(grid), dim3(kT), 0, st, B, H, gx, ldgx, gr, ldgr, bias, c_prev, ldcp, act, ldact, c, ldc, h, ldh);
-  else hipLaunchKernelGGL((k_lstm_cell_fwd<4, false>), dim3(grid), dim3(kT), 0, st, B, H, gx, ldgx, gr, ldgr, bias, c_prev, ldcp, act, ldact, c, ldc, h, ldh);
+  auto k = singly ? (l.rows ? k_lstm_cell_fwd<1, false, true> : k_lstm_cell_fwd<1, false, false>)
+           : stream_it ? (l.rows ? k_lstm_cell_fwd<4, true, true> : k_lstm_cell_fwd<4, true, false>)
+                       : (l.rows ? k_lstm_cell_fwd<4, false, true> : k_lstm_cell_fwd<4, false, false>);
+  hipLaunchKernelGGL(k, dim3((unsigned)l.grid), dim3(kT), 0, st, l.s, gx, ldgx, gr, ldgr, bias, c_prev, ldcp, act, ldact, c, ldc, h, ldh);
   MPT_LAUNCH_CHECK();
   return MPT_OK;
 }
@@ -185,12 +251,12 @@ extern "C" int mpt_lstm_cell_bwd(void* stream, int64_t B, int64_t H, const uint1
     return MPT_ERR_ALIGN;
   hipStream_t st = static_cast<hipStream_t>(stream);
   const bool singly = one_per_thread(B, H);
-  const int64_t units = singly ? B * H : B * (H / 4 + (H & 3));
-  const unsigned grid = (unsigned)((units + kT - 1) / kT);
+  const Launch l = plan(B, H, singly ? 1 : 4);
   const bool stream_it = B * H * 22 > (192LL << 20);
-  if (singly) hipLaunchKernelGGL((k_lstm_cell_bwd<1, false>), dim3(grid), dim3(kT), 0, st, B, H, dh, lddh, dc_next, lddcn, act, ldact, c, ldc, c_prev, ldcp, da, ldda, dc_prev, lddcp);
-  else if (stream_it) hipLaunchKernelGGL((k_lstm_cell_bwd<4, true>), dim3(grid), dim3(kT), 0, st, B, H, dh, lddh, dc_next, lddcn, act, ldact, c, ldc, c_prev, ldcp, da, ldda, dc_prev, lddcp);
-  else hipLaunchKernelGGL((k_lstm_cell_bwd<4, false>), dim3(grid), dim3(kT), 0, st, B, H, dh, lddh, dc_next, lddcn, act, ldact, c, ldc, c_prev, ldcp, da, ldda, dc_prev, lddcp);
+  auto k = singly ? (l.rows ? k_lstm_cell_bwd<1, false, true> : k_lstm_cell_bwd<1, false, false>)
+           : stream_it ? (l.rows ? k_lstm_cell_bwd<4, true, true> : k_lstm_cell_bwd<4, true, false>)
+                       : (l.rows ? k_lstm_cell_bwd<4, false, true> : k_lstm_cell_bwd<4, false, false>);
+  hipLaunchKernelGGL(k, dim3((unsigned)l.grid), dim3(kT), 0, st, l.s, dh, lddh, dc_next, lddcn, act, ldact, c, ldc, c_prev, ldcp, da, ldda, dc_prev, lddcp);
   MPT_LAUNCH_CHECK();
   return MPT_OK;
 }
