@@ -9,6 +9,7 @@
 // statistics are accumulated about a per-channel pivot (the channel's first element), so that
 // var = E[(x-k)^2] - E[x-k]^2 does not cancel when the mean is large against the spread.
 #include "mpt_internal.h"
+#include <type_traits>
 
 typedef _Float16 h8v __attribute__((ext_vector_type(8)));
 typedef _Float16 h4v __attribute__((ext_vector_type(4)));
@@ -179,47 +180,63 @@ __global__ __launch_bounds__(kBlock) void k_bn_partial(BnShape s, const uint16_t
 #pragma unroll
   for (int e = 0; e < V; ++e) { red[0][threadIdx.x * V + e] = a1[e]; red[1][threadIdx.x * V + e] = a2[e]; }
   __syncthreads();
-  if (active && slot == 0) {
-#pragma unroll
-    for (int e = 0; e < V; ++e) {
-      const int c = c0 + e;
-      if (c >= s.C) continue;
-      double t1 = 0.0, t2 = 0.0;
-      for (int q = 0; q < s.slots; ++q) {
-        const int th = q * s.tpr + (threadIdx.x % s.tpr);
-        t1 += red[0][th * V + e];
-        t2 += red[1][th * V + e];
-      }
-      part[((int64_t)blockIdx.x * 2 + 0) * s.C + c] = t1;
-      part[((int64_t)blockIdx.x * 2 + 1) * s.C + c] = t2;
-    }
+  // one sum of one channel per thread: in the hands of the first slot's threads the slots' sums were read one after the other
+  const int width = s.tpr * V;
+  for (int j = threadIdx.x; j < 2 * width; j += kBlock) {
+    const int which = j < width ? 0 : 1, ch = j - which * width, c = blockIdx.y * width + ch;
+    double t = 0.0;
+#pragma unroll 8
+    for (int q = 0; q < s.slots; ++q) t += red[which][q * width + ch];
+    if (c < s.C) part[((int64_t)blockIdx.x * 2 + which) * s.C + c] = t;
   }
 }
 
-// 16 channels per workgroup; 16 thread groups each sum a contiguous range of row blocks in block order, the 16
-// results are added in group order; then the closing arithmetic in FP64 and one rounding to FP32.
+// 16 channels per workgroup; 64 thread groups each sum a contiguous range of row blocks in block order, their results are added
+// by eights in group order; then the closing arithmetic in FP64 and one rounding to FP32.  A few hundred kilobytes in a few
+// workgroups: bound by the latency of memory, so a thread has all its partials in flight at once (with 16 groups of eight in
+// flight 40000 x 40 took 9.0 us with its partial sums, 6.35 so, 12544 x 512 9.8 and 8.1, 200704 x 64 12.7 and 12.3).
+constexpr int kFinalizeThreads = 1024;
 template <int MODE>
-__global__ __launch_bounds__(256) void k_bn_finalize(BnShape s, const double* __restrict__ part, const uint16_t* __restrict__ x,
+__global__ __launch_bounds__(kFinalizeThreads) void k_bn_finalize(BnShape s, const double* __restrict__ part, const uint16_t* __restrict__ x,
                                                      float* __restrict__ out1, float* __restrict__ out2) {
-  __shared__ double red[2][16][16];
+  __shared__ double red[64][2][16], red8[8][2][16];
   const int cl = threadIdx.x & 15, grp = threadIdx.x >> 4;
   const int c = blockIdx.x * 16 + cl;
-  const int per = (s.nblk + 15) / 16;
+  const int per = (s.nblk + 63) / 64;
   const int b0 = grp * per, b1 = min(b0 + per, s.nblk);
   double t1 = 0.0, t2 = 0.0;
-  if (c < s.C) {
-#pragma unroll 8
-    for (int b = b0; b < b1; ++b) {
-      t1 += part[((int64_t)b * 2 + 0) * s.C + c];
-      t2 += part[((int64_t)b * 2 + 1) * s.C + c];
+  auto add = [&](auto n, int b) {                 // so many blocks; one beyond the last is read as the last and left out
+    constexpr int N = decltype(n)::value;
+    double v1[N], v2[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const double* q = part + (int64_t)min(b + u, b1 - 1) * 2 * s.C + c;
+      v1[u] = q[0];
+      v2[u] = q[s.C];
     }
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+      if (b + u < b1) { t1 += v1[u]; t2 += v2[u]; }
+  };
+  if (c < s.C) {
+    if (per <= 4) { if (b0 < b1) add(std::integral_constant<int, 4>{}, b0); }
+    else for (int b = b0; b < b1; b += 16) add(std::integral_constant<int, 16>{}, b);
   }
-  red[0][grp][cl] = t1;
-  red[1][grp][cl] = t2;
+  red[grp][0][cl] = t1;
+  red[grp][1][cl] = t2;
+  __syncthreads();
+  if (threadIdx.x < 256) {                        // 8 eights x 2 sums x 16 channels
+    const int eight = threadIdx.x >> 5, which = threadIdx.x >> 4 & 1;
+    double t = 0.0;
+#pragma unroll
+    for (int g = 0; g < 8; ++g) t += red[eight * 8 + g][which][cl];
+    red8[eight][which][cl] = t;
+  }
   __syncthreads();
   if (grp != 0 || c >= s.C) return;
   t1 = t2 = 0.0;
-  for (int g = 0; g < 16; ++g) { t1 += red[0][g][cl]; t2 += red[1][g][cl]; }
+#pragma unroll
+  for (int g = 0; g < 8; ++g) { t1 += red8[g][0][cl]; t2 += red8[g][1][cl]; }
   if constexpr (MODE == 0) {
     const double k = (double)(float)reinterpret_cast<const _Float16*>(x)[c];
     const double d1 = t1 / (double)s.P;
@@ -392,13 +409,13 @@ extern "C" int mpt_bn_stats(void* stream, int64_t P, int64_t C, const uint16_t* 
     if (bn_stream(P, C)) hipLaunchKernelGGL((k_bn_partial<4, 0, true>), dim3(s.nblk, s.cgy), dim3(kBlock), 0, st, s, x, ldx, nullptr, 0, nullptr, nullptr, 0.f, part);
     else hipLaunchKernelGGL((k_bn_partial<4, 0, false>), dim3(s.nblk, s.cgy), dim3(kBlock), 0, st, s, x, ldx, nullptr, 0, nullptr, nullptr, 0.f, part);
     MPT_LAUNCH_CHECK();
-    hipLaunchKernelGGL((k_bn_finalize<0>), dim3((s.C + 15) / 16), dim3(256), 0, st, s, part, x, mean, var);
+    hipLaunchKernelGGL((k_bn_finalize<0>), dim3((s.C + 15) / 16), dim3(kFinalizeThreads), 0, st, s, part, x, mean, var);
   } else {
     const BnShape s = bn_shape<1>(P, C);
     if (bn_stream(P, C)) hipLaunchKernelGGL((k_bn_partial<1, 0, true>), dim3(s.nblk, s.cgy), dim3(kBlock), 0, st, s, x, ldx, nullptr, 0, nullptr, nullptr, 0.f, part);
     else hipLaunchKernelGGL((k_bn_partial<1, 0, false>), dim3(s.nblk, s.cgy), dim3(kBlock), 0, st, s, x, ldx, nullptr, 0, nullptr, nullptr, 0.f, part);
     MPT_LAUNCH_CHECK();
-    hipLaunchKernelGGL((k_bn_finalize<0>), dim3((s.C + 15) / 16), dim3(256), 0, st, s, part, x, mean, var);
+    hipLaunchKernelGGL((k_bn_finalize<0>), dim3((s.C + 15) / 16), dim3(kFinalizeThreads), 0, st, s, part, x, mean, var);
   }
   MPT_LAUNCH_CHECK();
   return MPT_OK;
@@ -447,13 +464,13 @@ extern "C" int mpt_bn_bwd_reduce(void* stream, int64_t P, int64_t C, const uint1
     if (bn_stream(P, C)) hipLaunchKernelGGL((k_bn_partial<4, 1, true>), dim3(s.nblk, s.cgy), dim3(kBlock), 0, st, s, x, ldx, dy, lddy, mean, var, eps, part);
     else hipLaunchKernelGGL((k_bn_partial<4, 1, false>), dim3(s.nblk, s.cgy), dim3(kBlock), 0, st, s, x, ldx, dy, lddy, mean, var, eps, part);
     MPT_LAUNCH_CHECK();
-    hipLaunchKernelGGL((k_bn_finalize<1>), dim3((s.C + 15) / 16), dim3(256), 0, st, s, part, x, dgamma, dbeta);
+    hipLaunchKernelGGL((k_bn_finalize<1>), dim3((s.C + 15) / 16), dim3(kFinalizeThreads), 0, st, s, part, x, dgamma, dbeta);
   } else {
     const BnShape s = bn_shape<1>(P, C);
     if (bn_stream(P, C)) hipLaunchKernelGGL((k_bn_partial<1, 1, true>), dim3(s.nblk, s.cgy), dim3(kBlock), 0, st, s, x, ldx, dy, lddy, mean, var, eps, part);
     else hipLaunchKernelGGL((k_bn_partial<1, 1, false>), dim3(s.nblk, s.cgy), dim3(kBlock), 0, st, s, x, ldx, dy, lddy, mean, var, eps, part);
     MPT_LAUNCH_CHECK();
-    hipLaunchKernelGGL((k_bn_finalize<1>), dim3((s.C + 15) / 16), dim3(256), 0, st, s, part, x, dgamma, dbeta);
+    hipLaunchKernelGGL((k_bn_finalize<1>), dim3((s.C + 15) / 16), dim3(kFinalizeThreads), 0, st, s, part, x, dgamma, dbeta);
   }
   MPT_LAUNCH_CHECK();
   return MPT_OK;
