@@ -476,19 +476,17 @@ __device__ __forceinline__ float wave_sum(float v) {
 
 // Softmax cross-entropy with the loss scale folded into the gradient: FP16 logits in, FP32 max / sum / probabilities,
 // FP16 scaled gradient out, FP32 loss of the row out.  A row is held in registers between its single read and its
-// single write (4 bytes of traffic per element): WAVES wavefronts per row, NCH 16-byte chunks per lane, so a row of
-// up to WAVES*64*8*NCH classes (65536 at most; the row stays packed in FP16 and the exponential is evaluated twice).
-// Exponentials use the hardware 2^x (about 1 ulp of FP32, far inside one FP16 step).
-template <int WAVES, int NCH, bool VEC>
-__global__ __launch_bounds__((WAVES * 64 > kThreads ? WAVES * 64 : kThreads)) void k_softmax_xent_rows(
-    int64_t B, int64_t C, const uint16_t* __restrict__ logits, int64_t ldl, const int32_t* __restrict__ labels,
-    float factor, uint16_t* __restrict__ dlogits, int64_t ldd, float* __restrict__ row_loss, bool stream) {
-  constexpr int NT = WAVES * 64 > kThreads ? WAVES * 64 : kThreads;   // threads per workgroup
-  constexpr int T = 64 * WAVES;                                        // threads per row
-  __shared__ float red[NT / 64];
+// single write (4 bytes of traffic per element): LANES lanes per row (a part of a wavefront, or whole ones), NCH 16-byte chunks
+// per lane, so a row of up to LANES*8*NCH classes (65536 at most; the row stays packed in FP16 and the exponential is evaluated
+// twice).  Exponentials use the hardware 2^x (about 1 ulp of FP32, far inside one FP16 step).
+// All of a workgroup's threads come here together; gives the row's loss to the row's first lane.
+template <int LANES, int NCH, bool VEC>
+__device__ __forceinline__ float softmax_xent_row(int64_t row, int tr, int64_t B, int64_t C, const uint16_t* __restrict__ logits, int64_t ldl,
+                                                  const int32_t* __restrict__ labels, float factor, uint16_t* __restrict__ dlogits, int64_t ldd,
+                                                  float* __restrict__ row_loss, bool stream, float* red) {
+  constexpr int T = LANES, WAVES = LANES / 64;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int rslot = wave / WAVES, tr = threadIdx.x - rslot * T;
-  const int64_t row = (int64_t)blockIdx.x * (NT / T) + rslot;
+  const int rslot = threadIdx.x / T;
   const bool live = row < B;
   const _Float16* z = reinterpret_cast<const _Float16*>(logits) + (live ? row : 0) * ldl;
   h8 q[NCH];                                                           // the row stays packed; padding is -inf
@@ -533,8 +531,12 @@ __global__ __launch_bounds__((WAVES * 64 > kThreads ? WAVES * 64 : kThreads)) vo
     m2 = __builtin_elementwise_max(m2, __builtin_elementwise_max(sm_h2{q[i][4], q[i][5]}, sm_h2{q[i][6], q[i][7]}));
     mx = fmaxf(mx, fmaxf((float)m2[0], (float)m2[1]));
   }
-  auto across = [&](float x, bool is_max) {                // over the row's wavefronts, fixed order
-    x = is_max ? wave_max(x) : wave_sum(x);
+  auto across = [&](float x, bool is_max) {                // over the row's lanes and wavefronts, fixed order
+#pragma unroll
+    for (int o = (T < 64 ? T : 64) / 2; o > 0; o >>= 1) {
+      const float y = __shfl_xor(x, o, 64);
+      x = is_max ? fmaxf(x, y) : __fadd_rn(x, y);
+    }
     if constexpr (WAVES > 1) {
       __syncthreads();
       if (lane == 0) red[wave] = x;
@@ -567,7 +569,7 @@ __global__ __launch_bounds__((WAVES * 64 > kThreads ? WAVES * 64 : kThreads)) vo
       sum = __fadd_rn(sum, x);
     }
   sum = across(sum, false);
-  if (!live) return;
+  if (!live) return 0.f;
   const int32_t lab = min(max(labels[row], 0), (int32_t)(C - 1));      // a label outside [0, C) is the caller's error; it must not become a wild read
   const float inv = div_rn(1.0f, sum);
   const float scale_all = __fmul_rn(inv, factor);                        // every element but the label's: p * factor in one multiplication
@@ -610,10 +612,51 @@ __global__ __launch_bounds__((WAVES * 64 > kThreads ? WAVES * 64 : kThreads)) vo
       }
     }
   }
-  if (row_loss != nullptr && tr == 0) {
-    // -log p[label] = log(sum) - (z[label] - max)
-    row_loss[row] = __fsub_rn(logf(sum), __fsub_rn((float)z[lab], mx));
+  if (row_loss == nullptr || tr != 0) return 0.f;
+  // -log p[label] = log(sum) - (z[label] - max)
+  const float l = __fsub_rn(logf(sum), __fsub_rn((float)z[lab], mx));
+  row_loss[row] = l;
+  return l;
+}
+
+template <int LANES, int NCH, bool VEC>
+__global__ __launch_bounds__((LANES > kThreads ? LANES : kThreads)) void k_softmax_xent_rows(
+    int64_t B, int64_t C, const uint16_t* __restrict__ logits, int64_t ldl, const int32_t* __restrict__ labels,
+    float factor, uint16_t* __restrict__ dlogits, int64_t ldd, float* __restrict__ row_loss, bool stream) {
+  constexpr int NT = LANES > kThreads ? LANES : kThreads;              // threads per workgroup
+  __shared__ float red[NT / 64];
+  softmax_xent_row<LANES, NCH, VEC>((int64_t)blockIdx.x * (NT / LANES) + threadIdx.x / LANES, threadIdx.x % LANES, B, C, logits, ldl, labels, factor,
+                                    dlogits, ldd, row_loss, stream, red);
+}
+
+// The sum of kThreads partial sums, in an order that depends on nothing; thread 0 stores it over B.
+__device__ __forceinline__ void store_mean(float acc, int64_t B, float* part, float* __restrict__ loss) {
+  if ((int)threadIdx.x < kThreads) part[threadIdx.x] = acc;
+  __syncthreads();
+  for (int w = kThreads / 2; w > 0; w >>= 1) {
+    if ((int)threadIdx.x < w) part[threadIdx.x] = __fadd_rn(part[threadIdx.x], part[threadIdx.x + w]);
+    __syncthreads();
   }
+  if (threadIdx.x == 0) loss[0] = div_rn(part[0], (float)B);
+}
+
+// Few short rows and their mean in one launch: a workgroup that takes all rows at once (256 x 10: 5.4 us as two launches, 3.5 so; rows that
+// it would take in two goes are faster in two launches, 1000 x 10 5.3 against 5.9).  The same sums in the same order as in two.
+constexpr int kSmallThreads = 1024;
+template <int LANES>
+__global__ __launch_bounds__(kSmallThreads) void k_softmax_xent_small(
+    int64_t B, int64_t C, const uint16_t* __restrict__ logits, int64_t ldl, const int32_t* __restrict__ labels, float factor,
+    uint16_t* __restrict__ dlogits, int64_t ldd, float* __restrict__ row_loss, float* __restrict__ loss) {
+  constexpr int ROWS = kSmallThreads / LANES;
+  __shared__ float of_row[ROWS], part[kThreads];
+  const int row = (int)threadIdx.x / LANES, tr = threadIdx.x % LANES;
+  const float l = softmax_xent_row<LANES, 1, false>(row, tr, B, C, logits, ldl, labels, factor, dlogits, ldd, row_loss, false, nullptr);
+  if (tr == 0) of_row[row] = l;
+  __syncthreads();
+  float acc = 0.f;
+  if ((int)threadIdx.x < kThreads)
+    for (int r = threadIdx.x; r < (int)B; r += kThreads) acc = __fadd_rn(acc, of_row[r]);
+  store_mean(acc, B, part, loss);
 }
 
 // Rows too long to hold in registers: one workgroup of 1024 threads per row, three passes over the row (the
@@ -707,13 +750,7 @@ __global__ __launch_bounds__(kThreads) void k_loss_mean(int64_t B, const float* 
     for (int u = 0; u < 4; ++u)
       if (r + u * kThreads < B) acc = __fadd_rn(acc, v[u]);
   }
-  part[threadIdx.x] = acc;
-  __syncthreads();
-  for (int w = kThreads / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) part[threadIdx.x] = __fadd_rn(part[threadIdx.x], part[threadIdx.x + w]);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) loss[0] = div_rn(part[0], (float)B);
+  store_mean(acc, B, part, loss);
 }
 
 // Grid size for a streaming pass over `units` thread-trips.
@@ -967,21 +1004,33 @@ extern "C" int mpt_softmax_xent_scaled(void* stream, int64_t B, int64_t C, const
   const float factor = scale / (float)B;
   const bool vec = mpt_aligned(logits, 16) && mpt_aligned(dlogits, 16) && (ldl % 8) == 0 && (ldd % 8) == 0 && (C % 8) == 0;
   const bool nontemporal = B * C * 2 > (192LL << 20);   // beyond the memory-side cache
-#define MPT_SM_LAUNCH(WAVES, NCH)                                                                                                   \
+  if (loss != nullptr && C <= 512) {
+    const int lanes = C <= 16 ? 2 : C <= 64 ? 8 : C <= 256 ? 32 : 64;
+    if (B * lanes <= kSmallThreads) {
+      auto k = lanes == 2 ? k_softmax_xent_small<2> : lanes == 8 ? k_softmax_xent_small<8> : lanes == 32 ? k_softmax_xent_small<32> : k_softmax_xent_small<64>;
+      hipLaunchKernelGGL(k, dim3(1), dim3(kSmallThreads), 0, s, B, C, logits, ldl, labels, factor, dlogits, ldd, row_loss, loss);
+      MPT_LAUNCH_CHECK();
+      return MPT_OK;
+    }
+  }
+  // Rows of up to 256 classes take a part of a wavefront each (8192 x 10 with its mean 8.5 -> 5.4 us, 2049 x 10 5.9 -> 5.3).
+#define MPT_SM_LAUNCH(LANES, NCH)                                                                                                   \
   do {                                                                                                                              \
-    constexpr unsigned nt = WAVES * 64 > kThreads ? WAVES * 64 : kThreads;                                                          \
-    const unsigned rows = nt / (64 * WAVES);                                                                                        \
+    constexpr unsigned nt = LANES > kThreads ? LANES : kThreads, rows = nt / LANES;                                                 \
     const unsigned grid = (unsigned)((B + rows - 1) / rows);                                                                        \
-    if (vec) hipLaunchKernelGGL((k_softmax_xent_rows<WAVES, NCH, true>), dim3(grid), dim3(nt), 0, s, B, C, logits, ldl, labels,     \
+    if (vec) hipLaunchKernelGGL((k_softmax_xent_rows<LANES, NCH, true>), dim3(grid), dim3(nt), 0, s, B, C, logits, ldl, labels,     \
                                 factor, dlogits, ldd, row_loss, nontemporal);                                                       \
-    else hipLaunchKernelGGL((k_softmax_xent_rows<WAVES, NCH, false>), dim3(grid), dim3(nt), 0, s, B, C, logits, ldl, labels,        \
+    else hipLaunchKernelGGL((k_softmax_xent_rows<LANES, NCH, false>), dim3(grid), dim3(nt), 0, s, B, C, logits, ldl, labels,        \
                             factor, dlogits, ldd, row_loss, nontemporal);                                                           \
   } while (0)
-  if (C <= 512) MPT_SM_LAUNCH(1, 1);
-  else if (C <= 2048) MPT_SM_LAUNCH(1, 4);
-  else if (C <= 8192) MPT_SM_LAUNCH(4, 4);
-  else if (C <= 32768) MPT_SM_LAUNCH(16, 4);      // measured: 16 wavefronts x 4 chunks 5.0 TB/s, 4 x 16 4.4 TB/s
-  else if (C <= 65536) MPT_SM_LAUNCH(16, 8);
+  if (C <= 16) MPT_SM_LAUNCH(2, 1);
+  else if (C <= 64) MPT_SM_LAUNCH(8, 1);
+  else if (C <= 256) MPT_SM_LAUNCH(32, 1);
+  else if (C <= 512) MPT_SM_LAUNCH(64, 1);
+  else if (C <= 2048) MPT_SM_LAUNCH(64, 4);
+  else if (C <= 8192) MPT_SM_LAUNCH(256, 4);
+  else if (C <= 32768) MPT_SM_LAUNCH(1024, 4);    // measured: 16 wavefronts x 4 chunks 5.0 TB/s, 4 x 16 4.4 TB/s
+  else if (C <= 65536) MPT_SM_LAUNCH(1024, 8);
   else if (vec) hipLaunchKernelGGL(k_softmax_xent_long<true>, dim3((unsigned)B), dim3(1024), 0, s, B, C, logits, ldl, labels, factor, dlogits, ldd, row_loss);
   else hipLaunchKernelGGL(k_softmax_xent_long<false>, dim3((unsigned)B), dim3(1024), 0, s, B, C, logits, ldl, labels, factor, dlogits, ldd, row_loss);
 #undef MPT_SM_LAUNCH
