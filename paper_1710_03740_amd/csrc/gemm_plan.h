@@ -167,4 +167,11 @@ inline bool ring_for_fp32(int64_t tiles256, int64_t ktiles, bool accumulate) {
 // over 1024 15.9 -> 13.4; 3072 x 2048 (192) over 256 9.5 -> 9.1, over 512 12.2 against 12.4.
 inline bool ring_for_fp16(int64_t tiles128, int64_t ktiles) { return tiles128 <= kCUs / 2 ? tiles128 * ktiles <= 6 * kCUs : ktiles <= 4 && tiles128 < kCUs; }
 
+// Convolutions (forward and input gradient) that k_conv_patch takes: a filter of at most 64 x 64 channels, rows of which two patches
+// and the outputs fit LDS, and pixels for half the CUs: 32768 of them (128 tiles) with 64 channels 13.3 -> 9.8 us, where the ring kernels
+// still work unsplit.  Measured at 23 sizes of 8 .. 64 channels: 0.67 to 1.0 of the ring kernels' time.
+inline bool conv_in_patches(int64_t Nb, int64_t H, int64_t W, int64_t C, int64_t Kf) {
+  return C <= 64 && Kf <= 64 && W <= 120 && Nb * H * W >= 128 * kCUs;
+}
+
 }  // namespace mpt_gemm

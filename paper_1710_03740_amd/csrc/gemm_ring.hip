@@ -11,6 +11,7 @@
 // Ragged edges cost no branch: rows beyond the output read the last row again, pieces beyond the reduction read a line
 // of zeros, and the store leaves out what does not exist.
 #include "gemm_parts.h"
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -789,6 +790,167 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   store_tile<FM, FN>(pb, ep, sp, i0 + wm * WM, j0 + wn * WN, lane, acc, lds + wave * (WM * WN * 4));
 }
 
+// ---------------------------------------------------------------- convolutions of at most 64 channels
+// Forward and input gradient over the pixels in order: a workgroup takes 256 of them at a time, with the W + 1 before and behind,
+// from which all nine taps are then read, and keeps the whole filter in registers (9 taps x 64 x 64, 288 a lane), going through
+// its share of the pixels.  k_gemm_ring fetches the pixels nine times and the filter once per 256 of them: 289 MB through LDS for
+// 64 x 56 x 56 with 64 channels where this one moves 57: 32.9 -> 26.9 us forward and 34.3 -> 27.1 backward there, 128 of them 58.7 -> 43.5.
+//
+// LDS holds the pixels of this trip and of the next (rows of 64 channels, zeros beyond Cin and the images), and the wavefronts'
+// outputs on their way out.  A tap that lies outside its image reads a row of zeros instead of its pixel.
+// One barrier per trip: the next pixels have landed, and all wavefronts are through with the ones they take the place of.
+struct PatchConv {
+  const uint16_t *img, *filter;    // [P][Cin]; [Kf][9][C]
+  uint16_t* out;                   // [P][Cout]
+  int P, H, W, Cin, Cout, Kf, C, rows, tiles;    // rows: of a patch, 256 + 2 (W + 1) rounded up to 8
+  FastDiv dHW, dW;
+};
+constexpr int kPatchPixels = 256, kFilterBytes = 9 * 64 * 128;
+inline int patch_rows(int64_t W) { return (int)((kPatchPixels + 2 * (W + 1) + 7) / 8 * 8); }
+// zeros | pixels | pixels | outputs; the filter comes in where the second pixels and the outputs will be
+inline int patch_lds_bytes(int rows) { return 128 + rows * 128 + std::max(rows * 128 + 4 * 8192, kFilterBytes); }
+
+// The filter's fragments of one half tap, waited for where they are read: 288 registers are more than the vector half of the file, and the
+// compiler moves them over as soon as it takes them to be there.
+template <bool RC, int HALF>
+__device__ __forceinline__ void read_filter(const RingFrag<RC, 64, 4>& r, uint32_t slot, uint4v (&frag)[4]) {
+  if constexpr (RC) {
+    asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:2048\n\tds_read_b128 %2, %4 offset:4096\n\tds_read_b128 %3, %4 offset:6144\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(frag[0]), "=&v"(frag[1]), "=&v"(frag[2]), "=&v"(frag[3]) : "v"(r.at[HALF] + slot) : "memory");
+  } else {
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+      uint2v lo, hi;
+      asm volatile("ds_read_b64_tr_b16 %0, %2 offset:%3\n\tds_read_b64_tr_b16 %1, %2 offset:%4\n\ts_waitcnt lgkmcnt(0)"
+                   : "=&v"(lo), "=&v"(hi) : "v"(r.at[f] + slot), "n"(HALF * 4096), "n"(HALF * 4096 + 512) : "memory");
+      frag[f] = uint4v{lo[0], lo[1], hi[0], hi[1]};
+    }
+  }
+}
+__device__ __forceinline__ void lds_write_b64(uint32_t addr, uint2v v) { asm volatile("ds_write_b64 %0, %1" ::"v"(addr), "v"(v) : "memory"); }
+
+template <bool MIRROR, int HALVES>                                     // HALVES: of 32 input channels
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_conv_patch(PatchConv c) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int li = lane & 15, lg = lane >> 4;
+  char* const patch0 = lds + 128;
+  const int patch_bytes = c.rows * 128;
+  const int first = (int)((int64_t)c.tiles * blockIdx.x / gridDim.x), last = (int)((int64_t)c.tiles * (blockIdx.x + 1) / gridDim.x);
+
+  // the pixels of a tile: blocks of 8 rows, one cache line each where there are 64 channels
+  const int in_block = lane >> 3;
+  auto fetch = [&](int tile, char* to) {
+    const int p0 = tile * kPatchPixels - (c.W + 1);
+    for (int b = wave; b < c.rows / 8; b += 4) {
+      const int r = b * 8 + in_block, p = p0 + r, col = ((lane & 7) ^ ((r >> 1) & 7)) * 8;
+      to_lds(there_or_zeros((unsigned)p < (unsigned)c.P && col < c.Cin, c.img + (int64_t)p * c.Cin + col), to + b * 1024);
+    }
+  };
+  fetch(first, patch0);
+  char* const filter = patch0 + patch_bytes;
+  for (int b = wave; b < 72; b += 4) {
+    const int tap = b >> 3, r = (b & 7) * 8 + in_block, pc = lane & 7;
+    const int col = MIRROR ? (2 * ((pc >> 1) ^ ring_key<64>(r)) + (pc & 1)) * 8 : (pc ^ ((r >> 1) & 7)) * 8;
+    to_lds(there_or_zeros(r < c.Kf && col < c.C, c.filter + ((int64_t)r * 9 + tap) * c.C + col), filter + b * 1024);
+  }
+  if (t < 8) *reinterpret_cast<uint4v*>(lds + t * 16) = uint4v{0u, 0u, 0u, 0u};
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  uint4v fb[9][HALVES][4];
+  const uint32_t lds0 = lds_offset(lds), patch_at = lds0 + 128;
+  {
+    RingFrag<!MIRROR, 64, 4> rb;
+    rb.init(0, lane, patch_at + patch_bytes);
+    static_for<9>([&](auto tc) {
+      constexpr int tap = decltype(tc)::value;
+      read_filter<!MIRROR, 0>(rb, tap * 8192, fb[tap][0]);
+      if constexpr (HALVES == 2) read_filter<!MIRROR, 1>(rb, tap * 8192, fb[tap][1]);
+    });
+    asm volatile("s_barrier" ::: "memory");
+  }
+  const uint32_t staging = patch_at + 2 * patch_bytes + wave * 8192;
+  if (first + 1 < last) fetch(first + 1, patch0 + patch_bytes);
+
+  for (int tile = first; tile < last; ++tile) {
+    const uint32_t at = patch_at + ((tile - first) & 1) * patch_bytes;
+    // where the lane's four pixels lie in their images: one bit per tap
+    const int p0 = tile * kPatchPixels + wave * 64 + li;
+    uint32_t taps[4];
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+      uint32_t n, rem, y, x;
+      c.dHW.divmod((uint32_t)min(p0 + f * 16, c.P - 1), n, rem);
+      c.dW.divmod(rem, y, x);
+      const bool up = MIRROR ? y + 1 < (uint32_t)c.H : y > 0, down = MIRROR ? y > 0 : y + 1 < (uint32_t)c.H;      // rows of taps 0-2 and 6-8
+      const bool left = MIRROR ? x + 1 < (uint32_t)c.W : x > 0, right = MIRROR ? x > 0 : x + 1 < (uint32_t)c.W;
+      const uint32_t cols = (left ? 1u : 0u) | 2u | (right ? 4u : 0u);
+      taps[f] = (up ? cols : 0u) | cols << 3 | (down ? cols << 6 : 0u);
+    }
+    float4v acc[4][4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int b = 0; b < 4; ++b) acc[a][b] = float4v{0.f, 0.f, 0.f, 0.f};
+    uint32_t from[4];
+    uint4v fa[2][4];
+    auto read = [&](auto sc, uint4v (&frag)[4]) {                      // of half stage s: tap s / HALVES
+      constexpr int s = decltype(sc)::value, tap = s / HALVES, tr = tap / 3 - 1, ts = tap % 3 - 1;
+      if constexpr (s % HALVES == 0) {
+        const int shift = c.W + 1 + (MIRROR ? -(tr * c.W + ts) : tr * c.W + ts);
+#pragma unroll
+        for (int f = 0; f < 4; ++f) {
+          const uint32_t r = (uint32_t)(wave * 64 + f * 16 + li + shift);
+          const uint32_t there = at + (r << 7) + (((r << 3) & 0x70u) ^ (uint32_t)(lg << 4));
+          from[f] = (taps[f] & (1u << tap)) != 0 ? there : lds0 + (uint32_t)(lg << 4);
+        }
+      } else {
+#pragma unroll
+        for (int f = 0; f < 4; ++f) from[f] ^= 64u;                    // (zeros and patches start on multiples of 128)
+      }
+#pragma unroll
+      for (int f = 0; f < 4; ++f) frag[f] = lds_read_b128_imm<0>(from[f]);
+    };
+    read(std::integral_constant<int, 0>{}, fa[0]);
+    static_for<9 * HALVES>([&](auto sc) {
+      constexpr int s = decltype(sc)::value, cur = s & 1;
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      arrived(fa[cur]);
+      if constexpr (s + 1 < 9 * HALVES) read(std::integral_constant<int, s + 1>{}, fa[1 - cur]);
+      multiply<0, 4>(acc, fa[cur], fb[s / HALVES][s % HALVES]);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    // out through the wavefront's own 8 KiB, as store_tile does, in 8 stores of whole row segments
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        half4 h;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) h[e] = (_Float16)acc[a][b][e];
+        lds_write_b64(staging + (uint32_t)((a * 16 + li) * 128 + (((2 * b + (lg >> 1)) ^ (li & 7)) << 4) + (lg & 1) * 8), __builtin_bit_cast(uint2v, h));
+      }
+    const int unit = lane & 7, r0 = lane >> 3;
+    uint4v q[8];
+#pragma unroll
+    for (int it = 0; it < 8; ++it) {
+      const int r = it * 8 + r0;
+      q[it] = lds_read_b128_imm<0>(staging + (uint32_t)(r * 128 + ((unit ^ (r & 7)) << 4)));
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    arrived(q);
+#pragma unroll
+    for (int it = 0; it < 8; ++it) {
+      const int p = tile * kPatchPixels + wave * 64 + it * 8 + r0;
+      if (p < c.P && unit * 8 < c.Cout) *reinterpret_cast<uint4v*>(c.out + (int64_t)p * c.Cout + unit * 8) = q[it];
+    }
+    if (tile + 1 == last) return;
+    // The next pixels were asked for before this trip's 8 stores (all 8 are there: only the very last tile lacks pixels); the stores
+    // need not be through.
+    asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");
+    if (tile + 2 < last) fetch(tile + 2, patch0 + ((tile - first) & 1) * patch_bytes);
+  }
+}
+
 // ---------------------------------------------------------------- launches
 Problem ring_problem(RingTile tile, int ktiles_per_split, int I, int J, int R) {
   const int bm = ring_tile_rows(tile), bn = ring_tile_cols(tile), kt = (R + 63) / 64;
@@ -836,6 +998,17 @@ int launch_plain(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool w
   if (tile == kRing64x64) return launch_ring<RingMat<A_RC, 64>, RingMat<B_RC, 64>, 64, 64, 32, 32, 4, CUT>(s, A, B, pb, ep, cut);
   if (tile == kRing128x64) return launch_ring<RingMat<A_RC, 128>, RingMat<B_RC, 64>, 128, 64, 64, 32, 2, CUT>(s, A, B, pb, ep, cut);
   return launch_ring<RingMat<A_RC, 128>, RingMat<B_RC, 128>, 128, 128, 64, 64, 2, CUT>(s, A, B, pb, ep, cut);
+}
+
+template <bool MIRROR, int HALVES>
+int launch_patch(hipStream_t s, const PatchConv& c) {
+  auto k = k_conv_patch<MIRROR, HALVES>;
+  const int lds = patch_lds_bytes(c.rows);
+  static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, 163840), true);
+  (void)once;
+  hipLaunchKernelGGL(k, dim3((unsigned)std::min(c.tiles, kCUs)), dim3(256), lds, s, c);
+  MPT_LAUNCH_CHECK();
+  return MPT_OK;
 }
 
 template <bool CUT>
@@ -891,6 +1064,13 @@ int launch_ring_plain(hipStream_t s, bool a_rc, bool b_rc, const RingMatSrc& A, 
 
 int launch_ring_conv(hipStream_t s, int op, int64_t Nb, int64_t H, int64_t W, int64_t C, int64_t Kf, const uint16_t* img, const uint16_t* other,
                      RingTile tile, int ktiles_per_split, int cut, const Epilogue& ep) {
+  if (op != MPT_OP_WGRAD && cut == 0 && ep.mode == 0 && conv_in_patches(Nb, H, W, C, Kf)) {
+    const int P = (int)(Nb * H * W), in = (int)(op == MPT_OP_FWD ? C : Kf), out = (int)(op == MPT_OP_FWD ? Kf : C);
+    const PatchConv c{img, other, reinterpret_cast<uint16_t*>(ep.out), P, (int)H, (int)W, in, out, (int)Kf, (int)C, patch_rows(W),
+                      (P + kPatchPixels - 1) / kPatchPixels, FastDiv((uint32_t)(H * W)), FastDiv((uint32_t)W)};
+    if (op == MPT_OP_FWD) return in <= 32 ? launch_patch<false, 1>(s, c) : launch_patch<false, 2>(s, c);
+    return in <= 32 ? launch_patch<true, 1>(s, c) : launch_patch<true, 2>(s, c);
+  }
   return cut > 0 ? launch_conv<true>(s, op, Nb, H, W, C, Kf, img, other, tile, ktiles_per_split, cut, ep)
                  : launch_conv<false>(s, op, Nb, H, W, C, Kf, img, other, tile, ktiles_per_split, 0, ep);
 }
