@@ -1,8 +1,8 @@
 // Pointwise part of an LSTM cell with FP16 tensors and FP32 math (paper Sec. 3.3, "point-wise operations"; the
 // recurrent layers of Sec. 4), forward and backward, for gfx950.  The matrix products around it are the GEMM entry
 // points.  Gate order (i, f, g, o) along the 4H axis.  A thread owns 4 consecutive hidden units of one batch row
-// (or one of the up to 3 that are left at its end), wherever the rows start (250 x 8001 forward: 19.5 us element by element, 15.9 so):
-// every tensor is touched once, 8 bytes per lane.  HBM-bound at large B*H: 30 bytes per hidden unit forward
+// (or one of the up to 3 that are left at its end), wherever the rows start (250 x 8001 forward: 19.5 us element by element, 15.9 so,
+// 11.6 with a thread's loads together): every tensor is touched once, 8 bytes per lane.  HBM-bound at large B*H: 30 bytes per hidden unit forward
 // (two pre-activation tensors of 4 gates, previous state in; activations, state, output out), 22 bytes backward.
 #include "gemm_parts.h"
 
