@@ -115,7 +115,7 @@ def lib():
         spec = importlib.util.spec_from_file_location("_calls", CALLS_PATH)
         calls = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(calls)
-        calls.bind({name: ctypes.cast(getattr(L, name), c_vp).value for name in SIGNATURES})
+        calls.bind({name: ctypes.cast(getattr(L, name), c_vp).value for name in SIGNATURES}, mpt_opt_params)
         _lib, _native = L, calls
     return _lib
 
@@ -441,6 +441,9 @@ def mpt_master_update_multi(tensors, inv_scale, lr, momentum, flag=None, scaler_
 
 
 def mpt_master_update_fused(w32_in, m32_in, grad, w32_out, m32_out, w16_out, inv_scale, lr, momentum, flag, scaler_dev=None):
+    st = _native.master_update_fused(w32_in, m32_in, grad, w32_out, m32_out, w16_out, inv_scale, lr, momentum, flag, scaler_dev)
+    if st is not None:
+        return _check("mpt_master_update_fused", st)
     n = _update_buffers(w32_in, [("m32_in", m32_in), ("m32_out", m32_out)], grad, w16_out, flag, scaler_dev)
     _want("w32_out", w32_out, _F32, numel=n); _flat("w32_out", w32_out)
     _want("flag", flag, _I32, numel=1)
@@ -454,6 +457,9 @@ def mpt_master_update_fused(w32_in, m32_in, grad, w32_out, m32_out, w16_out, inv
 
 def mpt_optimizer_update(kind, hp, w32, state1, state2, grad, w16, inv_scale, flag=None, scaler_dev=None):
     """kind: a key of OPT_KINDS; hp: an mpt_opt_params (host struct; its clip_factor_dev is a device address or None)."""
+    st = _native.optimizer_update(kind, hp, w32, state1, state2, grad, w16, inv_scale, flag, scaler_dev)
+    if st is not None:
+        return _check("mpt_optimizer_update", st)
     if kind not in OPT_KINDS:
         raise ValueError("kind: %r, expected one of %s" % (kind, sorted(OPT_KINDS)))
     _update_buffers(w32, [("state1", state1), ("state2", state2)], grad, w16, flag, scaler_dev)
@@ -471,6 +477,9 @@ def mpt_grad_norm_workspace_bytes():
 
 def mpt_grad_sumsq(grad, inv_scale, sumsq, ws, flag=None, accumulate=False, scaler_dev=None):
     """sumsq: float64[1] device tensor; ws: device scratch of mpt_grad_norm_workspace_bytes() bytes."""
+    st = _native.grad_sumsq(grad, inv_scale, sumsq, ws, flag, accumulate, scaler_dev)
+    if st is not None:
+        return _check("mpt_grad_sumsq", st)
     _want("grad", grad, (_F16, _F32)); _flat("grad", grad)
     _want("sumsq", sumsq, torch.float64, numel=1)
     _want("flag", flag, _I32, numel=1, optional=True)
@@ -484,6 +493,9 @@ def mpt_grad_sumsq(grad, inv_scale, sumsq, ws, flag=None, accumulate=False, scal
 
 def mpt_clip_factor(sumsq, max_norm, factor, norm=None):
     """factor (and the optional norm): float32[1] device tensors."""
+    st = _native.clip_factor(sumsq, max_norm, factor, norm)
+    if st is not None:
+        return _check("mpt_clip_factor", st)
     _want("sumsq", sumsq, torch.float64, numel=1); _want("factor", factor, _F32, numel=1); _want("norm", norm, _F32, numel=1, optional=True)
     _dev(sumsq, factor, norm)
     _check("mpt_clip_factor", lib().mpt_clip_factor(_stream(), _p(sumsq), max_norm, _p(factor), _p(norm)))
@@ -491,6 +503,9 @@ def mpt_clip_factor(sumsq, max_norm, factor, norm=None):
 
 def mpt_grad_stats(grad, hist, absmax_bits, accumulate=False):
     """hist: int64[42] device tensor; absmax_bits: int32[1] device tensor."""
+    st = _native.grad_stats(grad, hist, absmax_bits, accumulate)
+    if st is not None:
+        return _check("mpt_grad_stats", st)
     _want("grad", grad, _F16); _flat("grad", grad)
     _want("hist", hist, _I64, numel=42); _flat("hist", hist)
     _want("absmax_bits", absmax_bits, _I32, numel=1)
@@ -550,6 +565,9 @@ def mpt_add_fp16(a, b, out):
 
 
 def mpt_relu_fwd(y, h):
+    st = _native.relu_fwd(y, h)
+    if st is not None:
+        return _check("mpt_relu_fwd", st)
     _want("y", y, _F16); _flat("y", y); _want("h", h, _F16, numel=y.numel()); _flat("h", h)
     _dev(y, h)
     _check("mpt_relu_fwd", lib().mpt_relu_fwd(_stream(), y.numel(), _p(y), _p(h)))

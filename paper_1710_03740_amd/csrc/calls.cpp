@@ -15,6 +15,7 @@
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <string.h>
 #include <vector>
 #include "mpt.h"
 
@@ -27,10 +28,12 @@ struct Refused {};                                                    // the Pyt
   X(mpt_gemm_fwd) X(mpt_gemm_fwd_relu) X(mpt_gemm_dgrad) X(mpt_gemm_dgrad_relu) X(mpt_gemm_wgrad) X(mpt_conv3x3_fwd)               \
   X(mpt_conv3x3_dgrad) X(mpt_conv3x3_wgrad) X(mpt_unscale_check) X(mpt_master_update) X(mpt_master_update_multi)                  \
   X(mpt_loss_scale_update_dev) X(mpt_softmax_xent_scaled) X(mpt_add_fp16) X(mpt_relu_bwd) X(mpt_bn_stats) X(mpt_bn_apply)         \
-  X(mpt_bn_bwd_reduce) X(mpt_bn_bwd_apply) X(mpt_lstm_cell_fwd) X(mpt_lstm_cell_bwd)
+  X(mpt_bn_bwd_reduce) X(mpt_bn_bwd_apply) X(mpt_lstm_cell_fwd) X(mpt_lstm_cell_bwd) X(mpt_master_update_fused)                    \
+  X(mpt_optimizer_update) X(mpt_grad_sumsq) X(mpt_clip_factor) X(mpt_grad_stats) X(mpt_relu_fwd)
 #define X(name) decltype(&::name) p_##name = nullptr;
 MPT_CALLS(X)
 #undef X
+PyObject* params_type = nullptr;                                      // binding.mpt_opt_params
 
 // ---------------------------------------------------------------- arguments
 // A tensor as the checks below see it.  Sizes and strides are read once; what throws (symbolic sizes, no storage) ends in Refused.
@@ -240,6 +243,53 @@ int master_update_multi(Args a) {                                     // tensors
   return call(p_mpt_master_update_multi, (int)n, (const mpt_update_item*)items.data(), first, number(a[1]), sc.ptr<mpt_scaler>(), number(a[2]), number(a[3]),
               flag.ptr<uint32_t>());
 }
+int master_update_fused(Args a) {                                     // w32_in, m32_in, grad, w32_out, m32_out, w16_out, inv_scale, lr, momentum, flag, scaler_dev
+  int fp32;
+  const mpt_update_item in = update_item(a[0], a[1], a[2], a[5], &fp32);
+  const int64_t n = (int64_t)in.n;
+  const T out = flat(a[3], at::kFloat, n), m = flat(a[4], at::kFloat, n, false), flag = one(a[9], at::kInt), sc = scaler(a[10]);
+  want(flag && (a[1] == Py_None) == (a[4] == Py_None));
+  return call(p_mpt_master_update_fused, in.n, in.w32_dev, in.m32_dev, in.grad_dev, fp32, out.f(), m.f(), in.w16_dev, number(a[6]), sc.ptr<mpt_scaler>(),
+              number(a[7]), number(a[8]), flag.ptr<uint32_t>());
+}
+int optimizer_update(Args a) {                                        // kind, hp, w32, state1, state2, grad, w16, inv_scale, flag, scaler_dev
+  static const char* const kinds[] = {"momentum", "nesterov", "adagrad", "adam"};
+  want(PyUnicode_CheckExact(a[0]));
+  int kind = 0;
+  while (kind < 4 && PyUnicode_CompareWithASCIIString(a[0], kinds[kind]) != 0) ++kind;
+  want(kind < 4 && (PyObject*)Py_TYPE(a[1]) == params_type && a[3] != Py_None && (kind != 3 || a[4] != Py_None));
+  mpt_opt_params hp;
+  Py_buffer view;
+  want(PyObject_GetBuffer(a[1], &view, PyBUF_SIMPLE) == 0);
+  const bool whole = view.len == (Py_ssize_t)sizeof(hp);
+  if (whole) memcpy(&hp, view.buf, sizeof(hp));
+  PyBuffer_Release(&view);
+  want(whole);
+  int fp32;
+  const mpt_update_item u = update_item(a[2], a[3], a[5], a[6], &fp32);
+  const T second = flat(a[4], at::kFloat, (int64_t)u.n, false), flag = one(a[8], at::kInt), sc = scaler(a[9]);
+  return call(p_mpt_optimizer_update, u.n, kind, (const mpt_opt_params*)&hp, u.w32_dev, u.m32_dev, second.f(), u.grad_dev, fp32, u.w16_dev, number(a[7]),
+              sc.ptr<mpt_scaler>(), flag.ptr<uint32_t>());
+}
+int grad_sumsq(Args a) {                                              // grad, inv_scale, sumsq, ws, flag, accumulate, scaler_dev
+  int fp32;
+  const T g = gradient(a[0], &fp32), sum = one(a[2], at::kDouble), flag = one(a[4], at::kInt), sc = scaler(a[6]);
+  want((bool)sum);
+  const Ws ws = workspace(a[3]);
+  return call(p_mpt_grad_sumsq, g.ptr<const void>(), fp32, (size_t)g.numel(), number(a[1]), sc.ptr<mpt_scaler>(), truth(a[5]), sum.ptr<double>(),
+              flag.ptr<uint32_t>(), ws.p, ws.bytes);
+}
+int clip_factor(Args a) {                                             // sumsq, max_norm, factor, norm
+  const T sum = one(a[0], at::kDouble), factor = one(a[2], at::kFloat), norm = one(a[3], at::kFloat);
+  want(sum && factor);
+  return call(p_mpt_clip_factor, sum.ptr<double>(), number(a[1]), factor.f(), norm.f());
+}
+int grad_stats(Args a) {                                              // grad, hist, absmax_bits, accumulate
+  const T g = tensor(a[0]), most = one(a[2], at::kInt);
+  flat(a[0], at::kHalf, g.numel());
+  want((bool)most);
+  return call(p_mpt_grad_stats, g.h(), (size_t)g.numel(), truth(a[3]), flat(a[1], at::kLong, 42).ptr<uint64_t>(), most.ptr<uint32_t>());
+}
 int loss_scale_update_dev(Args a) {                                   // scaler_dev, flag
   const T sc = scaler(a[0]), flag = one(a[1], at::kInt);
   want(sc && flag);
@@ -258,6 +308,12 @@ int add_fp16(Args a) {                                                // a, b, o
   const int64_t n = x.numel();
   flat(a[0], at::kHalf, n);
   return call(p_mpt_add_fp16, (size_t)n, x.h(), flat(a[1], at::kHalf, n).h(), flat(a[2], at::kHalf, n).h());
+}
+int relu_fwd(Args a) {                                                // y, h
+  const T y = tensor(a[0]);
+  const int64_t n = y.numel();
+  flat(a[0], at::kHalf, n);
+  return call(p_mpt_relu_fwd, (size_t)n, y.h(), flat(a[1], at::kHalf, n).h());
 }
 int relu_bwd(Args a) {                                                // dh, y, dy
   const T y = tensor(a[1]);
@@ -311,11 +367,16 @@ int lstm_cell_bwd(Args a) {                                           // dh, dc_
   return call(p_mpt_lstm_cell_bwd, B, H, dh.h(), dh.ld(), dn.h(), dn.ld(), act.h(), act.ld(), c.h(), c.ld(), cp.h(), cp.ld(), da.h(), da.ld(), dp.h(), dp.ld());
 }
 
-// The entry points' addresses, by name, from the library that the binding loaded.
-PyObject* bind(PyObject*, PyObject* addresses) {
+// The entry points' addresses, by name, from the library that the binding loaded; and its class of the optimizers' parameters.
+PyObject* bind(PyObject*, PyObject* args) {
+  PyObject *addresses, *params;
+  if (!PyArg_ParseTuple(args, "O!O!", &PyDict_Type, &addresses, &PyType_Type, &params)) return nullptr;
+  Py_INCREF(params);
+  Py_XDECREF(params_type);
+  params_type = params;
 #define X(name)                                                                                          \
   {                                                                                                      \
-    PyObject* o = PyDict_Check(addresses) ? PyDict_GetItemString(addresses, #name) : nullptr;            \
+    PyObject* o = PyDict_GetItemString(addresses, #name);                                                \
     void* p = o == nullptr ? nullptr : PyLong_AsVoidPtr(o);                                              \
     if (p == nullptr) {                                                                                  \
       if (!PyErr_Occurred()) PyErr_SetString(PyExc_KeyError, #name);                                     \
@@ -330,13 +391,15 @@ PyObject* bind(PyObject*, PyObject* addresses) {
 
 #define M(name, n, ...) {name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(static_cast<PyObject* (*)(PyObject*, Args, Py_ssize_t)>(guarded<n, __VA_ARGS__>))), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {
-    {"bind", bind, METH_O, nullptr},
+    {"bind", bind, METH_VARARGS, nullptr},
     M("gemm_fwd", 4, gemm_fwd<&p_mpt_gemm_fwd>), M("gemm_fwd_relu", 4, gemm_fwd<&p_mpt_gemm_fwd_relu>), M("gemm_dgrad", 4, gemm_dgrad),
     M("gemm_dgrad_relu", 5, gemm_dgrad_relu), M("gemm_wgrad", 6, gemm_wgrad), M("conv3x3_fwd", 4, conv_fwd), M("conv3x3_dgrad", 4, conv_dgrad),
     M("conv3x3_wgrad", 5, conv_wgrad), M("unscale_check", 4, unscale_check), M("master_update", 9, master_update),
     M("master_update_multi", 6, master_update_multi), M("loss_scale_update_dev", 2, loss_scale_update_dev), M("softmax_xent_scaled", 6, softmax),
     M("add_fp16", 3, add_fp16), M("relu_bwd", 3, relu_bwd), M("bn_stats", 4, bn_stats), M("bn_apply", 8, bn_apply), M("bn_bwd_reduce", 8, bn_bwd_reduce),
-    M("bn_bwd_apply", 9, bn_bwd_apply), M("lstm_cell_fwd", 7, lstm_cell_fwd), M("lstm_cell_bwd", 7, lstm_cell_bwd), {nullptr, nullptr, 0, nullptr}};
+    M("bn_bwd_apply", 9, bn_bwd_apply), M("lstm_cell_fwd", 7, lstm_cell_fwd), M("lstm_cell_bwd", 7, lstm_cell_bwd),
+    M("master_update_fused", 11, master_update_fused), M("optimizer_update", 10, optimizer_update), M("grad_sumsq", 7, grad_sumsq), M("clip_factor", 4, clip_factor),
+    M("grad_stats", 4, grad_stats), M("relu_fwd", 2, relu_fwd), {nullptr, nullptr, 0, nullptr}};
 #undef M
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_calls", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 

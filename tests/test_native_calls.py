@@ -39,6 +39,11 @@ def _calls():
     lab = torch.randint(0, N, (M,), device="cuda", dtype=I32, generator=g)
     p = [(n(s, dtype=F32), n(s, dtype=F32), n(s), n(s)) for s in (7, 300)]
     sc = mpt.scaler_to_device(mpt.mpt_scaler_init(8.0, 2))
+    factor = n(1, dtype=F32).abs_()
+    hp = mpt.mpt_opt_params(1e-2, 0.9, 0.99, 1e-8, 0.01, 0.1, 0.01, 0.5, 0.5, factor.data_ptr())
+    hp.kept = factor
+    sq, nws = torch.ones(1, device="cuda", dtype=torch.float64), torch.empty(mpt.mpt_grad_norm_workspace_bytes(), device="cuda", dtype=torch.uint8)
+    second = n(300, dtype=F32).abs_()
     return [
         ("gemm_fwd", (n(M, K), n(K, N), n(M, N), ws), 2), ("gemm_fwd", (cut(M, K), cut(K, N), cut(M, N), None), 2),
         ("gemm_fwd_relu", (n(M, K), n(K, N), n(M, N), None), 2), ("gemm_dgrad", (n(M, N), n(K, N), n(M, K), ws), 2),
@@ -48,6 +53,12 @@ def _calls():
         ("conv3x3_wgrad", (x, n(2, 5, 6, 16), n(16, 3, 3, C), fl(), ws), 2), ("unscale_check", (n(99), 0.5, fl(), n(99, dtype=F32)), 3),
         ("master_update", (*p[0], 0.5, 1, 0.9, fl(), sc), 0), ("master_update", (p[1][0], None, n(300, dtype=F32), p[1][3], 0.5, 0.1, 0.0, None, None), 3),
         ("master_update_multi", (p, 0.5, 0.1, 0.9, fl(), None), None), ("loss_scale_update_dev", (sc.clone(), fl()), 0),
+        ("master_update_fused", (*p[1][:3], n(300, dtype=F32), n(300, dtype=F32), n(300), 0.5, 0.1, 0.9, fl(), sc), 3),
+        ("master_update_fused", (p[1][0], None, n(300, dtype=F32), n(300, dtype=F32), None, n(300), 0.5, 0.1, 0.9, fl(), None), 3),
+        ("optimizer_update", ("adam", hp, p[1][0], second, second.clone(), p[1][2], p[1][3], 0.5, fl(), sc), 2),
+        ("optimizer_update", ("adagrad", hp, p[1][0], second, None, n(300, dtype=F32), p[1][3], 0.5, None, None), 2),
+        ("grad_sumsq", (p[1][2], 0.5, sq, nws, fl(), True, sc), 2), ("clip_factor", (sq, 0.5, n(1, dtype=F32), n(1, dtype=F32)), 3), ("clip_factor", (sq, 0.5, n(1, dtype=F32), None), 2),
+        ("grad_stats", (n(999), torch.zeros(42, device="cuda", dtype=torch.int64), fl(), False), 1), ("relu_fwd", (n(77), n(77)), 1),
         ("softmax_xent_scaled", (n(M, N), lab, 64, n(M, N), fl().float(), n(M, dtype=F32)), 3), ("softmax_xent_scaled", (cut(M, N), lab, 64.0, cut(M, N), None, None), 3),
         ("add_fp16", (n(77), n(77), n(77)), 2), ("relu_bwd", (n(77), n(77), n(77)), 2), ("bn_stats", (n(60, C), vec(), vec(), ws), 2),
         ("bn_apply", (n(60, C), vec(), vec(), vec(), vec(), 1e-5, n(60, C), True), 6), ("bn_bwd_reduce", (n(60, C), n(60, C), vec(), vec(), 1e-5, vec(), vec(), ws), 6),
@@ -82,7 +93,7 @@ def test_both_ways_lead_to_the_same_bits(monkeypatch):
             getattr(mpt, "mpt_" + name)(*theirs)
         torch.cuda.synchronize()
         for k, (a, b) in enumerate(zip(mine, theirs)):
-            if not (isinstance(a, torch.Tensor) and a.numel() == 1 << 20):  # (the workspace)
+            if a is not b and not (isinstance(a, torch.Tensor) and (a.numel() == 1 << 20 or a.dtype is torch.uint8 and a.numel() > 32)):  # (not the workspaces)
                 assert _same(a, b), (name, k)
         if out is not None:
             assert not _same(mine[out], args[out]), name                    # it did run
@@ -97,6 +108,10 @@ def test_errors_and_unusual_forms_end_as_they_did():
     assert nat.gemm_fwd(X.as_subclass(Sub), W, Y, None) is None
     assert nat.gemm_fwd(X.t(), W, Y[:, ::2], None) is None and nat.gemm_fwd(X, W.float(), Y, None) is None
     assert nat.gemm_wgrad(X, W, Y, True, None, None) is None                # accumulating needs FP32
+    w, s, h, hp = torch.zeros(8, device="cuda"), torch.zeros(8, device="cuda"), torch.zeros(8, device="cuda", dtype=F16), mpt.mpt_opt_params()
+    assert nat.optimizer_update("adam", hp, w, s, None, h, h.clone(), 1.0, None, None) is None        # Adam without its second state
+    assert nat.optimizer_update("lamb", hp, w, s, None, h, h.clone(), 1.0, None, None) is None
+    assert nat.optimizer_update("nesterov", mpt.mpt_scaler(), w, s, None, h, h.clone(), 1.0, None, None) is None
     with torch.overrides.TorchFunctionMode():
         assert nat.gemm_fwd(X, W, Y, None) is None
     with pytest.raises(ValueError, match="W: shape"):
