@@ -288,10 +288,11 @@ __device__ __forceinline__ uint4v drop_front(uint4v v, int n) {
   return uint4v{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
 }
 
-// A load of device memory through a pointer that the compiler cannot trace to it.  As a flat load it would be counted with the LDS
+// Loads of device memory through a pointer that the compiler cannot trace to it.  As flat loads they would be counted with the LDS
 // reads too, and the next wait for those would wait for the stage that is fetched meanwhile (1001 x 1999 over 1503 28.9 us so, 22.1 now).
-template <class T>
-__device__ __forceinline__ T from_global(const void* p) { return *(const __attribute__((address_space(1))) T*)p; }
+// (No template over the loaded type: as its argument uint4u would lose the alignment of its elements and claim 16 bytes.)
+__device__ __forceinline__ uint4v eight_from_global(const void* p) { return *(const __attribute__((address_space(1))) uint4u*)p; }
+__device__ __forceinline__ uint16_t one_from_global(const void* p) { return *(const __attribute__((address_space(1))) uint16_t*)p; }
 
 // ANY: also rows of fewer than 8 elements, gathered element by element, and row strides too long for 32-bit offsets; kept apart, since
 // their branches around the loads cost the others a tenth (3999 x 1777 over 999 51 against 47 us).
@@ -344,7 +345,7 @@ struct RegMat {
         for (int k = 0; k < NB; ++k) o[k] -= back(s, l, k);
       }
 #pragma unroll
-      for (int k = 0; k < NB; ++k) reg[k] = from_global<uint4u>(at + o[k]);
+      for (int k = 0; k < NB; ++k) reg[k] = eight_from_global(at + o[k]);
       return;
     }
     if constexpr (ANY) {
@@ -356,12 +357,12 @@ struct RegMat {
         const int64_t place = (RC ? (int64_t)min(row, outer_left - 1) : (int64_t)row) * ld + col + kFront;
         const uint16_t* q = there_or_zeros(n > 0, reinterpret_cast<const uint16_t*>(at) + place);
         if (!narrow) {
-          reg[k] = from_global<uint4u>(q - (n > 0 ? 8 - n : 0));
+          reg[k] = eight_from_global(q - (n > 0 ? 8 - n : 0));
         } else {
           const int end = max(n, 1) - 1;
           uint32_t e[8];
 #pragma unroll
-          for (int i = 0; i < 8; ++i) e[i] = from_global<uint16_t>(q + min(i, end));
+          for (int i = 0; i < 8; ++i) e[i] = one_from_global(q + min(i, end));
           reg[k] = uint4v{e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16};
         }
       }
