@@ -167,6 +167,17 @@ inline bool ring_for_fp32(int64_t tiles256, int64_t ktiles, bool accumulate) {
 // over 1024 15.9 -> 13.4; 3072 x 2048 (192) over 256 9.5 -> 9.1, over 512 12.2 against 12.4.
 inline bool ring_for_fp16(int64_t tiles128, int64_t ktiles) { return tiles128 <= kCUs / 2 ? tiles128 * ktiles <= 6 * kCUs : ktiles <= 4 && tiles128 < kCUs; }
 
+// Products through registers in 64 x 64 tiles whose two operands are fetched one after the other, the second when the first is there:
+// with three or four workgroups on the busiest CU and a long reduction their loads get in each other's way.  2002 x 2002 over 2002 as
+// input gradient (4 on each CU) 41.7 us together, 38.8 apart, forward 47.1 and 45.0; 2501 x 1501 over 3001 forward (3.8) 72.8 and 65.4;
+// 847 x 2409 over 2945 as input gradient (2.1, so three on some) 48.9 and 46.3.  With fewer workgroups, with a fifth on some CU, or over a short
+// reduction there is a wait for nothing: 1001 x 1999 over 1503 forward (2.0) 23.1 and 26.6, 1247 x 3988 over 2239 (4.9) 1.14 times as long,
+// 2489 x 1543 over 301 as input gradient (3.8) 1.03 times; forward with three 1.01 to 1.1 times; weight gradients 1.0 to 1.18 times throughout.
+inline bool operands_apart(bool a_rc, bool b_rc, int64_t workgroups, int ktiles) {
+  const int64_t most = (workgroups + kCUs - 1) / kCUs;
+  return a_rc && ((most == 4 && ktiles >= 20) || (most == 3 && b_rc && ktiles >= 32));
+}
+
 // Convolutions (forward and input gradient) that k_conv_patch takes: a filter of at most 64 x 64 channels, rows of which two patches
 // and the outputs fit LDS, and pixels for half the CUs: 32768 of them (128 tiles) with 64 channels 13.3 -> 9.8 us, where the ring kernels
 // still work unsplit.  Measured at 23 sizes of 8 .. 64 channels: 0.67 to 1.0 of the ring kernels' time.

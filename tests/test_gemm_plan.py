@@ -21,6 +21,7 @@ extern "C" void ring(long I, long J, long R, int ws, int whole_chunks, int lines
   const RingPlan r = ring_plan(p, I, J, R, whole_chunks != 0, lines != 0, conv == 3, conv == 2, conv == 1);
   out[0] = r.tile; out[1] = r.splits; out[2] = r.ktiles_per_split; out[3] = r.cut;
 }
+extern "C" int apart(int a_rc, int b_rc, long workgroups, int ktiles) { return operands_apart(a_rc != 0, b_rc != 0, workgroups, ktiles); }
 """
 PLAIN, CONV_ROWS, CONV_WGRAD, ACCUMULATE = 0, 1, 2, 3
 
@@ -42,7 +43,8 @@ def planner(tmp_path_factory):
         out = (ctypes.c_int * 4)()
         f(*args, ctypes.addressof(out))
         return tuple(out)
-    return lambda *a: call(L.planned, *a)[:2], lambda *a: call(L.ring, *a)
+    L.apart.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_long, ctypes.c_int]
+    return lambda *a: call(L.planned, *a)[:2], lambda *a: call(L.ring, *a), L
 
 
 def shapes(n):
@@ -52,7 +54,7 @@ def shapes(n):
 
 
 def test_no_split_is_empty_and_the_partials_fit_the_workspace(planner):
-    planned, ring = planner
+    planned, ring = planner[:2]
     for I, J, R in shapes(2000):
         kt = -(-R // 64)
         splits, per = planned(I, J, R, 1)
@@ -67,7 +69,7 @@ def test_a_product_is_summed_in_the_planned_pieces(planner):
     """Split as planned, or in one launch that cuts its sums there: the result is the same at every alignment.  Among them: the
     projection of a recurrent layer, two whose 6 and 8 pieces were summed in groups, and weight gradients of convolutions (32 x 28 x
     28, 128 channels; 64 x 56 x 56, 64 channels) that took longer ones."""
-    planned, ring = planner
+    planned, ring = planner[:2]
     for I, J, R in shapes(4000) + [(256, 1024, 8192), (172, 1157, 714), (608, 2392, 3528), (128, 1152, 25088), (64, 576, 200704)]:
         splits, per = planned(I, J, R, 1)
         for args in ((1, 1, PLAIN), (1, 0, PLAIN), (0, 0, PLAIN), (1, 1, ACCUMULATE), (0, 0, ACCUMULATE), (1, 1, CONV_ROWS), (1, 1, CONV_WGRAD)):
@@ -78,7 +80,7 @@ def test_a_product_is_summed_in_the_planned_pieces(planner):
 
 def test_the_tile_priced_is_the_tile_launched(planner):
     """Operands through registers have kernels for 64 x 64 tiles and, where the sums are not cut, for 128 x 128 ones."""
-    planned, ring = planner
+    planned, ring = planner[:2]
     tile128, tile64 = 0, 1
     for I, J, R in shapes(4000) + [(3139, 991, 2269), (2518, 3052, 3968)]:
         for ws in (0, 1):
@@ -147,3 +149,20 @@ def test_small_convolutions_take_small_tiles(planner):
 def test_weight_gradients_of_the_wide_tile_tests_take_it(planner, Nb, H, W, C, Kf, splits, cut):
     tile, s, _, c = planner[1](Kf, 9 * C, Nb * H * W, 1, 1, 1, CONV_WGRAD)
     assert (tile, s, c) == (0, splits, cut)
+
+
+def test_operands_through_registers_are_fetched_apart_where_that_is_faster(planner):
+    """The busiest CU has four workgroups, or three of an input gradient, and a long reduction; never for a weight gradient."""
+    apart = planner[2].apart
+    fwd, dgrad, wgrad = (1, 0), (1, 1), (0, 0)
+    for form, workgroups, ktiles, want in ((dgrad, 1024, 32, 1), (dgrad, 769, 20, 1), (dgrad, 769, 19, 0), (dgrad, 1025, 63, 0), (dgrad, 768, 32, 1), (dgrad, 513, 32, 1),
+                                           (dgrad, 768, 31, 0), (dgrad, 512, 63, 0), (fwd, 1024, 20, 1), (fwd, 769, 47, 1), (fwd, 768, 47, 0), (fwd, 1025, 47, 0),
+                                           (wgrad, 1024, 32, 0), (wgrad, 768, 63, 0), (dgrad, 1, 1, 0)):
+        assert apart(*form, workgroups, ktiles) == want, (form, workgroups, ktiles)
+    from test_gpu_gemm_ring import APART
+    for op, M, N, K in APART:
+        I, J, R = {"f": (M, N, K), "d": (M, K, N)}[op]
+        for ws in (0, 1):
+            tile, splits, per, cut = planner[1](I, J, R, ws, 0, 0, PLAIN)
+            if ws or op == "d" and K == 1409:                                # (without a workspace four workgroups on a CU are tiles of 128 x 128)
+                assert tile == 1 and bool(cut) == bool(ws) and apart(1, op == "d", -(-I // 64) * -(-J // 64) * splits, per), (op, M, N, K)

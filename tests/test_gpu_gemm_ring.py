@@ -172,3 +172,27 @@ def test_rows_too_far_apart_for_32_bit_offsets(ld):
         _, out = window(*shape, ld - shape[1], 0)
         call(out)
         assert np.array_equal(host16(out.contiguous()).astype(np.float64), want)
+
+
+# (forward or input gradient, M, N, K): three and four workgroups on the busiest CU over reductions that are long enough for the operands
+# to be fetched one after the other, whose last stage holds one element, all but one or about half of them, with the sums whole and in pieces
+# (test_gemm_plan.py checks that they are of this kind)
+APART = [("f", 2047, 2003, 1281), ("f", 1999, 1921, 1279), ("d", 1921, 1345, 2001), ("d", 1473, 2049, 1409), ("d", 1475, 2111, 1409)]
+
+
+@pytest.mark.parametrize("op,M,N,K", APART)
+@pytest.mark.parametrize("split", [False, True])
+def test_operands_fetched_one_after_the_other(op, M, N, K, split):
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    ints = lambda *s: torch.randint(-1, 2, s, device="cuda", generator=gen).to(torch.float16)  # noqa: E731
+    print(op, (M, N, K), split, flush=True)
+    w = ints(K, N)
+    if op == "f":
+        x, out = ints(M, K), torch.empty(M, N, device="cuda", dtype=torch.float16)
+        mpt.mpt_gemm_fwd(x, w, out, ws_for(0, M, N, K) if split else None)
+        want = x.float() @ w.float()
+    else:
+        g, out = ints(M, N), torch.empty(M, K, device="cuda", dtype=torch.float16)
+        mpt.mpt_gemm_dgrad(g, w, out, ws_for(1, M, N, K) if split else None)
+        want = g.float() @ w.float().t()
+    assert torch.equal(out.float(), want)
