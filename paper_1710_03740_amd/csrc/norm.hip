@@ -191,18 +191,20 @@ __global__ __launch_bounds__(kBlock) void k_bn_partial(BnShape s, const uint16_t
   }
 }
 
-// 16 channels per workgroup; 64 thread groups each sum a contiguous range of row blocks in block order, their results are added
+// 16 channels per workgroup; GROUPS thread groups each sum a contiguous range of row blocks in block order, their results are added
 // by eights in group order; then the closing arithmetic in FP64 and one rounding to FP32.  A few hundred kilobytes in a few
-// workgroups: bound by the latency of memory, so a thread has all its partials in flight at once (with 16 groups of eight in
-// flight 40000 x 40 took 9.0 us with its partial sums, 6.35 so, 12544 x 512 9.8 and 8.1, 200704 x 64 12.7 and 12.3).
-constexpr int kFinalizeThreads = 1024;
-template <int MODE>
-__global__ __launch_bounds__(kFinalizeThreads) void k_bn_finalize(BnShape s, const double* __restrict__ part, const uint16_t* __restrict__ x,
-                                                     float* __restrict__ out1, float* __restrict__ out2) {
-  __shared__ double red[64][2][16], red8[8][2][16];
+// workgroups: bound by the latency of memory.  A thread has up to eight partials of each sum in flight; sixteen are more than the
+// compiler keeps there, it sends them out a few at a time (statistics of 131072 x 64 with their partial sums, 512 row blocks, 10.7 us so and
+// 8.8; 200704 x 66 37.9 and 34.6).  64 groups from 129 row blocks on: 12544 x 512 (196) 9.2 us in 16, 8.0 in 64, 200704 x 64 (784) 11.7 in both.  16 groups up to
+// eight row blocks each, whose 48 wavefronts fewer start sooner: 1000 x 32 (2) 8.3 us in 64, 8.1 in 16, 16384 x 64 (64) 6.5 and 5.7, 40000 x 40 (100) 6.4 and 6.2.
+constexpr int kFewRowBlocks = 128;
+template <int MODE, int GROUPS>
+__global__ __launch_bounds__(GROUPS * 16) void k_bn_finalize(BnShape s, const double* __restrict__ part, const uint16_t* __restrict__ x,
+                                                             float* __restrict__ out1, float* __restrict__ out2) {
+  __shared__ double red[GROUPS][2][16], red8[GROUPS / 8][2][16];
   const int cl = threadIdx.x & 15, grp = threadIdx.x >> 4;
   const int c = blockIdx.x * 16 + cl;
-  const int per = (s.nblk + 63) / 64;
+  const int per = (s.nblk + GROUPS - 1) / GROUPS;
   const int b0 = grp * per, b1 = min(b0 + per, s.nblk);
   double t1 = 0.0, t2 = 0.0;
   auto add = [&](auto n, int b) {                 // so many blocks; one beyond the last is read as the last and left out
@@ -220,12 +222,12 @@ __global__ __launch_bounds__(kFinalizeThreads) void k_bn_finalize(BnShape s, con
   };
   if (c < s.C) {
     if (per <= 4) { if (b0 < b1) add(std::integral_constant<int, 4>{}, b0); }
-    else for (int b = b0; b < b1; b += 16) add(std::integral_constant<int, 16>{}, b);
+    else for (int b = b0; b < b1; b += 8) add(std::integral_constant<int, 8>{}, b);
   }
   red[grp][0][cl] = t1;
   red[grp][1][cl] = t2;
   __syncthreads();
-  if (threadIdx.x < 256) {                        // 8 eights x 2 sums x 16 channels
+  if (threadIdx.x < GROUPS * 4) {                 // eights x 2 sums x 16 channels
     const int eight = threadIdx.x >> 5, which = threadIdx.x >> 4 & 1;
     double t = 0.0;
 #pragma unroll
@@ -236,7 +238,7 @@ __global__ __launch_bounds__(kFinalizeThreads) void k_bn_finalize(BnShape s, con
   if (grp != 0 || c >= s.C) return;
   t1 = t2 = 0.0;
 #pragma unroll
-  for (int g = 0; g < 8; ++g) { t1 += red8[g][0][cl]; t2 += red8[g][1][cl]; }
+  for (int g = 0; g < GROUPS / 8; ++g) { t1 += red8[g][0][cl]; t2 += red8[g][1][cl]; }
   if constexpr (MODE == 0) {
     const double k = (double)(float)reinterpret_cast<const _Float16*>(x)[c];
     const double d1 = t1 / (double)s.P;
@@ -248,6 +250,13 @@ __global__ __launch_bounds__(kFinalizeThreads) void k_bn_finalize(BnShape s, con
     out1[c] = (float)t2;                          // dgamma
     out2[c] = (float)t1;                          // dbeta
   }
+}
+
+template <int MODE>
+void launch_finalize(hipStream_t st, const BnShape& s, const double* part, const uint16_t* x, float* out1, float* out2) {
+  const dim3 grid((s.C + 15) / 16);
+  if (s.nblk <= kFewRowBlocks) hipLaunchKernelGGL((k_bn_finalize<MODE, 16>), grid, dim3(256), 0, st, s, part, x, out1, out2);
+  else hipLaunchKernelGGL((k_bn_finalize<MODE, 64>), grid, dim3(1024), 0, st, s, part, x, out1, out2);
 }
 
 // Per-channel constants of a pointwise pass are formed once per workgroup (square root and divisions are tens of
@@ -409,13 +418,13 @@ extern "C" int mpt_bn_stats(void* stream, int64_t P, int64_t C, const uint16_t* 
     if (bn_stream(P, C)) hipLaunchKernelGGL((k_bn_partial<4, 0, true>), dim3(s.nblk, s.cgy), dim3(kBlock), 0, st, s, x, ldx, nullptr, 0, nullptr, nullptr, 0.f, part);
     else hipLaunchKernelGGL((k_bn_partial<4, 0, false>), dim3(s.nblk, s.cgy), dim3(kBlock), 0, st, s, x, ldx, nullptr, 0, nullptr, nullptr, 0.f, part);
     MPT_LAUNCH_CHECK();
-    hipLaunchKernelGGL((k_bn_finalize<0>), dim3((s.C + 15) / 16), dim3(kFinalizeThreads), 0, st, s, part, x, mean, var);
+    launch_finalize<0>(st, s, part, x, mean, var);
   } else {
     const BnShape s = bn_shape<1>(P, C);
     if (bn_stream(P, C)) hipLaunchKernelGGL((k_bn_partial<1, 0, true>), dim3(s.nblk, s.cgy), dim3(kBlock), 0, st, s, x, ldx, nullptr, 0, nullptr, nullptr, 0.f, part);
     else hipLaunchKernelGGL((k_bn_partial<1, 0, false>), dim3(s.nblk, s.cgy), dim3(kBlock), 0, st, s, x, ldx, nullptr, 0, nullptr, nullptr, 0.f, part);
     MPT_LAUNCH_CHECK();
-    hipLaunchKernelGGL((k_bn_finalize<0>), dim3((s.C + 15) / 16), dim3(kFinalizeThreads), 0, st, s, part, x, mean, var);
+    launch_finalize<0>(st, s, part, x, mean, var);
   }
   MPT_LAUNCH_CHECK();
   return MPT_OK;
@@ -464,13 +473,13 @@ extern "C" int mpt_bn_bwd_reduce(void* stream, int64_t P, int64_t C, const uint1
     if (bn_stream(P, C)) hipLaunchKernelGGL((k_bn_partial<4, 1, true>), dim3(s.nblk, s.cgy), dim3(kBlock), 0, st, s, x, ldx, dy, lddy, mean, var, eps, part);
     else hipLaunchKernelGGL((k_bn_partial<4, 1, false>), dim3(s.nblk, s.cgy), dim3(kBlock), 0, st, s, x, ldx, dy, lddy, mean, var, eps, part);
     MPT_LAUNCH_CHECK();
-    hipLaunchKernelGGL((k_bn_finalize<1>), dim3((s.C + 15) / 16), dim3(kFinalizeThreads), 0, st, s, part, x, dgamma, dbeta);
+    launch_finalize<1>(st, s, part, x, dgamma, dbeta);
   } else {
     const BnShape s = bn_shape<1>(P, C);
     if (bn_stream(P, C)) hipLaunchKernelGGL((k_bn_partial<1, 1, true>), dim3(s.nblk, s.cgy), dim3(kBlock), 0, st, s, x, ldx, dy, lddy, mean, var, eps, part);
     else hipLaunchKernelGGL((k_bn_partial<1, 1, false>), dim3(s.nblk, s.cgy), dim3(kBlock), 0, st, s, x, ldx, dy, lddy, mean, var, eps, part);
     MPT_LAUNCH_CHECK();
-    hipLaunchKernelGGL((k_bn_finalize<1>), dim3((s.C + 15) / 16), dim3(kFinalizeThreads), 0, st, s, part, x, dgamma, dbeta);
+    launch_finalize<1>(st, s, part, x, dgamma, dbeta);
   }
   MPT_LAUNCH_CHECK();
   return MPT_OK;

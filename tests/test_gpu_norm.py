@@ -174,3 +174,23 @@ def test_tensor_beyond_the_memory_side_cache():
     t = (dy[rows].astype(F) - b) - ((x[rows].astype(F) - m32) * invstd) * g
     want = fp16.rne16((a * t).astype(np.float64))
     assert np.array_equal(fp16.bits(host16(dx[torch.from_numpy(rows).cuda()])), fp16.bits(want))
+
+
+# Row blocks of 1024 rows at 16 channels: one, four and eight blocks to each of 16 groups of threads and one block more, four and eight to each of 64
+# and one more, with the last block whole or of a few rows
+@pytest.mark.parametrize("blocks,last", [(1, 1024), (16, 1), (17, 1024), (64, 1024), (65, 1), (128, 1024), (129, 1), (256, 1024), (257, 1), (512, 3), (513, 1024), (576, 5)])
+def test_row_blocks_of_the_reductions(blocks, last):
+    P, C, eps = (blocks - 1) * 1024 + last, 16, 1e-5
+    x, dy, _, _ = _data(P, C, blocks)
+    mean = torch.empty(C, dtype=torch.float32, device="cuda"); var = torch.empty_like(mean)
+    d_x, ws = dev16(x), _ws(P, C)
+    mpt.mpt_bn_stats(d_x, mean, var, ws)
+    m32, v32 = host(mean), host(var)
+    _check_stats(x, m32, v32)
+    dgamma = torch.empty_like(mean); dbeta = torch.empty_like(mean)
+    mpt.mpt_bn_bwd_reduce(d_x, dev16(dy), mean, var, eps, dgamma, dbeta, ws)
+    dg, db = norm.bn_bwd_reduce(x, dy, m32, v32, eps)
+    dy64 = dy.astype(np.float64)
+    xhat = (x.astype(np.float64) - m32.astype(np.float64)) * (F(1.0) / np.sqrt(v32 + F(eps))).astype(np.float64)
+    assert (np.abs(host(dbeta) - db) <= (CHAIN + 1) * U32 * np.abs(dy64).sum(axis=0) + U32 * np.abs(db) + 1e-30).all()
+    assert (np.abs(host(dgamma) - dg) <= (CHAIN + 4) * U32 * np.abs(dy64 * xhat).sum(axis=0) + U32 * np.abs(dg) + 1e-30).all()
