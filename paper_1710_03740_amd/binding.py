@@ -11,6 +11,7 @@ that leaves, all other accepted forms and every error, goes through the checks h
 import ctypes
 import importlib.util
 import os
+import warnings
 
 import torch
 
@@ -91,7 +92,7 @@ SIGNATURES = {
 }
 
 class _NotLoaded:
-    """Stands for the native calls until the library is loaded: each says that it has not made the call."""
+    """Stands for the native calls until the library is loaded, or where there are none: each says that it has not made the call."""
     def __getattr__(self, name):
         return lambda *args: None
 
@@ -100,23 +101,32 @@ _lib = None
 _native = _NotLoaded()
 
 
+def _native_calls(L):
+    """The native calls into L, or, with a warning, what stands for them: all calls then go through the checks here and ctypes."""
+    if not os.path.exists(CALLS_PATH):
+        warnings.warn("%s is not built (%s): small calls take twice as long; run `python -m paper_1710_03740_amd.build`"
+                      % (os.path.basename(CALLS_PATH), CALLS_PATH), RuntimeWarning, stacklevel=3)
+        return _NotLoaded()
+    spec = importlib.util.spec_from_file_location("_calls", CALLS_PATH)
+    calls = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(calls)
+    calls.bind({name: ctypes.cast(getattr(L, name), c_vp).value for name in SIGNATURES}, mpt_opt_params)
+    return calls
+
+
 def lib():
-    """Load libmpt.so and the native calls into it (once).  Raises if they have not been built."""
+    """Load libmpt.so and the native calls into it (once).  Raises if libmpt.so has not been built."""
     global _lib, _native
     if _lib is None:
-        for path in (LIB_PATH, CALLS_PATH):
-            if not os.path.exists(path):
-                raise RuntimeError("%s is not built (%s); run `python -m paper_1710_03740_amd.build`. "
-                                   "There is no fallback path." % (os.path.basename(path), path))
+        if not os.path.exists(LIB_PATH):
+            raise RuntimeError("libmpt.so is not built (%s); run `python -m paper_1710_03740_amd.build`. "
+                               "There is no fallback path." % LIB_PATH)
         L = ctypes.CDLL(LIB_PATH)
         for name, (res, args) in SIGNATURES.items():
             f = getattr(L, name)
             f.restype, f.argtypes = res, args
-        spec = importlib.util.spec_from_file_location("_calls", CALLS_PATH)
-        calls = importlib.util.module_from_spec(spec)
-        spec.loader.exec_module(calls)
-        calls.bind({name: ctypes.cast(getattr(L, name), c_vp).value for name in SIGNATURES}, mpt_opt_params)
-        _lib, _native = L, calls
+        _native = _native_calls(L)
+        _lib = L
     return _lib
 
 

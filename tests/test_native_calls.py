@@ -22,6 +22,31 @@ def test_host_tensors_subclasses_and_function_modes_are_left_to_the_python_check
     assert mpt._native.master_update_multi([], 1.0, 0.1, 0.9, None, None) is None
 
 
+@pytest.fixture
+def unloaded(monkeypatch):
+    """The binding as it is before its first call; as it was afterwards."""
+    monkeypatch.setattr(mpt, "_lib", None)
+    monkeypatch.setattr(mpt, "_native", mpt._NotLoaded())
+    return monkeypatch
+
+
+def _goes_on_through_the_checks():
+    assert mpt.mpt_version() > 0 and mpt._native.gemm_fwd(*[torch.zeros(8, 8, dtype=F16)] * 3, None) is None
+    with pytest.raises(ValueError, match="W: shape"):
+        mpt.mpt_gemm_fwd(torch.zeros(8, 8, dtype=F16), torch.zeros(7, 8, dtype=F16), torch.zeros(8, 8, dtype=F16))
+
+
+def test_a_library_without_the_native_calls_is_used_all_the_same(unloaded, tmp_path):
+    unloaded.setattr(mpt, "CALLS_PATH", str(tmp_path / "_calls.so"))
+    with pytest.warns(RuntimeWarning, match="_calls.so is not built"):
+        mpt.lib()
+    _goes_on_through_the_checks()
+    unloaded.setattr(mpt, "LIB_PATH", str(tmp_path / "libmpt.so"))
+    unloaded.setattr(mpt, "_lib", None)
+    with pytest.raises(RuntimeError, match="libmpt.so is not built"):
+        mpt.lib()
+
+
 def _calls():
     g = torch.Generator(device="cuda")
     g.manual_seed(5)
