@@ -101,15 +101,25 @@ _lib = None
 _native = _NotLoaded()
 
 
+def torch_build():
+    """The torch that runs, as the native calls know the one that they were compiled against."""
+    return "%s %s" % (torch.__version__, torch.version.git_version)
+
+
 def _native_calls(L):
     """The native calls into L, or, with a warning, what stands for them: all calls then go through the checks here and ctypes."""
-    if not os.path.exists(CALLS_PATH):
-        warnings.warn("%s is not built (%s): small calls take twice as long; run `python -m paper_1710_03740_amd.build`"
-                      % (os.path.basename(CALLS_PATH), CALLS_PATH), RuntimeWarning, stacklevel=3)
+    try:
+        if not os.path.exists(CALLS_PATH):
+            raise ImportError("is not built (%s)" % CALLS_PATH)
+        spec = importlib.util.spec_from_file_location("_calls", CALLS_PATH)
+        calls = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(calls)
+        if getattr(calls, "torch", None) != torch_build():
+            raise ImportError("is built for torch %s, this is %s" % (getattr(calls, "torch", "of another kind"), torch_build()))
+    except ImportError as e:                     # (the loader's own, too: symbols that another torch lacks)
+        warnings.warn("%s %s: small calls take twice as long; run `python -m paper_1710_03740_amd.build`" % (os.path.basename(CALLS_PATH), e),
+                      RuntimeWarning, stacklevel=3)
         return _NotLoaded()
-    spec = importlib.util.spec_from_file_location("_calls", CALLS_PATH)
-    calls = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(calls)
     calls.bind({name: ctypes.cast(getattr(L, name), c_vp).value for name in SIGNATURES}, mpt_opt_params)
     return calls
 

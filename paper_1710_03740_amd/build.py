@@ -29,12 +29,13 @@ def _calls_command():
     """The extension module that unpacks torch's tensors: host code against the installed torch's headers."""
     import torch
     from torch.utils import cpp_extension
+    from . import binding
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
-    inc = [INCLUDE, *cpp_extension.include_paths(), os.path.join(rocm, "include"), sysconfig.get_path("include")]
+    inc = [*cpp_extension.include_paths(), os.path.join(rocm, "include"), sysconfig.get_path("include")]
     lib = os.path.join(os.path.dirname(torch.__file__), "lib")
-    return (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
-             "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI]
-            + ["-I" + d for d in inc] + [os.path.join(CSRC, "calls.cpp"), "-o", CALLS, "-L" + lib, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"])
+    return (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+             "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, '-DMPT_TORCH="%s"' % binding.torch_build(), "-I" + INCLUDE]
+            + ["-isystem" + d for d in inc] + [os.path.join(CSRC, "calls.cpp"), "-o", CALLS, "-L" + lib, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"])
 
 
 def _run(cmd):

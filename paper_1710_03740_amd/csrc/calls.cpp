@@ -405,4 +405,10 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_calls", nullptr, -1, methods, nul
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__calls(void) { return PyModule_Create(&module); }
+// `torch`: the torch whose headers this was compiled against, from the build.  The tensors' fields are read by inlined code, at places that
+// another torch may have elsewhere: the binding compares before it calls anything here.
+PyMODINIT_FUNC PyInit__calls(void) {
+  PyObject* m = PyModule_Create(&module);
+  if (m != nullptr && PyModule_AddStringConstant(m, "torch", MPT_TORCH) != 0) Py_CLEAR(m);
+  return m;
+}

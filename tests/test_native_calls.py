@@ -47,6 +47,20 @@ def test_a_library_without_the_native_calls_is_used_all_the_same(unloaded, tmp_p
         mpt.lib()
 
 
+def test_native_calls_of_another_torch_are_left_alone(unloaded, tmp_path):
+    """Compiled against other headers they could read a tensor's fields elsewhere."""
+    unloaded.setattr(mpt.torch.version, "git_version", "0" * 40)
+    with pytest.warns(RuntimeWarning, match="_calls.so is built for torch .*, this is .* 0{40}"):
+        mpt.lib()
+    _goes_on_through_the_checks()
+    unloaded.setattr(mpt, "_lib", None)
+    unloaded.setattr(mpt, "CALLS_PATH", str(tmp_path / "_calls.so"))
+    (tmp_path / "_calls.so").write_bytes(b"no shared object")
+    with pytest.warns(RuntimeWarning, match="_calls.so .*too short"):
+        mpt.lib()
+    _goes_on_through_the_checks()
+
+
 def _calls():
     g = torch.Generator(device="cuda")
     g.manual_seed(5)
