@@ -4,6 +4,7 @@ Run as `python -m paper_1710_03740_amd.build`.  hipcc cross-compiles without a
 GPU.  Both are built in-tree so that they travel with the source tree.
 """
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -23,6 +24,20 @@ CXX_SOURCES = ["host.cpp"]
 HIP_FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-ffp-contract=off",
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
              "-Wno-unused-command-line-argument", "-I", INCLUDE, "-I", CSRC]
+
+
+def _calls_missing():
+    """What it takes to compile the native calls and is not here, or None.  The library itself needs hipcc only."""
+    if shutil.which("g++") is None:
+        return "g++"
+    try:
+        from torch.utils import cpp_extension
+    except ImportError:
+        return "torch"
+    for header in ("torch/csrc/autograd/python_variable.h", "Python.h"):
+        if not any(os.path.exists(os.path.join(d, header)) for d in (*cpp_extension.include_paths(), sysconfig.get_path("include"))):
+            return header
+    return None
 
 
 def _calls_command():
@@ -63,10 +78,16 @@ def build(verbose=True):
         if verbose:
             print("[mpt build]", src, flush=True)
         procs.append((cmd, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
-    cmd = _calls_command()
-    if verbose:
-        print("[mpt build] calls.cpp", flush=True)
-    procs.append((cmd, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    missing = _calls_missing()
+    if missing is None:
+        cmd = _calls_command()
+        if verbose:
+            print("[mpt build] calls.cpp", flush=True)
+        procs.append((cmd, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    else:
+        print("[mpt build] no %s here: without %s, calls go through ctypes" % (missing, os.path.basename(CALLS)), flush=True)
+        if os.path.exists(CALLS):
+            os.remove(CALLS)                      # it may know another library's entry points
     for cmd, p in procs:
         out, _ = p.communicate()
         out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l)
@@ -76,7 +97,7 @@ def build(verbose=True):
             print(out)
     _run([hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB] + objs)
     if verbose:
-        print("[mpt build] wrote", LIB, CALLS, flush=True)
+        print("[mpt build] wrote", LIB, *([CALLS] if missing is None else []), flush=True)
     return LIB
 
 

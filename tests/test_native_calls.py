@@ -61,6 +61,32 @@ def test_native_calls_of_another_torch_are_left_alone(unloaded, tmp_path):
     _goes_on_through_the_checks()
 
 
+def test_the_library_is_built_where_the_native_calls_cannot_be(monkeypatch, tmp_path):
+    from paper_1710_03740_amd import build
+    commands = []
+
+    class Compiler:
+        returncode = 0
+
+        def __init__(self, cmd, **_):
+            commands.append(cmd)
+
+        def communicate(self):
+            return "", None
+    monkeypatch.setattr(build.subprocess, "Popen", Compiler)
+    monkeypatch.setattr(build, "_run", commands.append)
+    monkeypatch.setattr(build, "CALLS", str(tmp_path / "_calls.so"))
+    for there in (True, False):
+        (tmp_path / "_calls.so").write_bytes(b"of an earlier build")
+        commands.clear()
+        if not there:
+            which = build.shutil.which
+            monkeypatch.setattr(build.shutil, "which", lambda name: None if name == "g++" else which(name))
+        assert build._calls_missing() == (None if there else "g++")
+        assert build.build(verbose=False) == build.LIB and commands[-1][-1].endswith("host.cpp.o") and build.LIB in commands[-1]
+        assert any(c[0] == "g++" for c in commands) == there == (tmp_path / "_calls.so").exists()
+
+
 def _calls():
     g = torch.Generator(device="cuda")
     g.manual_seed(5)
