@@ -99,16 +99,15 @@ T gradient(PyObject* o, int* fp32) {
   *fp32 = t.type() == at::kFloat;
   return t;
 }
-float number(PyObject* o) {
-  if (PyFloat_CheckExact(o)) return (float)PyFloat_AS_DOUBLE(o);
-  want(PyLong_CheckExact(o));
-  const double d = PyLong_AsDouble(o);
+float number(PyObject* o) {                                          // what has a value as a float, as ctypes takes it: numpy's classes too
+  const double d = PyFloat_AsDouble(o);
   want(!(d == -1.0 && PyErr_Occurred()));
   return (float)d;
 }
 int truth(PyObject* o) {
-  want(o == Py_True || o == Py_False);
-  return o == Py_True;
+  const int t = PyObject_IsTrue(o);
+  want(t >= 0);
+  return t;
 }
 
 // ---------------------------------------------------------------- the call

@@ -1,5 +1,7 @@
 """The binding's native calls: what they take ends as it does through the Python checks, bit for bit, and what is not plainly
 as it should be is left to those (None)."""
+import ctypes
+
 import pytest
 import torch
 
@@ -184,3 +186,32 @@ def test_errors_and_unusual_forms_end_as_they_did():
     with pytest.raises(mpt.MptError, match="mpt_gemm_fwd failed: -4"):      # workspace too small: the library's own answer
         mpt.mpt_gemm_fwd(torch.zeros(64, 8192, device="cuda", dtype=F16), torch.zeros(8192, 64, device="cuda", dtype=F16), Y, torch.zeros(4, device="cuda"))
     mpt.mpt_gemm_fwd(X.as_subclass(Sub), W, Y)
+
+
+@pytest.mark.gpu
+def test_numbers_and_switches_of_any_class_go_the_native_way(monkeypatch):
+    """A learning rate or a scale out of numpy, a switch that is a number: what ctypes and Python's `if` take."""
+    import numpy as np
+
+    class Scale(float):
+        def __float__(self):                                               # neither way asks for this
+            return 3.0
+    mpt.lib()
+    native, g = mpt._native, torch.arange(64, device="cuda").to(F16)
+    for x in (0.1, np.float64(0.1), Scale(0.1), np.float32(0.1), 1, True, np.int64(2), torch.tensor(0.1)):
+        out, want, fl = torch.zeros(64, device="cuda"), torch.zeros(64, device="cuda"), torch.zeros(1, device="cuda", dtype=I32)
+        assert native.unscale_check(g, x, fl, out) == 0, type(x)
+        with monkeypatch.context() as m:
+            m.setattr(mpt, "_native", mpt._NotLoaded())
+            mpt.mpt_unscale_check(g, x, fl, want)
+        assert torch.equal(out.view(I32), want.view(I32)) and float(out[10]) > 0
+    assert native.unscale_check(g, np.float64(1e300), fl, out) == native.unscale_check(g, 1e300, fl, out) != 0     # infinite in 32 bits: refused
+    for x in ("0.1", None, 10 ** 400, [0.1]):                              # left to the checks and ctypes, which say why
+        assert native.unscale_check(g, x, fl, out) is None, type(x)
+        with pytest.raises((TypeError, ctypes.ArgumentError)):
+            mpt.mpt_unscale_check(g, x, fl, out)
+    X, W = torch.ones(64, 64, device="cuda", dtype=F16), torch.zeros(64, 64, device="cuda")
+    for switch, sum_ in ((0, 64), (1, 128), (np.bool_(True), 192), ("yes", 256), (None, 64)):
+        assert native.gemm_wgrad(X, X, W, switch, None, None) == 0
+        assert bool((W == sum_).all()), switch
+    assert native.gemm_wgrad(X, X, W, np.zeros(2), None, None) is None    # neither true nor false
