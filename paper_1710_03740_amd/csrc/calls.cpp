@@ -3,8 +3,8 @@
 //
 // In Python a product's checks, its twelve ctypes arguments and the stream took 3.5 us beside the 3.5 us of the launch itself, and
 // the small passes are bound by what issues their launches (a two-layer step, 256 x 1024-1024-10: 60 us of host time for 40 us
-// of kernels).  Here they take about half a microsecond: the step's nine launches are issued in 28 us, and it takes 41.5 us
-// instead of 58.7.
+// of kernels).  Here they take about half a microsecond: the step's launches, nine then, were issued in 28 us, and it took 41.5 us
+// instead of 58.7 (eight launches now, 39.5 us).
 //
 // A function returns the status of its entry point, or None where anything is not plainly as it should be: another type or
 // shape, a tensor subclass, an active torch function mode, a host tensor, the library not loaded yet.  The caller then goes

@@ -1448,8 +1448,9 @@ bool try_launch_dma(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, boo
     hipLaunchKernelGGL(k64, dim3(grid), dim3(256), 4 * 32768, s, DmaMat{A.base, A.ld}, DmaMat{B.base, B.ld}, pb, ep);
   } else if (ep.mode != 0 && depth32_f32 == 0 && pl.ktiles_per_split >= 8) {
     // FP32 outputs (store, accumulate, split partials; 16 bytes per lane, checked above) on the same kernel, unless
-    // the reduction is short: over 4 stages k_gemm_dma's two wavefronts per SIMD cover the fill and the write-out of
-    // each other (projection weight gradient 8192 x 1024 x 256, accumulated: 24.5 us there, 28.4 us here)
+    // the reduction is short: there k_gemm_dma's two wavefronts per SIMD cover the fill and the write-out of each other, which counts
+    // where old values are read too (3072 x 4096 over 256, accumulated: 26.3 us there, 29.9 here; 4096 x 4096 29.6 and 31.4; only stored
+    // 19.2 and 18.2, 20.0 and 20.3)
     hipLaunchKernelGGL(k64f, dim3(grid), dim3(256), 4 * 32768, s, DmaMat{A.base, A.ld}, DmaMat{B.base, B.ld}, pb, ep);
   } else {
     hipLaunchKernelGGL(k4, dim3(grid), dim3(512), 4 * 32768, s, DmaMat{A.base, A.ld}, DmaMat{B.base, B.ld}, pb, ep);

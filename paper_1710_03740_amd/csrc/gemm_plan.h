@@ -156,8 +156,9 @@ inline RingPlan ring_plan(const Plan& pl, int64_t I, int64_t J, int64_t R, bool 
 
 // Whole-tile products that one launch of the streamed kernels could take, but that the ring kernels' smaller tiles take in less time
 // (both sides measured over reductions of 64 .. 4096; the sums are the same).
-// FP32 outputs in tiles of 256 x 256: where these occupy half the chip (8192 x 1024 over 64 accumulated 20.4 -> 11.8 us, over 256
-// stored 18.5 -> 12.6, over 4096 79.6 -> 69.4; at 192 tiles over 256 18.6 against 19.0, over 1024 32.1 against 37.9), and adding to FP32
+// FP32 outputs in tiles of 256 x 256: where these occupy half the chip, which is 128 of them (fewer are not planned unsplit; with a workspace
+// neither are 128 over four stages and more), 8192 x 1024 over 64 accumulated 20.4 -> 11.8 us, over 256 stored 18.5 -> 12.6, over 4096 79.6 -> 69.4;
+// at 192 tiles over 256 18.6 against 19.0, over 1024 32.1 against 37.9, and the counts between are not measured.  And adding to FP32
 // values over two rounds of tiles or more, whose reads wait in the smaller tiles' shadow (16384 x 4096 over 64 124 -> 102 us,
 // over 1024 231 -> 210, over 2048 322 against 339).
 inline bool ring_for_fp32(int64_t tiles256, int64_t ktiles, bool accumulate) {
@@ -181,8 +182,9 @@ inline bool operands_apart(bool a_rc, bool b_rc, int64_t workgroups, int ktiles)
 // Convolutions (forward and input gradient) that k_conv_patch takes: a filter of at most 64 x 64 channels, rows of which two patches
 // and the outputs fit LDS, and pixels for half the CUs: 32768 of them (128 tiles) with 64 channels 13.3 -> 9.8 us, where the ring kernels
 // still work unsplit.  Measured at 23 sizes of 8 .. 64 channels: 0.67 to 1.0 of the ring kernels' time.
+constexpr int64_t kPatchWidth = 120;
 inline bool conv_in_patches(int64_t Nb, int64_t H, int64_t W, int64_t C, int64_t Kf) {
-  return C <= 64 && Kf <= 64 && W <= 120 && Nb * H * W >= 128 * kCUs;
+  return C <= 64 && Kf <= 64 && W <= kPatchWidth && Nb * H * W >= 128 * kCUs;
 }
 
 }  // namespace mpt_gemm

@@ -544,8 +544,8 @@ __device__ __forceinline__ void store_tile(const Problem& pb, const Epilogue& ep
           }
       }
     };
-    // Adding to what is there: 16 reads in flight (16 KiB a wavefront).  Two at a time, as the stores go out, were most of a short reduction's
-    // time (8192 x 1024 over 256 accumulated 20.0 -> 17.2 us; 14.2 without reading).
+    // Adding to what is there: up to 16 reads in flight, all of a 64 x 64 block (16 KiB a wavefront), the 4 or 8 of smaller ones.  Two at a
+    // time, as the stores go out, were most of a short reduction's time (8192 x 1024 over 256 accumulated 20.0 -> 17.2 us; 14.2 without reading).
     if (ep.mode == 2) {
       constexpr int AHEAD = 16 < IT ? 16 : IT;
 #pragma unroll 1
@@ -723,7 +723,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     db.store(s, q.b, st + A_BYTES + wave * (LB * 1024));
   };
   // The first two stages are fetched together: one after the other a
-  // short reduction waited for memory twice before its first product (500 x 300 over 100 as input gradient 6.5 -> 5.7 us, 256 x 10 over 1024 7.9 -> 7.4).
+  // short reduction waited for memory twice before its first product (100 x 500 over 300 as input gradient 6.5 -> 5.7 us, 256 x 10 over 1024 7.9 -> 7.4).
   Stage next_in;
   {
     Stage second;
@@ -808,9 +808,10 @@ struct PatchConv {
   FastDiv dHW, dW;
 };
 constexpr int kPatchPixels = 256, kFilterBytes = 9 * 64 * 128;
-inline int patch_rows(int64_t W) { return (int)((kPatchPixels + 2 * (W + 1) + 7) / 8 * 8); }
+constexpr int patch_rows(int64_t W) { return (int)((kPatchPixels + 2 * (W + 1) + 7) / 8 * 8); }
 // zeros | pixels | pixels | outputs; the filter comes in where the second pixels and the outputs will be
-inline int patch_lds_bytes(int rows) { return 128 + rows * 128 + std::max(rows * 128 + 4 * 8192, kFilterBytes); }
+constexpr int patch_lds_bytes(int rows) { return 128 + rows * 128 + std::max(rows * 128 + 4 * 8192, kFilterBytes); }
+static_assert(patch_lds_bytes(patch_rows(kPatchWidth)) <= 163840, "the widest rows' patches and outputs fit LDS");
 
 // The filter's fragments of one half tap, waited for where they are read: 288 registers are more than the vector half of the file, and the
 // compiler moves them over as soon as it takes them to be there.

@@ -14,13 +14,16 @@ SOURCE = r"""
 using namespace mpt_gemm;
 extern "C" void planned(long I, long J, long R, int ws, int* out) {
   const Plan p = make_plan(I, J, R, ws != 0);
-  out[0] = p.splits; out[1] = p.ktiles_per_split;
+  out[0] = p.splits; out[1] = p.ktiles_per_split; out[2] = p.big;
 }
 extern "C" void ring(long I, long J, long R, int ws, int whole_chunks, int lines, int conv, int* out) {
   const Plan p = make_plan(I, J, R, ws != 0);
   const RingPlan r = ring_plan(p, I, J, R, whole_chunks != 0, lines != 0, conv == 3, conv == 2, conv == 1);
   out[0] = r.tile; out[1] = r.splits; out[2] = r.ktiles_per_split; out[3] = r.cut;
 }
+extern "C" int fp32_ring(long tiles256, long ktiles, int accumulate) { return ring_for_fp32(tiles256, ktiles, accumulate != 0); }
+extern "C" int fp16_ring(long tiles128, long ktiles) { return ring_for_fp16(tiles128, ktiles); }
+extern "C" int patches(long Nb, long H, long W, long C, long Kf) { return conv_in_patches(Nb, H, W, C, Kf); }
 extern "C" int apart(int a_rc, int b_rc, long workgroups, int ktiles) { return operands_apart(a_rc != 0, b_rc != 0, workgroups, ktiles); }
 """
 PLAIN, CONV_ROWS, CONV_WGRAD, ACCUMULATE = 0, 1, 2, 3
@@ -43,6 +46,9 @@ def planner(tmp_path_factory):
         out = (ctypes.c_int * 4)()
         f(*args, ctypes.addressof(out))
         return tuple(out)
+    L.fp32_ring.argtypes = [ctypes.c_long, ctypes.c_long, ctypes.c_int]
+    L.fp16_ring.argtypes = [ctypes.c_long] * 2
+    L.patches.argtypes = [ctypes.c_long] * 5
     L.apart.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_long, ctypes.c_int]
     return lambda *a: call(L.planned, *a)[:2], lambda *a: call(L.ring, *a), L
 
@@ -166,3 +172,29 @@ def test_operands_through_registers_are_fetched_apart_where_that_is_faster(plann
             tile, splits, per, cut = planner[1](I, J, R, ws, 0, 0, PLAIN)
             if ws or op == "d" and K == 1409:                                # (without a workspace four workgroups on a CU are tiles of 128 x 128)
                 assert tile == 1 and bool(cut) == bool(ws) and apart(1, op == "d", -(-I // 64) * -(-J // 64) * splits, per), (op, M, N, K)
+
+
+def test_whole_tiles_that_smaller_tiles_take_in_less_time(planner):
+    """FP32 outputs of half the chip's tiles of 256 x 256, or added to over two rounds of them; FP16 outputs of few tiles of 128 x 256."""
+    fp32, fp16 = planner[2].fp32_ring, planner[2].fp16_ring
+    for tiles, ktiles, accumulate, want in ((128, 1, 0, 1), (128, 64, 1, 1), (128, 65, 0, 0), (129, 4, 0, 0), (192, 4, 1, 0), (511, 1, 1, 0), (512, 16, 1, 1),
+                                            (512, 17, 1, 0), (512, 16, 0, 0)):
+        assert fp32(tiles, ktiles, accumulate) == want, (tiles, ktiles, accumulate)
+    for tiles, ktiles, want in ((96, 16, 1), (96, 17, 0), (128, 12, 1), (128, 13, 0), (129, 4, 1), (129, 5, 0), (255, 4, 1), (256, 4, 0)):
+        assert fp16(tiles, ktiles) == want, (tiles, ktiles)
+    # what the first clause for FP32 outputs reaches: planned unsplit, in tiles of 256 x 256, half the chip's count is the least there is
+    for I, J, R in shapes(3000) + [(8192, 1024, 192), (8192, 1024, 256), (4096, 2048, 64)]:
+        tiles = -(-I // 256) * -(-J // 256)
+        for ws in (0, 1):
+            big = (ctypes.c_int * 4)()
+            planner[2].planned(I, J, R, ws, ctypes.addressof(big))
+            if big[2] and big[0] == 1:
+                assert tiles >= 128 and not (ws and tiles == 128 and R > 192)
+
+
+def test_convolutions_taken_in_patches(planner):
+    """At most 64 channels each way, rows of at most 120 pixels, half the CUs' tiles of 256 pixels."""
+    patches = planner[2].patches
+    for shape, want in (((32768, 1, 1, 8, 8), 1), ((32767, 1, 1, 8, 8), 0), ((64, 56, 56, 64, 64), 1), ((64, 56, 56, 72, 64), 0), ((64, 56, 56, 64, 72), 0),
+                        ((3, 95, 120, 64, 56), 1), ((3, 95, 121, 64, 56), 0), ((32768, 1, 1, 64, 64), 1)):
+        assert patches(*shape) == want, shape

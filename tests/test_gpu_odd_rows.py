@@ -99,6 +99,13 @@ def test_lstm_cell_has_the_same_bits_singly_and_in_fours(B, H, pad, offset):
         assert bool((buf == 7.0).all())
 
 
+# More than the memory-side cache holds (205 MB, more than 192 MiB), in rows so short (276 threads where two workgroups have 512) that threads are
+# dealt over the rows one after the other; a cell left over in each row
+@pytest.mark.parametrize("pad,offset", [(0, 0), (5, 2)])
+def test_lstm_cell_streamed_over_short_rows(pad, offset):
+    test_lstm_cell_has_the_same_bits_singly_and_in_fours(6200, 1101, pad, offset)
+
+
 @pytest.mark.parametrize("n", [1, 7, 8, 9, 2047, 4099])
 @pytest.mark.parametrize("offset", [0, 1, 3])
 def test_pointwise_glue(n, offset):
