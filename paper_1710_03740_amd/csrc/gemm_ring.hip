@@ -690,8 +690,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // pieces of stage s + 2 are written into the slot that stage s has left, and those of stage s + 3 are loaded.  What bounds it is the
 // rate of the loads: a row's 128 bytes lie in two cache lines (1001 x 1999 over 1503: 16 of its 22 us for them alone, 7.5 if rows started
 // on lines), so further stages in flight give nothing (two sets of registers: 24.4 us).
-template <class AOp, class BOp, int BM, int BN, int WM, int WN, bool CUT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_any(RingMatSrc A, RingMatSrc B, Problem pb, Epilogue ep, int cut, bool apart) {
+// APART: the second operand of a stage is fetched when the first is there (operands_apart).
+template <class AOp, class BOp, int BM, int BN, int WM, int WN, bool CUT, bool APART>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_any(RingMatSrc A, RingMatSrc B, Problem pb, Epilogue ep, int cut) {
   static_assert((BM / WM) * (BN / WN) == 4, "four wavefronts");
   constexpr int FM = WM / 16, FN = WN / 16, A_BYTES = BM * 128, STAGE = (BM + BN) * 128, LA = AOp::NB, LB = BOp::NB;
   static_assert(2 * STAGE >= 4 * WM * WN * 4, "the store's buffers fit the slots");
@@ -713,7 +714,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   auto load = [&](int s, Stage& q) {
     if (s >= nst) return;
     da.load(s, q.a);
-    if (AOp::kRC && BM == 64 && s >= 3 && apart) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // operands_apart
+    if (APART && s >= 3) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     db.load(s, q.b);
   };
   auto store = [&](int s, const Stage& q) {
@@ -982,13 +983,19 @@ int launch_any(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, RingTile
   const dim3 grid((unsigned)((int64_t)pb.tiles_i * pb.tiles_j * pb.splits));
   if constexpr (!CUT) {                                              // the cut sums of 128 x 128 tiles through registers would not fit the register file
     if (tile != kRing64x64) {
-      hipLaunchKernelGGL((k_gemm_any<RegMat<A_RC, 128, ANY>, RegMat<B_RC, 128, ANY>, 128, 128, 64, 64, false>), grid, dim3(256), 2 * 256 * 128, s, A, B, pb, ep, 0, false);
+      hipLaunchKernelGGL((k_gemm_any<RegMat<A_RC, 128, ANY>, RegMat<B_RC, 128, ANY>, 128, 128, 64, 64, false, false>), grid, dim3(256), 2 * 256 * 128, s, A, B, pb, ep, 0);
       MPT_LAUNCH_CHECK();
       return MPT_OK;
     }
   }
-  hipLaunchKernelGGL((k_gemm_any<RegMat<A_RC, 64, ANY>, RegMat<B_RC, 64, ANY>, 64, 64, 32, 32, CUT>), grid, dim3(256), 2 * 128 * 128, s, A, B, pb, ep, cut,
-                     operands_apart(A_RC, B_RC, grid.x, pb.ktiles_per_split));
+  if constexpr (A_RC && !ANY) {
+    if (operands_apart(A_RC, B_RC, grid.x, pb.ktiles_per_split)) {
+      hipLaunchKernelGGL((k_gemm_any<RegMat<A_RC, 64, ANY>, RegMat<B_RC, 64, ANY>, 64, 64, 32, 32, CUT, true>), grid, dim3(256), 2 * 128 * 128, s, A, B, pb, ep, cut);
+      MPT_LAUNCH_CHECK();
+      return MPT_OK;
+    }
+  }
+  hipLaunchKernelGGL((k_gemm_any<RegMat<A_RC, 64, ANY>, RegMat<B_RC, 64, ANY>, 64, 64, 32, 32, CUT, false>), grid, dim3(256), 2 * 128 * 128, s, A, B, pb, ep, cut);
   MPT_LAUNCH_CHECK();
   return MPT_OK;
 }

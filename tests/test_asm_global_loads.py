@@ -39,4 +39,4 @@ def test_loads_of_rows_at_any_address_claim_the_alignment_of_their_elements(tmp_
         for ty, align in re.findall(r"= load (<\d+ x \w+>), ptr addrspace\(1\) .*?align (\d+)", m.group(0)):
             wide += 1
             assert int(align) <= (4 if "float" in ty else 2), "%s: load %s, align %s" % (m.group(1), ty, align)
-    assert kernels == 18 and wide >= 16 * kernels         # 3 operand layouts; 64 x 64 tiles, with and without cuts, and 128 x 128; ordinary extents or any
+    assert kernels == 22 and wide >= 16 * kernels         # 3 operand layouts; 64 x 64 tiles, with and without cuts, and 128 x 128; ordinary extents or any; 4 with operands apart
