@@ -130,6 +130,9 @@ struct RingMatSrc { const uint16_t* base; int64_t ld; int O, R; };
 // sums in pieces of so many tiles of 64, added in order.
 int launch_ring_plain(hipStream_t s, bool a_rc, bool b_rc, const RingMatSrc& A, const RingMatSrc& B, bool whole_chunks, RingTile tile,
                       int ktiles_per_split, int cut, int I, int J, int R, const Epilogue& ep);
+// The same in 32 x 32 tiles whose `pieces` pieces of `piece` tiles of 64 are summed side by side (pieces_side_by_side); no partials (mode 3).
+int launch_pieces_plain(hipStream_t s, bool a_rc, bool b_rc, const RingMatSrc& A, const RingMatSrc& B, bool whole_chunks, int piece, int pieces, int I, int J, int R,
+                        const Epilogue& ep);
 // The three passes of the 3x3 convolution (op: MPT_OP_*): x[Nb,H,W,C], w[Kf,3,3,C], y / dy[Nb,H,W,Kf]; `cut` as above.
 int launch_ring_conv(hipStream_t s, int op, int64_t Nb, int64_t H, int64_t W, int64_t C, int64_t Kf, const uint16_t* img, const uint16_t* other,
                      RingTile tile, int ktiles_per_split, int cut, const Epilogue& ep);

@@ -37,7 +37,8 @@ __device__ __forceinline__ void static_for(F&& f) { static_for_each(f, std::make
 // unit positions and rows 1, 3, 9, 11 again.
 template <int BO>
 __device__ __forceinline__ int ring_key(int r) {
-  if constexpr (BO == 64) return ((r >> 1) & 1) | ((r >> 2) & 2);
+  if constexpr (BO == 32) return (r >> 3) & 1;
+  else if constexpr (BO == 64) return ((r >> 1) & 1) | ((r >> 2) & 2);
   else return oc_key(r);
 }
 
@@ -46,9 +47,9 @@ __device__ __forceinline__ int ring_key(int r) {
 // NB of them, lane l the 16 bytes at block + 16 l.  Which piece that is makes the LDS layout:
 //   RC: 8 rows of 128 bytes per block, one cache line each; 16-byte piece c of row o sits at piece c ^ ((o >> 1) & 7);
 //   OC: 512 / BO reduction rows per block; 32-byte unit u of row r sits at unit u ^ ring_key(r).
-template <bool RC, int BO>
+template <bool RC, int BO, int WAVES = 4>
 struct Piece {
-  static constexpr int NB = BO / 32;
+  static constexpr int NB = BO / 8 / WAVES;
   static constexpr int RPB = RC ? 8 : 512 / BO, LPR = 64 / RPB;
   // row inside the stage (RC: outer, OC: reduction) and first element of the piece along the row, of block k
   __device__ static __forceinline__ int row(int wave, int lane, int k) { return (wave * NB + k) * RPB + lane / LPR; }
@@ -79,10 +80,10 @@ __device__ __forceinline__ int here_only(int v) {
 // moves with the stage and a 32-bit lane offset.  (With a 64-bit address and a select per load the vector units had as much
 // to do as the matrix cores: 2000 x 3000 over 1000 took 24 us.)  The last, ragged stage and row strides too long for 32-bit offsets
 // form the whole address.
-template <bool RC, int BO>
+template <bool RC, int BO, int WAVES = 4>
 struct RingMat {
   typedef RingMatSrc Src;
-  typedef Piece<RC, BO> P;
+  typedef Piece<RC, BO, WAVES> P;
   static constexpr bool kRC = RC;
   static constexpr int NB = P::NB;
   const char* base;                // of the tile, stage 0 (wavefront-uniform)
@@ -277,6 +278,7 @@ struct RingImgOC {
 // shifted down.  Rows of fewer than 8 elements are gathered element by element.
 typedef uint32_t uint4u __attribute__((ext_vector_type(4), aligned(2)));
 typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t uint2u __attribute__((ext_vector_type(2), aligned(2)));
 
 // Drops the first `n` (0 .. 7) of 8 elements; zeros follow the others.  In 32-bit operations: a 64-bit shift whose amount lies in the last
 // register that a wavefront has been given, one of number 7 modulo 8, now and then takes its amount from elsewhere (a kernel of
@@ -306,10 +308,10 @@ __device__ __forceinline__ uint16_t one_from_global(const void* p) { return *(co
 
 // ANY: also rows of fewer than 8 elements, gathered element by element, and row strides too long for 32-bit offsets; kept apart, since
 // their branches around the loads cost the others a tenth (3999 x 1777 over 999 51 against 47 us).
-template <bool RC, int BO, bool ANY>
+template <bool RC, int BO, bool ANY, int WAVES = 4>
 struct RegMat {
   typedef RingMatSrc Src;
-  typedef Piece<RC, BO> P;
+  typedef Piece<RC, BO, WAVES> P;
   static constexpr bool kRC = RC;
   static constexpr int NB = P::NB;
   static constexpr int kFront = RC ? 128 : 8;
@@ -824,6 +826,201 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   store_tile<FM, FN>(pb, ep, sp, i0 + wm * WM, j0 + wn * WN, lane, acc, lds + wave * (WM * WN * 4));
 }
 
+// ---------------------------------------------------------------- few tiles: the pieces of a sum side by side
+// Outputs of few tiles whose sums are cut into pieces (gemm_plan.h).  Every wavefront of a workgroup multiplies one whole 32 x 32 tile over
+// a piece of its own, with its own slots of LDS and no barrier, and the workgroup adds the pieces up in order at the end: the sums
+// of the split reduction in one launch.  What bounds such a product is not the work but the chain: start, first fetch, one stage
+// after another, store.  The small tile gives four times the workgroups of a 64 x 64 one, the wavefronts side by side a chain of 2 to 4 stages
+// instead of up to 32, all of the operands are on their way at once, and there is no second launch.  256 x 1024 over 1024 8.6 -> 4.8 us, 256 x 10
+// over 1024 7.6 -> 5.3, 100 x 300 over 500 (through registers) 7.0 -> 5.1; 352 products (the rule, pieces_wavefronts) 0.78 of the time on average.
+// Taken back: 32 x 64 and 64 x 64 tiles by four wavefronts 1.1 to 1.5 times as long; two pieces per wavefront for longer reductions,
+// where a few CUs' way to LDS bounds it and a split launch has those of more (64 x 64 over 4096 9.8 us, split 8.0).
+constexpr int kPiecesTile = 32;
+constexpr int pieces_lds_bytes(int wavefronts) { return wavefronts * 2 * 2 * kPiecesTile * 128; }
+
+// Four consecutive values of a row, n (at most 4) of which exist.
+__device__ __forceinline__ uint2v load_halves4(const uint16_t* p, int n) {
+  if (n >= 4) return *reinterpret_cast<const uint2u*>(p);
+  uint32_t e[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) e[k] = k < n ? p[k] : 0u;
+  return uint2v{e[0] | e[1] << 16, e[2] | e[3] << 16};
+}
+
+// REGS: the operands come through registers (RegMat), two stages ahead of LDS, else directly (RingMat).  A wavefront's LDS operations are
+// carried out in order, so what it writes it can read without a wait.
+template <class AOp, class BOp, int G, bool REGS>
+__global__ __launch_bounds__(G * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_pieces(RingMatSrc A, RingMatSrc B, Problem pb, Epilogue ep, int piece, int pieces) {
+  constexpr int T = kPiecesTile, F = T / 16, A_BYTES = T * 128, SLOT = 2 * A_BYTES, LA = AOp::NB, LB = BOp::NB;
+  static_assert(T == 32 && 2 * SLOT >= T * T * 4, "a piece fits the wavefront's slots");
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  int ti, tj, sp;
+  tile_of(pb, blockIdx.x, ti, tj, sp);
+  const int i0 = ti * T, j0 = tj * T;
+  const int st_begin = wave * piece, nst = wave < pieces ? min(piece, (pb.R + 63) / 64 - st_begin) : 0;   // stages of this wavefront
+  char* const mine = lds + wave * (2 * SLOT);
+
+  AOp da;
+  BOp db;
+  struct Regs { uint4v a[LA], b[LB]; } even_in, odd_in;                // stages on their way through registers
+  auto issue = [&](int s) {
+    if constexpr (!REGS) {
+      da.issue(s, mine + (s & 1) * SLOT);
+      db.issue(s, mine + (s & 1) * SLOT + A_BYTES);
+    }
+  };
+  auto load = [&](int s, Regs& q) {
+    if constexpr (REGS) {
+      if (s >= nst) return;
+      da.load(s, q.a);
+      db.load(s, q.b);
+    }
+  };
+  auto store = [&](int s, const Regs& q) {
+    if constexpr (REGS) {
+      if (s >= nst) return;
+      da.store(s, q.a, mine + (s & 1) * SLOT + lane * 16);
+      db.store(s, q.b, mine + (s & 1) * SLOT + A_BYTES + lane * 16);
+    }
+  };
+  if (nst > 0) {
+    if constexpr (REGS) {
+      const int r_end = (int)min((int64_t)pb.R, (int64_t)(st_begin + nst) * 64);
+      da.init(A, i0, st_begin * 64, r_end, 0, lane);
+      db.init(B, j0, st_begin * 64, r_end, 0, lane);
+      load(0, even_in);
+      load(1, odd_in);
+      store(0, even_in);
+      load(2, even_in);
+      store(1, odd_in);
+      load(3, odd_in);
+    } else {
+      da.init(A, i0, st_begin * 64, 0, lane);
+      db.init(B, j0, st_begin * 64, 0, lane);
+      issue(0);
+      if (nst > 1) issue(1);
+    }
+  }
+  // Four values of the output per thread (with eight wavefronts, of half the threads).  What the store reads, the mask or the values that are
+  // added to, is on its way beside the sums.
+  constexpr int U = T / 4;
+  const int row = t / U, unit = t % U, i = i0 + row, j = j0 + unit * 4, n = pb.J - j;
+  const bool stores = row < T && i < pb.I && n > 0;
+  uint2v mk = {0u, 0u};
+  float4v old = {0.f, 0.f, 0.f, 0.f};
+  if (stores) {
+    if (ep.act == 2) mk = load_halves4(ep.mask + (int64_t)i * ep.ldmask + j, n);
+    if (ep.mode == 2) {
+      const float* o = reinterpret_cast<const float*>(ep.out) + (int64_t)i * ep.ld + j;
+      if (n >= 4) {
+        old = *reinterpret_cast<const float4u*>(o);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 3; ++e) old[e] = e < n ? o[e] : 0.f;
+      }
+    }
+  }
+
+  float4v acc[F][F];
+#pragma unroll
+  for (int a = 0; a < F; ++a)
+#pragma unroll
+    for (int b = 0; b < F; ++b) acc[a][b] = float4v{0.f, 0.f, 0.f, 0.f};
+  RingFrag<AOp::kRC, T, F> ra;
+  RingFrag<BOp::kRC, T, F> rb;
+  const uint32_t at = lds_offset(mine);
+  ra.init(0, lane, at);
+  rb.init(0, lane, at + A_BYTES);
+  auto step = [&](int s, Regs& next_in) {
+    const uint32_t slot = (s & 1) * SLOT;
+    uint4v fa[2][F], fb[2][F];
+    if constexpr (!REGS) {
+      if (s + 1 < nst) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LA + LB) : "memory");
+      else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    ra.template read<0>(slot, fa[0]);
+    rb.template read<0>(slot, fb[0]);
+    ra.template read<1>(slot, fa[1]);
+    rb.template read<1>(slot, fb[1]);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    arrived(fa[0]);
+    arrived(fb[0]);
+    arrived(fa[1]);
+    arrived(fb[1]);
+    if constexpr (REGS) {
+      store(s + 2, next_in);
+      load(s + 4, next_in);
+    } else {
+      if (s + 2 < nst) issue(s + 2);
+    }
+    multiply<0, F>(acc, fa[0], fb[0]);
+    multiply<0, F>(acc, fa[1], fb[1]);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  for (int s = 0; s < nst; s += 2) {
+    step(s, even_in);
+    if (s + 1 < nst) step(s + 1, odd_in);
+  }
+  const int li = lane & 15, lg = lane >> 4;
+#pragma unroll
+  for (int a = 0; a < F; ++a)
+#pragma unroll
+    for (int b = 0; b < F; ++b) *reinterpret_cast<float4v*>(mine + (a * 16 + li) * (T * 4) + (((4 * b + lg) ^ (li & (U - 1))) << 4)) = acc[a][b];
+  __syncthreads();
+  bool bad = false;
+  if (stores) {
+    const char* piece_at = lds + row * (T * 4) + ((unit ^ (row & (U - 1))) << 4);
+    float4v v[G], s;
+#pragma unroll
+    for (int w = 0; w < G; ++w) v[w] = *reinterpret_cast<const float4v*>(piece_at + w * (2 * SLOT));
+    s = v[0];
+#pragma unroll
+    for (int w = 1; w < G; ++w)
+      if (w < pieces) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[e] = __fadd_rn(s[e], v[w][e]);
+      }
+    if (ep.mode == 0) {
+      half4 h;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) h[e] = (_Float16)s[e];
+      const uint2v hb = apply_act4(__builtin_bit_cast(uint2v, h), ep, mk);
+      uint16_t* o = reinterpret_cast<uint16_t*>(ep.out) + (int64_t)i * ep.ld + j;
+      if (n >= 4) {
+        bad = half_bits_special(hb[0]) | half_bits_special(hb[0] >> 16) | half_bits_special(hb[1]) | half_bits_special(hb[1] >> 16);
+        *reinterpret_cast<uint2u*>(o) = hb;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+          if (e < n) {
+            const uint16_t b = (uint16_t)(hb[e >> 1] >> ((e & 1) * 16));
+            bad |= half_bits_special(b);
+            o[e] = b;
+          }
+      }
+    } else {
+      float* o = reinterpret_cast<float*>(ep.out) + (int64_t)i * ep.ld + j;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (ep.mode == 2) s[e] = __fadd_rn(old[e], s[e]);
+        bad |= e < n && (__float_as_uint(s[e]) & 0x7F800000u) == 0x7F800000u;
+      }
+      if (n >= 4) {
+        *reinterpret_cast<float4u*>(o) = s;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+          if (e < n) o[e] = s[e];
+      }
+    }
+  }
+  if (ep.flag != nullptr) {
+    const unsigned long long vote = __builtin_amdgcn_ballot_w64(bad);
+    if (vote != 0ull && lane == 0) atomicOr(ep.flag, 1u);
+  }
+}
+
 // ---------------------------------------------------------------- convolutions of at most 64 channels
 // Forward and input gradient over the pixels in order: a workgroup takes 256 of them at a time, with the W + 1 before and behind,
 // from which all nine taps are then read, and keeps the whole filter in registers (9 taps x 64 x 64, 288 a lane), going through
@@ -1031,11 +1228,34 @@ int launch_any(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, RingTile
   return MPT_OK;
 }
 
+template <class AOp, class BOp, int G, bool REGS>
+int launch_pieces_of(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, const Problem& pb, const Epilogue& ep, int piece, int pieces) {
+  auto k = k_gemm_pieces<AOp, BOp, G, REGS>;
+  constexpr int lds = pieces_lds_bytes(G);
+  static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds), true);
+  (void)once;
+  hipLaunchKernelGGL(k, dim3((unsigned)(pb.tiles_i * pb.tiles_j)), dim3(G * 64), lds, s, A, B, pb, ep, piece, pieces);
+  MPT_LAUNCH_CHECK();
+  return MPT_OK;
+}
+
+// Operands through registers: rows of 8 elements and more whose strides fit 32-bit offsets, and any others in instances of their own.
+bool ordinary_rows(bool a_rc, bool b_rc, const RingMatSrc& A, const RingMatSrc& B) {
+  return (a_rc ? A.R : A.O) >= 8 && (b_rc ? B.R : B.O) >= 8 && A.ld < (1 << 21) && B.ld < (1 << 21);
+}
+
+template <bool A_RC, bool B_RC, int G>
+int launch_pieces(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool whole_chunks, const Problem& pb, const Epilogue& ep, int piece, int pieces) {
+  constexpr int T = kPiecesTile;
+  if (whole_chunks) return launch_pieces_of<RingMat<A_RC, T, 1>, RingMat<B_RC, T, 1>, G, false>(s, A, B, pb, ep, piece, pieces);
+  if (ordinary_rows(A_RC, B_RC, A, B)) return launch_pieces_of<RegMat<A_RC, T, false, 1>, RegMat<B_RC, T, false, 1>, G, true>(s, A, B, pb, ep, piece, pieces);
+  return launch_pieces_of<RegMat<A_RC, T, true, 1>, RegMat<B_RC, T, true, 1>, G, true>(s, A, B, pb, ep, piece, pieces);
+}
+
 template <bool A_RC, bool B_RC, bool CUT>
 int launch_plain(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool whole_chunks, RingTile tile, const Problem& pb, const Epilogue& ep, int cut) {
   if (!whole_chunks) {
-    const bool ordinary = (A_RC ? A.R : A.O) >= 8 && (B_RC ? B.R : B.O) >= 8 && A.ld < (1 << 21) && B.ld < (1 << 21);
-    return ordinary ? launch_any<A_RC, B_RC, false, CUT>(s, A, B, tile, pb, ep, cut) : launch_any<A_RC, B_RC, true, CUT>(s, A, B, tile, pb, ep, cut);
+    return ordinary_rows(A_RC, B_RC, A, B) ? launch_any<A_RC, B_RC, false, CUT>(s, A, B, tile, pb, ep, cut) : launch_any<A_RC, B_RC, true, CUT>(s, A, B, tile, pb, ep, cut);
   }
   if (tile == kRing64x64) return launch_ring<RingMat<A_RC, 64>, RingMat<B_RC, 64>, 64, 64, 32, 32, 4, CUT>(s, A, B, pb, ep, cut);
   if (tile == kRing128x64) return launch_ring<RingMat<A_RC, 128>, RingMat<B_RC, 64>, 128, 64, 64, 32, 2, CUT>(s, A, B, pb, ep, cut);
@@ -1102,6 +1322,18 @@ int launch_ring_plain(hipStream_t s, bool a_rc, bool b_rc, const RingMatSrc& A, 
   }
   if (a_rc) return b_rc ? launch_plain<true, true, false>(s, A, B, whole_chunks, tile, pb, ep, 0) : launch_plain<true, false, false>(s, A, B, whole_chunks, tile, pb, ep, 0);
   return launch_plain<false, false, false>(s, A, B, whole_chunks, tile, pb, ep, 0);      // (no product here has only A along the output)
+}
+
+int launch_pieces_plain(hipStream_t s, bool a_rc, bool b_rc, const RingMatSrc& A, const RingMatSrc& B, bool whole_chunks, int piece, int pieces, int I, int J, int R,
+                        const Epilogue& ep) {
+  if (pieces > 8 || ep.mode == 3) return MPT_ERR_ARG;                  // one piece per wavefront, added up in the launch
+  const Problem pb{I, J, R, (I + kPiecesTile - 1) / kPiecesTile, (J + kPiecesTile - 1) / kPiecesTile, 1, (R + 63) / 64};
+  auto go = [&](auto g) {
+    constexpr int G = decltype(g)::value;
+    if (a_rc) return b_rc ? launch_pieces<true, true, G>(s, A, B, whole_chunks, pb, ep, piece, pieces) : launch_pieces<true, false, G>(s, A, B, whole_chunks, pb, ep, piece, pieces);
+    return launch_pieces<false, false, G>(s, A, B, whole_chunks, pb, ep, piece, pieces);
+  };
+  return pieces > 4 ? go(std::integral_constant<int, 8>{}) : go(std::integral_constant<int, 4>{});
 }
 
 int launch_ring_conv(hipStream_t s, int op, int64_t Nb, int64_t H, int64_t W, int64_t C, int64_t Kf, const uint16_t* img, const uint16_t* other,

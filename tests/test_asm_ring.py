@@ -28,7 +28,7 @@ def assembly(tmp_path_factory):
 
 def test_ring_kernels_keep_in_flight_read_registers_untouched(assembly):
     n = 0
-    for name, lines in asm_check.kernels(assembly, r"k_gemm_(ring|any)"):
+    for name, lines in asm_check.kernels(assembly, r"k_gemm_(ring|any|pieces)"):
         found = asm_check.check_kernel(lines)
         assert not found, "%s: %s" % (name, found[:5])
         assert sum("v_mfma" in l for l in lines) >= 8
@@ -42,6 +42,6 @@ def test_no_wide_shift_takes_its_amount_from_the_last_register(assembly):
     for name, lines in asm_check.kernels(assembly, r"k_(gemm|conv)"):
         assert not asm_check.shifts_by_the_last_register(lines, registers[name]), name
         n += 1
-    assert n >= 30
+    assert n >= 40
     assert asm_check.shifts_by_the_last_register(["\tv_lshlrev_b64 v[90:91], v127, v[86:87]"], 128) == [127]
     assert not asm_check.shifts_by_the_last_register(["\tv_lshlrev_b64 v[90:91], v127, v[86:87]"], 136)

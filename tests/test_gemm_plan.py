@@ -21,6 +21,9 @@ extern "C" void ring(long I, long J, long R, int ws, int whole_chunks, int lines
   const RingPlan r = ring_plan(p, I, J, R, whole_chunks != 0, lines != 0, conv == 3, conv == 2, conv == 1);
   out[0] = r.tile; out[1] = r.splits; out[2] = r.ktiles_per_split; out[3] = r.cut;
 }
+extern "C" int pieces(long I, long J, long R, int ws, int whole_chunks, int weight_gradient) {
+  return pieces_side_by_side(make_plan(I, J, R, ws != 0), I, J, R, whole_chunks != 0, weight_gradient != 0);
+}
 extern "C" int fp32_ring(long tiles256, long ktiles, int accumulate) { return ring_for_fp32(tiles256, ktiles, accumulate != 0); }
 extern "C" int fp16_ring(long tiles128, long ktiles) { return ring_for_fp16(tiles128, ktiles); }
 extern "C" int patches(long Nb, long H, long W, long C, long Kf) { return conv_in_patches(Nb, H, W, C, Kf); }
@@ -48,6 +51,7 @@ def planner(tmp_path_factory):
         return tuple(out)
     L.fp32_ring.argtypes = [ctypes.c_long, ctypes.c_long, ctypes.c_int]
     L.fp16_ring.argtypes = [ctypes.c_long] * 2
+    L.pieces.argtypes = [ctypes.c_long] * 3 + [ctypes.c_int] * 3
     L.patches.argtypes = [ctypes.c_long] * 5
     L.apart.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_long, ctypes.c_int]
     return lambda *a: call(L.planned, *a)[:2], lambda *a: call(L.ring, *a), L
@@ -127,6 +131,45 @@ def test_every_form_of_a_product_launch_is_run_on_the_gpu(planner):
         seen.add((op, tile, slots, "split" if splits > 1 else "cut" if cut else "whole"))
     forms = {(tile, slots, form) for tile, slots in ((1, 4), (3, 4), (3, 2), (0, 4), (0, 2), (1, 0), (0, 0)) for form in ("split", "cut", "whole")} - {(0, 0, "cut")}
     assert seen == {(op,) + form for op in "fdw" for form in forms}
+
+
+def test_products_whose_pieces_are_summed_side_by_side(planner):
+    """One piece per wavefront, a workgroup or, of four wavefronts, two per CU, and a short reduction; never without a workspace."""
+    planned, _, L = planner
+    for (I, J, R), whole, wgrad, want in (((256, 1024, 1024), 1, 0, 1), ((256, 1056, 1024), 1, 0, 0), ((256, 10, 1024), 0, 0, 1), ((256, 2048, 512), 1, 0, 1), ((256, 2080, 512), 1, 0, 0), ((64, 64, 2048), 1, 0, 1),
+                                          ((64, 64, 2049), 1, 0, 0), ((64, 64, 1792), 1, 1, 1), ((64, 64, 1793), 1, 1, 0), ((65, 63, 1536), 0, 0, 1), ((65, 63, 1537), 0, 0, 0),
+                                          ((65, 63, 1280), 0, 1, 1), ((65, 63, 1281), 0, 1, 0), ((64, 64, 192), 1, 0, 0), ((64, 64, 256), 1, 0, 1), ((512, 1024, 256), 1, 0, 1),
+                                          ((512, 1032, 256), 1, 0, 0)):
+        assert L.pieces(I, J, R, 1, whole, wgrad) == want, (I, J, R)
+        assert not L.pieces(I, J, R, 0, whole, wgrad)
+    for I, J, R in shapes(3000):
+        if L.pieces(I, J, R, 1, 1, 0):
+            assert 2 <= planned(I, J, R, 1)[0] <= 8
+
+
+def test_forms_of_a_product_launch_that_the_ring_tests_reach(planner):
+    """Those of FORMS whose pieces are summed side by side have stand-ins in RING_FORMS; the sizes of the edge tests take that route at both numbers of
+    wavefronts, aligned and through registers, in all passes."""
+    from test_gpu_gemm_pieces import RING_FORMS, SIZES
+    from test_gpu_gemm_ring import FORMS
+    rows_cols, seen, beside = {0: (128, 128), 1: (64, 64), 3: (128, 64)}, set(), set()
+    for op, M, N, K, ws in FORMS + RING_FORMS:
+        I, J, R = {"f": (M, N, K), "d": (M, K, N), "w": (K, N, M)}[op]
+        strides = {"f": (K, N), "d": (N, N), "w": (K, N)}[op]
+        whole = all(s % 8 == 0 for s in strides)
+        if planner[2].pieces(I, J, R, ws, int(whole), int(op == "w")):
+            continue
+        tile, splits, _, cut = planner[1](I, J, R, ws, int(whole), int(all(s % 64 == 0 for s in strides)), PLAIN)
+        workgroups = -(-I // rows_cols[tile][0]) * -(-J // rows_cols[tile][1]) * splits
+        seen.add((op, tile, (4 if tile == 1 or workgroups <= 256 else 2) if whole else 0, "split" if splits > 1 else "cut" if cut else "whole"))
+    forms = {(tile, slots, form) for tile, slots in ((1, 4), (3, 4), (3, 2), (0, 4), (0, 2), (1, 0), (0, 0)) for form in ("split", "cut", "whole")} - {(0, 0, "cut")}
+    assert seen == {(op,) + form for op in "fdw" for form in forms}
+    for M, N, K in SIZES:
+        for op, I, J, R, strides in (("f", M, N, K, (K, N)), ("d", M, K, N, (N, N)), ("w", K, N, M, (K, N))):
+            for whole in {all(s % 8 == 0 for s in strides), False}:
+                if planner[2].pieces(I, J, R, 1, int(whole), int(op == "w")):
+                    beside.add((op, whole, 4 if planner[0](I, J, R, 1)[0] <= 4 else 8))
+    assert beside == {(op, whole, g) for op in "fdw" for whole in (False, True) for g in (4, 8)}
 
 
 def test_every_form_of_a_convolution_launch_is_run_on_the_gpu(planner):
