@@ -192,6 +192,11 @@ inline bool operands_apart(bool a_rc, bool b_rc, int64_t workgroups, int ktiles)
   return a_rc && ((most == 4 && ktiles >= 20) || (most == 3 && b_rc && ktiles >= 32));
 }
 
+// Products through registers whose last columns are read over their rows' ends and masked (RegMat, OVER), not shifted: from 5 stages on.  Shorter
+// ones are faster shifted, since the masks' code is fetched too: 226 x 192 over 80 4.0 us, masked 4.5; 301 x 448 over 95 5.2 and 5.3; over 200 .. 260 the
+// same either way, 1146 x 1602 over 330 9.3 and 9.3, over 390 10.0 and 9.7, over 520 11.9 and 11.1.
+inline bool edges_read_over(int ktiles, bool ragged) { return ragged && ktiles >= 5; }
+
 // Convolutions (forward and input gradient) that k_conv_patch takes: a filter of at most 64 x 64 channels, rows of which two patches
 // and the outputs fit LDS, and pixels for half the CUs: 32768 of them (128 tiles) with 64 channels 13.3 -> 9.8 us, where the ring kernels
 // still work unsplit.  Measured at 23 sizes of 8 .. 64 channels: 0.67 to 1.0 of the ring kernels' time.

@@ -308,8 +308,12 @@ __device__ __forceinline__ uint16_t one_from_global(const void* p) { return *(co
 
 // ANY: also rows of fewer than 8 elements, gathered element by element, and row strides too long for 32-bit offsets; kept apart, since
 // their branches around the loads cost the others a tenth (3999 x 1777 over 999 51 against 47 us).
-template <bool RC, int BO, bool ANY, int WAVES = 4>
+// OVER (OC, ragged edges): pieces that run over their row's end are read over it and masked where another row follows, which all but the last stage's
+// do.  Shifted at every stage as in the last one, they were what all other workgroups waited for: 600 x 1201 over 805 12.7 us, 11.6 so.  Not for a few stages:
+// a launch pays for code that it fetches once (1778 x 11 over 46 3.97 -> 4.24 us).
+template <bool RC, int BO, bool ANY, int WAVES = 4, bool OVER = false>
 struct RegMat {
+  static_assert(!(OVER && (RC || ANY)), "rows of 8 elements and more along the output");
   typedef RingMatSrc Src;
   typedef Piece<RC, BO, WAVES> P;
   static constexpr bool kRC = RC;
@@ -318,10 +322,10 @@ struct RegMat {
   typedef uint4v Pieces[NB];       // of a stage, on their way
   const char* base;                // of the tile's corner, stage 0 (wavefront-uniform), kFront elements in front: a piece moved back over an edge has an offset >= 0
   int64_t ld, step;                // step: bytes per stage
-  uint32_t off[NB];
-  uint4v keep[RC ? 1 : NB];        // OC: what of a piece lies inside the row
+  uint32_t off[NB];                // OC: of the row's last 8 elements where the piece runs over its end, unless it is read over it
+  uint4v keep[OVER ? NB : 1];      // what of a piece lies inside the row
   int left, outer_left, inside, wave, lane;   // inside: stages that end before the reduction does
-  int followed;                    // OC: stages behind whose rows another one follows, so that a piece may be read over its row's end
+  int followed;                    // stages whose pieces are read where `off` says
   bool narrow, wide, ragged;       // ragged: the tile's last columns are no whole piece
   // elements of the piece of block k along the row that exist (8 or more: all)
   __device__ __forceinline__ int along(int s, int lane, int k) const { return (RC ? left - s * 64 : outer_left) - P::col(wave, lane, k); }
@@ -335,24 +339,26 @@ struct RegMat {
     wide = ANY && ld >= (1 << 21);
     ragged = !RC && outer_left < BO && (outer_left & 7) != 0;
     inside = narrow || wide ? 0 : left >> 6;
+    followed = OVER && ragged ? min(inside, (m.R - 1 - r0) >> 6) : inside;
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
       const int row = P::row(wave, lane, k), col = P::col(wave, lane, k);
-      // OC pieces that run over the row's end are read over it, those behind it are the row's last 8 elements (outer_left - 8 >= -7 unless narrow)
-      const int c = kFront + (RC || col < outer_left ? col : outer_left - 8);
+      const int c = kFront + (RC || (OVER && col < outer_left) ? col : min(col, outer_left - 8));      // (outer_left - 8 >= -7 unless narrow)
       off[k] = (uint32_t)(((RC ? (int64_t)min(row, outer_left - 1) : (int64_t)row) * ld + c) * 2);
-      if constexpr (!RC) {
+      if constexpr (OVER) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) keep[k][i] = (2 * i < outer_left - col ? 0x0000FFFFu : 0u) | (2 * i + 1 < outer_left - col ? 0xFFFF0000u : 0u);
       }
     }
-    followed = narrow || wide ? 0 : (m.R - 1 - r0) >> 6;
   }
-  // How far in front of its place the piece of block k is read in the last stage: pieces that run over their row's end as its last 8 elements
+  // How far in front of that the piece of block k is read in the stages from `followed` on: pieces that run over their row's end as its last 8 elements
   // (an RC piece starts at most 55 elements behind the end, less than the base lies in front), OC rows beyond the end as the last.
   __device__ __forceinline__ uint32_t back(int s, int l, int k) const {
+    if (RC) return 2u * (uint32_t)max(8 - along(s, l, k), 0);
+    const uint32_t rows = (uint32_t)max(P::row(wave, l, k) - (left - s * 64 - 1), 0) * (uint32_t)(ld * 2);
+    if (!OVER) return rows;
     const int n = along(s, l, k);
-    return RC ? 2u * (uint32_t)max(8 - n, 0) : (uint32_t)max(P::row(wave, l, k) - (left - s * 64 - 1), 0) * (uint32_t)(ld * 2) + (n > 0 ? 2u * (uint32_t)max(8 - n, 0) : 0u);
+    return n > 0 ? rows + 2u * (uint32_t)max(8 - n, 0) : rows;
   }
   __device__ __forceinline__ void load(int s, Pieces& reg) {
     const char* at = scalar_base(base + s * step);
@@ -360,7 +366,7 @@ struct RegMat {
       uint32_t o[NB];
 #pragma unroll
       for (int k = 0; k < NB; ++k) o[k] = off[k];
-      if (s >= (RC ? inside : followed)) {
+      if (s >= followed) {
         const int l = here_only(lane);
 #pragma unroll
         for (int k = 0; k < NB; ++k) o[k] -= back(s, l, k);
@@ -395,8 +401,8 @@ struct RegMat {
       for (int k = 0; k < NB; ++k) *reinterpret_cast<uint4v*>(lds_lane + k * 1024) = reg[k];
       return;
     }
-    if constexpr (!RC) {                                             // (shifted instead, as in the last stage, 600 x 1201 over 805 took 13.1 us)
-      if (s < followed && s < inside) {
+    if constexpr (OVER) {
+      if (s < followed) {
 #pragma unroll
         for (int k = 0; k < NB; ++k) {
           uint4v v = reg[k];
@@ -1206,24 +1212,27 @@ int launch_ring(hipStream_t s, const typename AOp::Src& A, const typename BOp::S
   return MPT_OK;
 }
 
-template <bool A_RC, bool B_RC, bool ANY, bool CUT>
+template <bool A_RC, bool B_RC, bool ANY, bool CUT, bool OVER>
 int launch_any(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, RingTile tile, const Problem& pb, const Epilogue& ep, int cut) {
   const dim3 grid((unsigned)((int64_t)pb.tiles_i * pb.tiles_j * pb.splits));
   if constexpr (!CUT) {                                              // the cut sums of 128 x 128 tiles through registers would not fit the register file
     if (tile != kRing64x64) {
-      hipLaunchKernelGGL((k_gemm_any<RegMat<A_RC, 128, ANY>, RegMat<B_RC, 128, ANY>, 128, 128, 64, 64, false, false>), grid, dim3(256), 2 * 256 * 128, s, A, B, pb, ep, 0);
+      hipLaunchKernelGGL((k_gemm_any<RegMat<A_RC, 128, ANY, 4, OVER && !A_RC>, RegMat<B_RC, 128, ANY, 4, OVER && !B_RC>, 128, 128, 64, 64, false, false>), grid, dim3(256), 2 * 256 * 128, s,
+                         A, B, pb, ep, 0);
       MPT_LAUNCH_CHECK();
       return MPT_OK;
     }
   }
+  typedef RegMat<A_RC, 64, ANY, 4, OVER && !A_RC> AOp;
+  typedef RegMat<B_RC, 64, ANY, 4, OVER && !B_RC> BOp;
   if constexpr (A_RC && !ANY) {
     if (operands_apart(A_RC, B_RC, grid.x, pb.ktiles_per_split)) {
-      hipLaunchKernelGGL((k_gemm_any<RegMat<A_RC, 64, ANY>, RegMat<B_RC, 64, ANY>, 64, 64, 32, 32, CUT, true>), grid, dim3(256), 2 * 128 * 128, s, A, B, pb, ep, cut);
+      hipLaunchKernelGGL((k_gemm_any<AOp, BOp, 64, 64, 32, 32, CUT, true>), grid, dim3(256), 2 * 128 * 128, s, A, B, pb, ep, cut);
       MPT_LAUNCH_CHECK();
       return MPT_OK;
     }
   }
-  hipLaunchKernelGGL((k_gemm_any<RegMat<A_RC, 64, ANY>, RegMat<B_RC, 64, ANY>, 64, 64, 32, 32, CUT, false>), grid, dim3(256), 2 * 128 * 128, s, A, B, pb, ep, cut);
+  hipLaunchKernelGGL((k_gemm_any<AOp, BOp, 64, 64, 32, 32, CUT, false>), grid, dim3(256), 2 * 128 * 128, s, A, B, pb, ep, cut);
   MPT_LAUNCH_CHECK();
   return MPT_OK;
 }
@@ -1255,7 +1264,11 @@ int launch_pieces(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool 
 template <bool A_RC, bool B_RC, bool CUT>
 int launch_plain(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool whole_chunks, RingTile tile, const Problem& pb, const Epilogue& ep, int cut) {
   if (!whole_chunks) {
-    return ordinary_rows(A_RC, B_RC, A, B) ? launch_any<A_RC, B_RC, false, CUT>(s, A, B, tile, pb, ep, cut) : launch_any<A_RC, B_RC, true, CUT>(s, A, B, tile, pb, ep, cut);
+    if (!ordinary_rows(A_RC, B_RC, A, B)) return launch_any<A_RC, B_RC, true, CUT, false>(s, A, B, tile, pb, ep, cut);
+    if constexpr (!A_RC || !B_RC) {
+      if (edges_read_over(pb.ktiles_per_split, (!A_RC && A.O % 8 != 0) || (!B_RC && B.O % 8 != 0))) return launch_any<A_RC, B_RC, false, CUT, true>(s, A, B, tile, pb, ep, cut);
+    }
+    return launch_any<A_RC, B_RC, false, CUT, false>(s, A, B, tile, pb, ep, cut);
   }
   if (tile == kRing64x64) return launch_ring<RingMat<A_RC, 64>, RingMat<B_RC, 64>, 64, 64, 32, 32, 4, CUT>(s, A, B, pb, ep, cut);
   if (tile == kRing128x64) return launch_ring<RingMat<A_RC, 128>, RingMat<B_RC, 64>, 128, 64, 64, 32, 2, CUT>(s, A, B, pb, ep, cut);

@@ -21,6 +21,7 @@ extern "C" void ring(long I, long J, long R, int ws, int whole_chunks, int lines
   const RingPlan r = ring_plan(p, I, J, R, whole_chunks != 0, lines != 0, conv == 3, conv == 2, conv == 1);
   out[0] = r.tile; out[1] = r.splits; out[2] = r.ktiles_per_split; out[3] = r.cut;
 }
+extern "C" int over(int ktiles, int ragged) { return edges_read_over(ktiles, ragged != 0); }
 extern "C" int pieces(long I, long J, long R, int ws, int whole_chunks, int weight_gradient) {
   return pieces_side_by_side(make_plan(I, J, R, ws != 0), I, J, R, whole_chunks != 0, weight_gradient != 0);
 }
@@ -215,6 +216,21 @@ def test_operands_through_registers_are_fetched_apart_where_that_is_faster(plann
             tile, splits, per, cut = planner[1](I, J, R, ws, 0, 0, PLAIN)
             if ws or op == "d" and K == 1409:                                # (without a workspace four workgroups on a CU are tiles of 128 x 128)
                 assert tile == 1 and bool(cut) == bool(ws) and apart(1, op == "d", -(-I // 64) * -(-J // 64) * splits, per), (op, M, N, K)
+
+
+def test_ragged_edges_of_longer_reductions_are_read_over(planner):
+    """And the edge tests of the ring kernels run both forms: forward and weight gradients, in tiles of 64 x 64 cut and whole and of 128 x 128."""
+    from test_gpu_gemm_pieces import RING_FORMS
+    from test_gpu_gemm_ring import FORMS, SIZES
+    over, seen = planner[2].over, set()
+    assert [over(k, 1) for k in (1, 4, 5, 60)] == [0, 0, 1, 1] and not over(60, 0)
+    for op, M, N, K, ws in FORMS + RING_FORMS + [(op, *size, ws) for size in SIZES for op in "fw" for ws in (0, 1)]:
+        I, J, R = (M, N, K) if op == "f" else (K, N, M)
+        through_registers = (op, M, N, K, ws) not in FORMS + RING_FORMS or J % 8 or (K % 8 if op == "f" else I % 8)   # (SIZES are run with odd strides too)
+        if op in "fw" and through_registers and not planner[2].pieces(I, J, R, ws, 0, int(op == "w")):
+            tile, _, per, cut = planner[1](I, J, R, ws, 0, 0, PLAIN)
+            seen.add((op, tile, bool(cut), over(per, int(J % 8 != 0 or (op == "w" and I % 8 != 0)))))
+    assert {(op, tile, cut, o) for op in "fw" for tile, cut in ((1, False), (1, True), (0, False)) for o in (0, 1)} <= seen
 
 
 def test_whole_tiles_that_smaller_tiles_take_in_less_time(planner):

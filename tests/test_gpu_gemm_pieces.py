@@ -68,10 +68,11 @@ def test_a_special_value_is_seen_where_it_is_stored(where, dtype):
     assert torch.isinf(out).any(0).tolist() == [k == where for k in range(31)]
 
 
-# the ring kernels' split and cut launches of 64 x 64 and 128 x 64 tiles, at sizes beyond those that k_gemm_pieces takes (test_gemm_plan.py counts them)
+# the ring kernels' split and cut launches of 64 x 64 and 128 x 64 tiles, at sizes beyond those that k_gemm_pieces takes, and two with ragged edges over many
+# stages (test_gemm_plan.py counts them)
 RING_FORMS = [("d", 1288, 197, 400, 1), ("d", 8, 1734, 8, 1), ("d", 856, 200, 592, 1), ("d", 8, 2064, 8, 1), ("d", 344, 2280, 656, 1), ("d", 680, 2344, 136, 1),
               ("f", 459, 1090, 196, 1), ("f", 9, 10, 1546, 1), ("f", 752, 680, 208, 1), ("f", 8, 8, 2184, 1), ("f", 136, 672, 2296, 1), ("w", 206, 295, 1776, 1),
-              ("w", 1350, 8, 10, 1), ("w", 216, 720, 720, 1), ("w", 1936, 8, 8, 1), ("w", 1856, 272, 408, 1)]
+              ("w", 1350, 8, 10, 1), ("w", 216, 720, 720, 1), ("w", 1936, 8, 8, 1), ("w", 1856, 272, 408, 1), ("f", 885, 586, 267, 1), ("w", 2130, 387, 981, 1)]
 
 
 @pytest.mark.parametrize("op,M,N,K,split", RING_FORMS)
