@@ -106,8 +106,8 @@ constexpr int ring_tile_cols(RingTile t) { return t == kRing128x128 ? 128 : 64; 
 // over 64 through registers 26.5 us so, in 64 x 64 tiles 21.4.
 struct RingCost { double start, each, stage, alone = 1.0, old = 0.0; };   // alone: shares of a workgroup that has its CU to itself (what its waits
                                                                            // leave idle); old: more for `each` where the store adds to FP32 values
-inline constexpr RingCost kRing64[2] = {{2.3, 0.98, 0.24, 1.23, 0.8}, {2.0, 1.1, 0.2, 1.44, 0.8}}, kRing128x64Cost[2] = {{3.2, 0.89, 0.36, 1.12, 2.5}, {2.95, 1.04, 0.29, 1.32, 2.5}},
-                          kRing128[2] = {{3.3, 2.16, 0.51, 1.16, 4.2}, {2.6, 2.46, 0.45, 1.31, 4.2}};
+inline constexpr RingCost kRing64[2] = {{2.3, 0.98, 0.24, 1.23, 0.8}, {2.0, 1.1, 0.2, 1.44, 0.8}}, kRing128x64Cost[2] = {{3.2, 0.89, 0.36, 1.04, 2.5}, {2.95, 1.04, 0.29, 1.23, 2.5}},
+                          kRing128[2] = {{3.3, 2.16, 0.51, 1.04, 4.2}, {2.6, 2.46, 0.45, 1.18, 4.2}};
 inline constexpr RingCost kAny64 = {2.7, 0.55, 0.37, 1.68, 0.7}, kAny128 = {1.7, 3.03, 0.83, 1.39, 4.5}, kWhole256 = {6.0, 0.0, 1.5};
 inline constexpr RingCost kConvRows = {2.5, 3.2, 0.52, 1.25}, kConvRows64 = {2.2, 1.0, 0.25, 1.65}, kConvWgrad64 = {4.0, 0.0, 0.26, 1.6}, kConvWgrad128 = {6.0, 0.0, 0.6, 1.3};
 inline double ring_cost(const RingCost& c, int64_t tiles, int64_t I, int64_t J, int stages, int64_t splits, bool accumulate = false) {

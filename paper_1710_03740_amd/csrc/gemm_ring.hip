@@ -6,7 +6,8 @@
 //
 // Both hold the operands in LDS as gemm.hip's streamed kernels do (reduction-contiguous rows of 128 bytes, or
 // outer-contiguous rows read with the transposing LDS read), so no operand is transposed in registers, and both work on
-// four wavefronts per workgroup with two workgroups on a CU, which cover each other's barriers, fills and stores.
+// four wavefronts per workgroup with two workgroups on a CU, which cover each other's barriers, fills and stores, or eight
+// where a workgroup has its CU to itself.
 //
 // Ragged edges cost no branch: rows beyond the output read the last row again, pieces beyond the reduction read a line
 // of zeros, and the store leaves out what does not exist.
@@ -631,11 +632,12 @@ __device__ __forceinline__ void add_piece(float4v (&total)[FM][FN], float4v (&ac
       }
 }
 template <class AOp, class BOp, int BM, int BN, int WM, int WN, int NS, bool CUT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_ring(typename AOp::Src A, typename BOp::Src B, Problem pb, Epilogue ep, int cut) {
-  static_assert((BM / WM) * (BN / WN) == 4, "four wavefronts");
+__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_ring(typename AOp::Src A, typename BOp::Src B, Problem pb, Epilogue ep, int cut) {
+  constexpr int WAVES = (BM / WM) * (BN / WN);
+  static_assert(WAVES == 4 || WAVES == 8, "wavefronts");
   constexpr int FM = WM / 16, FN = WN / 16, A_BYTES = BM * 128, STAGE = (BM + BN) * 128, LA = AOp::NB, LB = BOp::NB, L = LA + LB;
   static_assert((NS & (NS - 1)) == 0 && (NS - 1) * L < 64, "slots; loads in flight fit the counter");
-  static_assert(NS * STAGE >= 4 * WM * WN * 4, "the store's buffers fit the ring");
+  static_assert(NS * STAGE >= WAVES * WM * WN * 4, "the store's buffers fit the ring");
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wm = wave / (BN / WN), wn = wave % (BN / WN);
@@ -1197,17 +1199,11 @@ Problem ring_problem(RingTile tile, int ktiles_per_split, int I, int J, int R) {
 
 template <class AOp, class BOp, int BM, int BN, int WM, int WN, int NS, bool CUT = false>
 int launch_ring(hipStream_t s, const typename AOp::Src& A, const typename BOp::Src& B, const Problem& pb, const Epilogue& ep, int cut = 0) {
-  // Two slots let two workgroups share a CU, which cover each other's waits.  A workgroup that has its CU to itself has only
-  // its own loads in flight: four slots (2000 x 1000 over 3000 in 256 tiles of 128 x 64: 39 -> 25 us; with 752 workgroups four
-  // slots would cost a quarter).  Not for the convolutions: their small ones lose a microsecond.
-  if constexpr (NS == 2 && 4 * (BM + BN) * 128 <= 163840 && std::is_same<typename AOp::Src, RingMatSrc>::value && std::is_same<typename BOp::Src, RingMatSrc>::value) {
-    if ((int64_t)pb.tiles_i * pb.tiles_j * pb.splits <= kCUs) return launch_ring<AOp, BOp, BM, BN, WM, WN, 4, CUT>(s, A, B, pb, ep, cut);
-  }
   auto k = k_gemm_ring<AOp, BOp, BM, BN, WM, WN, NS, CUT>;
   constexpr int lds = NS * (BM + BN) * 128;
   static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds), true);
   (void)once;
-  hipLaunchKernelGGL(k, dim3((unsigned)((int64_t)pb.tiles_i * pb.tiles_j * pb.splits)), dim3(256), lds, s, A, B, pb, ep, cut);
+  hipLaunchKernelGGL(k, dim3((unsigned)((int64_t)pb.tiles_i * pb.tiles_j * pb.splits)), dim3((BM / WM) * (BN / WN) * 64), lds, s, A, B, pb, ep, cut);
   MPT_LAUNCH_CHECK();
   return MPT_OK;
 }
@@ -1271,7 +1267,17 @@ int launch_plain(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool w
     return launch_any<A_RC, B_RC, false, CUT, false>(s, A, B, tile, pb, ep, cut);
   }
   if (tile == kRing64x64) return launch_ring<RingMat<A_RC, 64>, RingMat<B_RC, 64>, 64, 64, 32, 32, 4, CUT>(s, A, B, pb, ep, cut);
-  if (tile == kRing128x64) return launch_ring<RingMat<A_RC, 128>, RingMat<B_RC, 64>, 128, 64, 64, 32, 2, CUT>(s, A, B, pb, ep, cut);
+  // Two slots let two workgroups share a CU, which cover each other's waits.  A workgroup that has its CU to itself has only its own loads and
+  // its own wavefronts: four slots (2000 x 1000 over 3000 in 256 tiles of 128 x 64: 39 -> 25 us; with 752 workgroups four slots would cost a quarter)
+  // and eight wavefronts of half the block, two to a SIMD, so that one reads its fragments while the other multiplies.  Over 39 such products
+  // 0.85 to 0.98 of the time of four wavefronts (3000 x 1000 over 2000 27.2 -> 23.3 us, 744 x 3840 over 3944 45.4 -> 39.2); where CUs are shared 0.97 to
+  // 1.4 times as long, and of 64 x 64 tiles, whose wavefronts would have 32 x 16 left, 0.93 to 1.04.
+  const bool alone = (int64_t)pb.tiles_i * pb.tiles_j * pb.splits <= kCUs;
+  if (tile == kRing128x64) {
+    if (alone) return launch_ring<RingMat<A_RC, 128, 8>, RingMat<B_RC, 64, 8>, 128, 64, 32, 32, 4, CUT>(s, A, B, pb, ep, cut);
+    return launch_ring<RingMat<A_RC, 128>, RingMat<B_RC, 64>, 128, 64, 64, 32, 2, CUT>(s, A, B, pb, ep, cut);
+  }
+  if (alone) return launch_ring<RingMat<A_RC, 128, 8>, RingMat<B_RC, 128, 8>, 128, 128, 64, 32, 4, CUT>(s, A, B, pb, ep, cut);
   return launch_ring<RingMat<A_RC, 128>, RingMat<B_RC, 128>, 128, 128, 64, 64, 2, CUT>(s, A, B, pb, ep, cut);
 }
 
