@@ -156,15 +156,16 @@ inline RingPlan ring_plan(const Plan& pl, int64_t I, int64_t J, int64_t R, bool 
 
 // Products that k_gemm_pieces (gemm_ring.hip) takes: their sums are cut into pieces, 2 to 8 of them, their tiles of 32 x 32 are no more than
 // there are CUs (twice as many where four wavefronts hold the pieces, two workgroups then share a CU), and the reduction is short, since a
-// workgroup walks all of it.  630 products of 8 .. 3000 rows and columns over 64 .. 8192, operands not in the L2: the 358 taken here 0.72 to 0.95 of
-// the time that the others' best took, by size (kt <= 16 0.71 aligned and 0.80 through registers, 16 .. 24 0.79 and 0.92, 24 .. 32 0.85), 3 of them
-// longer (at most 1.07).  Beyond: 256 .. 512 tiles in eight wavefronts 0.96 to 1.03 times as fast, 512 .. 1024 in four 0.70 to 1.05, kt of 32 .. 48 1.02 aligned and 1.07 through registers (whose
-// loads take a CU longer), weight gradients, whose rows are half cache lines here, 1.08 at 32 and 1.07 to 1.1 through registers at 23 .. 26.
+// workgroup walks all of it.  Products of 8 .. 3000 rows and columns over 64 .. 8192, operands not in the L2, against what the other kernels
+// take: aligned ones (kt <= 16 0.71 of the time, 16 .. 24 0.79, 24 .. 32 0.85; 1 of 170 longer, 1.09), through registers (kt <= 14 0.73 .. 0.95, 14 .. 20
+// 0.85 .. 1.0).  Beyond: 256 .. 512 tiles in eight wavefronts 0.96 to 1.03 times as fast, 512 .. 1024 in four 0.70 to 1.05, kt of 32 .. 48 1.02 times as
+// long, weight gradients, whose rows are half cache lines here, 1.08 times at 32; through registers, whose loads take a CU longer, up to
+// 1.04 times at 20 .. 24, weight gradients 1.05 at 15.
 inline bool pieces_side_by_side(const Plan& pl, int64_t I, int64_t J, int64_t R, bool whole_chunks, bool weight_gradient) {
   static const bool enabled = MPT_TUNABLE("MPT_PIECES", 1) != 0;      // tuning builds only
   const int64_t tiles = ((I + 31) / 32) * ((J + 31) / 32), kt = (R + BK - 1) / BK;
   return enabled && pl.splits >= 2 && pl.splits <= 8 && tiles <= (pl.splits <= 4 ? 2 * kCUs : kCUs) &&
-         kt <= (whole_chunks ? (weight_gradient ? 28 : 32) : (weight_gradient ? 20 : 24));
+         kt <= (whole_chunks ? (weight_gradient ? 28 : 32) : (weight_gradient ? 14 : 20));
 }
 
 // Whole-tile products that one launch of the streamed kernels could take, but that the ring kernels' smaller tiles take in less time

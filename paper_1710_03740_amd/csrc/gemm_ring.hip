@@ -733,10 +733,11 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) __attribute__((amdgpu_w
 // on lines), so further stages in flight give nothing (two sets of registers: 24.4 us).
 // APART: the second operand of a stage is fetched when the first is there (operands_apart).
 template <class AOp, class BOp, int BM, int BN, int WM, int WN, bool CUT, bool APART>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_any(RingMatSrc A, RingMatSrc B, Problem pb, Epilogue ep, int cut) {
-  static_assert((BM / WM) * (BN / WN) == 4, "four wavefronts");
+__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_any(RingMatSrc A, RingMatSrc B, Problem pb, Epilogue ep, int cut) {
+  constexpr int WAVES = (BM / WM) * (BN / WN);
+  static_assert(WAVES == 4 || WAVES == 8, "wavefronts");
   constexpr int FM = WM / 16, FN = WN / 16, A_BYTES = BM * 128, STAGE = (BM + BN) * 128, LA = AOp::NB, LB = BOp::NB;
-  static_assert(2 * STAGE >= 4 * WM * WN * 4, "the store's buffers fit the slots");
+  static_assert(2 * STAGE >= WAVES * WM * WN * 4, "the store's buffers fit the slots");
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wm = wave / (BN / WN), wn = wave % (BN / WN);
@@ -840,7 +841,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // of the split reduction in one launch.  What bounds such a product is not the work but the chain: start, first fetch, one stage
 // after another, store.  The small tile gives four times the workgroups of a 64 x 64 one, the wavefronts side by side a chain of 2 to 4 stages
 // instead of up to 32, all of the operands are on their way at once, and there is no second launch.  256 x 1024 over 1024 8.6 -> 4.8 us, 256 x 10
-// over 1024 7.6 -> 5.3, 100 x 300 over 500 (through registers) 7.0 -> 5.1; 352 products (the rule, pieces_wavefronts) 0.78 of the time on average.
+// over 1024 7.6 -> 5.3, 100 x 300 over 500 (through registers) 7.0 -> 5.1; 352 products (pieces_side_by_side) 0.78 of the time on average.
 // Taken back: 32 x 64 and 64 x 64 tiles by four wavefronts 1.1 to 1.5 times as long; two pieces per wavefront for longer reductions,
 // where a few CUs' way to LDS bounds it and a split launch has those of more (64 x 64 over 4096 9.8 us, split 8.0).
 constexpr int kPiecesTile = 32;
@@ -1208,29 +1209,38 @@ int launch_ring(hipStream_t s, const typename AOp::Src& A, const typename BOp::S
   return MPT_OK;
 }
 
-template <bool A_RC, bool B_RC, bool ANY, bool CUT, bool OVER>
-int launch_any(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, RingTile tile, const Problem& pb, const Epilogue& ep, int cut) {
-  const dim3 grid((unsigned)((int64_t)pb.tiles_i * pb.tiles_j * pb.splits));
-  if constexpr (!CUT) {                                              // the cut sums of 128 x 128 tiles through registers would not fit the register file
-    if (tile != kRing64x64) {
-      hipLaunchKernelGGL((k_gemm_any<RegMat<A_RC, 128, ANY, 4, OVER && !A_RC>, RegMat<B_RC, 128, ANY, 4, OVER && !B_RC>, 128, 128, 64, 64, false, false>), grid, dim3(256), 2 * 256 * 128, s,
-                         A, B, pb, ep, 0);
-      MPT_LAUNCH_CHECK();
-      return MPT_OK;
-    }
-  }
-  typedef RegMat<A_RC, 64, ANY, 4, OVER && !A_RC> AOp;
-  typedef RegMat<B_RC, 64, ANY, 4, OVER && !B_RC> BOp;
-  if constexpr (A_RC && !ANY) {
-    if (operands_apart(A_RC, B_RC, grid.x, pb.ktiles_per_split)) {
-      hipLaunchKernelGGL((k_gemm_any<AOp, BOp, 64, 64, 32, 32, CUT, true>), grid, dim3(256), 2 * 128 * 128, s, A, B, pb, ep, cut);
-      MPT_LAUNCH_CHECK();
-      return MPT_OK;
-    }
-  }
-  hipLaunchKernelGGL((k_gemm_any<AOp, BOp, 64, 64, 32, 32, CUT, false>), grid, dim3(256), 2 * 128 * 128, s, A, B, pb, ep, cut);
+template <class AOp, class BOp, int BM, int BN, int WM, int WN, bool CUT, bool APART = false>
+int launch_any_of(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, const Problem& pb, const Epilogue& ep, int cut) {
+  hipLaunchKernelGGL((k_gemm_any<AOp, BOp, BM, BN, WM, WN, CUT, APART>), dim3((unsigned)((int64_t)pb.tiles_i * pb.tiles_j * pb.splits)), dim3((BM / WM) * (BN / WN) * 64),
+                     2 * (BM + BN) * 128, s, A, B, pb, ep, cut);
   MPT_LAUNCH_CHECK();
   return MPT_OK;
+}
+
+// Eight wavefronts where a workgroup has its CU to itself, as in the ring (launch_plain), and for one more reason: each has half the loads
+// to send out and to put away.  70 such products 0.80 to 0.96 of the time of four wavefronts (1548 x 698 over 2805 29.7 -> 24.7 us, 255 x 290 over 2265 10.2 -> 9.7);
+// where CUs are shared 0.95 to 1.2 times as long.
+template <bool A_RC, bool B_RC, bool ANY, bool CUT, bool OVER>
+int launch_any(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, RingTile tile, const Problem& pb, const Epilogue& ep, int cut) {
+  constexpr bool AO = OVER && !A_RC, BO = OVER && !B_RC;
+  const int64_t workgroups = (int64_t)pb.tiles_i * pb.tiles_j * pb.splits;
+  const bool alone = workgroups <= kCUs;
+  if constexpr (!CUT) {                                              // the cut sums of 128 x 128 tiles through registers would not fit the register file
+    if (tile != kRing64x64) {
+      if constexpr (!ANY) {
+        if (alone) return launch_any_of<RegMat<A_RC, 128, false, 8, AO>, RegMat<B_RC, 128, false, 8, BO>, 128, 128, 64, 32, false>(s, A, B, pb, ep, 0);
+      }
+      return launch_any_of<RegMat<A_RC, 128, ANY, 4, AO>, RegMat<B_RC, 128, ANY, 4, BO>, 128, 128, 64, 64, false>(s, A, B, pb, ep, 0);
+    }
+  }
+  if constexpr (!ANY) {
+    if (alone) return launch_any_of<RegMat<A_RC, 64, false, 8, AO>, RegMat<B_RC, 64, false, 8, BO>, 64, 64, 32, 16, CUT>(s, A, B, pb, ep, cut);
+  }
+  if constexpr (A_RC && !ANY) {
+    if (operands_apart(A_RC, B_RC, workgroups, pb.ktiles_per_split))
+      return launch_any_of<RegMat<A_RC, 64, false, 4, AO>, RegMat<B_RC, 64, false, 4, BO>, 64, 64, 32, 32, CUT, true>(s, A, B, pb, ep, cut);
+  }
+  return launch_any_of<RegMat<A_RC, 64, ANY, 4, AO>, RegMat<B_RC, 64, ANY, 4, BO>, 64, 64, 32, 32, CUT>(s, A, B, pb, ep, cut);
 }
 
 template <class AOp, class BOp, int G, bool REGS>

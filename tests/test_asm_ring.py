@@ -31,7 +31,7 @@ def test_ring_kernels_keep_in_flight_read_registers_untouched(assembly):
     for name, lines in asm_check.kernels(assembly, r"k_gemm_(ring|any|pieces)"):
         found = asm_check.check_kernel(lines)
         assert not found, "%s: %s" % (name, found[:5])
-        assert sum("v_mfma" in l for l in lines) >= 8
+        assert sum("v_mfma" in l for l in lines) >= (4 if "ELi32ELi16E" in name else 8)      # (two blocks per half stage where a wavefront has 32 x 16)
         n += 1
     assert n >= 15
 

@@ -138,8 +138,8 @@ def test_products_whose_pieces_are_summed_side_by_side(planner):
     """One piece per wavefront, a workgroup or, of four wavefronts, two per CU, and a short reduction; never without a workspace."""
     planned, _, L = planner
     for (I, J, R), whole, wgrad, want in (((256, 1024, 1024), 1, 0, 1), ((256, 1056, 1024), 1, 0, 0), ((256, 10, 1024), 0, 0, 1), ((256, 2048, 512), 1, 0, 1), ((256, 2080, 512), 1, 0, 0), ((64, 64, 2048), 1, 0, 1),
-                                          ((64, 64, 2049), 1, 0, 0), ((64, 64, 1792), 1, 1, 1), ((64, 64, 1793), 1, 1, 0), ((65, 63, 1536), 0, 0, 1), ((65, 63, 1537), 0, 0, 0),
-                                          ((65, 63, 1280), 0, 1, 1), ((65, 63, 1281), 0, 1, 0), ((64, 64, 192), 1, 0, 0), ((64, 64, 256), 1, 0, 1), ((512, 1024, 256), 1, 0, 1),
+                                          ((64, 64, 2049), 1, 0, 0), ((64, 64, 1792), 1, 1, 1), ((64, 64, 1793), 1, 1, 0), ((65, 63, 1280), 0, 0, 1), ((65, 63, 1281), 0, 0, 0),
+                                          ((65, 63, 896), 0, 1, 1), ((65, 63, 897), 0, 1, 0), ((64, 64, 192), 1, 0, 0), ((64, 64, 256), 1, 0, 1), ((512, 1024, 256), 1, 0, 1),
                                           ((512, 1032, 256), 1, 0, 0)):
         assert L.pieces(I, J, R, 1, whole, wgrad) == want, (I, J, R)
         assert not L.pieces(I, J, R, 0, whole, wgrad)

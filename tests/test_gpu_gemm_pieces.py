@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 # (M, N, K): forward, input and weight gradient of each reduce over K, N, M.  2 .. 8 pieces, so four and eight wavefronts; rows and columns below, at and
 # above a tile of 32; last columns of 1, 2 and 3; a last piece shorter than the others; rows of fewer than 8 elements
 SIZES = [(129, 33, 31), (256, 10, 1024), (31, 257, 192), (33, 323, 130), (64, 512, 512), (1000, 24, 264), (97, 1100, 1030), (200, 2048, 40), (300, 5, 387),
-         (190, 3, 7), (1, 1536, 1), (1280, 34, 1023), (500, 100, 1408), (200, 40, 1024)]
+         (190, 3, 7), (1, 1536, 1), (1280, 34, 1023), (500, 100, 1408), (200, 40, 1024), (640, 33, 100)]
 LAYOUTS = [(0, 0), (8, 16), (1, 0), (3, 5)]
 
 
