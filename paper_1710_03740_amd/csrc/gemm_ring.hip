@@ -2,10 +2,11 @@
 // sizes, narrow outputs, small matrices, and 3x3 convolutions with any channel count (paper Sec. 3.1, 3.3).  gfx950 only.
 //
 //   k_gemm_ring  operands in 16-byte aligned pieces: global -> LDS directly, through a ring of stages of reduction depth 64;
-//   k_gemm_any   any alignment and stride: the same pieces through registers with 2-byte aligned 16-byte loads.
+//   k_gemm_any   any alignment and stride: the same pieces through registers with 2-byte aligned 16-byte loads;
+//   k_gemm_pieces  few tiles over short reductions: either way, the pieces of a sum side by side.
 //
-// Both hold the operands in LDS as gemm.hip's streamed kernels do (reduction-contiguous rows of 128 bytes, or
-// outer-contiguous rows read with the transposing LDS read), so no operand is transposed in registers, and both work on
+// They hold the operands in LDS as gemm.hip's streamed kernels do (reduction-contiguous rows of 128 bytes, or
+// outer-contiguous rows read with the transposing LDS read), so no operand is transposed in registers; the first two work on
 // four wavefronts per workgroup with two workgroups on a CU, which cover each other's barriers, fills and stores, or eight
 // where a workgroup has its CU to itself.
 //
