@@ -198,6 +198,19 @@ inline bool operands_apart(bool a_rc, bool b_rc, int64_t workgroups, int ktiles)
 // same either way, 1146 x 1602 over 330 9.3 and 9.3, over 390 10.0 and 9.7, over 520 11.9 and 11.1.
 inline bool edges_read_over(int ktiles, bool ragged) { return ragged && ktiles >= 5; }
 
+// Products through registers that eight wavefronts of half the block take, not four: where a workgroup has its CU to itself, as in the ring
+// (launch_plain), and for one more reason, each has half the loads to send out and to put away.  70 such products 0.80 to 0.96 of the time
+// of four wavefronts (1548 x 698 over 2805 29.7 -> 24.7 us, 255 x 290 over 2265 10.2 -> 9.7); where CUs are shared 0.95 to 1.2 times as long.
+// Over one stage what the second four wavefronts save is the second trip of the store, and they take 0.1 to 0.3 us to start.  In FP16 there
+// is no such trip up to 16 rows (97 products 0.97 to 1.07 times as long, 1.03 on average), and it costs little where at most one of the last
+// columns goes out by itself, or up to three in a wavefront that has no others (94 products 1.01 times on average, 833 x 65 over 34 3.42 -> 3.72 us;
+// 17 columns in a tile, of which the one then has a wavefront of its own, 0.98).  The other 355 took 0.94 of the time, FP32 outputs 0.96, added to 0.88.
+inline int any_wavefronts(int64_t workgroups, int64_t I, int64_t J, int ktiles, bool fp16) {
+  if (workgroups > kCUs) return 4;
+  const int64_t c = J % 32;
+  return fp16 && ktiles == 1 && (I <= 16 || c <= 3 || (c % 8 <= 1 && c != 17)) ? 4 : 8;
+}
+
 // Convolutions (forward and input gradient) that k_conv_patch takes: a filter of at most 64 x 64 channels, rows of which two patches
 // and the outputs fit LDS, and pixels for half the CUs: 32768 of them (128 tiles) with 64 channels 13.3 -> 9.8 us, where the ring kernels
 // still work unsplit.  Measured at 23 sizes of 8 .. 64 channels: 0.67 to 1.0 of the ring kernels' time.

@@ -1218,24 +1218,21 @@ int launch_any_of(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, const
   return MPT_OK;
 }
 
-// Eight wavefronts where a workgroup has its CU to itself, as in the ring (launch_plain), and for one more reason: each has half the loads
-// to send out and to put away.  70 such products 0.80 to 0.96 of the time of four wavefronts (1548 x 698 over 2805 29.7 -> 24.7 us, 255 x 290 over 2265 10.2 -> 9.7);
-// where CUs are shared 0.95 to 1.2 times as long.
 template <bool A_RC, bool B_RC, bool ANY, bool CUT, bool OVER>
 int launch_any(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, RingTile tile, const Problem& pb, const Epilogue& ep, int cut) {
   constexpr bool AO = OVER && !A_RC, BO = OVER && !B_RC;
   const int64_t workgroups = (int64_t)pb.tiles_i * pb.tiles_j * pb.splits;
-  const bool alone = workgroups <= kCUs;
+  const bool eight = !ANY && any_wavefronts(workgroups, pb.I, pb.J, pb.ktiles_per_split, ep.mode == 0) == 8;
   if constexpr (!CUT) {                                              // the cut sums of 128 x 128 tiles through registers would not fit the register file
     if (tile != kRing64x64) {
       if constexpr (!ANY) {
-        if (alone) return launch_any_of<RegMat<A_RC, 128, false, 8, AO>, RegMat<B_RC, 128, false, 8, BO>, 128, 128, 64, 32, false>(s, A, B, pb, ep, 0);
+        if (eight) return launch_any_of<RegMat<A_RC, 128, false, 8, AO>, RegMat<B_RC, 128, false, 8, BO>, 128, 128, 64, 32, false>(s, A, B, pb, ep, 0);
       }
       return launch_any_of<RegMat<A_RC, 128, ANY, 4, AO>, RegMat<B_RC, 128, ANY, 4, BO>, 128, 128, 64, 64, false>(s, A, B, pb, ep, 0);
     }
   }
   if constexpr (!ANY) {
-    if (alone) return launch_any_of<RegMat<A_RC, 64, false, 8, AO>, RegMat<B_RC, 64, false, 8, BO>, 64, 64, 32, 16, CUT>(s, A, B, pb, ep, cut);
+    if (eight) return launch_any_of<RegMat<A_RC, 64, false, 8, AO>, RegMat<B_RC, 64, false, 8, BO>, 64, 64, 32, 16, CUT>(s, A, B, pb, ep, cut);
   }
   if constexpr (A_RC && !ANY) {
     if (operands_apart(A_RC, B_RC, workgroups, pb.ktiles_per_split))

@@ -22,6 +22,7 @@ extern "C" void ring(long I, long J, long R, int ws, int whole_chunks, int lines
   out[0] = r.tile; out[1] = r.splits; out[2] = r.ktiles_per_split; out[3] = r.cut;
 }
 extern "C" int over(int ktiles, int ragged) { return edges_read_over(ktiles, ragged != 0); }
+extern "C" int any_waves(long workgroups, long I, long J, int ktiles, int fp16) { return any_wavefronts(workgroups, I, J, ktiles, fp16 != 0); }
 extern "C" int pieces(long I, long J, long R, int ws, int whole_chunks, int weight_gradient) {
   return pieces_side_by_side(make_plan(I, J, R, ws != 0), I, J, R, whole_chunks != 0, weight_gradient != 0);
 }
@@ -53,6 +54,7 @@ def planner(tmp_path_factory):
     L.fp32_ring.argtypes = [ctypes.c_long, ctypes.c_long, ctypes.c_int]
     L.fp16_ring.argtypes = [ctypes.c_long] * 2
     L.pieces.argtypes = [ctypes.c_long] * 3 + [ctypes.c_int] * 3
+    L.any_waves.argtypes = [ctypes.c_long] * 3 + [ctypes.c_int] * 2
     L.patches.argtypes = [ctypes.c_long] * 5
     L.apart.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_long, ctypes.c_int]
     return lambda *a: call(L.planned, *a)[:2], lambda *a: call(L.ring, *a), L
@@ -216,6 +218,14 @@ def test_operands_through_registers_are_fetched_apart_where_that_is_faster(plann
             tile, splits, per, cut = planner[1](I, J, R, ws, 0, 0, PLAIN)
             if ws or op == "d" and K == 1409:                                # (without a workspace four workgroups on a CU are tiles of 128 x 128)
                 assert tile == 1 and bool(cut) == bool(ws) and apart(1, op == "d", -(-I // 64) * -(-J // 64) * splits, per), (op, M, N, K)
+
+
+def test_eight_wavefronts_through_registers_where_they_have_work(planner):
+    """Alone on a CU; over one stage only where the FP16 store would make a second trip that takes time (833 x 65 over 34 3.42 us by four, 3.72 by eight)."""
+    for workgroups, I, J, ktiles, fp16, want in ((256, 500, 500, 2, 1, 8), (257, 500, 500, 2, 1, 4), (1, 16, 62, 1, 1, 4), (1, 17, 62, 1, 1, 8), (28, 833, 65, 1, 1, 4), (28, 833, 65, 2, 1, 8),
+                                                 (28, 833, 65, 1, 0, 8), (1, 16, 62, 2, 1, 8), (1, 16, 62, 1, 0, 8), (54, 94, 1721, 1, 1, 4), (203, 393, 1827, 1, 1, 4),
+                                                 (1, 50, 17, 1, 1, 8), (1, 50, 19, 1, 1, 8), (1, 50, 24, 1, 1, 4), (1, 50, 20, 1, 1, 8)):
+        assert planner[2].any_waves(workgroups, I, J, ktiles, fp16) == want, (workgroups, I, J, ktiles, fp16)
 
 
 def test_ragged_edges_of_longer_reductions_are_read_over(planner):
