@@ -1524,7 +1524,8 @@ int run(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool aligned, i
     MPT_LAUNCH_CHECK();
     return MPT_OK;
   }
-  if (!ring_only && pieces_side_by_side(pl, I, J, R, aligned, !A_RC)) return launch_pieces_plain(s, A_RC, B_RC, A, B, aligned, pl.ktiles_per_split, pl.splits, I, J, R, ep);
+  if (!ring_only && pieces_side_by_side(pl, I, J, R, aligned, A_RC, B_RC))
+    return launch_pieces_plain(s, A_RC, B_RC, A, B, aligned, pl.ktiles_per_split, pl.splits, I, J, R, ep);
   Epilogue first = ep;
   if (pl.splits > 1) {
     first.out = ws; first.ld = J; first.mode = 3; first.flag = nullptr;
