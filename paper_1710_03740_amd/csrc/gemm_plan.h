@@ -156,21 +156,21 @@ inline RingPlan ring_plan(const Plan& pl, int64_t I, int64_t J, int64_t R, bool 
 
 // Products that k_gemm_pieces (gemm_ring.hip) takes: their sums are cut into pieces, 2 to 8 of them, their tiles of 32 x 32 are no more than
 // there are CUs (twice as many where four wavefronts hold the pieces, two workgroups then share a CU), and the reduction is short, since a
-// workgroup walks all of it.  1001 products of 8 .. 4000 rows and columns over 200 .. 2048, operands not in the L2, 0.80 of the time that the other
-// kernels take: aligned ones over kt <= 16 0.69, 17 .. 24 0.80, 25 .. 32 0.84; through registers over kt <= 8 0.75, 9 .. 14 0.82, 15 .. 20 0.86; two of them
-// longer by more than 0.02, 80 x 32 over 1992 (input gradient, 1.05) and 12 x 36 over 969 (the same, 1.04).
+// workgroup walks all of it.  1010 products of 8 .. 4000 rows and columns over 200 .. 2048, operands not in the L2, 0.80 of the time that the other
+// kernels take: aligned ones over kt <= 16 0.69, 17 .. 24 0.80, 25 .. 32 0.85; through registers over kt <= 8 0.75, 9 .. 14 0.82, 15 .. 20 0.86; three of them
+// longer by more than 0.02, as input gradients 80 x 32 over 1992 (1.05) and 12 x 36 over 969 (1.04), as weight gradient 88 x 376 over 1520 (1.03).
 // Tiles of 32 columns of an operand whose rows run along the output are half cache lines, and parts of two where the row is no multiple of
 // 32.  Such aligned forward products of more than 64 columns and weight gradients of more than 64 rows and columns therefore end earlier where they are
-// few tiles: beyond the line 31 took 0.90 to 1.09 of the time (32 x 240 over 1944 forward 7.25 and 7.90 us, 344 x 88 over 1776 as weight gradient 7.66
-// and 8.27; rows of a multiple of 32: 8 x 192 over 1824 0.88, 160 x 544 over 1952 0.92, 288 x 128 over 1544 as weight gradient 0.89).  From 96 tiles on
-// the partials, which the others write and read, cost more: 504 x 496 over 1720 0.72, 320 x 456 over 1840 0.74, 304 x 352 over 1744 0.94.
+// few tiles: beyond the line 22 took 0.96 to 1.09 of the time (32 x 240 over 1944 forward 7.25 and 7.90 us, 344 x 88 over 1776 as weight gradient 7.66
+// and 8.27; rows of a multiple of 32: 8 x 192 over 1824 0.88, 160 x 544 over 1952 0.92, 288 x 128 over 1544 as weight gradient 0.89).  From 80 tiles on
+// the partials, which the others write and read, cost more: 504 x 496 over 1720 0.72, 320 x 456 over 1840 0.74, 688 x 120 over 1888 0.90.
 // Beyond: 256 .. 512 tiles in eight wavefronts 0.96 to 1.03 times as fast, 512 .. 1024 in four 0.70 to 1.05; aligned over kt of 32 .. 48 1.02 times as
 // long, weight gradients 1.08 times at 32; through registers, whose loads take a CU longer, up to 1.04 times at 20 .. 24, weight gradients 1.05 at 15.
 inline int64_t pieces_longest(int64_t I, int64_t J, int64_t tiles, bool whole_chunks, bool a_rc, bool b_rc) {
   if (!whole_chunks) return a_rc ? 20 : 14;
-  const bool few = tiles < 96;
+  const bool few = tiles < 80;
   if (a_rc) return !b_rc && J > 64 && J % 32 != 0 && few ? 28 : 32;
-  return std::min(I, J) > 64 && (I % 32 != 0 || J % 32 != 0) && few ? 23 : 28;
+  return std::min(I, J) > 64 && (I % 32 != 0 || J % 32 != 0) && few ? 25 : 28;
 }
 inline bool pieces_side_by_side(const Plan& pl, int64_t I, int64_t J, int64_t R, bool whole_chunks, bool a_rc, bool b_rc) {
   static const bool enabled = MPT_TUNABLE("MPT_PIECES", 1) != 0;      // tuning builds only

@@ -157,7 +157,7 @@ def test_pieces_side_by_side_end_where_they_are_slower(planner):
     8.27 and 7.66; not where the reduction runs along the rows, where a row of the output is one line, or it is no part of two, or of many tiles."""
     fwd, dgrad, wgrad = (1, 0), (1, 1), (0, 0)
     for form, I, J, kt, want in ((fwd, 32, 240, 29, 0), (fwd, 32, 240, 28, 1), (fwd, 32, 64, 32, 1), (fwd, 32, 72, 29, 0), (fwd, 304, 592, 32, 1), (fwd, 256, 384, 32, 1), (fwd, 256, 376, 32, 1),
-                                 (fwd, 224, 376, 32, 0), (fwd, 224, 384, 32, 1), (dgrad, 32, 240, 32, 1), (dgrad, 32, 240, 33, 0), (wgrad, 344, 88, 24, 0), (wgrad, 344, 88, 23, 1), (wgrad, 288, 128, 28, 1), (wgrad, 288, 120, 24, 0), (wgrad, 280, 128, 24, 0), (wgrad, 344, 64, 28, 1),
+                                 (fwd, 192, 376, 32, 0), (fwd, 192, 384, 32, 1), (dgrad, 32, 240, 32, 1), (dgrad, 32, 240, 33, 0), (wgrad, 344, 88, 26, 0), (wgrad, 344, 88, 25, 1), (wgrad, 288, 128, 28, 1), (wgrad, 288, 120, 26, 0), (wgrad, 280, 128, 26, 0), (wgrad, 344, 64, 28, 1),
                                  (wgrad, 64, 344, 28, 1), (wgrad, 64, 344, 29, 0), (wgrad, 504, 496, 28, 1), (wgrad, 504, 496, 29, 0)):
         assert planner[2].pieces_of(I, J, 64 * kt, 1, 1, *form) == want, (form, I, J, kt)
 
