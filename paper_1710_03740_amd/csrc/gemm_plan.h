@@ -133,7 +133,7 @@ inline RingPlan ring_plan(const Plan& pl, int64_t I, int64_t J, int64_t R, bool 
       const double cost = ring_cost(c, tiles, I, J, per, splits, accumulate);
       if (cost < best.cost) best = RingPlan{tile, splits, per, cut, cost};
     };
-    // (k_gemm_any cuts the sums of 64 x 64 tiles only, see launch_plain; outputs of few enough 256 x 64 tiles to be split take 64 x 64 ones)
+    // (k_gemm_any cuts the sums of 64 x 64 tiles only, see launch_any; outputs of few enough 256 x 64 tiles to be split take 64 x 64 ones)
     const bool cuts = tile != kRing256x64 && (whole_chunks || tile == kRing64x64);
     if ((pl.splits == 1 || force_split <= 1) && (cuts || pieces == 0)) form(1, kt, pieces);
     if (pl.splits > 1 && force_split != 1) form(pl.splits, pl.ktiles_per_split, 0);
@@ -209,7 +209,7 @@ inline bool operands_apart(bool a_rc, bool b_rc, int64_t workgroups, int ktiles)
 inline bool edges_read_over(int ktiles, bool ragged) { return ragged && ktiles >= 5; }
 
 // Products through registers that eight wavefronts of half the block take, not four: where a workgroup has its CU to itself, as in the ring
-// (launch_plain), and for one more reason, each has half the loads to send out and to put away.  70 such products 0.80 to 0.96 of the time
+// (product_form), and for one more reason, each has half the loads to send out and to put away.  70 such products 0.80 to 0.96 of the time
 // of four wavefronts (1548 x 698 over 2805 29.7 -> 24.7 us, 255 x 290 over 2265 10.2 -> 9.7); where CUs are shared 0.95 to 1.2 times as long.
 // Over one stage what the second four wavefronts save is the second trip of the store, and they take 0.1 to 0.3 us to start.  In FP16 there
 // is no such trip up to 16 rows (97 products 0.97 to 1.07 times as long, 1.03 on average), and it costs little where at most one of the last
@@ -220,6 +220,25 @@ inline int any_wavefronts(int64_t workgroups, int64_t I, int64_t J, int ktiles, 
   const int64_t c = J % 32;
   return fp16 && ktiles == 1 && (I <= 16 || c <= 3 || (c % 8 <= 1 && c != 17)) ? 4 : 8;
 }
+
+// The instance that a product of the ring kernels is launched with.
+// Two slots let two workgroups share a CU, which cover each other's waits.  A workgroup that has its CU to itself has only its own loads and
+// its own wavefronts: four slots (2000 x 1000 over 3000 in 256 tiles of 128 x 64: 39 -> 25 us; with 752 workgroups four slots would cost a quarter)
+// and eight wavefronts of half the block, two to a SIMD, so that one reads its fragments while the other multiplies.  Over 39 such products
+// 0.85 to 0.98 of the time of four wavefronts (3000 x 1000 over 2000 27.2 -> 23.3 us, 744 x 3840 over 3944 45.4 -> 39.2); where CUs are shared 0.97 to
+// 1.4 times as long, and of 64 x 64 tiles, whose wavefronts would have 32 x 16 left, 0.93 to 1.04.
+// ordinary: rows of 8 elements and more whose strides fit 32-bit offsets; others through registers have instances of their own (any).
+struct ProductForm { int wavefronts, slots; bool any, over, apart; };   // slots: of the ring; 0 through registers
+inline ProductForm product_form(RingTile tile, bool a_rc, bool b_rc, bool whole_chunks, bool ordinary, int64_t workgroups, int64_t I, int64_t J, int ktiles, bool fp16) {
+  if (whole_chunks) {
+    const bool alone = workgroups <= kCUs;
+    return ProductForm{alone && tile != kRing64x64 ? 8 : 4, alone || tile == kRing64x64 ? 4 : 2, false, false, false};
+  }
+  if (!ordinary) return ProductForm{4, 0, true, false, false};
+  const bool over = edges_read_over(ktiles, (!a_rc && I % 8 != 0) || (!b_rc && J % 8 != 0));
+  return ProductForm{any_wavefronts(workgroups, I, J, ktiles, fp16), 0, false, over, tile == kRing64x64 && operands_apart(a_rc, b_rc, workgroups, ktiles)};
+}
+inline int pieces_wavefronts(int pieces) { return pieces > 4 ? 8 : 4; }   // of k_gemm_pieces
 
 // Convolutions (forward and input gradient) that k_conv_patch takes: a filter of at most 64 x 64 channels, rows of which two patches
 // and the outputs fit LDS, and pixels for half the CUs: 32768 of them (128 tiles) with 64 channels 13.3 -> 9.8 us, where the ring kernels

@@ -1219,24 +1219,21 @@ int launch_any_of(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, const
 }
 
 template <bool A_RC, bool B_RC, bool ANY, bool CUT, bool OVER>
-int launch_any(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, RingTile tile, const Problem& pb, const Epilogue& ep, int cut) {
+int launch_any(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, RingTile tile, const ProductForm& form, const Problem& pb, const Epilogue& ep, int cut) {
   constexpr bool AO = OVER && !A_RC, BO = OVER && !B_RC;
-  const int64_t workgroups = (int64_t)pb.tiles_i * pb.tiles_j * pb.splits;
-  const bool eight = !ANY && any_wavefronts(workgroups, pb.I, pb.J, pb.ktiles_per_split, ep.mode == 0) == 8;
   if constexpr (!CUT) {                                              // the cut sums of 128 x 128 tiles through registers would not fit the register file
     if (tile != kRing64x64) {
       if constexpr (!ANY) {
-        if (eight) return launch_any_of<RegMat<A_RC, 128, false, 8, AO>, RegMat<B_RC, 128, false, 8, BO>, 128, 128, 64, 32, false>(s, A, B, pb, ep, 0);
+        if (form.wavefronts == 8) return launch_any_of<RegMat<A_RC, 128, false, 8, AO>, RegMat<B_RC, 128, false, 8, BO>, 128, 128, 64, 32, false>(s, A, B, pb, ep, 0);
       }
       return launch_any_of<RegMat<A_RC, 128, ANY, 4, AO>, RegMat<B_RC, 128, ANY, 4, BO>, 128, 128, 64, 64, false>(s, A, B, pb, ep, 0);
     }
   }
   if constexpr (!ANY) {
-    if (eight) return launch_any_of<RegMat<A_RC, 64, false, 8, AO>, RegMat<B_RC, 64, false, 8, BO>, 64, 64, 32, 16, CUT>(s, A, B, pb, ep, cut);
+    if (form.wavefronts == 8) return launch_any_of<RegMat<A_RC, 64, false, 8, AO>, RegMat<B_RC, 64, false, 8, BO>, 64, 64, 32, 16, CUT>(s, A, B, pb, ep, cut);
   }
   if constexpr (A_RC && !ANY) {
-    if (operands_apart(A_RC, B_RC, workgroups, pb.ktiles_per_split))
-      return launch_any_of<RegMat<A_RC, 64, false, 4, AO>, RegMat<B_RC, 64, false, 4, BO>, 64, 64, 32, 32, CUT, true>(s, A, B, pb, ep, cut);
+    if (form.apart) return launch_any_of<RegMat<A_RC, 64, false, 4, AO>, RegMat<B_RC, 64, false, 4, BO>, 64, 64, 32, 32, CUT, true>(s, A, B, pb, ep, cut);
   }
   return launch_any_of<RegMat<A_RC, 64, ANY, 4, AO>, RegMat<B_RC, 64, ANY, 4, BO>, 64, 64, 32, 32, CUT>(s, A, B, pb, ep, cut);
 }
@@ -1267,25 +1264,22 @@ int launch_pieces(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool 
 
 template <bool A_RC, bool B_RC, bool CUT>
 int launch_plain(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool whole_chunks, RingTile tile, const Problem& pb, const Epilogue& ep, int cut) {
+  const ProductForm form = product_form(tile, A_RC, B_RC, whole_chunks, ordinary_rows(A_RC, B_RC, A, B), (int64_t)pb.tiles_i * pb.tiles_j * pb.splits, pb.I, pb.J,
+                                        pb.ktiles_per_split, ep.mode == 0);
   if (!whole_chunks) {
-    if (!ordinary_rows(A_RC, B_RC, A, B)) return launch_any<A_RC, B_RC, true, CUT, false>(s, A, B, tile, pb, ep, cut);
+    if (form.any) return launch_any<A_RC, B_RC, true, CUT, false>(s, A, B, tile, form, pb, ep, cut);
     if constexpr (!A_RC || !B_RC) {
-      if (edges_read_over(pb.ktiles_per_split, (!A_RC && A.O % 8 != 0) || (!B_RC && B.O % 8 != 0))) return launch_any<A_RC, B_RC, false, CUT, true>(s, A, B, tile, pb, ep, cut);
+      if (form.over) return launch_any<A_RC, B_RC, false, CUT, true>(s, A, B, tile, form, pb, ep, cut);
     }
-    return launch_any<A_RC, B_RC, false, CUT, false>(s, A, B, tile, pb, ep, cut);
+    return launch_any<A_RC, B_RC, false, CUT, false>(s, A, B, tile, form, pb, ep, cut);
   }
   if (tile == kRing64x64) return launch_ring<RingMat<A_RC, 64>, RingMat<B_RC, 64>, 64, 64, 32, 32, 4, CUT>(s, A, B, pb, ep, cut);
-  // Two slots let two workgroups share a CU, which cover each other's waits.  A workgroup that has its CU to itself has only its own loads and
-  // its own wavefronts: four slots (2000 x 1000 over 3000 in 256 tiles of 128 x 64: 39 -> 25 us; with 752 workgroups four slots would cost a quarter)
-  // and eight wavefronts of half the block, two to a SIMD, so that one reads its fragments while the other multiplies.  Over 39 such products
-  // 0.85 to 0.98 of the time of four wavefronts (3000 x 1000 over 2000 27.2 -> 23.3 us, 744 x 3840 over 3944 45.4 -> 39.2); where CUs are shared 0.97 to
-  // 1.4 times as long, and of 64 x 64 tiles, whose wavefronts would have 32 x 16 left, 0.93 to 1.04.
-  const bool alone = (int64_t)pb.tiles_i * pb.tiles_j * pb.splits <= kCUs;
+  const bool eight = form.wavefronts == 8;
   if (tile == kRing128x64) {
-    if (alone) return launch_ring<RingMat<A_RC, 128, 8>, RingMat<B_RC, 64, 8>, 128, 64, 32, 32, 4, CUT>(s, A, B, pb, ep, cut);
+    if (eight) return launch_ring<RingMat<A_RC, 128, 8>, RingMat<B_RC, 64, 8>, 128, 64, 32, 32, 4, CUT>(s, A, B, pb, ep, cut);
     return launch_ring<RingMat<A_RC, 128>, RingMat<B_RC, 64>, 128, 64, 64, 32, 2, CUT>(s, A, B, pb, ep, cut);
   }
-  if (alone) return launch_ring<RingMat<A_RC, 128, 8>, RingMat<B_RC, 128, 8>, 128, 128, 64, 32, 4, CUT>(s, A, B, pb, ep, cut);
+  if (eight) return launch_ring<RingMat<A_RC, 128, 8>, RingMat<B_RC, 128, 8>, 128, 128, 64, 32, 4, CUT>(s, A, B, pb, ep, cut);
   return launch_ring<RingMat<A_RC, 128>, RingMat<B_RC, 128>, 128, 128, 64, 64, 2, CUT>(s, A, B, pb, ep, cut);
 }
 
@@ -1360,7 +1354,7 @@ int launch_pieces_plain(hipStream_t s, bool a_rc, bool b_rc, const RingMatSrc& A
     if (a_rc) return b_rc ? launch_pieces<true, true, G>(s, A, B, whole_chunks, pb, ep, piece, pieces) : launch_pieces<true, false, G>(s, A, B, whole_chunks, pb, ep, piece, pieces);
     return launch_pieces<false, false, G>(s, A, B, whole_chunks, pb, ep, piece, pieces);
   };
-  return pieces > 4 ? go(std::integral_constant<int, 8>{}) : go(std::integral_constant<int, 4>{});
+  return pieces_wavefronts(pieces) == 8 ? go(std::integral_constant<int, 8>{}) : go(std::integral_constant<int, 4>{});
 }
 
 int launch_ring_conv(hipStream_t s, int op, int64_t Nb, int64_t H, int64_t W, int64_t C, int64_t Kf, const uint16_t* img, const uint16_t* other,

@@ -33,13 +33,15 @@ def test_ring_kernels_have_no_flat_accesses(tmp_path):
 
 def test_loads_of_rows_at_any_address_claim_the_alignment_of_their_elements(tmp_path):
     """In the compiler's intermediate form, where a load states its alignment: operands are FP16 at any address, outputs FP16 or FP32."""
-    text, kernels, beside, wide = compiled(tmp_path / "gemm_ring.ll", "-S", "-emit-llvm"), 0, 0, 0
+    text, kernels, beside = compiled(tmp_path / "gemm_ring.ll", "-S", "-emit-llvm"), 0, 0
     for m in re.finditer(r"^define [^\n]*?@(\w*k_gemm_(?:any|pieces)\w*)\(.*?^}", text, re.M | re.S):
-        kernels += "k_gemm_any" in m.group(1)
-        beside += "k_gemm_pieces" in m.group(1)
-        for ty, align in re.findall(r"= load (<\d+ x \w+>), ptr addrspace\(1\) .*?align (\d+)", m.group(0)):
-            wide += 1
-            assert int(align) <= (4 if "float" in ty else 2), "%s: load %s, align %s" % (m.group(1), ty, align)
-    # k_gemm_any: 3 operand layouts; 64 x 64 tiles, with and without cuts, and 128 x 128; four wavefronts or eight, of which each has half the loads; any extents (four
-    # wavefronts); edges read over in the 2 layouts that have them; 6 with operands apart.  k_gemm_pieces: 3 layouts, four or eight wavefronts, pieces, ordinary extents or any
-    assert kernels == 18 + 9 + 12 + 6 and beside == 18 and wide >= 8 * (kernels + beside)
+        name = m.group(1)
+        kernels += "k_gemm_any" in name
+        beside += "k_gemm_pieces" in name
+        loads = re.findall(r"= load (<\d+ x \w+>), ptr addrspace\(1\) .*?align (\d+)", m.group(0))
+        for ty, align in loads:
+            assert int(align) <= (4 if "float" in ty else 2), "%s: load %s, align %s" % (name, ty, align)
+        # four pieces of a stage and the first two stages ahead of the loop, half of them where eight wavefronts share a 64 x 64 tile; pieces side by side that go to
+        # LDS directly have the mask's and the old values' loads only
+        assert len(loads) >= (2 if "RingMat" in name else 8 if "ELi32ELi16E" in name else 16), name
+    assert kernels >= 40 and beside >= 18

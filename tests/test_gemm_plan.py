@@ -1,6 +1,7 @@
 """The planner of the matrix products (csrc/gemm_plan.h), compiled by itself for the host: which tile a product is launched with
 and which pieces its reduction is summed in."""
 import ctypes
+import math
 import os
 import random
 import shutil
@@ -25,6 +26,17 @@ extern "C" int over(int ktiles, int ragged) { return edges_read_over(ktiles, rag
 extern "C" int any_waves(long workgroups, long I, long J, int ktiles, int fp16) { return any_wavefronts(workgroups, I, J, ktiles, fp16 != 0); }
 extern "C" int pieces_of(long I, long J, long R, int ws, int whole_chunks, int a_rc, int b_rc) {
   return pieces_side_by_side(make_plan(I, J, R, ws != 0), I, J, R, whole_chunks != 0, a_rc != 0, b_rc != 0);
+}
+// The launch of a product of the ring kernels: pieces side by side with out[0] wavefronts, or out[0] == 0 and the ring's or the registers' form
+extern "C" void launched(long I, long J, long R, int ws, int whole_chunks, int lines, int a_rc, int b_rc, int far_rows, int fp16, int* out) {
+  const Plan p = make_plan(I, J, R, ws != 0);
+  const bool ordinary = (a_rc ? R : I) >= 8 && (b_rc ? R : J) >= 8 && !far_rows;
+  out[0] = pieces_of(I, J, R, ws, whole_chunks, a_rc, b_rc) ? pieces_wavefronts(p.splits) : 0;
+  const RingPlan r = ring_plan(p, I, J, R, whole_chunks != 0, lines != 0, false);
+  const int64_t tiles = ((I + ring_tile_rows(r.tile) - 1) / ring_tile_rows(r.tile)) * ((J + ring_tile_cols(r.tile) - 1) / ring_tile_cols(r.tile));
+  const ProductForm f = product_form(r.tile, a_rc != 0, b_rc != 0, whole_chunks != 0, ordinary, tiles * r.splits, I, J, r.ktiles_per_split, fp16 && r.splits == 1);
+  const int rest[9] = {r.tile, r.splits, r.cut, f.wavefronts, f.slots, f.any, f.over, f.apart, ordinary};
+  for (int k = 0; k < 9; ++k) out[1 + k] = rest[k];
 }
 extern "C" int pieces(long I, long J, long R, int ws, int whole_chunks, int weight_gradient) { return pieces_of(I, J, R, ws, whole_chunks, !weight_gradient, 0); }
 extern "C" int fp32_ring(long tiles256, long ktiles, int accumulate) { return ring_for_fp32(tiles256, ktiles, accumulate != 0); }
@@ -55,6 +67,7 @@ def planner(tmp_path_factory):
     L.fp32_ring.argtypes = [ctypes.c_long, ctypes.c_long, ctypes.c_int]
     L.fp16_ring.argtypes = [ctypes.c_long] * 2
     L.pieces.argtypes = [ctypes.c_long] * 3 + [ctypes.c_int] * 3
+    L.launched.argtypes = [ctypes.c_long] * 3 + [ctypes.c_int] * 7 + [ctypes.c_void_p]
     L.pieces_of.argtypes = [ctypes.c_long] * 3 + [ctypes.c_int] * 4
     L.any_waves.argtypes = [ctypes.c_long] * 3 + [ctypes.c_int] * 2
     L.patches.argtypes = [ctypes.c_long] * 5
@@ -122,22 +135,6 @@ def test_a_long_reduction_of_few_tiles_through_registers_is_split(planner):
         assert planner[1](I, J, R, 1, 0, 0, PLAIN)[1] > 1
 
 
-def test_every_form_of_a_product_launch_is_run_on_the_gpu(planner):
-    from test_gpu_gemm_ring import FORMS
-    rows_cols, seen = {0: (128, 128), 1: (64, 64), 3: (128, 64)}, set()
-    for op, M, N, K, ws in FORMS:
-        I, J, R = {"f": (M, N, K), "d": (M, K, N), "w": (K, N, M)}[op]
-        strides = {"f": (K, N), "d": (N, N), "w": (K, N)}[op]
-        whole = all(s % 8 == 0 for s in strides)
-        assert not (whole and I % 128 == J % 256 == R % 64 == 0)             # (the streamed kernels may have those)
-        tile, splits, _, cut = planner[1](I, J, R, ws, int(whole), int(all(s % 64 == 0 for s in strides)), PLAIN)
-        workgroups = -(-I // rows_cols[tile][0]) * -(-J // rows_cols[tile][1]) * splits
-        slots = (4 if tile == 1 or workgroups <= 256 else 2) if whole else 0     # launch_ring
-        seen.add((op, tile, slots, "split" if splits > 1 else "cut" if cut else "whole"))
-    forms = {(tile, slots, form) for tile, slots in ((1, 4), (3, 4), (3, 2), (0, 4), (0, 2), (1, 0), (0, 0)) for form in ("split", "cut", "whole")} - {(0, 0, "cut")}
-    assert seen == {(op,) + form for op in "fdw" for form in forms}
-
-
 def test_products_whose_pieces_are_summed_side_by_side(planner):
     """One piece per wavefront, a workgroup or, of four wavefronts, two per CU, and a short reduction; never without a workspace."""
     planned, _, L = planner
@@ -162,29 +159,63 @@ def test_pieces_side_by_side_end_where_they_are_slower(planner):
         assert planner[2].pieces_of(I, J, 64 * kt, 1, 1, *form) == want, (form, I, J, kt)
 
 
-def test_forms_of_a_product_launch_that_the_ring_tests_reach(planner):
-    """Those of FORMS whose pieces are summed side by side have stand-ins in RING_FORMS; the sizes of the edge tests take that route at both numbers of
-    wavefronts, aligned and through registers, in all passes."""
-    from test_gpu_gemm_pieces import RING_FORMS, SIZES
-    from test_gpu_gemm_ring import FORMS
-    rows_cols, seen, beside = {0: (128, 128), 1: (64, 64), 3: (128, 64)}, set(), set()
-    for op, M, N, K, ws in FORMS + RING_FORMS:
-        I, J, R = {"f": (M, N, K), "d": (M, K, N), "w": (K, N, M)}[op]
-        strides = {"f": (K, N), "d": (N, N), "w": (K, N)}[op]
-        whole = all(s % 8 == 0 for s in strides)
-        if planner[2].pieces(I, J, R, ws, int(whole), int(op == "w")):
-            continue
-        tile, splits, _, cut = planner[1](I, J, R, ws, int(whole), int(all(s % 64 == 0 for s in strides)), PLAIN)
-        workgroups = -(-I // rows_cols[tile][0]) * -(-J // rows_cols[tile][1]) * splits
-        seen.add((op, tile, (4 if tile == 1 or workgroups <= 256 else 2) if whole else 0, "split" if splits > 1 else "cut" if cut else "whole"))
-    forms = {(tile, slots, form) for tile, slots in ((1, 4), (3, 4), (3, 2), (0, 4), (0, 2), (1, 0), (0, 0)) for form in ("split", "cut", "whole")} - {(0, 0, "cut")}
-    assert seen == {(op,) + form for op in "fdw" for form in forms}
-    for M, N, K in SIZES:
-        for op, I, J, R, strides in (("f", M, N, K, (K, N)), ("d", M, K, N, (N, N)), ("w", K, N, M, (K, N))):
-            for whole in {all(s % 8 == 0 for s in strides), False}:
-                if planner[2].pieces(I, J, R, 1, int(whole), int(op == "w")):
-                    beside.add((op, whole, 4 if planner[0](I, J, R, 1)[0] <= 4 else 8))
-    assert beside == {(op, whole, g) for op in "fdw" for whole in (False, True) for g in (4, 8)}
+def instance(L, op, M, N, K, ws, pad=0, offset=0, fp16=1, far_rows=0):
+    """The launch of a product whose operands have rows `pad` elements longer than their contents and start `offset` elements from a whole line, as
+    run (gemm.hip) and launch_plain (gemm_ring.hip) choose it; None for whole tiles, which the streamed kernels may take."""
+    I, J, R = {"f": (M, N, K), "d": (M, K, N), "w": (K, N, M)}[op]
+    extents = {"f": (K, N), "d": (N, N), "w": (K, N)}[op]
+    whole = all(e % 8 == 0 for e in extents) and pad % 8 == 0 and offset % 8 == 0
+    lines = all((e + pad) % 64 == 0 for e in extents) and offset % 64 == 0
+    if whole and I % 128 == J % 256 == R % 64 == 0:
+        return None
+    out = (ctypes.c_int * 10)()
+    L.launched(I, J, R, ws, int(whole), int(lines), int(op != "w"), int(op == "d"), far_rows, fp16, ctypes.addressof(out))
+    side_by_side, tile, splits, cut, wavefronts, slots, any_rows, over, apart, ordinary = out
+    if side_by_side:
+        return op, "pieces", side_by_side, "aligned" if whole else "ordinary" if ordinary else "any"
+    return op, {0: 128, 1: 64, 3: 12864}[tile], "split" if splits > 1 else "cut" if cut else "whole", wavefronts, slots, any_rows, over, apart
+
+
+def test_every_instance_of_a_product_launch_is_run_on_the_gpu(planner):
+    """With exact sums: each kernel instance that some product of up to 8192 rows, columns and reduction is launched with, in each pass and with its sums split, cut
+    and whole, by tile, wavefronts, slots, kind of rows, edges read over and operands apart; the pieces side by side at both numbers of wavefronts."""
+    from test_gpu_gemm_pieces import LAYOUTS as PIECES_LAYOUTS, RING_FORMS, SIZES as PIECES_SIZES
+    from test_gpu_gemm_ring import APART, FORMS, INSTANCES, LAYOUTS, SIZES
+    L, run = planner[2], set()
+    products = [f + (0, 0) for f in FORMS + INSTANCES + RING_FORMS] + [f + (ws, 0, 0) for f in APART for ws in (0, 1)]
+    products += [(op, *size, ws, *layout) for size in SIZES for layout in LAYOUTS if size[0] <= 1000 or layout in ((0, 0), (3, 5)) for op in "fdw" for ws in (0, 1)]
+    products += [(op, *size, 1, *layout) for size in PIECES_SIZES for layout in PIECES_LAYOUTS for op in "fdw"]
+    for product in products:
+        run |= {instance(L, *product, fp16=fp16) for fp16 in ((0, 1) if product[0] == "w" else (1,))}
+    run.discard(None)
+    for f in INSTANCES:                                                      # each stands for one that nothing else reaches
+        others = {instance(L, *p, fp16=fp16) for p in products if p[:5] != f for fp16 in ((0, 1) if p[0] == "w" else (1,))}
+        assert instance(L, *f) not in others, f
+    rng = random.Random(1)
+    for _ in range(120000):
+        top = rng.choice((512, 4096, 8192))
+        M, N, K = (int(2 ** rng.uniform(0, math.log2(top))) for _ in range(3))
+        if rng.random() < 0.5:
+            M, N, K = (max(8, n // 8 * 8) for n in (M, N, K))
+        if M * N * K < 6e10:
+            for op in "fdw":
+                got = instance(L, op, M, N, K, rng.randrange(2))
+                assert got is None or got in run, (got, op, M, N, K)
+    assert len(run) == 123
+    assert {k[1:] for k in run if k[1] == "pieces"} == {("pieces", g, kind) for g in (4, 8) for kind in ("aligned", "ordinary", "any")}
+
+
+def test_products_with_ordered_pieces_sum_them_side_by_side(planner):
+    from test_gpu_gemm_pieces import ORDERED
+    seen, pieces = set(), set()
+    for I, J, R in ORDERED:
+        for op, M, N, K in (("f", I, J, R), ("d", I, R, J)):
+            for pad in (0, 1):
+                got = instance(planner[2], op, M, N, K, 1, pad)
+                assert got[1] == "pieces", (op, I, J, R, pad)
+                seen.add(got)
+        pieces.add(planner[0](I, J, R, 1)[0])
+    assert seen == {(op, "pieces", g, kind) for op in "fd" for g in (4, 8) for kind in ("aligned", "ordinary")} and pieces == {2, 3, 4, 5, 7, 8}
 
 
 def test_every_form_of_a_convolution_launch_is_run_on_the_gpu(planner):
@@ -241,18 +272,8 @@ def test_eight_wavefronts_through_registers_where_they_have_work(planner):
 
 
 def test_ragged_edges_of_longer_reductions_are_read_over(planner):
-    """And the edge tests of the ring kernels run both forms: forward and weight gradients, in tiles of 64 x 64 cut and whole and of 128 x 128."""
-    from test_gpu_gemm_pieces import RING_FORMS
-    from test_gpu_gemm_ring import FORMS, SIZES
-    over, seen = planner[2].over, set()
+    over = planner[2].over
     assert [over(k, 1) for k in (1, 4, 5, 60)] == [0, 0, 1, 1] and not over(60, 0)
-    for op, M, N, K, ws in FORMS + RING_FORMS + [(op, *size, ws) for size in SIZES for op in "fw" for ws in (0, 1)]:
-        I, J, R = (M, N, K) if op == "f" else (K, N, M)
-        through_registers = (op, M, N, K, ws) not in FORMS + RING_FORMS or J % 8 or (K % 8 if op == "f" else I % 8)   # (SIZES are run with odd strides too)
-        if op in "fw" and through_registers and not planner[2].pieces(I, J, R, ws, 0, int(op == "w")):
-            tile, _, per, cut = planner[1](I, J, R, ws, 0, 0, PLAIN)
-            seen.add((op, tile, bool(cut), over(per, int(J % 8 != 0 or (op == "w" and I % 8 != 0)))))
-    assert {(op, tile, cut, o) for op in "fw" for tile, cut in ((1, False), (1, True), (0, False)) for o in (0, 1)} <= seen
 
 
 def test_whole_tiles_that_smaller_tiles_take_in_less_time(planner):

@@ -511,7 +511,13 @@ def test_smallest_outputs_over_the_longest_reductions():
     gemm_check(run_fwd(X, Wf, split=True), y, sa, s_, "fwd 256x1024 over 32768")
 
 
-@pytest.mark.parametrize("M,N,K", [(256, 1024, 1024), (256, 10, 1024), (100, 72, 2048), (512, 384, 4096), (256, 1024, 8192), (384, 768, 8192)])
+# Products with room for partials that one launch sums in their pieces all the same, side by side (test_gpu_gemm_pieces.py compares those bit for bit) or
+# by cutting its sums (test_gpu_gemm_cut.py)
+UNSPLIT = {("fwd", 256, 1024, 1024), ("dgrad", 256, 1024, 1024), ("wgrad", 256, 1024, 1024), ("fwd", 256, 10, 1024), ("wgrad", 256, 10, 1024), ("wgrad", 256, 10, 2048),
+           ("dgrad", 512, 384, 4096), ("wgrad", 512, 384, 4096), ("dgrad", 256, 1024, 8192), ("wgrad", 256, 1024, 8192)}
+
+
+@pytest.mark.parametrize("M,N,K", [(256, 1024, 1024), (256, 10, 1024), (256, 10, 2048), (100, 72, 2048), (512, 384, 4096), (256, 1024, 8192), (384, 768, 8192)])
 def test_split_reduction_adds_every_partial_in_split_order(M, N, K):
     """Few output tiles and a long reduction: the launcher splits the reduction and a second pass adds the FP32 partials
     up.  The partials stay in the caller's workspace as [split][I][J], so the stored FP16 result must be, bit for bit,
@@ -542,9 +548,10 @@ def test_split_reduction_adds_every_partial_in_split_order(M, N, K):
             splits = len(written)
             part = part[:splits]
             assert splits == 0 or not np.isnan(part).any()
+            assert (splits == 0) == ((name, M, N, K) in UNSPLIT), name
             if rep == 0 and splits == 0:
                 # the workspace size is an upper bound over the kernels the launcher may pick; this shape went
-                # through a whole-tile kernel without a split and left the workspace untouched
+                # through one launch without a split and left the workspace untouched
                 print("[split order] %s %dx%dx%d: not split" % (name, M, N, K), flush=True)
                 break
             acc = part[0].copy()

@@ -1,6 +1,6 @@
 """Products of few tiles whose pieces are summed side by side (k_gemm_pieces), at the edges of its tiles, stages, pieces and stores, and the
 ring kernels' forms at sizes that still reach them.  Operands of -1, 0 and 1 have exact sums in any order; windows as in test_gpu_gemm_ring.py.
-That the bits are those of the pieces added in order is test_gpu_gemm_cut.py's."""
+That the bits are those of the pieces added in order is checked here for FP16 results, in test_gpu_gemm_cut.py for FP32 weight gradients."""
 import numpy as np
 import pytest
 import torch
@@ -40,6 +40,43 @@ def test_edges(M, N, K, pad, offset):
     mpt.mpt_gemm_wgrad(x, g, out, accumulate=True, flag=flag, ws=ws_for(2, M, N, K))
     assert np.array_equal(host(out.contiguous()).astype(np.float64), 2 * dw) and outside_untouched(buf, out)
     assert int(flag.item()) == 0
+
+
+# (output rows, columns, reduction), forward and input gradient: two, three, four, five, seven and eight pieces, with and without a ragged last stage; whole 16-byte
+# pieces where the sizes have them (test_gemm_plan.py checks that all take this route, at both numbers of wavefronts)
+ORDERED = [(256, 10, 1024), (256, 1000, 1024), (100, 72, 1280), (40, 1000, 264), (300, 200, 424), (65, 63, 509), (264, 40, 640), (33, 35, 899), (31, 130, 1215)]
+
+
+@pytest.mark.parametrize("odd", [False, True])
+@pytest.mark.parametrize("I,J,R", ORDERED)
+def test_fp16_results_are_the_pieces_added_in_order(I, J, R, odd):
+    """Bit for bit: each planned piece as an FP32 product of its own (a weight gradient of the transposed operands, in one chain), added in FP32 and rounded once."""
+    gen = torch.Generator(device="cuda").manual_seed(I + 3 * J + 7 * R)
+    a, b = torch.empty(I, R, device="cuda").normal_(generator=gen).half(), torch.empty(R, J, device="cuda").normal_(generator=gen).half()
+    h = torch.empty(I, J, device="cuda").normal_(generator=gen).half()
+    pieces, total = mpt.mpt_gemm_workspace_bytes(mpt.OP_FWD, I, J, R) // (4 * I * J), None
+    rows = -(-(-(-R // 64)) // pieces) * 64
+    for r in range(0, R, rows):
+        part = torch.empty(I, J, device="cuda")
+        mpt.mpt_gemm_wgrad(a[:, r:r + rows].t().contiguous(), b[r:r + rows].contiguous(), part)
+        total = part if total is None else total + part
+    assert pieces >= 2 and -(-R // rows) == pieces
+    want = total.half()
+
+    def view(t):
+        return window(*t.shape, int(odd), 0, host16(t.contiguous()))[1]
+    x, w, g, wt, mask = view(a), view(b), view(a), view(b.t()), view(h)
+    for name, op, expect, call in (("fwd", 0, want, lambda o, ws: mpt.mpt_gemm_fwd(x, w, o, ws)), ("fwd relu", 0, want.clamp(min=0), lambda o, ws: mpt.mpt_gemm_fwd_relu(x, w, o, ws)),
+                                   ("dgrad", 1, want, lambda o, ws: mpt.mpt_gemm_dgrad(g, wt, o, ws)),
+                                   ("dgrad relu", 1, torch.where(h > 0, want, torch.zeros_like(want)), lambda o, ws: mpt.mpt_gemm_dgrad_relu(g, wt, mask, o, ws))):
+        print("in order", name, (I, J, R), odd, flush=True)
+        ws = ws_for(op, *((I, J, R) if op == 0 else (I, R, J)))
+        assert ws.numel() == pieces * I * J
+        ws.fill_(float("nan"))
+        out = torch.empty(I, J, device="cuda", dtype=torch.float16)
+        call(out, ws)
+        assert torch.isnan(ws).all()                                     # one launch, no partials
+        assert torch.equal(out, expect), name
 
 
 def test_strides_beyond_32_bit_offsets():

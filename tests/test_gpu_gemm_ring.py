@@ -71,8 +71,8 @@ def test_edges_of_tiles_stages_and_pieces(M, N, K, pad, offset):
         assert int(flag.item()) == 0
 
 
-# One product (pass, M, N, K, with workspace) for each form of launch that the planner chooses: operands in whole pieces (sizes are multiples of 8)
-# and through registers, tiles, two or four slots, split, cut and whole (test_gemm_plan.py counts them)
+# Products (pass, M, N, K, with workspace) for the forms of launch that the planner chooses: operands in whole pieces (sizes are multiples of 8) and through
+# registers, tiles, two or four slots, split, cut and whole; some now sum their pieces side by side, and RING_FORMS of test_gpu_gemm_pieces.py stands in for them
 FORMS = [("d", 577, 1549, 839, 1), ("d", 1415, 265, 2123, 0), ("d", 9, 211, 9, 1), ("d", 9, 329, 9, 1), ("d", 9, 9, 9, 0), ("d", 8048, 200, 800, 1),
          ("d", 672, 5904, 784, 1), ("d", 2888, 136, 2120, 0), ("d", 2336, 1488, 1040, 1), ("d", 776, 3104, 592, 1), ("d", 1168, 720, 2232, 0),
          ("d", 2888, 976, 1520, 1), ("d", 368, 2048, 648, 1), ("d", 136, 8, 11040, 0), ("d", 776, 216, 1328, 1), ("d", 344, 1320, 392, 1),
@@ -86,7 +86,16 @@ FORMS = [("d", 577, 1549, 839, 1), ("d", 1415, 265, 2123, 0), ("d", 9, 211, 9, 1
          ("w", 1304, 328, 424, 1), ("w", 8, 136, 7992, 0), ("w", 200, 8, 8, 1), ("w", 720, 8, 8, 1), ("w", 8, 8, 8, 0)]
 
 
-@pytest.mark.parametrize("op,M,N,K,split", FORMS)
+# And one for each instance through registers, or form of its launch, that neither those nor the edge tests reach: tiles, wavefronts, split, cut and whole, edges read
+# over, operands apart, rows of fewer than 8 elements, in four wavefronts beside other workgroups and in eight alone (test_gemm_plan.py counts them)
+INSTANCES = [("d", 590, 621, 449, 1), ("d", 771, 4059, 827, 1), ("d", 1048, 9, 6819, 0), ("d", 6857, 3, 1027, 0), ("f", 33, 5, 1293, 1), ("f", 70, 203, 2100, 1),
+             ("f", 300, 5, 1173, 1), ("f", 352, 321, 2302, 1), ("f", 424, 594, 613, 1), ("f", 538, 921, 1640, 1), ("f", 898, 4144, 1505, 0), ("f", 1001, 1999, 1503, 1),
+             ("f", 1054, 3264, 1313, 1), ("f", 1080, 283, 6950, 1), ("f", 1419, 4975, 3, 1), ("f", 2305, 264, 3827, 1), ("f", 2511, 1538, 1417, 0), ("f", 3005, 722, 271, 0),
+             ("f", 4968, 1415, 11, 1), ("w", 5, 2508, 2823, 1), ("w", 194, 781, 1280, 1), ("w", 258, 1485, 3449, 0), ("w", 265, 387, 7085, 1), ("w", 272, 645, 778, 1),
+             ("w", 321, 65, 130, 0), ("w", 821, 5, 300, 1), ("w", 901, 37, 5, 1), ("w", 2064, 38, 49, 1), ("w", 2386, 322, 326, 1), ("w", 4356, 774, 790, 1)]
+
+
+@pytest.mark.parametrize("op,M,N,K,split", FORMS + INSTANCES)
 def test_every_form_of_launch(op, M, N, K, split):
     g = torch.Generator(device="cuda").manual_seed(M + 3 * N + 7 * K)
     shapes = {"f": ((M, K), (K, N)), "d": ((M, N), (K, N)), "w": ((M, K), (M, N))}[op]
