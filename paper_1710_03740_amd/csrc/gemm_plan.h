@@ -212,13 +212,13 @@ inline bool edges_read_over(int ktiles, bool ragged) { return ragged && ktiles >
 // (product_form), and for one more reason, each has half the loads to send out and to put away.  70 such products 0.80 to 0.96 of the time
 // of four wavefronts (1548 x 698 over 2805 29.7 -> 24.7 us, 255 x 290 over 2265 10.2 -> 9.7); where CUs are shared 0.95 to 1.2 times as long.
 // Over one stage what the second four wavefronts save is the second trip of the store, and they take 0.1 to 0.3 us to start.  In FP16 there
-// is no such trip up to 16 rows (97 products 0.97 to 1.07 times as long, 1.03 on average), and it costs little where at most one of the last
-// columns goes out by itself, or up to three in a wavefront that has no others (94 products 1.01 times on average, 833 x 65 over 34 3.42 -> 3.72 us;
-// 17 columns in a tile, of which the one then has a wavefront of its own, 0.98).  The other 355 took 0.94 of the time, FP32 outputs 0.96, added to 0.88.
+// is no such trip up to 16 rows (97 products 0.97 to 1.07 times as long, 1.03 on average), and it costs little where the last columns are one to three that have a
+// wavefront to themselves either way (41 products 1.02 times on average, 833 x 65 over 34 3.42 -> 3.72 us).  The other 408 took 0.95 of the time, FP32
+// outputs 0.96, added to 0.88; where at most one of the last columns goes out by itself it is the same on average (69 products, 0.94 to 1.08).
 inline int any_wavefronts(int64_t workgroups, int64_t I, int64_t J, int ktiles, bool fp16) {
   if (workgroups > kCUs) return 4;
-  const int64_t c = J % 32;
-  return fp16 && ktiles == 1 && (I <= 16 || c <= 3 || (c % 8 <= 1 && c != 17)) ? 4 : 8;
+  const int64_t last = J % 32;
+  return fp16 && ktiles == 1 && (I <= 16 || (last >= 1 && last <= 3)) ? 4 : 8;
 }
 
 // The instance that a product of the ring kernels is launched with.
