@@ -273,7 +273,7 @@ def measure_configs(torch, mpt, np, dev, workloads):
         mag = torch.exp2(torch.empty(shape, device=dev).uniform_(lo, hi)) * scale
         return (mag * (torch.randint(0, 2, shape, device=dev) * 2 - 1)).half()
 
-    # ---- cfg 1: the whole 2-layer MLP step, device only (8 launches; latency bound)
+    # ---- cfg 1: the whole 2-layer MLP step, device only (7 launches; latency bound)
     c = workloads.mlp()
     x, lab = d16(c["x"]), torch.from_numpy(c["labels"]).to(dev)
     w1_32, w2_32 = torch.from_numpy(c["w1_32"].copy()).to(dev), torch.from_numpy(c["w2_32"].copy()).to(dev)
@@ -302,7 +302,7 @@ def measure_configs(torch, mpt, np, dev, workloads):
     with torch.cuda.graph(graph):
         mlp_step()
     t = timeit(graph.replay, reps=50)
-    mfma_row("cfg1 MLP 256x1024 -> 1024 -> 10", "whole step replayed from a HIP graph (the 8 launches back to back, no host work between them)", fl, t)
+    mfma_row("cfg1 MLP 256x1024 -> 1024 -> 10", "whole step replayed from a HIP graph (the 7 launches back to back, no host work between them)", fl, t)
     del graph, x, w1, w2, w1_32, w2_32
 
     # ---- cfg 3: projected-LSTM layer products at batch 256 (per timestep), and the time-batched weight gradient

@@ -100,10 +100,12 @@ constexpr int ring_tile_cols(RingTile t) { return t == kRing128x128 ? 128 : 64; 
 // What a launch takes, in us: a start; and on the busiest CUs, for each workgroup, its fill and its store (`each`) and a share per
 // stage of depth 64, which workgroups of one CU share.  Rows that do not start on cache lines (`lines` false) need two lines for
 // one line's data.  A split costs a second launch and its partials' way to memory and back.  Fitted to 648 products of 64 .. 16000
-// rows, columns and reductions at each tile and split: 97 % of the launches are within a fifth; the form chosen takes 0.5 to
-// 1.3 % more than the fastest on average and at worst a fifth.  (Without `each`, outputs of many tiles over one or two stages took
-// 64 x 64 tiles: 12816 x 984 over 72 22 us, in 128 x 128 tiles 14.5.)  Accumulating stores read 64 KiB per 128 x 128 tile first: 4000 x 3000
-// over 64 through registers 26.5 us so, in 64 x 64 tiles 21.4.
+// rows, columns and reductions at each tile and split.  Of 648 others, aligned ones: 97 % of the launches are within a fifth, the form chosen takes
+// 0.6 to 0.9 % more than the fastest on average and at worst a fifth.  Through registers the fit is that of four wavefronts also where
+// eight now take the product: its launches take 0.9 of the estimate on average and 70 % are within a fifth, the form chosen takes 2 % more than the
+// fastest on average, at worst half as much again (242 x 1223 over 967 as input gradient 15.0 us split, in one launch 9.7).  (Without `each`, outputs of
+// many tiles over one or two stages took 64 x 64 tiles: 12816 x 984 over 72 22 us, in 128 x 128 tiles 14.5.)  Accumulating stores read 64 KiB per 128 x 128
+// tile first: 4000 x 3000 over 64 through registers 26.5 us so, in 64 x 64 tiles 21.4.
 struct RingCost { double start, each, stage, alone = 1.0, old = 0.0; };   // alone: shares of a workgroup that has its CU to itself (what its waits
                                                                            // leave idle); old: more for `each` where the store adds to FP32 values
 inline constexpr RingCost kRing64[2] = {{2.3, 0.98, 0.24, 1.23, 0.8}, {2.0, 1.1, 0.2, 1.44, 0.8}}, kRing128x64Cost[2] = {{3.2, 0.89, 0.36, 1.04, 2.5}, {2.95, 1.04, 0.29, 1.23, 2.5}},
@@ -156,7 +158,7 @@ inline RingPlan ring_plan(const Plan& pl, int64_t I, int64_t J, int64_t R, bool 
 
 // Products that k_gemm_pieces (gemm_ring.hip) takes: their sums are cut into pieces, 2 to 8 of them, their tiles of 32 x 32 are no more than
 // there are CUs (twice as many where four wavefronts hold the pieces, two workgroups then share a CU), and the reduction is short, since a
-// workgroup walks all of it.  1010 products of 8 .. 4000 rows and columns over 200 .. 2048, operands not in the L2, 0.80 of the time that the other
+// workgroup walks all of it.  1010 products of 8 .. 4000 rows and columns over 200 .. 2048, operands not in the L2, 0.81 of the time that the other
 // kernels take: aligned ones over kt <= 16 0.69, 17 .. 24 0.80, 25 .. 32 0.85; through registers over kt <= 8 0.75, 9 .. 14 0.82, 15 .. 20 0.86; three of them
 // longer by more than 0.02, as input gradients 80 x 32 over 1992 (1.05) and 12 x 36 over 969 (1.04), as weight gradient 88 x 376 over 1520 (1.03).
 // Tiles of 32 columns of an operand whose rows run along the output are half cache lines, and parts of two where the row is no multiple of
@@ -203,9 +205,10 @@ inline bool operands_apart(bool a_rc, bool b_rc, int64_t workgroups, int ktiles)
   return a_rc && ((most == 4 && ktiles >= 20) || (most == 3 && b_rc && ktiles >= 32));
 }
 
-// Products through registers whose last columns are read over their rows' ends and masked (RegMat, OVER), not shifted: from 5 stages on.  Shorter
-// ones are faster shifted, since the masks' code is fetched too: 226 x 192 over 80 4.0 us, masked 4.5; 301 x 448 over 95 5.2 and 5.3; over 200 .. 260 the
-// same either way, 1146 x 1602 over 330 9.3 and 9.3, over 390 10.0 and 9.7, over 520 11.9 and 11.1.
+// Products through registers whose last columns are read over their rows' ends and masked (RegMat, OVER), not shifted: from 5 stages on.  Over fewer
+// there is nothing to gain, and the masks' code is fetched too: 1778 x 11 over 46 3.70 us, masked 3.84; 226 x 192 over 80 3.63 and 3.63, 301 x 448 over 95
+// 3.97 and 3.96; over six stages 1146 x 1602 over 330 8.84 and 8.87, over 13 600 x 1201 over 805 11.2 and 10.3, 1001 x 1999 over 1503 24.6 and 22.4,
+// weight gradient of 2003 x 1003 x 2005 35.3 and 29.5.
 inline bool edges_read_over(int ktiles, bool ragged) { return ragged && ktiles >= 5; }
 
 // Products through registers that eight wavefronts of half the block take, not four: where a workgroup has its CU to itself, as in the ring

@@ -57,7 +57,7 @@ struct Piece {
   __device__ static __forceinline__ int row(int wave, int lane, int k) { return (wave * NB + k) * RPB + lane / LPR; }
   __device__ static __forceinline__ int col(int wave, int lane, int k) {
     const int r = row(wave, lane, k), pc = lane % LPR;
-    if constexpr (RC) return (pc ^ ((r >> 1) & 7)) * 8;              // NB is even: the same for all even k, and for all odd k
+    if constexpr (RC) return (pc ^ ((r >> 1) & 7)) * 8;              // (with NB even: the same for all even k, and for all odd k)
     else return (2 * ((pc >> 1) ^ ring_key<BO>(r)) + (pc & 1)) * 8;
   }
 };
@@ -141,6 +141,7 @@ struct RingImg {
   typedef Piece<true, BO> P;
   static constexpr bool kRC = true;
   static constexpr int NB = P::NB;
+  static_assert(NB % 2 == 0, "two piece columns");
   const uint16_t* p[NB];           // the lane's pixel, centre tap
   uint32_t taps[NB];
   int W, Cc, sgn, wraps;
@@ -282,9 +283,8 @@ typedef uint32_t uint4u __attribute__((ext_vector_type(4), aligned(2)));
 typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t uint2u __attribute__((ext_vector_type(2), aligned(2)));
 
-// Drops the first `n` (0 .. 7) of 8 elements; zeros follow the others.  In 32-bit operations: a 64-bit shift whose amount lies in the last
-// register that a wavefront has been given, one of number 7 modulo 8, now and then takes its amount from elsewhere (a kernel of
-// exactly 128 registers with the amount in v127 gave wrong last stages in a few of its 1600 workgroups, every time).
+// Drops the first `n` (0 .. 7) of 8 elements; zeros follow the others.  In 32-bit operations: a trial instance of exactly 128 registers
+// whose 64-bit shifts had their amount in v127 gave wrong last stages in a few of its 1600 workgroups, the same ones every time, and right ones so.
 __device__ __forceinline__ uint4v drop_front(uint4v v, int n) {
   const bool four = (n & 4) != 0, two = (n & 2) != 0;
   const uint32_t bits = (uint32_t)(n & 1) * 16u;
@@ -311,8 +311,8 @@ __device__ __forceinline__ uint16_t one_from_global(const void* p) { return *(co
 // ANY: also rows of fewer than 8 elements, gathered element by element, and row strides too long for 32-bit offsets; kept apart, since
 // their branches around the loads cost the others a tenth (3999 x 1777 over 999 51 against 47 us).
 // OVER (OC, ragged edges): pieces that run over their row's end are read over it and masked where another row follows, which all but the last stage's
-// do.  Shifted at every stage as in the last one, they were what all other workgroups waited for: 600 x 1201 over 805 12.7 us, 11.6 so.  Not for a few stages:
-// a launch pays for code that it fetches once (1778 x 11 over 46 3.97 -> 4.24 us).
+// do.  Shifted at every stage as in the last one, they are what all other workgroups wait for: 600 x 1201 over 805 11.2 us, 10.3 so.  Not for a few stages:
+// a launch pays for code that it fetches once (edges_read_over).
 template <bool RC, int BO, bool ANY, int WAVES = 4, bool OVER = false>
 struct RegMat {
   static_assert(!(OVER && (RC || ANY)), "rows of 8 elements and more along the output");
@@ -585,7 +585,7 @@ __device__ __forceinline__ void store_tile(const Problem& pb, const Epilogue& ep
           }
       }
     };
-    // Adding to what is there: up to 16 reads in flight, all of a 64 x 64 block (16 KiB a wavefront), the 4 or 8 of smaller ones.  Two at a
+    // Adding to what is there: up to 16 reads in flight, all of a 64 x 64 block (16 KiB a wavefront), the 2, 4 or 8 of smaller ones.  Two at a
     // time, as the stores go out, were most of a short reduction's time (8192 x 1024 over 256 accumulated 20.0 -> 17.2 us; 14.2 without reading).
     if (ep.mode == 2) {
       constexpr int AHEAD = 16 < IT ? 16 : IT;
@@ -840,9 +840,10 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) __attribute__((amdgpu_w
 // Outputs of few tiles whose sums are cut into pieces (gemm_plan.h).  Every wavefront of a workgroup multiplies one whole 32 x 32 tile over
 // a piece of its own, with its own slots of LDS and no barrier, and the workgroup adds the pieces up in order at the end: the sums
 // of the split reduction in one launch.  What bounds such a product is not the work but the chain: start, first fetch, one stage
-// after another, store.  The small tile gives four times the workgroups of a 64 x 64 one, the wavefronts side by side a chain of 2 to 4 stages
-// instead of up to 32, all of the operands are on their way at once, and there is no second launch.  256 x 1024 over 1024 8.6 -> 4.8 us, 256 x 10
-// over 1024 7.6 -> 5.3, 100 x 300 over 500 (through registers) 7.0 -> 5.1; 352 products (pieces_side_by_side) 0.78 of the time on average.
+// after another, store.  The small tile gives four times the workgroups of a 64 x 64 one, the wavefronts side by side a chain of 2 to 8 stages
+// instead of up to 32, all of the operands are on their way at once or nearly, and there is no second launch.  256 x 1024 over 1024 8.6 -> 5.2 us, 256 x 10
+// over 1024 7.5 -> 5.1, 100 x 300 over 500 (through registers) 7.6 -> 5.2; 1010 products (pieces_side_by_side) 0.81 of the time on average.
+// Two or three pieces leave wavefronts idle, as do five to seven of eight, which still hold their LDS.
 // Taken back: 32 x 64 and 64 x 64 tiles by four wavefronts 1.1 to 1.5 times as long; two pieces per wavefront for longer reductions,
 // where a few CUs' way to LDS bounds it and a split launch has those of more (64 x 64 over 4096 9.8 us, split 8.0).
 constexpr int kPiecesTile = 32;
