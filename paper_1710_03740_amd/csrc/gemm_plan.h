@@ -64,11 +64,11 @@ inline size_t plan_ws_bytes(const Plan& p, int64_t I, int64_t J) {
   return p.splits > 1 ? (size_t)p.splits * (size_t)I * (size_t)J * sizeof(float) : 0;
 }
 
-// A second way to split: 128 x 256 tiles of the streamed kernel, for outputs whose row count is an odd multiple of 128
-// (256-row tiles would compute a padded half tile: 128 x 4096 x 4096 forward 27.5 -> 18.8 us) and whose time the memory
+// A second way to split weight gradients that are kept in FP32: 128 x 256 tiles of the streamed kernel, for outputs whose row count is an odd multiple of
+// 128 (256-row tiles would compute a padded half tile: 128 x 4096 over 4096 27.5 -> 18.8 us) and whose time the memory
 // traffic decides: few tiles and an arithmetic intensity (every operand and the result once) below the ridge of
 // 2.5 PFLOP/s / 8 TB/s.  (For row counts that are multiples of 256 it measured within 2 % of the 256-row plans either
-// way - gate input gradient 55.8 against 55.5 us, projection 22.7 against 23.2 - and is used only as noted below.)
+// way, and is used only as noted below.  FP16 results, which once were split so too, take fp16_plan's pieces: 128 x 4096 over 4096 14.1 us, 256 x 1024 over 32768 26.6.)
 // Depends on the shape only, so that the workspace size can be asked for beforehand.
 inline bool plan_split128(int64_t I, int64_t J, int64_t R, Plan& p) {
   if ((I % 128) || (J % 256) || (R % 64)) return false;
@@ -154,6 +154,53 @@ inline RingPlan ring_plan(const Plan& pl, int64_t I, int64_t J, int64_t R, bool 
   if (whole_chunks && !conv_wgrad) consider(kRing128x64, kRing128x64Cost[lines]);
   consider(kRing128x128, conv_wgrad ? kConvWgrad128 : whole_chunks ? kRing128[lines] : kAny128);
   return best;
+}
+
+// FP16 outputs are summed in fewer and longer pieces than make_plan's, which let an FP32 result keep short chains: rounded to 11 bits a result
+// does not show whether its chain had 512 terms or 4096.  What counts is that the workgroups fill the chip once: the second half of make_plan's
+// partials (16 MB for 256 x 1024 over 8192) bought nothing but their way to memory and back.  Candidates are, for each tile, the splits that make one or two
+// workgroups per CU, make_plan's own and none; never more than make_plan's, so the workspace it asks for holds them.  110 aligned products of
+// 32 .. 4096 rows and columns over 512 .. 32768 0.6 % slower than the best of them on average, 100 odd ones over 256 .. 4096 0.5 %; against make_plan's
+// pieces 256 x 1024 over 8192 15.9 -> 13.5 us, 512 x 1024 over 8192 28.5 -> 18.7, 1000 x 600 over 4000 16.5 -> 15.6, 694 x 613 over 1711 16.0 -> 12.4,
+// 1610 x 2163 over 3908 67 -> 48 (the costs of operands through registers above are those of four wavefronts; these are of eight where there is a CU for each).
+inline constexpr RingCost kAny64Fp16 = {3.9, 0.43, 0.30, 1.27}, kAny128x64Fp16 = {4.0, 1.1, 0.45, 1.1}, kAny128Fp16 = {4.2, 2.3, 0.67, 1.0};
+struct Fp16Form { RingTile tile; int splits, ktiles_per_split; double cost; };
+// The cheapest tile, and split of at most `most`; or the cheapest tile for pieces of `per` tiles of 64 if that is not 0.
+inline Fp16Form fp16_form(int64_t I, int64_t J, int64_t R, int most, int per, bool whole_chunks, bool lines) {
+  const int kt = (int)((R + BK - 1) / BK);
+  Fp16Form best{kRing64x64, 1, kt, 1e30};
+  auto consider = [&](RingTile tile, const RingCost& c) {
+    const int64_t tiles = ((I + ring_tile_rows(tile) - 1) / ring_tile_rows(tile)) * ((J + ring_tile_cols(tile) - 1) / ring_tile_cols(tile));
+    auto form = [&](int each) {
+      const int splits = (kt + each - 1) / each;                       // no empty split
+      const double cost = ring_cost(c, tiles, I, J, each, splits);
+      if (cost < best.cost) best = Fp16Form{tile, splits, each, cost};
+    };
+    if (per > 0) return form(per);
+    form(kt);
+    const int once = tiles > kCUs ? 0 : kCUs / (int)tiles, twice = tiles > 2 * kCUs ? 0 : 2 * kCUs / (int)tiles;
+    if (once > 1 && once < most) form((kt + once - 1) / once);
+    if (twice > 1 && twice < most) form((kt + twice - 1) / twice);
+    form((kt + most - 1) / most);
+  };
+  consider(kRing64x64, whole_chunks ? kRing64[lines] : kAny64Fp16);
+  consider(kRing128x64, whole_chunks ? kRing128x64Cost[lines] : kAny128x64Fp16);
+  consider(kRing128x128, whole_chunks ? kRing128[lines] : kAny128Fp16);
+  return best;
+}
+// The pieces of an FP16 result (fp16_planned: or make_plan's), from its shape alone, so that it has the same bits at every alignment.  whole_rows: the operands' rows are whole 16-byte
+// pieces where they are aligned.  Where the order of a sum shows beyond its last bit the pieces stay make_plan's: a ReLU's results (relu) and what a convolution's
+// normalisation makes of them are zero or not by the sign of a sum near zero, and with them go whole elements of the gradient.  So forward products over a multiple of
+// 9 x 8 stay too, which may be a convolution's gathered window and then have its bits, and weight gradients of so many columns (the convolutions' own, whose pixels
+// are gathered, are faster with more workgroups per CU: 64 x 56 x 56 with 64 channels 41 us in 64 pieces, 50 in 28).
+inline bool fp16_planned(const Plan& pl, int64_t J, int64_t R, bool forward, bool weight_gradient, bool relu) {
+  return !(pl.splits == 1 || relu || (forward && R % 72 == 0) || (weight_gradient && J % 72 == 0));
+}
+// The launch of an FP16 result: its pieces, in the tile that is the cheapest for the operands at hand.
+inline Fp16Form fp16_launch(const Plan& pl, int64_t I, int64_t J, int64_t R, bool whole_rows, bool whole_chunks, bool lines) {
+  if (pl.splits == 1) return fp16_form(I, J, R, 1, pl.ktiles_per_split, whole_chunks, lines);
+  const Fp16Form f = fp16_form(I, J, R, pl.splits, 0, whole_rows, false);
+  return whole_chunks == whole_rows && !lines ? f : fp16_form(I, J, R, f.splits, f.ktiles_per_split, whole_chunks, lines);
 }
 
 // Products that k_gemm_pieces (gemm_ring.hip) takes: their sums are cut into pieces, 2 to 8 of them, their tiles of 32 x 32 are no more than

@@ -1223,6 +1223,12 @@ template <bool A_RC, bool B_RC, bool ANY, bool CUT, bool OVER>
 int launch_any(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, RingTile tile, const ProductForm& form, const Problem& pb, const Epilogue& ep, int cut) {
   constexpr bool AO = OVER && !A_RC, BO = OVER && !B_RC;
   if constexpr (!CUT) {                                              // the cut sums of 128 x 128 tiles through registers would not fit the register file
+    if (tile == kRing128x64) {
+      if constexpr (!ANY) {
+        if (form.wavefronts == 8) return launch_any_of<RegMat<A_RC, 128, false, 8, AO>, RegMat<B_RC, 64, false, 8, BO>, 128, 64, 32, 32, false>(s, A, B, pb, ep, 0);
+      }
+      return launch_any_of<RegMat<A_RC, 128, ANY, 4, AO>, RegMat<B_RC, 64, ANY, 4, BO>, 128, 64, 64, 32, false>(s, A, B, pb, ep, 0);
+    }
     if (tile != kRing64x64) {
       if constexpr (!ANY) {
         if (form.wavefronts == 8) return launch_any_of<RegMat<A_RC, 128, false, 8, AO>, RegMat<B_RC, 128, false, 8, BO>, 128, 128, 64, 32, false>(s, A, B, pb, ep, 0);
@@ -1336,7 +1342,7 @@ int launch_conv(hipStream_t s, int op, int64_t Nb, int64_t H, int64_t W, int64_t
 int launch_ring_plain(hipStream_t s, bool a_rc, bool b_rc, const RingMatSrc& A, const RingMatSrc& B, bool whole_chunks, RingTile tile,
                       int ktiles_per_split, int cut, int I, int J, int R, const Epilogue& ep) {
   // the forms that there are kernels for, and ring_plan asks for no others
-  if (tile != kRing64x64 && (whole_chunks ? tile == kRing256x64 : tile != kRing128x128 || cut > 0)) return MPT_ERR_ARG;
+  if (tile == kRing256x64 || (tile != kRing64x64 && !whole_chunks && cut > 0)) return MPT_ERR_ARG;
   const Problem pb = ring_problem(tile, ktiles_per_split, I, J, R);
   if (cut > 0) {
     if (a_rc) return b_rc ? launch_plain<true, true, true>(s, A, B, whole_chunks, tile, pb, ep, cut) : launch_plain<true, false, true>(s, A, B, whole_chunks, tile, pb, ep, cut);
