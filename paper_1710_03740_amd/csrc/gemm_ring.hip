@@ -306,6 +306,7 @@ __device__ __forceinline__ uint4v drop_one(uint4v v) {
 // reads too, and the next wait for those would wait for the stage that is fetched meanwhile (1001 x 1999 over 1503 28.9 us so, 22.1 now).
 // (No template over the loaded type: as its argument uint4u would lose the alignment of its elements and claim 16 bytes.)
 __device__ __forceinline__ uint4v eight_from_global(const void* p) { return *(const __attribute__((address_space(1))) uint4u*)p; }
+__device__ __forceinline__ float4v four_from_global(const void* p) { return *(const __attribute__((address_space(1))) float4u*)p; }
 __device__ __forceinline__ uint16_t one_from_global(const void* p) { return *(const __attribute__((address_space(1))) uint16_t*)p; }
 
 // ANY: also rows of fewer than 8 elements, gathered element by element, and row strides too long for 32-bit offsets; kept apart, since
@@ -490,9 +491,27 @@ __device__ __forceinline__ void multiply(float4v (&acc)[FM][FN], const uint4v (&
 // guards and the three kinds of store were 10 KiB of code that a short launch fetched once and ran once (a 128 x 128 tile
 // over one stage: 7.1 us against 4.0 us for 64 x 64).  Pieces and mask reads need only the elements' alignment; the last
 // columns of a row that is no whole number of pieces go out one by one.
+// What an accumulating store adds to, four consecutive values per trip of its loop (store_tile): one load each whatever exists, so that they can be counted.
 template <int FM, int FN>
-__device__ __forceinline__ void store_tile(const Problem& pb, const Epilogue& ep, int sp, int i0, int j0, int lane, const float4v (&acc)[FM][FN], char* mine) {
+struct OldValues {
+  static constexpr int U = FN * 4, RPI = 64 / U, N = FM * 16 / RPI;
+  float4v v[N];
+  __device__ __forceinline__ void load(const Problem& pb, const Epilogue& ep, int i0, int j0, int lane) {
+    const int j = j0 + (lane % U) * 4, r0 = lane / U;
+    const float* out = reinterpret_cast<const float*>(ep.out) + j;
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      const int i = i0 + k * RPI + r0;
+      v[k] = four_from_global(there_or_zeros(i < pb.I && pb.J - j >= 4, reinterpret_cast<const uint16_t*>(out + (int64_t)i * ep.ld)));
+    }
+  }
+};
+struct NoOldValues {};
+
+template <int FM, int FN, class Old = NoOldValues>
+__device__ __forceinline__ void store_tile(const Problem& pb, const Epilogue& ep, int sp, int i0, int j0, int lane, const float4v (&acc)[FM][FN], char* mine, const Old& before = Old{}) {
   constexpr int WM = FM * 16, WN = FN * 16;
+  constexpr bool kBefore = !std::is_same<Old, NoOldValues>::value;   // an accumulating store whose old values are here
   const int li = lane & 15, lg = lane >> 4;
   bool bad = false;
   if (ep.mode == 0) {
@@ -587,7 +606,10 @@ __device__ __forceinline__ void store_tile(const Problem& pb, const Epilogue& ep
     };
     // Adding to what is there: up to 16 reads in flight, all of a 64 x 64 block (16 KiB a wavefront), the 2, 4 or 8 of smaller ones.  Two at a
     // time, as the stores go out, were most of a short reduction's time (8192 x 1024 over 256 accumulated 20.0 -> 17.2 us; 14.2 without reading).
-    if (ep.mode == 2) {
+    if constexpr (kBefore) {
+#pragma unroll
+      for (int it = 0; it < IT; ++it) put(it, before.v[it]);
+    } else if (ep.mode == 2) {
       constexpr int AHEAD = 16 < IT ? 16 : IT;
 #pragma unroll 1
       for (int it = 0; it < IT; it += AHEAD) {
@@ -632,7 +654,7 @@ __device__ __forceinline__ void add_piece(float4v (&total)[FM][FN], float4v (&ac
         acc[a][b][v] = 0.f;
       }
 }
-template <class AOp, class BOp, int BM, int BN, int WM, int WN, int NS, bool CUT>
+template <class AOp, class BOp, int BM, int BN, int WM, int WN, int NS, bool CUT, bool OLD>
 __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_ring(typename AOp::Src A, typename BOp::Src B, Problem pb, Epilogue ep, int cut) {
   constexpr int WAVES = (BM / WM) * (BN / WN);
   static_assert(WAVES == 4 || WAVES == 8, "wavefronts");
@@ -657,15 +679,29 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) __attribute__((amdgpu_w
     da.issue(s, st + wave * (LA * 1024));
     db.issue(s, st + A_BYTES + wave * (LB * 1024));
   };
-  // wait until at most `newer` stages' loads of this wavefront are in flight
-  auto wait_stages = [&](int newer) {
+  typedef typename std::conditional<OLD, OldValues<FM, FN>, NoOldValues>::type Old;
+  Old before;
+  // wait until at most `newer` stages' loads of this wavefront are in flight; and the old values', where the stages behind them need not be there
+  auto wait_stages = [&](int newer, bool old_too) {
     static_for<NS>([&](auto k) {
       constexpr int n = NS - 1 - decltype(k)::value;
-      if (newer == n || (n == 0 && newer < 0)) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(n * L) : "memory");
+      if (newer == n || (n == 0 && newer < 0)) {
+        if constexpr (OLD) {
+          if (old_too) { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(n * L + Old::N) : "memory"); return; }
+        }
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(n * L) : "memory");
+      }
     });
   };
 
   for (int q = 0; q < min(NS, nst); ++q) issue(q);
+  if constexpr (OLD) {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    before.load(pb, ep, i0 + wm * WM, j0 + wn * WN, lane);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  }
   float4v acc[FM][FN], total[CUT ? FM : 1][CUT ? FN : 1];
   int to_cut = cut;
 #pragma unroll
@@ -686,7 +722,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) __attribute__((amdgpu_w
   ra.init(wm * WM, lane, lds0);
   rb.init(wn * WN, lane, lds0 + A_BYTES);
   uint4v fa[2][FM], fb[2][FN];
-  wait_stages(min(NS, nst) - 1);
+  wait_stages(min(NS, nst) - 1, true);
   asm volatile("s_barrier" ::: "memory");
   ra.template read<0>(0, fa[0]);
   rb.template read<0>(0, fb[0]);
@@ -699,7 +735,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) __attribute__((amdgpu_w
     rb.template read<1>(slot, fb[1]);
     multiply<0, FM>(acc, fa[0], fb[0]);
     __builtin_amdgcn_sched_barrier(0);
-    wait_stages(min(NS - 2, nst - 2 - s));
+    wait_stages(min(NS - 2, nst - 2 - s), s + 1 < NS);
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     arrived(fa[1]);
     arrived(fb[1]);
@@ -722,10 +758,10 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) __attribute__((amdgpu_w
   arrived(fb[0]);
   if constexpr (CUT) {
     if (to_cut != cut) add_piece<FM, FN>(total, acc);
-    store_tile<FM, FN>(pb, ep, sp, i0 + wm * WM, j0 + wn * WN, lane, total, lds + wave * (WM * WN * 4));
+    store_tile<FM, FN>(pb, ep, sp, i0 + wm * WM, j0 + wn * WN, lane, total, lds + wave * (WM * WN * 4), before);
     return;
   }
-  store_tile<FM, FN>(pb, ep, sp, i0 + wm * WM, j0 + wn * WN, lane, acc, lds + wave * (WM * WN * 4));
+  store_tile<FM, FN>(pb, ep, sp, i0 + wm * WM, j0 + wn * WN, lane, acc, lds + wave * (WM * WN * 4), before);
 }
 
 // The same with the pieces of one stage in registers on their way to one of two LDS slots: behind the barrier of stage s the
@@ -1200,9 +1236,19 @@ Problem ring_problem(RingTile tile, int ktiles_per_split, int I, int J, int R) {
   return Problem{I, J, R, (I + bm - 1) / bm, (J + bn - 1) / bn, (kt + ktiles_per_split - 1) / ktiles_per_split, ktiles_per_split};
 }
 
-template <class AOp, class BOp, int BM, int BN, int WM, int WN, int NS, bool CUT = false>
+// Weight gradients that are added to FP32 values fetch these beside the operands, not when their sums are there (OLD): over the one to four stages of a
+// recurrent layer's step the reads were as long as all before them (8192 x 1024 over 128 14.2 -> 13.5 us, 4096 x 1024 over 64 10.3 -> 9.1, 3392 x 192 over 60 4.6 ->
+// 4.05, 3000 x 3000 over 512 30.8 -> 29.7).  Not for cut sums in 64 x 64 blocks, which have no registers left (one word of every line into the L2 instead made
+// 8192 x 1024 over 256 16.9 -> 18.2 us), and not over more than two rounds of workgroups, where those that wait cover each other (4096 x 8192 over 128
+// 51.8 -> 54.1); operands through registers 0.985 to 1.03 of the time (513 x 2047 over 129 7.4 -> 7.6).
+constexpr bool may_read_ahead(int wm, int wn, bool cut) { return !(cut && wm == 64 && wn == 64); }
+bool reads_ahead(const Problem& pb, const Epilogue& ep) { return ep.mode == 2 && (int64_t)pb.tiles_i * pb.tiles_j * pb.splits <= 4 * kCUs; }
+
+template <class AOp, class BOp, int BM, int BN, int WM, int WN, int NS, bool CUT = false, bool OLD = false>
 int launch_ring(hipStream_t s, const typename AOp::Src& A, const typename BOp::Src& B, const Problem& pb, const Epilogue& ep, int cut = 0) {
-  auto k = k_gemm_ring<AOp, BOp, BM, BN, WM, WN, NS, CUT>;
+  if constexpr (!OLD && may_read_ahead(WM, WN, CUT) && std::is_same<AOp, RingMat<false, BM, (BM / WM) * (BN / WN)>>::value && std::is_same<BOp, RingMat<false, BN, (BM / WM) * (BN / WN)>>::value)
+    if (reads_ahead(pb, ep)) return launch_ring<AOp, BOp, BM, BN, WM, WN, NS, CUT, true>(s, A, B, pb, ep, cut);
+  auto k = k_gemm_ring<AOp, BOp, BM, BN, WM, WN, NS, CUT, OLD>;
   constexpr int lds = NS * (BM + BN) * 128;
   static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds), true);
   (void)once;

@@ -1,6 +1,7 @@
 """The ring and any-alignment GEMM kernels, compiled for gfx950, never touch a register that an LDS read in flight will
 still write (see asm_check.py).  Compiles csrc/gemm_ring.hip to device assembly and walks every instantiation."""
 import os
+import re
 import shutil
 import subprocess
 
@@ -45,3 +46,22 @@ def test_no_wide_shift_takes_its_amount_from_the_last_register(assembly):
     assert n >= 40
     assert asm_check.shifts_by_the_last_register(["\tv_lshlrev_b64 v[90:91], v127, v[86:87]"], 128) == [127]
     assert not asm_check.shifts_by_the_last_register(["\tv_lshlrev_b64 v[90:91], v127, v[86:87]"], 136)
+
+
+def test_values_fetched_ahead_are_counted(assembly):
+    """Kernels that fetch what they add to beside their operands let so many loads be in flight at the first barriers: they have to be there, one each, behind all
+    loads of the first stages and in front of the first barrier, or a stage would be read before it has landed."""
+    n = 0
+    for name, lines in asm_check.kernels(assembly, r"k_gemm_ring.*Lb[01]ELb1EEEv"):
+        bm, bn, wm, wn, slots = map(int, re.search(r"Li(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELb", name).groups())
+        ops = [l.split()[0] for l in lines[:next(k for k, l in enumerate(lines) if l.split()[:1] == ["s_barrier"])] if l.split()]
+        loads = [k for k, o in enumerate(ops) if o == "global_load_dwordx4"]
+        stage = [k for k, o in enumerate(ops) if o.startswith("global_load_lds")]
+        other = [o for o in ops if o.startswith(("global_load", "flat_load", "buffer_load", "scratch_load", "global_store")) and o != "global_load_dwordx4" and not o.startswith("global_load_lds")]
+        waves = (bm // wm) * (bn // wn)
+        per_stage, old = (bm + bn) // 8 // waves, wm * wn // 256
+        assert len(loads) == old and stage and max(stage) < min(loads) and not other, name
+        counts = [int(m.group(1)) for l in lines[:] for m in [re.search(r"s_waitcnt vmcnt\((\d+)\)$", l.strip())] if m]
+        assert (slots - 1) * per_stage + old in counts, (name, counts)
+        n += 1
+    assert n == 9

@@ -1,0 +1,31 @@
+"""Weight gradients added to FP32 values that are fetched ahead (OLD in csrc/gemm_ring.hip): every tile at ragged rows and columns, over one stage and over more than
+the ring holds.  Operands of -1, 0 and 1 and whole numbers to add to: exact in any order.  Surroundings are NaN, so a value fetched from outside the output that reached it would show."""
+import pytest
+import torch
+
+from paper_1710_03740_amd import binding as mpt
+from test_gpu_gemm_ring import outside_untouched, window, ws_for
+
+pytestmark = pytest.mark.gpu
+
+# (rows, output rows, columns), all columns multiples of 8: 64 x 64, 128 x 64 and 128 x 128 tiles, with one, two and more workgroups per CU, uncut and cut
+SIZES = [(1, 8, 8), (40, 64, 72), (64, 136, 200), (65, 1000, 264), (128, 520, 1032), (192, 3392, 192), (200, 4096, 1000), (128, 8192, 1024), (64, 5000, 1288), (500, 1096, 2056),
+         (600, 2048, 2048), (1500, 136, 520), (2000, 968, 1032), (700, 2050 // 8 * 8, 520)]
+
+
+@pytest.mark.parametrize("pad", [0, 8])
+@pytest.mark.parametrize("M,K,N", SIZES)
+@pytest.mark.parametrize("split", [False, True])
+def test_added_to_what_is_there(M, K, N, pad, split):
+    g = torch.Generator(device="cuda").manual_seed(M + K + N)
+    x, d = torch.randint(-1, 2, (M, K), device="cuda", generator=g).half(), torch.randint(-1, 2, (M, N), device="cuda", generator=g).half()
+    buf, out = window(K, N, pad, pad, dtype=torch.float32)
+    out.copy_(torch.randint(-99, 100, (K, N), device="cuda", generator=g))
+    want = out.double() + x.double().t() @ d.double()
+    flag = torch.zeros(1, dtype=torch.int32, device="cuda")
+    print("accumulate", (M, K, N), pad, split, flush=True)
+    mpt.mpt_gemm_wgrad(x, d, out, accumulate=True, flag=flag, ws=ws_for(2, M, N, K) if split else None)
+    assert torch.equal(out.double(), want) and outside_untouched(buf, out) and int(flag.item()) == 0
+    out[K - 1, N - 1] = float("inf")
+    mpt.mpt_gemm_wgrad(x, d, out, accumulate=True, flag=flag, ws=ws_for(2, M, N, K) if split else None)
+    assert int(flag.item()) == 1 and torch.isinf(out).sum().item() == 1
