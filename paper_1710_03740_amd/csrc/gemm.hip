@@ -5,7 +5,8 @@
 // Kernels that compute C[i,j] = sum_r A(i,r) * B(r,j):
 //   k_gemm_dma64  whole 256 x 256 tiles of aligned operands - plain matrices, or the convolution's gathered image and
 //                 filter - streamed global -> LDS in stages of reduction depth 64, one wavefront per SIMD; FP16 store,
-//                 or (second instance) FP32 store / accumulate / split partials.  The square 4096^3 workload runs here;
+//                 or (second instance) FP32 store / accumulate / split partials.  The square 4096^3 workload runs here, and with
+//                 edges (DmaEdge64) FP16 outputs of more than half the chip's tiles that are no whole ones;
 //   k_gemm_dma4   the same in stages of depth 32: 128 x 256 tiles (few-row outputs, split or not) and the convolution's
 //                 weight gradient with its per-tap gathered operand;
 //   k_gemm_dma    depth 32 with two wavefronts per SIMD: FP16 outputs with odd row strides, FP32 outputs over short
@@ -955,6 +956,54 @@ struct DmaOperand64 {
   }
 };
 
+// The same slices of a matrix that is no whole number of tiles or stages: rows and columns beyond it are its last ones again, pieces beyond the reduction a
+// line of zeros.  A scalar base that moves with the stage and 32-bit lane offsets (ld < 2^21); only the last, ragged stage selects.
+template <bool RC>
+struct DmaEdge64 {
+  typedef RingMatSrc Src;
+  static constexpr bool kRC = RC;
+  const char *base, *at;             // of the tile; of the stage being fetched (wavefront-uniform), set by its first load
+  int64_t step;
+  uint32_t off[8];
+  int R, inside, wave, lane;         // inside: stages that end before the reduction does
+  __device__ __forceinline__ int row(int lane, int k) const { return RC ? wave * 64 + k * 8 + (lane >> 3) : (k >> 2) * 32 + (wave * 4 + (k & 3)) * 2 + (lane >> 5); }
+  __device__ __forceinline__ int col(int lane, int k) const {
+    const int r = row(lane, k), pc = lane & 31;
+    return RC ? ((lane & 7) ^ ((r >> 1) & 7)) * 8 : (2 * ((pc >> 1) ^ oc_key(r)) + (pc & 1)) * 8;
+  }
+  __device__ __forceinline__ void init(const Src& m, int o0, int wave_, int lane_) {
+    wave = wave_; lane = lane_; R = m.R; inside = m.R >> 6;
+    base = at = reinterpret_cast<const char*>(m.base + (RC ? (int64_t)o0 * m.ld : (int64_t)o0));
+    step = RC ? 128 : 128 * m.ld;
+    const int left = m.O - o0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int r = row(lane, k), c = col(lane, k);
+      off[k] = (uint32_t)((RC ? (int64_t)min(r, left - 1) * m.ld + c : (int64_t)r * m.ld + min(c, left - 8)) * 2);
+    }
+  }
+  template <int K>
+  __device__ __forceinline__ void issue(int d, char* slot, int w) {
+    if constexpr (K == 0) {
+      at = base + d * step;
+      asm("" : "+s"(at));                                            // stays a scalar address
+    }
+    char* const to = slot + (RC ? (w * 8 + K) * 1024 : (K >> 2) * 16384 + (w * 4 + (K & 3)) * 1024);
+    const char* p = at + off[K];
+    if (d >= inside) {
+      int l = lane;
+      asm volatile("" : "+v"(l));                                    // worked out here, not ahead of the loop
+      const uintptr_t there = d * 64 + (RC ? col(l, K) : row(l, K)) < R ? ~(uintptr_t)0 : (uintptr_t)0;
+      p = reinterpret_cast<const char*>((reinterpret_cast<uintptr_t>(p) & there) | (reinterpret_cast<uintptr_t>(k_zero_line) & ~there));
+      __builtin_amdgcn_global_load_lds((global_void_ptr)p, (lds_void_ptr)to, 16, 0, 0);
+    } else {
+      __builtin_amdgcn_global_load_lds((global_void_ptr)p, (lds_void_ptr)to, 16, 0, 0);
+    }
+  }
+};
+template <class Op> struct HasEdges { static constexpr bool value = false; };
+template <bool RC> struct HasEdges<DmaEdge64<RC>> { static constexpr bool value = true; };
+
 // The convolution's gathered image rows (see DmaImgRC) for stages of depth 64: Cc is a multiple of 64, so a stage is
 // 64 consecutive channels of one tap, a whole 128-byte line per pixel.  Src::dSpt divides by the stages per tap, Cc / 64.
 struct DmaImgRC64 {
@@ -1068,7 +1117,7 @@ struct FragAddr64 {
 
 template <class AOp, class BOp, bool F32OUT = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_gemm_dma64(typename AOp::Src A, typename BOp::Src B, Problem pb, Epilogue ep) {
-  constexpr bool A_RC = AOp::kRC, B_RC = BOp::kRC;
+  constexpr bool A_RC = AOp::kRC, B_RC = BOp::kRC, EDGES = HasEdges<AOp>::value;
   constexpr int NA = 8, HALF = 4, BM = 256;
   typedef FragSched<NA> Sched;
   constexpr int AD = Sched::kADist;
@@ -1082,7 +1131,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   tile_of(pb, blockIdx.x, ti, tj, sp);
   const int i0 = ti * BM, j0 = tj * 256;
   const int d0 = sp * pb.ktiles_per_split;                             // first stage of this workgroup's share of the reduction
-  const int nd = min(pb.ktiles_per_split, pb.R / 64 - d0);             // its stages (>= 1: the host plans no empty split)
+  const int nd = min(pb.ktiles_per_split, (EDGES ? (pb.R + 63) / 64 : pb.R / 64) - d0);             // its stages (>= 1: the host plans no empty split)
   const int nst = 2 * nd;                                              // half stages
 
   AOp da;
@@ -1287,6 +1336,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   for (int it = 0; it < BM / 8; ++it) {
     const int r = it * 4 + lg;
     uint4v q = *reinterpret_cast<const uint4v*>(mine + r * 256 + ((li ^ (r & 15)) << 4));
+    if constexpr (EDGES) {
+      if (i0 + wm * (BM / 2) + r >= pb.I || j0 + wn * 128 + li * 8 >= pb.J) continue;
+    }
     if (ep.act == 1) {
 #pragma unroll
       for (int e = 0; e < 4; ++e)
@@ -1459,6 +1511,20 @@ bool try_launch_dma(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, boo
   return true;
 }
 
+// FP16 outputs that are no whole tiles, unsplit, on the depth-64 kernel (where: edges_in_256).
+template <bool A_RC, bool B_RC>
+bool try_launch_edges(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool aligned, int I, int J, int R, const Epilogue& ep, int& status) {
+  if (!aligned || ep.mode != 0 || (J % 8) || (ep.ld % 8) || !mpt_aligned(ep.out, 16) || (ep.act == 2 && ((ep.ldmask % 8) || !mpt_aligned(ep.mask, 16)))) return false;
+  if (A.ld >= (1 << 21) || B.ld >= (1 << 21) || (!A_RC && I < 8)) return false;
+  auto k = k_gemm_dma64<DmaEdge64<A_RC>, DmaEdge64<B_RC>>;
+  static bool once = ((void)hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, 4 * 32768), true);
+  (void)once;
+  Problem pb{I, J, R, (I + 255) / 256, (J + 255) / 256, 1, (R + 63) / 64};
+  hipLaunchKernelGGL(k, dim3((unsigned)((int64_t)pb.tiles_i * pb.tiles_j)), dim3(256), 4 * 32768, s, A, B, pb, ep);
+  status = hipGetLastError() == hipSuccess ? MPT_OK : MPT_ERR_HIP;
+  return true;
+}
+
 // Problems with few 256-row tiles but many 128 x 256 ones (a batch-256 product against a wide weight matrix): one
 // unsplit launch of the 128-row variant of the one-wavefront-per-SIMD kernel fills the chip where 256 x 256 tiles
 // leave half of it idle; a workspace, if given, is not needed then.
@@ -1559,6 +1625,7 @@ int run(hipStream_t s, const RingMatSrc& A, const RingMatSrc& B, bool aligned, i
   if (rp.splits > 1) {
     first.out = ws; first.ld = J; first.mode = 3; first.flag = nullptr;
   }
+  if (rp.splits == 1 && rp.cut == 0 && edges_in_256(I, J, R, rp.cost) && try_launch_edges<A_RC, B_RC>(s, A, B, aligned, I, J, R, ep, st)) return st;
   st = launch_ring_plain(s, A_RC, B_RC, A, B, aligned, rp.tile, rp.ktiles_per_split, rp.cut, I, J, R, first);
   if (st == MPT_OK && rp.splits > 1) {
     launch_split_reduce(s, ws, rp.splits, I, J, ep);

@@ -188,6 +188,18 @@ inline Fp16Form fp16_form(int64_t I, int64_t J, int64_t R, int most, int per, bo
   consider(kRing128x128, whole_chunks ? kRing128[lines] : kAny128Fp16);
   return best;
 }
+// FP16 results in one chain that are no whole tiles of 256 x 256 on the streamed kernel all the same (DmaEdge64 in gemm.hip), where that costs less than the
+// cheapest tile of the ring kernels, whose smaller tiles read the operands twice as often.  A round of its tiles, 130 or 256 of them, takes 11 us and 1.3 per stage.  90
+// products of 48 .. 756 tiles: the 56 of up to 128 tiles stay where they were (this way 1.0 to 2.7 times as long), the others take 0.72 to 1.03 of the time
+// (2480 x 3528 over 2448 80 -> 61 us, 904 x 9240 over 3504 as input gradient 112 -> 81, 3616 x 3504 over 776 as weight gradient 34.5 -> 28.9, 3000 cubed 97 -> 72).
+inline constexpr RingCost kEdges256 = {3.0, 8.5, 1.42, 0.93};
+inline bool edges_in_256(int64_t I, int64_t J, int64_t R, double otherwise) {
+  const int64_t tiles = ((I + 255) / 256) * ((J + 255) / 256);
+  const int kt = (int)((R + BK - 1) / BK), force = MPT_TUNABLE("MPT_EDGES", 1);   // tuning builds only: 0 never, 2 always
+  if (force != 1) return force == 2;
+  if (kt < 3 || (kt < 8 && tiles > kCUs)) return false;                // (short reductions: 5328 x 5448 over 96 25.1 -> 29.6 us, 3840 x 3848 over 72 14.5 -> 15.7)
+  return ring_cost(kEdges256, tiles, I, J, kt, 1) < (kt < 8 ? 0.9 : 1.0) * otherwise;
+}
 // The pieces of an FP16 result (fp16_planned: or make_plan's), from its shape alone, so that it has the same bits at every alignment.  whole_rows: the operands' rows are whole 16-byte
 // pieces where they are aligned.  Where the order of a sum shows beyond its last bit the pieces stay make_plan's: a ReLU's results (relu) and what a convolution's
 // normalisation makes of them are zero or not by the sign of a sum near zero, and with them go whole elements of the gradient.  So forward products over a multiple of

@@ -20,6 +20,12 @@ extern "C" void planned(long I, long J, long R, int ws, int a_rc, int b_rc, int 
   const int r[7] = {own, f.splits, f.ktiles_per_split, f.tile, p.splits, p.ktiles_per_split, rows};
   for (int k = 0; k < 7; ++k) out[k] = r[k];
 }
+extern "C" int edges(long I, long J, long R, int a_rc, int b_rc) {
+  const Plan p = make_plan(I, J, R, true);
+  if (p.splits > 1 && !fp16_planned(p, J, R, a_rc && !b_rc, !a_rc, false)) return 0;
+  const Fp16Form f = fp16_launch(p, I, J, R, true, true, false);
+  return f.splits == 1 && edges_in_256(I, J, R, f.cost);
+}
 """
 FORMS = {"f": (1, 0), "d": (1, 1), "w": (0, 0)}
 
@@ -40,6 +46,8 @@ def plan(tmp_path_factory):
         out = (ctypes.c_int * 7)()
         L.planned(I, J, R, ws, *FORMS[op], relu, aligned, lines, ctypes.addressof(out))
         return tuple(out)
+    L.edges.argtypes = [ctypes.c_long] * 3 + [ctypes.c_int] * 2
+    call.edges = lambda op, I, J, R: L.edges(I, J, R, *FORMS[op])
     return call
 
 
@@ -86,3 +94,12 @@ def test_the_forms_run_on_the_gpu(plan):
         _, _, _, tile, _, _, rows = plan(op, I, J, R)
         assert tile == 3 and not rows, (op, I, J, R)
     assert {plan(*p)[6] for p in LONG if plan(*p)[3] == 0 and plan(*p)[1] > 1} == {0, 1}
+
+
+def test_large_outputs_that_are_no_whole_tiles(plan):
+    """More than half the chip's tiles of 256 x 256, and the rule stands where both sides were measured."""
+    for op, I, J, R, want in (("f", 3000, 3000, 3000, 1), ("f", 2480, 3528, 2448, 1), ("d", 904, 9240, 3504, 1), ("w", 3616, 3504, 776, 1), ("f", 2112, 2696, 1376, 0), ("w", 848, 7712, 1728, 0),
+                              ("d", 1304, 5160, 1040, 0), ("f", 1616, 5200, 168, 0), ("d", 4752, 4736, 240, 0), ("w", 3568, 10688, 176, 0), ("f", 2000, 3000, 1000, 0)):
+        assert plan.edges(op, I, J, R) == want, (op, I, J, R)
+    from test_gpu_gemm_edges import SIZES
+    assert all(plan.edges(*s) for s in SIZES)

@@ -1,0 +1,59 @@
+"""FP16 products of large outputs that are no whole tiles of 256 x 256 on the streamed kernel (DmaEdge64 in csrc/gemm.hip): last rows, columns and stages at, one piece
+before and one piece behind their ends, each pass, ReLU and mask, special values.  Operands of -1, 0 and 1 over at most 2047 have exact sums in any order."""
+import pytest
+import torch
+
+from paper_1710_03740_amd import binding as mpt
+from test_gpu_gemm_ring import outside_untouched, window, ws_for
+
+pytestmark = pytest.mark.gpu
+
+# (pass, output rows, columns, reduction): every remainder of rows (any where the reduction runs along them), of columns and reduction (multiples of 8); three stages and
+# more, an odd and an even number of them; one round of tiles and more
+SIZES = [("f", 3001, 3000, 1000), ("f", 2817, 3320, 712), ("f", 4095, 4088, 328), ("f", 1000, 13568, 192), ("f", 3327, 4104, 200), ("f", 6000, 5008, 1032), ("f", 2560, 3592, 1544),
+         ("d", 3001, 3000, 1000), ("d", 3585, 3848, 264), ("d", 2303, 4608, 1992), ("d", 5000, 5128, 520),
+         ("w", 3000, 3000, 1001), ("w", 2824, 3320, 711), ("w", 4088, 4096, 257), ("w", 1696, 7360, 151), ("w", 4608, 4616, 1543)]
+
+
+def mnk(op, I, J, R):
+    return {"f": (I, J, R), "d": (I, R, J), "w": (R, J, I)}[op]
+
+
+def operands(op, I, J, R, pad, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    M, N, K = mnk(op, I, J, R)
+    shapes = {"f": ((M, K), (K, N)), "d": ((M, N), (K, N)), "w": ((M, K), (M, N))}[op]
+    out = []
+    for s in shapes:
+        v = window(*s, pad, pad)[1]
+        out.append(v.copy_(torch.randint(-1, 2, s, device="cuda", generator=g)))
+    a, b = (t.float() for t in out)
+    return out, {"f": lambda: a @ b, "d": lambda: a @ b.t(), "w": lambda: a.t() @ b}[op]()
+
+
+@pytest.mark.parametrize("pad", [0, 8])
+@pytest.mark.parametrize("op,I,J,R", SIZES)
+def test_edges(op, I, J, R, pad):
+    (a, b), want = operands(op, I, J, R, pad, I + J + R)
+    ws = ws_for("fdw".index(op), *mnk(op, I, J, R))
+    h = window(I, J, pad, pad)[1]
+    h.copy_(torch.randint(-1, 2, (I, J), device="cuda"))
+    flag = torch.zeros(1, dtype=torch.int32, device="cuda")
+    calls = {"f": [(lambda o: mpt.mpt_gemm_fwd(a, b, o, ws), want), (lambda o: mpt.mpt_gemm_fwd_relu(a, b, o, ws), want.clamp(min=0))],
+             "d": [(lambda o: mpt.mpt_gemm_dgrad(a, b, o, ws), want), (lambda o: mpt.mpt_gemm_dgrad_relu(a, b, h, o, ws), torch.where(h > 0, want, torch.zeros_like(want)))],
+             "w": [(lambda o: mpt.mpt_gemm_wgrad(a, b, o, flag=flag, ws=ws), want)]}[op]
+    for k, (call, expect) in enumerate(calls):
+        print("edges", op, (I, J, R), pad, k, flush=True)
+        buf, out = window(I, J, pad, pad)
+        call(out)
+        assert torch.equal(out.float(), expect) and outside_untouched(buf, out)
+    assert int(flag.item()) == 0
+
+
+def test_special_values_stay_in_their_rows_and_columns():
+    M, N, K = 1001, 3000, 3000
+    x, g = torch.ones(M, K, device="cuda").half(), torch.ones(M, N, device="cuda").half()
+    x[M - 1, K - 1], g[0, N - 1] = float("inf"), float("nan")
+    flag, dw = torch.zeros(1, dtype=torch.int32, device="cuda"), torch.empty(K, N, device="cuda", dtype=torch.float16)
+    mpt.mpt_gemm_wgrad(x, g, dw, flag=flag)
+    assert int(flag.item()) == 1 and torch.isnan(dw[:, N - 1]).all() and torch.isinf(dw[K - 1, :N - 1]).all() and (dw[:K - 1, :N - 1] == M).all()
