@@ -892,7 +892,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
         for (int e = 0; e < 4; ++e) emax.add(q[e]);
       }
-      *reinterpret_cast<uint4v*>(out + (int64_t)r * ep.ld) = q;
+      // nontemporal, as in k_gemm_dma64's store: 512 x 8192 over 1024 16.5 -> 16.1 us, a recurrent layer's 20 steps 1284 -> 1273
+      __builtin_nontemporal_store(q, reinterpret_cast<uint4v*>(out + (int64_t)r * ep.ld));
     }
     bad = emax.special();
   }
