@@ -191,22 +191,19 @@ __global__ __launch_bounds__(kBlock) void k_bn_partial(BnShape s, const uint16_t
   }
 }
 
-// CH channels per workgroup; GROUPS thread groups each sum a contiguous range of row blocks in block order, their results are added
+// 16 channels per workgroup; GROUPS thread groups each sum a contiguous range of row blocks in block order, their results are added
 // by eights in group order; then the closing arithmetic in FP64 and one rounding to FP32.  A few hundred kilobytes in a few
 // workgroups: bound by the latency of memory.  A thread has up to eight partials of each sum in flight; sixteen are more than the
 // compiler keeps there, it sends them out a few at a time (statistics of 131072 x 64 with their partial sums, 512 row blocks, 10.7 us so and
 // 8.8; 200704 x 66 37.9 and 34.6).  64 groups from 129 row blocks on: 12544 x 512 (196) 9.2 us in 16, 8.0 in 64, 200704 x 64 (784) 11.7 in both.  16 groups up to
 // eight row blocks each, whose 48 wavefronts fewer start sooner: 1000 x 32 (2) 8.3 us in 64, 8.1 in 16, 16384 x 64 (64) 6.5 and 5.7, 40000 x 40 (100) 6.4 and 6.2.
-// Up to 128 channels 128 groups of eight: twice the workgroups, each thread half the partials (statistics with their partial sums, 200704 x 64 11.65 -> 10.6 us, 100352 x 128
-// 11.9 -> 11.6; 50176 x 256 12.7 both ways, 12544 x 512 8.0 in 64 groups of sixteen, 8.4 so).
 constexpr int kFewRowBlocks = 128;
-template <int MODE, int GROUPS, int CH>
-__global__ __launch_bounds__(GROUPS * CH) void k_bn_finalize(BnShape s, const double* __restrict__ part, const uint16_t* __restrict__ x,
+template <int MODE, int GROUPS>
+__global__ __launch_bounds__(GROUPS * 16) void k_bn_finalize(BnShape s, const double* __restrict__ part, const uint16_t* __restrict__ x,
                                                              float* __restrict__ out1, float* __restrict__ out2) {
-  constexpr int EIGHTS = GROUPS / 8;
-  __shared__ double red[GROUPS][2][CH], red8[EIGHTS][2][CH];
-  const int cl = threadIdx.x % CH, grp = threadIdx.x / CH;
-  const int c = blockIdx.x * CH + cl;
+  __shared__ double red[GROUPS][2][16], red8[GROUPS / 8][2][16];
+  const int cl = threadIdx.x & 15, grp = threadIdx.x >> 4;
+  const int c = blockIdx.x * 16 + cl;
   const int per = (s.nblk + GROUPS - 1) / GROUPS;
   const int b0 = grp * per, b1 = min(b0 + per, s.nblk);
   double t1 = 0.0, t2 = 0.0;
@@ -230,8 +227,8 @@ __global__ __launch_bounds__(GROUPS * CH) void k_bn_finalize(BnShape s, const do
   red[grp][0][cl] = t1;
   red[grp][1][cl] = t2;
   __syncthreads();
-  if (threadIdx.x < EIGHTS * 2 * CH) {            // eights x 2 sums x channels
-    const int eight = threadIdx.x / (2 * CH), which = threadIdx.x / CH & 1;
+  if (threadIdx.x < GROUPS * 4) {                 // eights x 2 sums x 16 channels
+    const int eight = threadIdx.x >> 5, which = threadIdx.x >> 4 & 1;
     double t = 0.0;
 #pragma unroll
     for (int g = 0; g < 8; ++g) t += red[eight * 8 + g][which][cl];
@@ -241,7 +238,7 @@ __global__ __launch_bounds__(GROUPS * CH) void k_bn_finalize(BnShape s, const do
   if (grp != 0 || c >= s.C) return;
   t1 = t2 = 0.0;
 #pragma unroll
-  for (int g = 0; g < EIGHTS; ++g) { t1 += red8[g][0][cl]; t2 += red8[g][1][cl]; }
+  for (int g = 0; g < GROUPS / 8; ++g) { t1 += red8[g][0][cl]; t2 += red8[g][1][cl]; }
   if constexpr (MODE == 0) {
     const double k = (double)(float)reinterpret_cast<const _Float16*>(x)[c];
     const double d1 = t1 / (double)s.P;
@@ -257,9 +254,9 @@ __global__ __launch_bounds__(GROUPS * CH) void k_bn_finalize(BnShape s, const do
 
 template <int MODE>
 void launch_finalize(hipStream_t st, const BnShape& s, const double* part, const uint16_t* x, float* out1, float* out2) {
-  if (s.nblk <= kFewRowBlocks) hipLaunchKernelGGL((k_bn_finalize<MODE, 16, 16>), dim3((s.C + 15) / 16), dim3(256), 0, st, s, part, x, out1, out2);
-  else if (s.C <= 128) hipLaunchKernelGGL((k_bn_finalize<MODE, 128, 8>), dim3((s.C + 7) / 8), dim3(1024), 0, st, s, part, x, out1, out2);
-  else hipLaunchKernelGGL((k_bn_finalize<MODE, 64, 16>), dim3((s.C + 15) / 16), dim3(1024), 0, st, s, part, x, out1, out2);
+  const dim3 grid((s.C + 15) / 16);
+  if (s.nblk <= kFewRowBlocks) hipLaunchKernelGGL((k_bn_finalize<MODE, 16>), grid, dim3(256), 0, st, s, part, x, out1, out2);
+  else hipLaunchKernelGGL((k_bn_finalize<MODE, 64>), grid, dim3(1024), 0, st, s, part, x, out1, out2);
 }
 
 // Per-channel constants of a pointwise pass are formed once per workgroup (square root and divisions are tens of
